@@ -12,7 +12,7 @@ namespace ofdft {
 
 namespace {
 
-constexpr int kMgThreads = 256;
+constexpr int kMgCoarseThreads = 1024;
 
 struct MgDims {
     int nx, ny, nz;
@@ -25,35 +25,19 @@ MgDims dims_of(const MgLevel &L, double2 kappa) {
     return MgDims{L.nx, L.ny, L.nz, L.cx, L.cy, L.cz, 2.0 * (L.cx + L.cy + L.cz), kappa.x, kappa.y, L.n};
 }
 
-// Launch geometry: 64 x 4 threads over (x, y); each thread runs down a
-// column of kMgKZ consecutive z planes (grid z = chunks), keeping the column's
-// values in registers so that the z neighbours are loaded once.  Point
-// coordinates come from the launch indices (no divisions).
-constexpr int kMgBX = 64, kMgBY = 4, kMgKZ = 4;
-static_assert(kMgBX * kMgBY == kMgThreads, "block shape");
-
-// z chunks of one system; the systems of a launch are stacked along grid z
-__host__ __device__ inline int mg_zch(int nz) { return (nz + kMgKZ - 1) / kMgKZ; }
-
-dim3 mg_grid(int nx, int ny, int nz, int count = 1) {
-    return dim3((nx + kMgBX - 1) / kMgBX, (ny + kMgBY - 1) / kMgBY, mg_zch(nz) * count);
-}
-
-struct MgPt {
-    int x, y, z;     // z: first plane of the thread's column chunk
-    int64_t i;       // index of (x, y, z)
+// Launch geometry of the two cycle kernels of a level: a workgroup owns a
+// W x H tile of (x, y) (both even) and marches along z over zl planes (even);
+// tiles in x, y and z of one system, the systems of a launch one after
+// another.
+struct MgTile {
+    int W, H, zl;
+    int tx, ty, tz;
+    __host__ __device__ int blocks() const { return tx * ty * tz; }
 };
 
-// System of the workgroup within its launch (grid z = system * chunks + chunk).
-__device__ inline int mg_sys(int nz) { return blockIdx.z / mg_zch(nz); }
-
-__device__ inline bool mg_point(int nx, int ny, int nz, MgPt &p) {
-    p.x = blockIdx.x * kMgBX + threadIdx.x;
-    p.y = blockIdx.y * kMgBY + threadIdx.y;
-    p.z = (blockIdx.z - mg_sys(nz) * mg_zch(nz)) * kMgKZ;
-    p.i = ((int64_t)p.z * ny + p.y) * nx + p.x;
-    return p.x < nx && p.y < ny;
-}
+// z chunks of four planes times systems of a launch: the limit mg_create
+// keeps on systems per hierarchy.
+inline int mg_zch(int nz) { return (nz + 3) / 4; }
 
 // Element types: the cycle's input f and output z are FP64 (real or complex);
 // the levels' arrays are stored, and their arithmetic done, in S (FP64 or
@@ -99,45 +83,6 @@ template <typename C> __device__ inline C mk_c(double a, double b);
 template <> __device__ inline double2 mk_c<double2>(double a, double b) { return make_double2(a, b); }
 template <> __device__ inline float2 mk_c<float2>(double a, double b) { return make_float2((float)a, (float)b); }
 
-// A u on the thread's column chunk for the periodic 7-point operator
-// A = -Delta_h + kappa (second order), u of element type TI, computed in S:
-// au[k] and the centre values cen[k] for planes p.z + k, k < kMgKZ (planes
-// at or beyond nz are left unset).
-template <typename S, typename TI>
-__device__ inline void apply7_col(const TI *__restrict__ u, const MgDims &d, const MgPt &p, S (&cen)[kMgKZ],
-                                  S (&au)[kMgKZ]) {
-    using V = VT<S>;
-    using R = typename MgT<S>::R;
-    using C = typename MgT<S>::C;
-    const int64_t nxy = (int64_t)d.nx * d.ny;
-    const int64_t row = (int64_t)p.y * d.nx + p.x;
-    const int dxp = p.x + 1 == d.nx ? -p.x : 1, dxm = p.x == 0 ? d.nx - 1 : -1;
-    const int64_t dyp = p.y + 1 == d.ny ? -(int64_t)p.y * d.nx : d.nx;
-    const int64_t dym = p.y == 0 ? (int64_t)(d.ny - 1) * d.nx : -(int64_t)d.nx;
-    S col[kMgKZ + 2];
-#pragma unroll
-    for (int k = 0; k < kMgKZ + 2; ++k) {
-        int z = p.z - 1 + k;
-        z = z < 0 ? z + d.nz : (z >= d.nz ? z - d.nz : z);
-        z = z >= d.nz ? d.nz - 1 : z;        // chunk tail past nz: any valid plane
-        col[k] = cv<S>(u[(int64_t)z * nxy + row]);
-    }
-    const C kap = mk_c<C>(d.kre, d.kim);
-#pragma unroll
-    for (int k = 0; k < kMgKZ; ++k) {
-        if (p.z + k < d.nz) {
-            const int64_t i = (int64_t)(p.z + k) * nxy + row;
-            const S c = col[k + 1];
-            S a = V::mul((R)d.diag, c);
-            a = mg_axpy((R)-d.cx, V::add(cv<S>(u[i + dxp]), cv<S>(u[i + dxm])), a);
-            a = mg_axpy((R)-d.cy, V::add(cv<S>(u[i + dyp]), cv<S>(u[i + dym])), a);
-            a = mg_axpy((R)-d.cz, V::add(col[k], col[k + 2]), a);
-            cen[k] = c;
-            au[k] = V::add(a, mg_scale(kap, c));
-        }
-    }
-}
-
 // Per-launch shift source: when `kap` is given, kappa is read from device
 // memory (so a captured launch follows the current shift); when `run` is
 // given the kernel returns at once unless *run == 0 (a converged system of a
@@ -176,274 +121,340 @@ __device__ inline C jacobi_factor(const MgDims &d, double w) {
     return mk_c<C>(w * re / den, -w * im / den);
 }
 
-// The two pre-smoothing sweeps from u = 0 in one pass: with the Jacobi factor
-// s = omega / (diag + kappa), u1 = s f and u2 = u1 + s (f - A u1) = s (2 f - s A f).
-// When fl is given, f is also stored there in S (the fine level's later
-// passes then read the narrower copy).
-template <typename TF, typename S>
-__global__ void __launch_bounds__(kMgThreads) mg_pre2(MgDims d, double w, MgArr<const TF> fa, MgArr<S> ua,
-                                                      MgArr<S> fla, MgShift sh) {
-    const int q = mg_sys(d.nz);
-    if (!take_shift(sh, d, q)) return;
-    MgPt p;
-    if (!mg_point(d.nx, d.ny, d.nz, p)) return;
-    const TF *__restrict__ f = fa.at(q);
-    S *__restrict__ u = ua.at(q);
-    S *__restrict__ fl = fla.at(q);
-    using V = VT<S>;
-    const auto s = jacobi_factor<typename MgT<S>::C>(d, w);
-    S fc[kMgKZ], af[kMgKZ];
-    apply7_col(f, d, p, fc, af);
-    const int64_t nxy = (int64_t)d.nx * d.ny;
-#pragma unroll
-    for (int k = 0; k < kMgKZ; ++k)
-        if (p.z + k < d.nz) {
-            const int64_t i = p.i + k * nxy;
-            u[i] = mg_scale(s, V::sub(V::add(fc[k], fc[k]), mg_scale(s, af[k])));
-            if (fl) fl[i] = fc[k];
-        }
-}
+// Columns of a workgroup: thread t takes columns t, t + NT, ... (SL of them)
+// of the tile's (W + 2 HALO) x (H + 2 HALO) region less `trim` on its far
+// sides, and walks them down z together, one plane per step.  `off` is the
+// column's periodic (x, y) offset in a plane; `depth` its distance from the
+// region's near/far edge (a stage of stencil reach k is formed where depth
+// >= k); own marks the tile's own points inside the grid.
+template <int SL>
+struct MgCols {
+    int off[SL], depth[SL];
+    bool own[SL];
+};
 
-// t = u + omega (f - A u) / (diag + kappa), computed in S, stored as TO
-template <typename TF, typename S, typename TO>
-__global__ void __launch_bounds__(kMgThreads) mg_smooth(MgDims d, double w, MgArr<const TF> fa,
-                                                        MgArr<const S> ua, MgArr<TO> ta, MgShift sh) {
-    const int q = mg_sys(d.nz);
-    if (!take_shift(sh, d, q)) return;
-    MgPt p;
-    if (!mg_point(d.nx, d.ny, d.nz, p)) return;
-    const TF *__restrict__ f = fa.at(q);
-    const S *__restrict__ u = ua.at(q);
-    TO *__restrict__ t = ta.at(q);
-    using V = VT<S>;
-    const auto s = jacobi_factor<typename MgT<S>::C>(d, w);
-    S uc[kMgKZ], au[kMgKZ];
-    apply7_col(u, d, p, uc, au);
-    const int64_t nxy = (int64_t)d.nx * d.ny;
+template <int NT, int SL>
+__device__ __forceinline__ void mg_cols(const MgDims &d, const MgTile &tl, int x0, int y0, int halo, int RW,
+                                        int RH, MgCols<SL> &c) {
 #pragma unroll
-    for (int k = 0; k < kMgKZ; ++k)
-        if (p.z + k < d.nz) {
-            const int64_t i = p.i + k * nxy;
-            t[i] = cv<TO>(V::add(uc[k], mg_scale(s, V::sub(cv<S>(f[i]), au[k]))));
-        }
-}
-
-// r = f - A u
-template <typename TF, typename S>
-__global__ void __launch_bounds__(kMgThreads) mg_residual(MgDims d, MgArr<const TF> fa, MgArr<const S> ua,
-                                                          MgArr<S> ra, MgShift sh) {
-    const int q = mg_sys(d.nz);
-    if (!take_shift(sh, d, q)) return;
-    MgPt p;
-    if (!mg_point(d.nx, d.ny, d.nz, p)) return;
-    const TF *__restrict__ f = fa.at(q);
-    const S *__restrict__ u = ua.at(q);
-    S *__restrict__ r = ra.at(q);
-    S uc[kMgKZ], au[kMgKZ];
-    apply7_col(u, d, p, uc, au);
-    const int64_t nxy = (int64_t)d.nx * d.ny;
-#pragma unroll
-    for (int k = 0; k < kMgKZ; ++k)
-        if (p.z + k < d.nz) {
-            const int64_t i = p.i + k * nxy;
-            r[i] = VT<S>::sub(cv<S>(f[i]), au[k]);
-        }
-}
-
-// Full weighting: fc[I] = sum over the 27 fine points around 2I of
-// (1/8) w(dx) w(dy) w(dz) r, w(0) = 1, w(+-1) = 1/2 (= P^T / 8).  A thread
-// runs down kMgKZ coarse planes; each fine plane's 9-point (x, y) sum is
-// formed once and shared by the coarse planes it touches.
-template <typename S>
-__global__ void __launch_bounds__(kMgThreads) mg_restrict(MgDims fd, MgDims cd, MgArr<const S> ra,
-                                                          MgArr<S> fca, MgShift sh) {
-    const int qs = mg_sys(cd.nz);
-    if (sh.skip(qs)) return;
-    MgPt P;
-    if (!mg_point(cd.nx, cd.ny, cd.nz, P)) return;
-    const S *__restrict__ r = ra.at(qs);
-    S *__restrict__ fc = fca.at(qs);
-    using V = VT<S>;
-    using R = typename MgT<S>::R;
-    const int64_t fnxy = (int64_t)fd.nx * fd.ny, cnxy = (int64_t)cd.nx * cd.ny;
-    int xs[3];
-    int64_t ys[3];
-    xs[0] = P.x == 0 ? fd.nx - 1 : 2 * P.x - 1;
-    xs[1] = 2 * P.x;
-    xs[2] = 2 * P.x + 1;         // fine axes are even, so 2X + 1 < n
-    ys[0] = (int64_t)(P.y == 0 ? fd.ny - 1 : 2 * P.y - 1) * fd.nx;
-    ys[1] = (int64_t)(2 * P.y) * fd.nx;
-    ys[2] = (int64_t)(2 * P.y + 1) * fd.nx;
-    // plane sums q[j] for fine planes 2 Z0 - 1 + j, j = 0 .. 2 kMgKZ
-    S q[2 * kMgKZ + 1];
-#pragma unroll
-    for (int j = 0; j < 2 * kMgKZ + 1; ++j) {
-        int z = 2 * P.z - 1 + j;
-        z = z < 0 ? z + fd.nz : (z >= fd.nz ? fd.nz - 1 : z);    // past the end: unused, any valid plane
-        const int64_t base = (int64_t)z * fnxy;
-        S acc = V::zero();
-#pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            const R wy = b == 1 ? (R)1 : (R)0.5;
-            const S rowsum = V::add(mg_axpy((R)0.5, V::add(r[base + ys[b] + xs[0]], r[base + ys[b] + xs[2]]),
-                                            V::zero()),
-                                    r[base + ys[b] + xs[1]]);
-            acc = mg_axpy(wy, rowsum, acc);
-        }
-        q[j] = acc;
+    for (int i = 0; i < SL; ++i) {
+        const int k = threadIdx.x + i * NT;
+        const int ly = k / RW, lx = k - ly * RW;
+        const bool act = ly < RH;
+        int gx = (x0 - halo + lx) % d.nx, gy = (y0 - halo + ly) % d.ny;
+        gx += gx < 0 ? d.nx : 0;
+        gy += gy < 0 ? d.ny : 0;
+        c.off[i] = act ? gy * d.nx + gx : 0;
+        c.depth[i] = act ? min(min(lx, RW - 1 - lx), min(ly, RH - 1 - ly)) : -1;
+        c.own[i] = act && lx >= halo && lx < halo + tl.W && ly >= halo && ly < halo + tl.H &&
+                   x0 + lx - halo < d.nx && y0 + ly - halo < d.ny;
     }
-#pragma unroll
-    for (int k = 0; k < kMgKZ; ++k)
-        if (P.z + k < cd.nz) {
-            const S sz = V::add(mg_axpy((R)0.5, V::add(q[2 * k], q[2 * k + 2]), V::zero()), q[2 * k + 1]);
-            fc[P.i + k * cnxy] = V::mul((R)0.125, sz);
-        }
 }
 
-// Coarse correction (P uc) on fine plane z + K (K = -1 .. kMgKZ) from the
-// corner sums cs[j][c] of coarse block plane j (coarse plane z / 2 - 1 + j)
-// for the fine column c: 1/4 of one plane's sum (even fine plane) or 1/8 of
-// two (odd fine plane).
-template <int K, int CI, typename S, int NZC>
-__device__ __forceinline__ S mg_corr(const S (&cs)[NZC][5]) {
+// A c for the periodic 7-point operator A = -Delta_h + kappa from the centre c
+// and its neighbours' values, in the cycle's fixed order of operations.
+template <typename S, typename C>
+__device__ __forceinline__ S mg_op(const MgDims &d, C kap, S c, S xp, S xm, S yp, S ym, S zm, S zp) {
     using V = VT<S>;
     using R = typename MgT<S>::R;
-    constexpr int J = (K + 2) >> 1;              // block plane of coarse plane (z + K) >> 1
-    if constexpr (K & 1)
-        return mg_axpy((R)0.125, V::add(cs[J][CI], cs[J + 1][CI]), V::zero());
-    else
-        return V::mul((R)0.25, cs[J][CI]);
+    S a = V::mul((R)d.diag, c);
+    a = mg_axpy((R)-d.cx, V::add(xp, xm), a);
+    a = mg_axpy((R)-d.cy, V::add(yp, ym), a);
+    a = mg_axpy((R)-d.cz, V::add(zm, zp), a);
+    return V::add(a, mg_scale(kap, c));
 }
 
-// The first post-smoothing sweep with the coarse correction folded in:
-// t = v + omega (f - A v) / (diag + kappa), v = u + P uc, with P the
-// trilinear prolongation (per axis, fine index i takes coarse i/2 when i is
-// even and the mean of coarse (i-1)/2 and (i+1)/2 when odd), formed in
-// registers; v is never stored: it is the corrected u that the two
-// post-sweeps start from.  The thread's column needs v on planes z - 1 ..
-// z + kMgKZ at (x, y) and on planes z .. z + kMgKZ - 1 at the four (x, y)
-// neighbours; their coarse corners lie in a 3 x 3 block of coarse columns
-// around (x / 2, y / 2) on coarse planes z / 2 - 1 .. z / 2 + kMgKZ / 2, each
-// loaded once.
-template <typename TF, typename S>
-__global__ void __launch_bounds__(kMgThreads) mg_prolong_smooth(MgDims d, MgDims cd, double w,
-                                                                MgArr<const TF> fa, MgArr<const S> ua,
-                                                                MgArr<const S> uca, MgArr<S> ta, MgShift sh) {
-    const int q = mg_sys(d.nz);
-    if (!take_shift(sh, d, q)) return;
-    MgPt p;
-    if (!mg_point(d.nx, d.ny, d.nz, p)) return;
-    const TF *__restrict__ f = fa.at(q);
-    const S *__restrict__ u = ua.at(q);
-    const S *__restrict__ uc = uca.at(q);
-    S *__restrict__ t = ta.at(q);
+// Tile of the workgroup: origin, planes [z0, z0 + zl) and system.
+struct MgWhere {
+    int x0, y0, z0, zl, q;
+};
+__device__ inline MgWhere mg_where(const MgTile &tl, int nz) {
+    int b = xcd_remap(blockIdx.x, gridDim.x);
+    MgWhere m;
+    m.x0 = (b % tl.tx) * tl.W;
+    b /= tl.tx;
+    m.y0 = (b % tl.ty) * tl.H;
+    b /= tl.ty;
+    m.z0 = (b % tl.tz) * tl.zl;
+    m.q = b / tl.tz;
+    m.zl = min(tl.zl, nz - m.z0);
+    return m;
+}
+
+// Downward half of a level, one pass over f: the two pre-smoothing sweeps from
+// u = 0 (with the Jacobi factor s = omega / (diag + kappa), u1 = s f and
+// u2 = u1 + s (f - A u1) = s (2 f - s A f)), the residual r = f - A u2 and its
+// full weighting fc[I] = sum over the 27 fine points around 2I of
+// (1/8) w(dx) w(dy) w(dz) r, w(0) = 1, w(+-1) = 1/2 (= P^T / 8).  Stores u2,
+// fc and, when fl is given, f in S (the upward half then reads the narrower
+// copy); r is never stored.
+//
+// Bound by HBM: 16.5 B/point for FP64 f and FP32 levels (read f; write u, its
+// FP32 copy and 1/8 fc) where three separate passes moved 32.5.  The tile is
+// marched along z with one plane of f, u and r each in LDS (double-buffered:
+// every step writes one buffer and reads the one the step before wrote, so
+// one barrier per plane serves all three stages, each one plane behind the
+// one that feeds it); the z neighbours stay in registers; f is fetched two
+// planes ahead.  The (x, y) halo of 3 (2 on the far side) and 5 warm-up planes
+// per z chunk are re-read through L2.  Measured, the cycle (back to back,
+// FP64 vectors and FP32 levels, five passes per level before): 320^3 723 ->
+// 393 us, 160^3 169 -> 102 us, 96^3 109 -> 58 us; complex 160^3 260 -> 157 us.
+template <typename TF, typename S, int NT, int SL>
+__global__ void __launch_bounds__(NT) mg_down(MgDims d, MgDims cd, MgTile tl, double w, MgArr<const TF> fa,
+                                              MgArr<S> ua, MgArr<S> fla, MgArr<S> cfa, MgShift sh) {
     using V = VT<S>;
     using R = typename MgT<S>::R;
     using C = typename MgT<S>::C;
-    static_assert(kMgKZ % 2 == 0, "chunks start on even planes");
-    constexpr int NZC = kMgKZ / 2 + 2;             // coarse planes z/2 - 1 .. z/2 + kMgKZ/2
-    const int64_t nxy = (int64_t)d.nx * d.ny, cnxy = (int64_t)cd.nx * cd.ny;
-    const int cx0 = p.x >> 1, cy0 = p.y >> 1;
-    int64_t cxo[3], cyo[3];                        // block columns cx0 - 1 .. cx0 + 1, likewise y
+    __shared__ S fb[2][NT * SL], ub[2][NT * SL], rb[2][NT * SL];
+    const MgWhere m = mg_where(tl, d.nz);
+    if (!take_shift(sh, d, m.q)) return;
+    // global-space views: a pointer from a table is generic to the compiler,
+    // and flat loads would share the LDS wait counter
+    const GPtr<TF> f(fa.at(m.q));
+    const GPtr<S> u(ua.at(m.q)), fl(fla.at(m.q)), fc(cfa.at(m.q));
+    const bool keep = fla.base != nullptr;
+    const int RW = tl.W + 5, RH = tl.H + 5;
+    MgCols<SL> co;
+    mg_cols<NT, SL>(d, tl, m.x0, m.y0, 3, RW, RH, co);
+    const C s = jacobi_factor<C>(d, w), kap = mk_c<C>(d.kre, d.kim);
+    const int64_t nxy = (int64_t)d.nx * d.ny;
+    // the thread's coarse point of the tile: fine (2X, 2Y) is region column cc
+    const int tid = threadIdx.x, cw = tl.W / 2;
+    const int ciy = tid / cw, cix = tid - ciy * cw;
+    const int X = m.x0 / 2 + cix, Y = m.y0 / 2 + ciy;
+    const bool cown = ciy < tl.H / 2 && X < cd.nx && Y < cd.ny;
+    const int cc = cown ? (3 + 2 * ciy) * RW + 3 + 2 * cix : RW + 1;
+    const int64_t cxy = (int64_t)cd.nx * cd.ny;
+    const int64_t crow = (int64_t)Y * cd.nx + X;
+
+    TF fn[2][SL];                                  // f two planes ahead
+    S f0[SL], f1[SL], u0[SL], u1[SL];              // f[p-2], f[p-1], u[p-3], u[p-2] of step plane p
+    S q0 = V::zero(), q1 = V::zero();              // plane sums of the coarse point
+    int kf = (m.z0 - 3) % d.nz;                    // plane of the next fetch
+    kf += kf < 0 ? d.nz : 0;
+    int p = kf;                                    // plane of the step (periodic)
 #pragma unroll
-    for (int m = 0; m < 3; ++m) {
-        int X = cx0 - 1 + m, Y = cy0 - 1 + m;
-        X = X < 0 ? X + cd.nx : (X >= cd.nx ? X - cd.nx : X);
-        Y = Y < 0 ? Y + cd.ny : (Y >= cd.ny ? Y - cd.ny : Y);
-        cxo[m] = X;
-        cyo[m] = (int64_t)Y * cd.nx;
+    for (int j = 0; j < 2; ++j) {
+#pragma unroll
+        for (int i = 0; i < SL; ++i) fn[j][i] = f[kf * nxy + co.off[i]];
+        kf = kf + 1 == d.nz ? 0 : kf + 1;
     }
-    // Corner sums of the fine columns c = 0: (x, y), 1: (x + 1, y), 2: (x - 1, y),
-    // 3: (x, y + 1), 4: (x, y - 1) on each block plane j.  Per axis the fine
-    // column at x + dx takes block columns (x0, x1) = (0, 1), (1, 1), (1, 2)
-    // for dx = -1, 0, 1 when x is even and (1, 1), (1, 2), (2, 2) when odd
-    // (grids are even, so the parity survives the periodic wrap); a corner sum
-    // is (x0 + x1 on row y0) + (x0 + x1 on row y1).  The row sums are formed
-    // for every candidate pair and the parity selects among the values.
-    const bool px = p.x & 1, py = p.y & 1;
-    S cs[NZC][5];
 #pragma unroll
-    for (int j = 0; j < NZC; ++j) {
-        int Z = (p.z >> 1) - 1 + j;
-        Z = Z < 0 ? Z + cd.nz : (Z >= cd.nz ? Z - cd.nz : Z);
-        Z = Z >= cd.nz ? cd.nz - 1 : Z;            // chunk tail past the end: unused, any valid plane
-        const int64_t b = (int64_t)Z * cnxy;
-        S rm[3], r0[3], rp[3];                     // row sums for dx = -1, 0, +1 on block rows 0..2
+    for (int i = 0; i < SL; ++i) f0[i] = f1[i] = u0[i] = u1[i] = V::zero();
+
+    // step t: f[p] enters (p = z0 - 3 + t), u[p-1], r[p-2] are formed, r[p-3] restricted
+    auto step = [&](int t, auto pc) __attribute__((always_inline)) {
+        constexpr int B = decltype(pc)::value, Q = B ^ 1;
+        const bool live = t <= m.zl + 4;           // the last step only restricts
+        if (live) {
+            S f2[SL], un[SL];
 #pragma unroll
-        for (int my = 0; my < 3; ++my) {
-            const S c0 = uc[b + cyo[my] + cxo[0]], c1 = uc[b + cyo[my] + cxo[1]], c2 = uc[b + cyo[my] + cxo[2]];
-            const S s01 = V::add(c0, c1), s11 = V::add(c1, c1), s12 = V::add(c1, c2), s22 = V::add(c2, c2);
-            rm[my] = px ? s11 : s01;
-            r0[my] = px ? s12 : s11;
-            rp[my] = px ? s22 : s12;
+            for (int i = 0; i < SL; ++i) f2[i] = cv<S>(fn[B][i]);
+            if (t + 2 <= m.zl + 4) {
+#pragma unroll
+                for (int i = 0; i < SL; ++i) fn[B][i] = f[kf * nxy + co.off[i]];
+                kf = kf + 1 == d.nz ? 0 : kf + 1;
+            }
+#pragma unroll
+            for (int i = 0; i < SL; ++i) {
+                const int c = tid + i * NT;
+                fb[B][c] = f2[i];
+                if (keep && co.own[i] && t >= 3 && t <= m.zl + 2) fl.st(p * nxy + co.off[i], f2[i]);
+                un[i] = V::zero();
+                if (t >= 2 && co.depth[i] >= 1) {
+                    const S af = mg_op<S>(d, kap, f1[i], fb[Q][c + 1], fb[Q][c - 1], fb[Q][c + RW], fb[Q][c - RW],
+                                          f0[i], f2[i]);
+                    un[i] = mg_scale(s, V::sub(V::add(f1[i], f1[i]), mg_scale(s, af)));
+                    ub[B][c] = un[i];
+                    if (co.own[i] && t >= 4 && t <= m.zl + 3)
+                        u.st((p == 0 ? d.nz - 1 : p - 1) * nxy + co.off[i], un[i]);
+                }
+                if (t >= 4 && co.depth[i] >= 2) {
+                    const S au = mg_op<S>(d, kap, u1[i], ub[Q][c + 1], ub[Q][c - 1], ub[Q][c + RW], ub[Q][c - RW],
+                                          u0[i], un[i]);
+                    rb[B][c] = V::sub(f0[i], au);
+                }
+                f0[i] = f1[i];
+                f1[i] = f2[i];
+                u0[i] = u1[i];
+                u1[i] = un[i];
+            }
+            p = p + 1 == d.nz ? 0 : p + 1;
         }
-        // rows (y0, y1): dy = 0 -> (1, 1) even / (1, 2) odd; +1 -> (1, 2) / (2, 2); -1 -> (0, 1) / (1, 1)
-        cs[j][0] = py ? V::add(r0[1], r0[2]) : V::add(r0[1], r0[1]);
-        cs[j][1] = py ? V::add(rp[1], rp[2]) : V::add(rp[1], rp[1]);
-        cs[j][2] = py ? V::add(rm[1], rm[2]) : V::add(rm[1], rm[1]);
-        cs[j][3] = py ? V::add(r0[2], r0[2]) : V::add(r0[1], r0[2]);
-        cs[j][4] = py ? V::add(r0[1], r0[1]) : V::add(r0[0], r0[1]);
+        if (t >= 5 && cown) {
+            S acc = V::zero();
+#pragma unroll
+            for (int b = -1; b <= 1; ++b) {
+                const S *row = rb[Q] + cc + b * RW;
+                const S rowsum = V::add(mg_axpy((R)0.5, V::add(row[-1], row[1]), V::zero()), row[0]);
+                acc = mg_axpy(b == 0 ? (R)1 : (R)0.5, rowsum, acc);
+            }
+            if constexpr (B == 1) {                // odd fine plane: closes coarse plane Z, opens Z + 1
+                if (t >= 7) {
+                    const S sz = V::add(mg_axpy((R)0.5, V::add(q0, acc), V::zero()), q1);
+                    fc.st(((m.z0 + t - 7) >> 1) * cxy + crow, V::mul((R)0.125, sz));
+                }
+                q0 = acc;
+            } else {
+                q1 = acc;
+            }
+        }
+        __syncthreads();
+    };
+    for (int t = 0; t <= m.zl + 5; t += 2) {       // zl is even
+        step(t, std::integral_constant<int, 0>{});
+        step(t + 1, std::integral_constant<int, 1>{});
     }
-    const int64_t row = (int64_t)p.y * d.nx + p.x;
-    const int dxp = p.x + 1 == d.nx ? -p.x : 1, dxm = p.x == 0 ? d.nx - 1 : -1;
-    const int64_t dyp = p.y + 1 == d.ny ? -(int64_t)p.y * d.nx : d.nx;
-    const int64_t dym = p.y == 0 ? (int64_t)(d.ny - 1) * d.nx : -(int64_t)d.nx;
-    // v on the centre column, planes z - 1 .. z + kMgKZ
-    S col[kMgKZ + 2];
-    static_for<0, kMgKZ + 2>([&](auto kc) __attribute__((always_inline)) {
-        constexpr int k = decltype(kc)::value;
-        int z = p.z - 1 + k;
-        z = z < 0 ? z + d.nz : (z >= d.nz ? z - d.nz : z);
-        z = z >= d.nz ? d.nz - 1 : z;              // chunk tail past nz: any valid plane
-        col[k] = V::add(u[(int64_t)z * nxy + row], mg_corr<k - 1, 0>(cs));
-    });
-    const C kap = mk_c<C>(d.kre, d.kim);
-    const auto s = jacobi_factor<C>(d, w);
-    static_for<0, kMgKZ>([&](auto kc) __attribute__((always_inline)) {
-        constexpr int k = decltype(kc)::value;
-        if (p.z + k < d.nz) {
-            const int64_t i = (int64_t)(p.z + k) * nxy + row;
-            const S c = col[k + 1];
-            const S vxp = V::add(u[i + dxp], mg_corr<k, 1>(cs));
-            const S vxm = V::add(u[i + dxm], mg_corr<k, 2>(cs));
-            const S vyp = V::add(u[i + dyp], mg_corr<k, 3>(cs));
-            const S vym = V::add(u[i + dym], mg_corr<k, 4>(cs));
-            S a = V::mul((R)d.diag, c);
-            a = mg_axpy((R)-d.cx, V::add(vxp, vxm), a);
-            a = mg_axpy((R)-d.cy, V::add(vyp, vym), a);
-            a = mg_axpy((R)-d.cz, V::add(col[k], col[k + 2]), a);
-            const S av = V::add(a, mg_scale(kap, c));
-            t[i] = V::add(c, mg_scale(s, V::sub(cv<S>(f[i]), av)));
-        }
-    });
 }
 
-// Exact solve on the coarsest grid (at most 16^3 points, one workgroup, FP64):
-// A is diagonalised by the DFT, eigenvalue sum_a c_a (2 - 2 cos(2 pi k_a / n_a))
-// + kappa; with kappa = 0 the k = 0 (constant) component is set to zero.
-// tw[m] = (cos, sin)(2 pi m / len) for m < len, one table per axis.
-__device__ void dft_axis(const double2 *in, double2 *out, int nx, int ny, int nz, int axis, double sign,
-                         const double2 *tw) {
-    const int n = nx * ny * nz;
-    const int len = axis == 0 ? nx : (axis == 1 ? ny : nz);
-    const int stride = axis == 0 ? 1 : (axis == 1 ? nx : nx * ny);
-    for (int o = threadIdx.x; o < n; o += blockDim.x) {
-        const int x = o % nx, y = (o / nx) % ny, z = o / (nx * ny);
-        const int k = axis == 0 ? x : (axis == 1 ? y : z);
-        const int base = o - k * stride;
-        double re = 0.0, im = 0.0;
-        int m = 0;                                 // (j k) mod len
-        for (int j = 0; j < len; ++j) {
-            const double cs = tw[m].x, sn = sign * tw[m].y;
-            const double2 v = in[base + j * stride];
-            re += v.x * cs - v.y * sn;
-            im += v.x * sn + v.y * cs;
-            m += k;
-            if (m >= len) m -= len;
+// Upward half of a level: v = u + P uc (trilinear: per axis, fine index i takes
+// coarse i/2 when i is even and the mean of coarse (i-1)/2 and (i+1)/2 when
+// odd), then the two post-smoothing sweeps t = v + s (f - A v) and
+// z = t + s (f - A t); v and t are never stored.
+//
+// Bound by HBM: 16.5 B/point for FP32 levels and FP64 z (read f, u, 1/8 uc;
+// write z) where two passes moved 28.5.  The march of mg_down with halo 2 and
+// four warm-up planes per z chunk: v[p], t[p-1] and z[p-2] are formed in the
+// step of plane p.  A column keeps the (x, y)-interpolated coarse value of the
+// two coarse planes around it; the next one's corners are fetched a step
+// ahead.
+template <typename TF, typename S, typename TO, int NT, int SL>
+__global__ void __launch_bounds__(NT) mg_up(MgDims d, MgDims cd, MgTile tl, double w, MgArr<const TF> fa,
+                                            MgArr<const S> ua, MgArr<const S> uca, MgArr<TO> za, MgShift sh) {
+    using V = VT<S>;
+    using R = typename MgT<S>::R;
+    using C = typename MgT<S>::C;
+    __shared__ S vb[2][NT * SL], tb[2][NT * SL];
+    const MgWhere m = mg_where(tl, d.nz);
+    if (!take_shift(sh, d, m.q)) return;
+    const GPtr<TF> f(fa.at(m.q));
+    const GPtr<S> u(ua.at(m.q)), uc(uca.at(m.q));
+    const GPtr<TO> z(za.at(m.q));
+    const int tid = threadIdx.x, RW = tl.W + 4, RH = tl.H + 4;
+    MgCols<SL> co;
+    mg_cols<NT, SL>(d, tl, m.x0, m.y0, 2, RW, RH, co);
+    const C s = jacobi_factor<C>(d, w), kap = mk_c<C>(d.kre, d.kim);
+    const int64_t nxy = (int64_t)d.nx * d.ny, cxy = (int64_t)cd.nx * cd.ny;
+    // coarse corners of each column: (ya, xa), (ya, xb), (yb, xa), (yb, xb)
+    int c00[SL], dxc[SL], dyc[SL];
+#pragma unroll
+    for (int i = 0; i < SL; ++i) {
+        const int gy = co.off[i] / d.nx, gx = co.off[i] - gy * d.nx;
+        const int xa = gx >> 1, ya = gy >> 1;
+        const int xb = gx & 1 ? (xa + 1 == cd.nx ? 0 : xa + 1) : xa;
+        const int yb = gy & 1 ? (ya + 1 == cd.ny ? 0 : ya + 1) : ya;
+        c00[i] = ya * cd.nx + xa;
+        dxc[i] = xb - xa;
+        dyc[i] = (yb - ya) * cd.nx;
+    }
+    int p = (m.z0 - 2) % d.nz;                     // plane of the step (periodic)
+    p += p < 0 ? d.nz : 0;
+    int kf = p;                                    // plane of the next fetch
+    S un[2][SL];
+    TF fn[2][SL];
+    S cn[4][SL];                                   // corners of the next coarse plane
+    S ca[SL];                                      // corner sum on coarse plane floor(p / 2)
+    auto corners = [&](int Z) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < SL; ++i) {
+            const int64_t b = Z * cxy + c00[i];
+            cn[0][i] = uc[b];
+            cn[1][i] = uc[b + dxc[i]];
+            cn[2][i] = uc[b + dyc[i]];
+            cn[3][i] = uc[b + dyc[i] + dxc[i]];
         }
-        out[o] = make_double2(re, im);
+    };
+    corners(p >> 1);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+#pragma unroll
+        for (int i = 0; i < SL; ++i) {
+            un[j][i] = u[kf * nxy + co.off[i]];
+            fn[j][i] = f[kf * nxy + co.off[i]];
+        }
+        kf = kf + 1 == d.nz ? 0 : kf + 1;
+    }
+    S f0[SL], f1[SL], v0[SL], v1[SL], t0[SL], t1[SL];   // f, v at p-2, p-1; t at p-3, p-2
+#pragma unroll
+    for (int i = 0; i < SL; ++i) {
+        ca[i] = V::add(V::add(cn[0][i], cn[1][i]), V::add(cn[2][i], cn[3][i]));
+        f0[i] = f1[i] = v0[i] = v1[i] = t0[i] = t1[i] = V::zero();
+    }
+    auto step = [&](int t, auto pc) __attribute__((always_inline)) {
+        constexpr int B = decltype(pc)::value, Q = B ^ 1;
+        S f2[SL], v2[SL];
+#pragma unroll
+        for (int i = 0; i < SL; ++i) {
+            f2[i] = cv<S>(fn[B][i]);
+            S corr;
+            if constexpr (B == 0) {                // even plane
+                corr = V::mul((R)0.25, ca[i]);
+            } else {
+                const S cb = V::add(V::add(cn[0][i], cn[1][i]), V::add(cn[2][i], cn[3][i]));
+                corr = mg_axpy((R)0.125, V::add(ca[i], cb), V::zero());
+                ca[i] = cb;
+            }
+            v2[i] = V::add(un[B][i], corr);
+        }
+        if constexpr (B == 0) corners((p >> 1) + 1 == cd.nz ? 0 : (p >> 1) + 1);
+        if (t + 2 <= m.zl + 3) {
+#pragma unroll
+            for (int i = 0; i < SL; ++i) {
+                un[B][i] = u[kf * nxy + co.off[i]];
+                fn[B][i] = f[kf * nxy + co.off[i]];
+            }
+            kf = kf + 1 == d.nz ? 0 : kf + 1;
+        }
+        const int64_t zo = (int64_t)(m.z0 + t - 4) * nxy;
+#pragma unroll
+        for (int i = 0; i < SL; ++i) {
+            const int c = tid + i * NT;
+            vb[B][c] = v2[i];
+            S tn = V::zero();
+            if (t >= 2 && co.depth[i] >= 1) {
+                const S av = mg_op<S>(d, kap, v1[i], vb[Q][c + 1], vb[Q][c - 1], vb[Q][c + RW], vb[Q][c - RW],
+                                      v0[i], v2[i]);
+                tn = V::add(v1[i], mg_scale(s, V::sub(f1[i], av)));
+                tb[B][c] = tn;
+            }
+            if (t >= 4 && co.own[i]) {
+                const S at = mg_op<S>(d, kap, t1[i], tb[Q][c + 1], tb[Q][c - 1], tb[Q][c + RW], tb[Q][c - RW],
+                                      t0[i], tn);
+                z.st(zo + co.off[i], cv<TO>(V::add(t1[i], mg_scale(s, V::sub(f0[i], at)))));
+            }
+            f0[i] = f1[i];
+            f1[i] = f2[i];
+            v0[i] = v1[i];
+            v1[i] = v2[i];
+            t0[i] = t1[i];
+            t1[i] = tn;
+        }
+        p = p + 1 == d.nz ? 0 : p + 1;
+        __syncthreads();
+    };
+    for (int t = 0; t <= m.zl + 3; t += 2) {       // zl is even
+        step(t, std::integral_constant<int, 0>{});
+        step(t + 1, std::integral_constant<int, 1>{});
     }
 }
+
+// Exact solve on the coarsest grid (at most 16^3 points, one workgroup per
+// system, FP64): A is diagonalised by the real Fourier basis (per axis the
+// orthonormal cosines and sines of 2 pi k j / n, which share the eigenvalue
+// 2 - 2 cos(2 pi k / n)), eigenvalue sum_a c_a (2 - 2 cos(2 pi k_a / n_a)) +
+// kappa; with kappa = 0 the k = 0 (constant) component is set to zero.  The
+// basis is real, so a complex system is two real ones up to the division.
+//
+// Bound by latency (six dependent axis passes in one workgroup).  An axis pass
+// is the product of the basis matrix with all pencils of the axis, on the
+// FP64 matrix cores: 16 pencils at a time, v_mfma_f64_16x16x4 over the axis
+// (lane (n, kq) supplies Q[n][4 s + kq] and point 4 s + kq of pencil n in
+// step s, and receives outputs kq + 4 i of pencil n), zero-padded to 16.  The
+// lane's part of Q stays in registers for the pass.  The cycle's coarse solve
+// at 10^3 / 12^3 took 18 / 30 us as a complex DFT with one LDS read per
+// multiply, 11 / 13 us so (profiled, real).
+constexpr int kMgTab = kMgCoarseMax * kMgCoarseMax;
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 __device__ inline double2 mg_to_c(double v) { return make_double2(v, 0.0); }
 __device__ inline double2 mg_to_c(float v) { return make_double2(v, 0.0); }
@@ -454,54 +465,102 @@ __device__ inline void mg_from_c(double2 v, float &o) { o = (float)v.x; }
 __device__ inline void mg_from_c(double2 v, double2 &o) { o = v; }
 __device__ inline void mg_from_c(double2 v, float2 &o) { o = make_float2((float)v.x, (float)v.y); }
 
+// tab: per axis the basis matrix Q (row k, column j, kMgCoarseMax apart), then
+// per axis its transpose, then per axis 2 - 2 cos(2 pi k / n).
 template <typename TI, typename TO>
-__global__ void __launch_bounds__(kMgThreads) mg_coarse_solve(MgDims d, MgArr<const TI> fa, MgArr<TO> ua,
-                                                              MgShift sh) {
-    const int q = blockIdx.x;                  // one workgroup per system
+__global__ void __launch_bounds__(kMgCoarseThreads) mg_coarse_solve(MgDims d, MgArr<const TI> fa, MgArr<TO> ua,
+                                                                    MgShift sh, const double *__restrict__ tab) {
+    constexpr int NC = VT<TI>::ncomp;
+    constexpr int kRow = kMgCoarseMax + 1;         // odd row pitch: no bank conflicts along x
+    constexpr int kPlane = kRow * kMgCoarseMax * kMgCoarseMax;
+    __shared__ double a[NC * kPlane];
+    constexpr int kTab = 6 * kMgTab + 3 * kMgCoarseMax;
+    __shared__ double tl[kTab];
+    const int q = blockIdx.x;                      // one workgroup per system
     if (!take_shift(sh, d, q)) return;
-    const TI *__restrict__ f = fa.at(q);
-    TO *__restrict__ u = ua.at(q);
-    __shared__ double2 a[kMgCoarseMax * kMgCoarseMax * kMgCoarseMax];
-    __shared__ double2 b[kMgCoarseMax * kMgCoarseMax * kMgCoarseMax];
-    __shared__ double2 tw[3][kMgCoarseMax];
-    const int n = (int)d.n;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) a[i] = mg_to_c(f[i]);
-    for (int i = threadIdx.x; i < 3 * kMgCoarseMax; i += blockDim.x) {
-        const int ax = i / kMgCoarseMax, m = i % kMgCoarseMax;
-        const int len = ax == 0 ? d.nx : (ax == 1 ? d.ny : d.nz);
-        double sn = 0.0, cs = 1.0;
-        if (m < len) sincospi(2.0 * (double)m / (double)len, &sn, &cs);
-        tw[ax][m] = make_double2(cs, sn);
+    const GPtr<TI> f(fa.at(q));
+    const GPtr<TO> u(ua.at(q));
+    const int nx = d.nx, ny = d.ny, nz = d.nz, n = (int)d.n;
+    const int sy = nx | 1, sz = sy * ny;
+    // i / m for the small ranges here (i < 2^13): exact, without the integer division
+    auto quot = [](int i, float inv) { return (int)(((float)i + 0.5f) * inv); };
+    const float inx = 1.0f / (float)nx, iny = 1.0f / (float)ny;
+    const double *eig = tl + 6 * kMgTab;
+#pragma unroll
+    for (int j = 0; j < (kTab + kMgCoarseThreads - 1) / kMgCoarseThreads; ++j) {
+        const int i = threadIdx.x + j * kMgCoarseThreads;
+        if (i < kTab) tl[i] = tab[i];
     }
-    __syncthreads();
-    dft_axis(a, b, d.nx, d.ny, d.nz, 0, -1.0, tw[0]);
-    __syncthreads();
-    dft_axis(b, a, d.nx, d.ny, d.nz, 1, -1.0, tw[1]);
-    __syncthreads();
-    dft_axis(a, b, d.nx, d.ny, d.nz, 2, -1.0, tw[2]);
-    __syncthreads();
-    for (int o = threadIdx.x; o < n; o += blockDim.x) {
-        const int x = o % d.nx, y = (o / d.nx) % d.ny, z = o / (d.nx * d.ny);
-        const double lr = d.cx * (2.0 - 2.0 * tw[0][x].x) + d.cy * (2.0 - 2.0 * tw[1][y].x) +
-                          d.cz * (2.0 - 2.0 * tw[2][z].x) + d.kre;
-        const double li = d.kim, den = lr * lr + li * li;
-        double2 v = b[o];
-        if (den == 0.0) {
-            v = make_double2(0.0, 0.0);
-        } else {   // v / (lr + i li) / n
-            const double sr = lr / (den * n), si = -li / (den * n);
-            v = make_double2(v.x * sr - v.y * si, v.x * si + v.y * sr);
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, pn = lane & 15, kq = lane >> 4;
+    constexpr int kPer = kMgCoarseMax * kMgCoarseMax * kMgCoarseMax / kMgCoarseThreads;
+    TI fv[kPer];                                   // every load in flight before the first use
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const int i = threadIdx.x + j * kMgCoarseThreads;
+        fv[j] = f[i < n ? i : 0];
+    }
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const int i = threadIdx.x + j * kMgCoarseThreads;
+        if (i < n) {
+            const int r = quot(i, inx), o = r * sy + i - r * nx;
+            const double2 v = mg_to_c(fv[j]);
+            a[o] = v.x;
+            if constexpr (NC == 2) a[kPlane + o] = v.y;
         }
-        b[o] = v;
     }
     __syncthreads();
-    dft_axis(b, a, d.nx, d.ny, d.nz, 0, 1.0, tw[0]);
-    __syncthreads();
-    dft_axis(a, b, d.nx, d.ny, d.nz, 1, 1.0, tw[1]);
-    __syncthreads();
-    dft_axis(b, a, d.nx, d.ny, d.nz, 2, 1.0, tw[2]);
-    __syncthreads();
-    for (int i = threadIdx.x; i < n; i += blockDim.x) mg_from_c(a[i], u[i]);
+    for (int pass = 0; pass < 6; ++pass) {         // Q on x, y, z, then Q^T on x, y, z
+        const int ax = pass < 3 ? pass : pass - 3;
+        const int len = ax == 0 ? nx : (ax == 1 ? ny : nz);
+        const int stride = ax == 0 ? 1 : (ax == 1 ? sy : sz);
+        const int m = ax == 0 ? ny : nx;           // pencils: (y, z), (x, z) or (x, y)
+        const int sa = ax == 0 ? sy : 1, sb = ax == 2 ? sy : sz;
+        const int pencils = n / len;
+        double qv[4];                              // Q[pn][4 s + kq]; zero beyond the axis
+#pragma unroll
+        for (int st = 0; st < 4; ++st) qv[st] = tl[pass * kMgTab + pn * kMgCoarseMax + 4 * st + kq];
+        for (int t0 = wave * 16; t0 < NC * pencils; t0 += (kMgCoarseThreads / 64) * 16) {
+            const int t = min(t0 + pn, NC * pencils - 1);
+            const int c = NC == 2 && t >= pencils ? 1 : 0, pt = t - c * pencils;
+            const int pb = quot(pt, ax == 0 ? iny : inx), pa = pt - pb * m;
+            double *v = a + c * kPlane + pa * sa + pb * sb;
+            f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int st = 0; st < 4; ++st) {
+                const int k = 4 * st + kq;
+                const double x = k < len ? v[k * stride] : 0.0;
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(qv[st], x, acc, 0, 0, 0);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (kq + 4 * i < len && t0 + pn < NC * pencils) v[(kq + 4 * i) * stride] = acc[i];
+        }
+        __syncthreads();
+        if (pass == 2) {
+            for (int i = threadIdx.x; i < n; i += blockDim.x) {
+                const int r = quot(i, inx), x = i - r * nx, z = quot(r, iny), y = r - z * ny, o = r * sy + x;
+                const double lr = d.cx * eig[x] + d.cy * eig[kMgCoarseMax + y] + d.cz * eig[2 * kMgCoarseMax + z] + d.kre;
+                const double li = d.kim, den = lr * lr + li * li;
+                const double id = den == 0.0 ? 0.0 : 1.0 / den, wr = lr * id, wi = -li * id;
+                const double vr = a[o];
+                if constexpr (NC == 2) {
+                    const double vi = a[kPlane + o];
+                    a[o] = vr * wr - vi * wi;
+                    a[kPlane + o] = vr * wi + vi * wr;
+                } else {
+                    a[o] = vr * wr;
+                }
+            }
+            __syncthreads();
+        }
+    }
+    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+        const int r = quot(i, inx), o = r * sy + i - r * nx;
+        TO v;
+        mg_from_c(make_double2(a[o], NC == 2 ? a[(NC - 1) * kPlane + o] : 0.0), v);
+        u.st(i, v);
+    }
 }
 
 // Level array of systems q0 .. q0 + count - 1 of a hierarchy.
@@ -510,84 +569,150 @@ MgArr<S> lvl(void *base, const MgLevel &L, int q0) {
     return MgArr<S>{base ? (S *)base + (int64_t)q0 * L.n : nullptr, L.n, nullptr};
 }
 
-// V(2,2) cycle on level l >= 1 (arrays of S) of `count` systems from q0: f -> u.
-template <typename S>
-int vcycle_coarse(Multigrid &mg, int l, int q0, int count, double2 kappa, MgShift sh, hipStream_t s) {
-    MgLevel &L = mg.lv[l];
-    const MgDims d = dims_of(L, kappa);
-    const MgArr<S> f = lvl<S>(L.f, L, q0), u = lvl<S>(L.u, L, q0), t = lvl<S>(L.t, L, q0), r = lvl<S>(L.r, L, q0);
-    const MgArr<const S> fc{f.base, f.stride, nullptr}, uc_{u.base, u.stride, nullptr},
-        tc{t.base, t.stride, nullptr}, rc{r.base, r.stride, nullptr};
-    if (l + 1 == (int)mg.lv.size()) {
-        hipLaunchKernelGGL((mg_coarse_solve<S, S>), dim3(count), dim3(kMgThreads), 0, s, d, fc, u, sh);
-        OFDFT_CHECK_HIP(hipGetLastError());
-        return OFDFT_OK;
+// Column capacities of the cycle kernels' workgroups (threads x columns per
+// thread).
+constexpr int kMgCaps[4] = {256, 512, 1024, 2048};
+
+// The tile of a level: the smallest modelled time over the column capacities
+// and the even splits of the axes.  `halo` is the (x, y) region's excess over
+// the tile, `warm` the extra z steps of a chunk, `bufs` the LDS planes held.
+// A step of a workgroup costs a latency (barrier, LDS round trip, the wait
+// for the fetch two planes back) or, with enough columns resident on the
+// compute unit, its columns' share of the bandwidth.  So large grids take
+// large tiles and long chunks (little halo and warm-up), and small ones many
+// small workgroups.  Measured at 320^3 (down / up, us): 2048 columns 148 / 140,
+// 1024 columns 150 / 174, 512 200 / 168, 256 225 / 217; at 96^3 2048 columns
+// 13 / 12, 256 columns 12 / 10; at 24^3 9 / 10 and 6 / 6.
+MgTile mg_pick_tile(const MgLevel &L, int count, size_t elem, int halo, int warm, int bufs, int &cap) {
+    constexpr double kStep = 0.55, kCol = 0.0008;     // us; kCol per column of 4 bytes
+    MgTile best{};
+    double best_cost = -1.0;
+    cap = kMgCaps[0];
+    for (int cols : kMgCaps) {
+        const size_t lds = elem * cols * bufs;
+        if (lds > 100 * 1024 || (elem == 16 && cols > 1024)) break;    // complex128: registers
+        const int threads = cols >= 1024 ? 512 : 256;
+        const int occ = std::max(1, std::min((int)(160 * 1024 / lds), 1536 / threads));
+        for (int tx = 1; tx <= L.nx / 2; ++tx) {
+            const int W = 2 * ((L.nx / 2 + tx - 1) / tx);
+            if (W > 128) continue;
+            if (W < 8 && tx > 1) break;
+            if (tx > 1 && W * (tx - 1) >= L.nx) continue;          // an empty last tile
+            const int hmax = (cols / (W + halo) - halo) & ~1;
+            if (hmax < 2) continue;
+            const int ty = (L.ny / 2 + hmax / 2 - 1) / (hmax / 2);
+            const int H = 2 * ((L.ny / 2 + ty - 1) / ty);
+            for (int tz = 1; tz <= L.nz / 2; ++tz) {
+                const int zl = 2 * ((L.nz / 2 + tz - 1) / tz);
+                if (tz > 1 && zl * (tz - 1) >= L.nz) continue;
+                const double blocks = (double)tx * ty * tz * count;
+                const double cu = std::min((double)occ, std::ceil(blocks / 256.0));
+                const double waves = std::ceil(blocks / (256.0 * occ));
+                const double step = std::max(kStep, cu * cols * kCol * (double)elem / 4.0);
+                const double cost = waves * (zl + warm) * step;
+                if (best_cost < 0.0 || cost < best_cost) {
+                    best_cost = cost;
+                    best = MgTile{W, H, zl, tx, ty, tz};
+                    cap = cols;
+                }
+                if (zl <= 4) break;
+            }
+        }
     }
-    const dim3 grid = mg_grid(L.nx, L.ny, L.nz, count), block(kMgBX, kMgBY);
-    MgLevel &C = mg.lv[l + 1];
-    const MgDims cd = dims_of(C, kappa);
-    const MgArr<S> cf = lvl<S>(C.f, C, q0);
-    const MgArr<const S> cu{(const S *)C.u + (int64_t)q0 * C.n, C.n, nullptr};
-    const MgArr<S> none{nullptr, 0, nullptr};
-    hipLaunchKernelGGL((mg_pre2<S, S>), grid, block, 0, s, d, mg.omega, fc, u, none, sh);
-    hipLaunchKernelGGL((mg_residual<S, S>), grid, block, 0, s, d, fc, uc_, r, sh);
-    hipLaunchKernelGGL(mg_restrict<S>, mg_grid(C.nx, C.ny, C.nz, count), block, 0, s, d, cd, rc, cf, sh);
-    OFDFT_CHECK_HIP(hipGetLastError());
-    OFDFT_TRY(vcycle_coarse<S>(mg, l + 1, q0, count, kappa, sh, s));
-    hipLaunchKernelGGL((mg_prolong_smooth<S, S>), grid, block, 0, s, d, cd, mg.omega, fc, uc_, cu, t, sh);
-    hipLaunchKernelGGL((mg_smooth<S, S, S>), grid, block, 0, s, d, mg.omega, fc, tc, u, sh);
+    return best;
+}
+
+template <typename TF, typename S>
+int launch_down(const MgLevel &L, const MgLevel &C, int count, double2 kappa, double omega, MgArr<const TF> f,
+                MgArr<S> u, MgArr<S> fl, MgArr<S> cf, MgShift sh, hipStream_t s) {
+    int cap;
+    const MgTile t = mg_pick_tile(L, count, sizeof(S), 5, 5, 6, cap);
+    const MgDims d = dims_of(L, kappa), cd = dims_of(C, kappa);
+    const dim3 grid(t.blocks() * count);
+    switch (cap) {
+        case 256: hipLaunchKernelGGL((mg_down<TF, S, 256, 1>), grid, dim3(256), 0, s, d, cd, t, omega, f, u, fl, cf, sh); break;
+        case 512: hipLaunchKernelGGL((mg_down<TF, S, 256, 2>), grid, dim3(256), 0, s, d, cd, t, omega, f, u, fl, cf, sh); break;
+        case 1024: hipLaunchKernelGGL((mg_down<TF, S, 512, 2>), grid, dim3(512), 0, s, d, cd, t, omega, f, u, fl, cf, sh); break;
+        default:
+            if constexpr (sizeof(S) <= 8)
+                hipLaunchKernelGGL((mg_down<TF, S, 512, 4>), grid, dim3(512), 0, s, d, cd, t, omega, f, u, fl, cf, sh);
+    }
     OFDFT_CHECK_HIP(hipGetLastError());
     return OFDFT_OK;
 }
 
+template <typename TF, typename S, typename TO>
+int launch_up(const MgLevel &L, const MgLevel &C, int count, double2 kappa, double omega, MgArr<const TF> f,
+              MgArr<const S> u, MgArr<const S> cu, MgArr<TO> z, MgShift sh, hipStream_t s) {
+    int cap;
+    const MgTile t = mg_pick_tile(L, count, sizeof(S), 4, 4, 4, cap);
+    const MgDims d = dims_of(L, kappa), cd = dims_of(C, kappa);
+    const dim3 grid(t.blocks() * count);
+    switch (cap) {
+        case 256: hipLaunchKernelGGL((mg_up<TF, S, TO, 256, 1>), grid, dim3(256), 0, s, d, cd, t, omega, f, u, cu, z, sh); break;
+        case 512: hipLaunchKernelGGL((mg_up<TF, S, TO, 256, 2>), grid, dim3(256), 0, s, d, cd, t, omega, f, u, cu, z, sh); break;
+        case 1024: hipLaunchKernelGGL((mg_up<TF, S, TO, 512, 2>), grid, dim3(512), 0, s, d, cd, t, omega, f, u, cu, z, sh); break;
+        default:
+            if constexpr (sizeof(S) <= 8)
+                hipLaunchKernelGGL((mg_up<TF, S, TO, 512, 4>), grid, dim3(512), 0, s, d, cd, t, omega, f, u, cu, z, sh);
+    }
+    OFDFT_CHECK_HIP(hipGetLastError());
+    return OFDFT_OK;
+}
+
+// V(2,2) cycle on level l >= 1 (arrays of S) of `count` systems from q0:
+// f -> t (the coarsest level: f -> t by the exact solve).
+template <typename S>
+int vcycle_coarse(Multigrid &mg, int l, int q0, int count, double2 kappa, MgShift sh, hipStream_t s) {
+    MgLevel &L = mg.lv[l];
+    const MgArr<S> u = lvl<S>(L.u, L, q0), t = lvl<S>(L.t, L, q0);
+    const MgArr<const S> f{(const S *)L.f + (int64_t)q0 * L.n, L.n, nullptr}, uc{u.base, u.stride, nullptr};
+    if (l + 1 == (int)mg.lv.size()) {
+        const MgDims d = dims_of(L, kappa);
+        hipLaunchKernelGGL((mg_coarse_solve<S, S>), dim3(count), dim3(kMgCoarseThreads), 0, s, d, f, t, sh, mg.tab);
+        OFDFT_CHECK_HIP(hipGetLastError());
+        return OFDFT_OK;
+    }
+    MgLevel &C = mg.lv[l + 1];
+    const MgArr<S> none{nullptr, 0, nullptr};
+    OFDFT_TRY((launch_down<S, S>(L, C, count, kappa, mg.omega, f, u, none, lvl<S>(C.f, C, q0), sh, s)));
+    OFDFT_TRY(vcycle_coarse<S>(mg, l + 1, q0, count, kappa, sh, s));
+    const MgArr<const S> ct{(const S *)C.t + (int64_t)q0 * C.n, C.n, nullptr};
+    return launch_up<S, S, S>(L, C, count, kappa, mg.omega, f, uc, ct, t, sh, s);
+}
+
 // The whole cycle z = M f for `count` systems from q0 of the hierarchy: level
-// 0 reads f and writes z in FP64 (TIO), its work arrays are S.  V(2,2): both
-// pre-sweeps in one pass into u, residual, coarse correction folded into the
-// first post-sweep u -> t, second post-sweep t -> z.  With S narrower than
-// TIO the pre-sweep pass also stores f in S (level 0's f array), which the
-// residual and the post-sweeps read instead of the FP64 input.  f, z and sh
-// address system q0 first.
+// 0 reads f and writes z in FP64 (TIO), its work arrays are S.  V(2,2), two
+// kernels per level.  With S narrower than TIO the downward half also stores
+// f in S (level 0's f array), which the upward half reads instead of the FP64
+// input.  f, z and sh address system q0 first.
 template <typename TIO, typename S>
 int vcycle(Multigrid &mg, int q0, int count, MgArr<const TIO> f, MgArr<TIO> z, double2 kappa, MgShift sh,
            hipStream_t s) {
     MgLevel &L = mg.lv[0];
-    const MgDims d = dims_of(L, kappa);
     if (mg.lv.size() == 1) {
-        hipLaunchKernelGGL((mg_coarse_solve<TIO, TIO>), dim3(count), dim3(kMgThreads), 0, s, d, f, z, sh);
+        const MgDims d = dims_of(L, kappa);
+        hipLaunchKernelGGL((mg_coarse_solve<TIO, TIO>), dim3(count), dim3(kMgCoarseThreads), 0, s, d, f, z, sh, mg.tab);
         OFDFT_CHECK_HIP(hipGetLastError());
         return OFDFT_OK;
     }
-    const dim3 grid = mg_grid(L.nx, L.ny, L.nz, count), block(kMgBX, kMgBY);
-    const MgArr<S> u = lvl<S>(L.u, L, q0), t = lvl<S>(L.t, L, q0), r = lvl<S>(L.r, L, q0);
-    const MgArr<const S> uc_{u.base, u.stride, nullptr}, tc{t.base, t.stride, nullptr},
-        rc{r.base, r.stride, nullptr};
+    const MgArr<S> u = lvl<S>(L.u, L, q0);
+    const MgArr<const S> uc{u.base, u.stride, nullptr};
     MgLevel &C = mg.lv[1];
-    const MgDims cd = dims_of(C, kappa);
     const MgArr<S> cf = lvl<S>(C.f, C, q0);
-    const MgArr<const S> cu{(const S *)C.u + (int64_t)q0 * C.n, C.n, nullptr};
+    const MgArr<const S> ct{(const S *)C.t + (int64_t)q0 * C.n, C.n, nullptr};
     if constexpr (sizeof(S) < sizeof(TIO)) {
         const MgArr<S> fl = lvl<S>(L.f, L, q0);
         const MgArr<const S> flc{fl.base, fl.stride, nullptr};
-        hipLaunchKernelGGL((mg_pre2<TIO, S>), grid, block, 0, s, d, mg.omega, f, u, fl, sh);
-        hipLaunchKernelGGL((mg_residual<S, S>), grid, block, 0, s, d, flc, uc_, r, sh);
+        OFDFT_TRY((launch_down<TIO, S>(L, C, count, kappa, mg.omega, f, u, fl, cf, sh, s)));
+        OFDFT_TRY(vcycle_coarse<S>(mg, 1, q0, count, kappa, sh, s));
+        return launch_up<S, S, TIO>(L, C, count, kappa, mg.omega, flc, uc, ct, z, sh, s);
     } else {
         const MgArr<S> none{nullptr, 0, nullptr};
-        hipLaunchKernelGGL((mg_pre2<TIO, S>), grid, block, 0, s, d, mg.omega, f, u, none, sh);
-        hipLaunchKernelGGL((mg_residual<TIO, S>), grid, block, 0, s, d, f, uc_, r, sh);
+        OFDFT_TRY((launch_down<TIO, S>(L, C, count, kappa, mg.omega, f, u, none, cf, sh, s)));
+        OFDFT_TRY(vcycle_coarse<S>(mg, 1, q0, count, kappa, sh, s));
+        return launch_up<TIO, S, TIO>(L, C, count, kappa, mg.omega, f, uc, ct, z, sh, s);
     }
-    hipLaunchKernelGGL(mg_restrict<S>, mg_grid(C.nx, C.ny, C.nz, count), block, 0, s, d, cd, rc, cf, sh);
-    OFDFT_CHECK_HIP(hipGetLastError());
-    OFDFT_TRY(vcycle_coarse<S>(mg, 1, q0, count, kappa, sh, s));
-    if constexpr (sizeof(S) < sizeof(TIO)) {
-        const MgArr<const S> flc{(const S *)L.f + (int64_t)q0 * L.n, L.n, nullptr};
-        hipLaunchKernelGGL((mg_prolong_smooth<S, S>), grid, block, 0, s, d, cd, mg.omega, flc, uc_, cu, t, sh);
-        hipLaunchKernelGGL((mg_smooth<S, S, TIO>), grid, block, 0, s, d, mg.omega, flc, tc, z, sh);
-    } else {
-        hipLaunchKernelGGL((mg_prolong_smooth<TIO, S>), grid, block, 0, s, d, cd, mg.omega, f, uc_, cu, t, sh);
-        hipLaunchKernelGGL((mg_smooth<TIO, S, TIO>), grid, block, 0, s, d, mg.omega, f, tc, z, sh);
-    }
-    OFDFT_CHECK_HIP(hipGetLastError());
-    return OFDFT_OK;
 }
 
 }  // namespace
@@ -636,10 +761,15 @@ int mg_create(Multigrid &mg, const ofdft_grid &g, int elem_bytes, bool fp32, int
     for (int l = 0; l < nlev; ++l) {
         MgLevel &M = mg.lv[l];
         const size_t b = es * (size_t)M.n * (size_t)groups;
-        void **own[4] = {&M.t, &M.r, &M.u, &M.f};
-        // level 0 reads the caller's f (and keeps an FP32 copy of it when the
-        // levels are FP32); a one-level hierarchy needs nothing
-        const int count = nlev == 1 ? 0 : (l == 0 && !fp32 ? 3 : 4);
+        // u: every level with a coarser one; f: levels below the first, and an
+        // FP32 copy of the caller's f on the first when the levels are FP32;
+        // t: the level's solution, below the first (the caller's z there).  A
+        // one-level hierarchy needs nothing.
+        void **own[3];
+        int count = 0;
+        if (l + 1 < nlev) own[count++] = &M.u;
+        if (nlev > 1 && (l > 0 || fp32)) own[count++] = &M.f;
+        if (l > 0) own[count++] = &M.t;
         for (int k = 0; k < count; ++k) {
             void *p = nullptr;
             if (hipMalloc(&p, b) != hipSuccess) {
@@ -651,6 +781,35 @@ int mg_create(Multigrid &mg, const ofdft_grid &g, int elem_bytes, bool fp32, int
             *own[k] = p;
         }
     }
+    // tables of the coarsest grid's exact solve
+    const MgLevel &B = mg.lv.back();
+    std::vector<double> tab(6 * kMgTab + 3 * kMgCoarseMax, 0.0);
+    for (int ax = 0; ax < 3; ++ax) {
+        const int len = ax == 0 ? B.nx : (ax == 1 ? B.ny : B.nz);
+        for (int k = 0; k < len; ++k) {
+            const double th = 2.0 * 3.14159265358979323846 / len;
+            const double c = std::sqrt((k == 0 || 2 * k == len ? 1.0 : 2.0) / len);
+            for (int j = 0; j < len; ++j) {
+                const double w = 2 * k <= len ? c * std::cos(th * (k * j % len)) : c * std::sin(th * ((len - k) * j % len));
+                tab[ax * kMgTab + k * kMgCoarseMax + j] = w;
+                tab[(3 + ax) * kMgTab + j * kMgCoarseMax + k] = w;
+            }
+            tab[6 * kMgTab + ax * kMgCoarseMax + k] = k == 0 ? 0.0 : 2.0 - 2.0 * std::cos(th * k);
+        }
+    }
+    void *p = nullptr;
+    if (hipMalloc(&p, sizeof(double) * tab.size()) != hipSuccess) {
+        mg_free(mg);
+        set_error("multigrid: out of device memory");
+        return OFDFT_NO_MEMORY;
+    }
+    mg.allocs.push_back(p);
+    mg.tab = (double *)p;
+    if (hipMemcpy(p, tab.data(), sizeof(double) * tab.size(), hipMemcpyHostToDevice) != hipSuccess) {
+        mg_free(mg);
+        set_error("multigrid: table upload failed");
+        return OFDFT_HIP_ERROR;
+    }
     return OFDFT_OK;
 }
 
@@ -658,6 +817,7 @@ void mg_free(Multigrid &mg) {
     for (void *p : mg.allocs) (void)hipFree(p);
     mg.allocs.clear();
     mg.lv.clear();
+    mg.tab = nullptr;
 }
 
 int mg_apply(Multigrid &mg, const double *r, double *z, hipStream_t s, double kappa) {
@@ -705,21 +865,19 @@ int mg_apply_shifted_group(Multigrid &mg, int count, const double2 *const *r, do
                    : vcycle<double2, double2>(mg, 0, count, f, o, k, sh, s);
 }
 
-// Algorithmic bytes of one cycle.  Fine level, FP64 levels: f is read by the
-// pre-smoothing, the residual and both post-sweeps, z written once, and the
-// work arrays move 7.25 elements per point (u written; residual reads u and
-// writes r; restriction reads r and writes an eighth; the first post-sweep
-// reads u and an eighth (the coarse correction) and writes t; the second
-// reads t).  FP32 levels: f (FP64) is read once and stored as FP32, which the
-// other three passes read (4 more FP32 moves).  Each coarser level moves
-// 12.25 elements per point, and they hold 1/7 of the fine points in all.
+// Algorithmic bytes of one cycle.  Fine level, FP64 levels: the downward half
+// reads f and writes u and an eighth of an element (the restricted residual),
+// the upward half reads f, u and an eighth (the coarse correction) and writes
+// z: 5.25 elements per point.  FP32 levels: f (FP64) is read once and stored
+// as FP32, which the upward half reads.  Each coarser level moves 5.25
+// elements per point, and they hold 1/7 of the fine points in all.
 double mg_cycle_bytes(const Multigrid &mg) {
     if (mg.lv.empty()) return 0.0;
     const double E = (double)mg.elem, e = mg.fp32 ? E / 2 : E;
     const double n = (double)mg.lv[0].n;
     if (mg.lv.size() == 1) return 2.0 * n * E;
-    const double fine = mg.fp32 ? 2.0 * E + 11.25 * e : 5.0 * E + 7.25 * e;
-    return n * fine + n / 7.0 * 12.25 * e;
+    const double fine = mg.fp32 ? 2.0 * E + 4.25 * e : 3.0 * E + 2.25 * e;
+    return n * fine + n / 7.0 * 5.25 * e;
 }
 
 // CG on the projected Poisson system preconditioned by the V-cycle (flexible

@@ -22,7 +22,7 @@ struct MgLevel {
     int nx = 0, ny = 0, nz = 0;
     double cx = 0, cy = 0, cz = 0;   // 1 / h_a^2
     int64_t n = 0;
-    void *u = nullptr, *t = nullptr, *f = nullptr, *r = nullptr;   // FP64 or complex128
+    void *u = nullptr, *t = nullptr, *f = nullptr;   // element type of the levels
 };
 
 struct Multigrid {
@@ -32,6 +32,7 @@ struct Multigrid {
     int elem = 8;                // input / output element bytes: 8 (FP64) or 16 (complex128)
     bool fp32 = true;            // level arrays and their arithmetic in FP32 (else FP64)
     int groups = 1;              // systems whose level arrays the hierarchy holds (same grid)
+    const double *tab = nullptr; // coarsest grid: basis matrices and eigenvalues (device)
     std::vector<void *> allocs;
 };
 
