@@ -284,11 +284,11 @@ extern "C" int ofdft_anderson_create(int64_t n, int m, double zeta, ofdft_anders
         hipMalloc(&a->f_prev, n * sizeof(double)) != hipSuccess ||
         hipMalloc(&a->st, sizeof(AndState)) != hipSuccess ||
         hipMalloc(&a->partials, sizeof(double) * kAndBlocks * kAndMaxK) != hipSuccess ||
-        hipMalloc(&a->counter, 256) != hipSuccess) {
+        hipMalloc(&a->counter, sizeof(unsigned int) * kArriveWords) != hipSuccess) {
         set_error("ofdft_anderson_create: out of device memory");
         return fail(OFDFT_NO_MEMORY);
     }
-    if (hipMemset(a->counter, 0, 256) != hipSuccess) return fail(OFDFT_HIP_ERROR);
+    if (hipMemset(a->counter, 0, sizeof(unsigned int) * kArriveWords) != hipSuccess) return fail(OFDFT_HIP_ERROR);
     int st = ofdft_anderson_reset(a);
     if (st != OFDFT_OK) return fail(st);
     *out = a;

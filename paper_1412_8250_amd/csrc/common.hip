@@ -84,8 +84,8 @@ int check_grid(const ofdft_grid *g, int radius) {
 
 int redbuf_alloc(RedBuf &rb) {
     OFDFT_CHECK_HIP(hipMalloc(&rb.partials, sizeof(double) * kRedSlots * kRedMaxK));
-    OFDFT_CHECK_HIP(hipMalloc(&rb.counter, 256));
-    OFDFT_CHECK_HIP(hipMemset(rb.counter, 0, 256));
+    OFDFT_CHECK_HIP(hipMalloc(&rb.counter, sizeof(unsigned int) * kArriveWords));
+    OFDFT_CHECK_HIP(hipMemset(rb.counter, 0, sizeof(unsigned int) * kArriveWords));
     return OFDFT_OK;
 }
 

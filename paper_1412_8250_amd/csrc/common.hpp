@@ -160,9 +160,23 @@ __device__ inline void block_sum(double (&x)[K], double *scratch) {
     }
 }
 
+// Arrival counters of a reduction: a root and kArriveGroups group counters,
+// kArriveStride words apart (different memory channels), kArriveWords in all,
+// zero before the first use.  Device-scope RMWs on one address are served one
+// after another (about 12 ns each), so with one counter a launch of B blocks
+// that finish together ends no sooner than 12 B ns after: 864 blocks over
+// 884,736 points took 15.4 us, 3.5 us of them for the work.  Blocks therefore
+// arrive at a group counter and only each group's last block at the root;
+// up to kArriveDirect blocks go to the root alone (one RMW round trip less).
+constexpr int kArriveGroups = 32;
+constexpr int kArriveStride = 64;
+constexpr int kArriveWords = (1 + kArriveGroups) * kArriveStride;
+constexpr int kArriveDirect = 64;
+
 // Publish a block partial (thread 0 holds it) and return true in thread 0 of
-// the last block to arrive.  `counter` must start at 0; the last block resets
-// it.  `partials` has K * gridDim slots laid out [k][block].
+// the last block to arrive.  `counter` points to kArriveWords words that start
+// at 0; the last block (of each group and of all) resets them.  `partials` has
+// K * gridDim slots laid out [k][block].
 //
 // Visibility without a device-wide cache flush: the partials are written
 // with agent-scope atomic stores, which the gfx9 cache policy makes coherent
@@ -171,12 +185,22 @@ __device__ inline void block_sum(double (&x)[K], double *scratch) {
 // stalls the wave until every vector-memory operation it issued, stores
 // included, has been acknowledged by the memory system, and the asm
 // statement's memory clobber keeps the compiler from moving the stores past
-// it.  The last block reads the partials with agent-scope atomic loads, which
-// do not hit a stale L2 line, issued after its counter RMW has returned.  No
-// other data crosses blocks inside the kernel, so no agent-scope release
-// fence (which writes back the L2 of the XCD and costs in proportion to the
-// dirty data the kernel has produced) is needed.
+// it.  A group's last block arrives at the root after its own RMW has
+// returned, i.e. after every partial of the group has completed.  The last
+// block reads the partials with agent-scope atomic loads, which do not hit a
+// stale L2 line, issued after its RMWs have returned.  No other data crosses
+// blocks inside the kernel, so no agent-scope release fence (which writes back
+// the L2 of the XCD and costs in proportion to the dirty data the kernel has
+// produced) is needed.
 __device__ inline void wait_vector_memory() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// One arrival at `c`, true for the last of `count` (which resets the counter).
+__device__ inline bool arrive(unsigned int *c, unsigned int count) {
+    const unsigned int prev = __hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const bool last = prev == count - 1;
+    if (last) __hip_atomic_store(c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return last;
+}
 
 template <int K>
 __device__ inline bool publish_partial(const double (&x)[K], double *partials, int nblocks,
@@ -188,10 +212,17 @@ __device__ inline bool publish_partial(const double (&x)[K], double *partials, i
             __hip_atomic_store(partials + (size_t)k * nblocks + block, x[k], __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
         wait_vector_memory();
-        const unsigned int prev =
-            __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        last = (prev == (unsigned int)nblocks - 1);
-        if (last) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (nblocks <= kArriveDirect) {
+            last = arrive(counter, (unsigned int)nblocks);
+        } else {
+            const int g = block % kArriveGroups;
+            const unsigned int members = (unsigned int)((nblocks - g + kArriveGroups - 1) / kArriveGroups);
+            last = arrive(counter + (1 + g) * kArriveStride, members);
+            if (last) {
+                wait_vector_memory();
+                last = arrive(counter, (unsigned int)kArriveGroups);
+            }
+        }
     }
     return last;
 }

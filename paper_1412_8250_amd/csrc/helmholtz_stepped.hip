@@ -158,7 +158,7 @@ step_stencil(const HSys *sys, StepState *st, const int *ublk, const int *xpre, i
         double acc[4] = {ep.acc[0], ep.acc[1], ep.acc[2], ep.acc[3]};
         block_sum<4>(acc, scratch);
         double t[4];
-        if (reduce_grid<4>(acc, pj, nunits, unit, ctr + j, scratch, t)) {
+        if (reduce_grid<4>(acc, pj, nunits, unit, ctr + (size_t)j * kArriveWords, scratch, t)) {
             sj->rr_re = t[0];
             sj->rr_im = t[1];
             sj->rn2 = t[2];
@@ -186,7 +186,7 @@ step_stencil(const HSys *sys, StepState *st, const int *ublk, const int *xpre, i
         double acc[2] = {ep.acc[0], ep.acc[1]};
         block_sum<2>(acc, scratch);
         double t[2];
-        if (reduce_grid<2>(acc, pj, nunits, unit, ctr + j, scratch, t)) {
+        if (reduce_grid<2>(acc, pj, nunits, unit, ctr + (size_t)j * kArriveWords, scratch, t)) {
             const double den = t[0] * t[0] + t[1] * t[1];
             // the previous direction's x update is applied by now
             sj->xpend = 0;
@@ -232,7 +232,7 @@ step_update(const HSys *sys, StepState *st, const int *vblk, int nsys, unsigned 
     }
     block_sum<3>(acc, scratch);
     double t[3];
-    if (reduce_grid<3>(acc, part + 4 * (size_t)vblk[j], nb, lb, ctr + j, scratch, t)) {
+    if (reduce_grid<3>(acc, part + 4 * (size_t)vblk[j], nb, lb, ctr + (size_t)j * kArriveWords, scratch, t)) {
         const bool pre = h.z != nullptr;        // rho and beta come from the dot phase
         if (!pre) {
             const double rr_re = sj->rr_re, rr_im = sj->rr_im;
@@ -299,7 +299,7 @@ step_dot(const HSys *sys, StepState *st, const int *vblk, int nsys, unsigned int
     }
     block_sum<3>(acc, scratch);
     double t[3];
-    if (reduce_grid<3>(acc, part + 4 * (size_t)vblk[j], nb, lb, ctr + j, scratch, t)) {
+    if (reduce_grid<3>(acc, part + 4 * (size_t)vblk[j], nb, lb, ctr + (size_t)j * kArriveWords, scratch, t)) {
         if (!isfinite(t[0]) || !isfinite(t[1]) || !isfinite(t[2])) {
             sj->done = H_NONFINITE;
         } else if (t[0] * t[0] + t[1] * t[1] <= 1e-60 * sj->rn2 * t[2]) {
@@ -490,10 +490,10 @@ int prepare_layout(ofdft_batch *b, const std::vector<HSys> &hs, hipStream_t s) {
         OFDFT_CHECK_HIP(hipMalloc(&b->d_xpre, sizeof(int) * 8 * (nsys + 1)));
         OFDFT_CHECK_HIP(hipMalloc(&b->d_ublk, sizeof(int) * (nsys + 1)));
         OFDFT_CHECK_HIP(hipMalloc(&b->d_vblk, sizeof(int) * (nsys + 1)));
-        OFDFT_CHECK_HIP(hipMalloc(&b->d_ctr, sizeof(unsigned int) * nsys));
+        OFDFT_CHECK_HIP(hipMalloc(&b->d_ctr, sizeof(unsigned int) * kArriveWords * nsys));
         OFDFT_CHECK_HIP(hipMalloc(&b->d_step, sizeof(StepState) * nsys));
         OFDFT_CHECK_HIP(hipHostMalloc(&b->h_step, sizeof(StepState) * nsys, hipHostMallocDefault));
-        OFDFT_CHECK_HIP(hipMemsetAsync(b->d_ctr, 0, sizeof(unsigned int) * nsys, s));
+        OFDFT_CHECK_HIP(hipMemsetAsync(b->d_ctr, 0, sizeof(unsigned int) * kArriveWords * nsys, s));
     }
     const size_t slots = 4 * ((size_t)ublk[nsys] + (size_t)vblk[nsys]);
     const size_t have = 4 * ((size_t)(b->h_ublk.empty() ? 0 : b->h_ublk[nsys]) +

@@ -484,11 +484,11 @@ extern "C" int ofdft_multishift_create(const ofdft_grid *grid, int radius, int m
         (st = ms_alloc(&m->pB, vb)) || (st = ms_alloc(&m->d_state, sizeof(MsState))) ||
         (st = ms_alloc(&m->d_shift, sizeof(MsShift) * kMsMax)) ||
         (st = ms_alloc(&m->d_part, sizeof(double) * 3 * nslots)) ||
-        (st = ms_alloc(&m->d_ctr, 256)) || (st = ms_alloc(&m->d_res, sizeof(double) * kMsMax)))
+        (st = ms_alloc(&m->d_ctr, sizeof(unsigned int) * kArriveWords)) || (st = ms_alloc(&m->d_res, sizeof(double) * kMsMax)))
         return fail(st);
     for (auto &p : m->p)
         if ((st = ms_alloc(&p, vb))) return fail(st);
-    if (hipMemset(m->d_ctr, 0, 256) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
+    if (hipMemset(m->d_ctr, 0, sizeof(unsigned int) * kArriveWords) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
         set_error("ofdft_multishift_create: clearing the reduction counter failed");
         return fail(OFDFT_HIP_ERROR);
     }

@@ -2,13 +2,13 @@
 // 3.3 Poisson equation; Section 4 zero-mean convention) for callers that
 // cannot allocate device memory.  The solver's workspace -- the projected
 // right-hand side, the CG vectors r, p (two buffers) and A p, the device
-// scalars, the reduction partials and their arrival counter -- lives in one
+// scalars, the reduction partials and their arrival counters -- lives in one
 // file-scope device array instead of a context, so the call makes no device
 // allocation, no host pinned allocation, creates no event and no graph.
 //
 // Every call on a GPU shares that GPU's copy of the array and leaves its
 // contents behind; calls that overlap on one GPU (different streams or
-// threads) race on it.  The arrival counter is cleared by a kernel at the
+// threads) race on it.  The arrival counters are cleared by a kernel at the
 // start of each call; everything else is written before it is read.
 #include <chrono>
 #include <mutex>
@@ -23,13 +23,13 @@ namespace {
 constexpr int64_t kNoAllocMaxPoints = int64_t(1) << 20;
 
 // Layout in doubles: five vectors, then the CG state, totals, partials and
-// the arrival counter (each part 256-byte aligned).
+// the arrival counters (each part 256-byte aligned).
 constexpr size_t kNaVec = (size_t)kNoAllocMaxPoints;
 constexpr size_t kNaState = 5 * kNaVec;
 constexpr size_t kNaTotals = kNaState + 64;
 constexpr size_t kNaPart = kNaTotals + 32;
 constexpr size_t kNaCtr = kNaPart + (size_t)kRedSlots * kRedMaxK;
-constexpr size_t kNaDoubles = kNaCtr + 32;
+constexpr size_t kNaDoubles = kNaCtr + (kArriveWords + 1) / 2;
 static_assert(sizeof(CgState) <= 64 * sizeof(double), "CG state slot too small");
 
 static __device__ __align__(256) double scratch[kNaDoubles];
@@ -60,7 +60,7 @@ int na_base(double **out) {
 }
 
 __global__ void na_clear_counter(unsigned int *ctr) {
-    if (threadIdx.x < 64) ctr[threadIdx.x] = 0u;
+    for (int i = threadIdx.x; i < kArriveWords; i += blockDim.x) ctr[i] = 0u;
 }
 
 }  // namespace
@@ -109,7 +109,7 @@ extern "C" int cg_poisson_solve_noalloc(const ofdft_grid *grid, int radius, cons
     s.rb.partials = base + kNaPart;
     s.rb.counter = (unsigned int *)(base + kNaCtr);
     s.use_graphs = false;
-    hipLaunchKernelGGL(na_clear_counter, dim3(1), dim3(64), 0, st, s.rb.counter);
+    hipLaunchKernelGGL(na_clear_counter, dim3(1), dim3(256), 0, st, s.rb.counter);
     OFDFT_CHECK_HIP(hipGetLastError());
     ofdft_solve_stats local{};
     const int status = poisson_solve(&s, rhs, x, rel_tol, max_iter, local, st);

@@ -114,8 +114,8 @@ extern "C" int ofdft_tune_stencil(const ofdft_grid *grid, int radius, ofdft_dtyp
         OFDFT_TRY(buf.alloc(&pB, bytes));
         OFDFT_TRY(buf.alloc(&st, sizeof(CgState)));
         OFDFT_TRY(buf.alloc((void **)&rb.partials, sizeof(double) * kRedSlots * kRedMaxK));
-        OFDFT_TRY(buf.alloc((void **)&rb.counter, 256));
-        OFDFT_CHECK_HIP(hipMemsetAsync(rb.counter, 0, 256, s));
+        OFDFT_TRY(buf.alloc((void **)&rb.counter, sizeof(unsigned int) * kArriveWords));
+        OFDFT_CHECK_HIP(hipMemsetAsync(rb.counter, 0, sizeof(unsigned int) * kArriveWords, s));
         OFDFT_TRY(real64 ? fill<double>(pA, n, s) : fill<float>(pA, n, s));
         CgState hs{};
         hs.rr = 1.0;
