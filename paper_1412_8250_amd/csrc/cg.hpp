@@ -28,6 +28,7 @@ struct CgState {
 
 template <typename T>
 struct LoadCgP {      // operand of K1: r + beta p_old (first iteration: p_old := r, beta := 0)
+    static constexpr int kArrays = 2;
     const T *__restrict__ r;
     const T *__restrict__ p_old;
     const CgState *st;

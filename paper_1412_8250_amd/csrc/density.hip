@@ -116,6 +116,7 @@ struct ResidOp {        // r = -2 (Hu - eta u); totals {<r,r>, <r,r_prev>}
 // d' = r + xi d_prev (xi = 0: steepest descent, with d_prev := r); with the
 // preconditioner r is z, and the stored direction is d = d' - cu u (EpiLd).
 struct LoadDir {
+    static constexpr int kArrays = 2;
     const double *__restrict__ r;
     const double *__restrict__ d_prev;
     double xi;
@@ -463,6 +464,7 @@ struct FinDots {
 };
 
 struct LoadDirD {        // d' = r + xi d_prev, xi from the device state
+    static constexpr int kArrays = 2;
     const double *__restrict__ r;
     const double *__restrict__ d_prev;
     const UDev *U;

@@ -349,6 +349,154 @@ stencil_kernel(TileGeom g, Coef<typename VT<T>::S> w, Load ld, Epi ep) {
     ep.finish(blockIdx.x, g.nblocks, red_scratch);
 }
 
+// Brick kernel for grids that stay in the caches: a workgroup of 256 threads
+// owns W x H columns (W H <= 256, fitted to the grid's axes) of KZ planes.
+// Every load is issued up front -- each thread its column's KZ + 12 z values,
+// and the planes' star halos (12 (W + H) cells each, no corners) shared out
+// among the threads -- then the KZ planes stand in LDS and are computed after
+// one barrier.  Bound by latency and then by L1 (about 12 / KZ + 1 + 12 (W +
+// H) / (W H) loads per point); it has no prologue of 15 planes before the first
+// output, which is most of the march's time on a small grid, and its bricks
+// spread over the chip where the march has few tiles.  Same operations in
+// the same order per point as the march.  Needs every axis to reach
+// kBrickMinAxis points (one periodic wrap per z offset).
+constexpr int kBrickThreads = 256;
+constexpr int kBrickMinAxis = 10;
+constexpr int kBrickRing = 4;           // halo cells per thread and plane at most
+
+struct BrickGeom {
+    int nx, ny, nz, nxy;
+    int W, H, tx, ty, nblocks;
+};
+
+// The column tile with the fewest loads over the plane: splits of nx into
+// tiles of 8 to 64 columns, H = 256 / W evened out over ny.
+inline BrickGeom make_brick_geom(const ofdft_grid &g, int kz) {
+    BrickGeom b{g.nx, g.ny, g.nz, g.nx * g.ny, 0, 0, 0, 0, 0};
+    int64_t best = -1;
+    for (int tx = 1; tx <= g.nx; ++tx) {
+        const int W = (g.nx + tx - 1) / tx;
+        if (W > 64) continue;
+        if (W < 8 && tx > 1) break;
+        int H = kBrickThreads / W;
+        const int ty = (g.ny + H - 1) / H;
+        H = (g.ny + ty - 1) / ty;
+        if (12 * (W + H) > kBrickRing * kBrickThreads) continue;
+        const int64_t cost = (int64_t)tx * ty * (kBrickThreads * (kz + 12) + 12 * (W + H) * kz);
+        if (best < 0 || cost < best) {
+            best = cost;
+            b.W = W;
+            b.H = H;
+            b.tx = (g.nx + W - 1) / W;
+            b.ty = ty;
+        }
+    }
+    b.nblocks = b.tx * b.ty * ((g.nz + kz - 1) / kz);
+    return b;
+}
+
+inline size_t brick_lds_bytes(const BrickGeom &b, int kz, size_t elem) {
+    return (size_t)(b.W + 2 * kMaxRadius) * (b.H + 2 * kMaxRadius) * kz * elem;
+}
+
+// One brick (logical index b): `buf` holds brick_lds_bytes of LDS.
+template <typename T, int KZ, class Load, class Epi>
+__device__ __forceinline__ void stencil_brick(const BrickGeom g, const Coef<typename VT<T>::S> w, const Load &ld,
+                                              Epi &ep, int b, T *buf) {
+    using V = VT<T>;
+    constexpr int R = kMaxRadius;
+    const int x0 = (b % g.tx) * g.W;
+    b /= g.tx;
+    const int y0 = (b % g.ty) * g.H, z0 = (b / g.ty) * KZ;
+    const int tid = threadIdx.x, P = g.W + 2 * R, SL = P * (g.H + 2 * R);
+    const int ly = tid / g.W, lx = tid - ly * g.W;
+    const bool act = ly < g.H;
+    const int own = act ? ((y0 + ly) % g.ny) * g.nx + (x0 + lx) % g.nx : 0;
+    const bool valid = act && x0 + lx < g.nx && y0 + ly < g.ny;
+    int64_t pz[KZ + 2 * R];                        // planes z0 - R .. z0 + KZ - 1 + R
+#pragma unroll
+    for (int j = 0; j < KZ + 2 * R; ++j) {
+        int z = z0 - R + j;
+        z = z < 0 ? z + g.nz : (z >= g.nz ? z - g.nz : z);
+        pz[j] = (int64_t)z * g.nxy;
+    }
+    T q[KZ + 2 * R];
+#pragma unroll
+    for (int j = 0; j < KZ + 2 * R; ++j) q[j] = ld(pz[j] + own);
+    // halo cells of a plane: 12 rows of W above and below, then 12 cells left
+    // and right of each of the H rows
+    const int ncell = 2 * R * (g.W + g.H);
+    T halo[kBrickRing][KZ];
+    int cell[kBrickRing];
+#pragma unroll
+    for (int i = 0; i < kBrickRing; ++i) {
+        const int c = tid + i * kBrickThreads;
+        cell[i] = -1;
+        if (c < ncell) {
+            int hx, hy;
+            if (c < 2 * R * g.W) {
+                const int r = c / g.W;
+                hx = c - r * g.W + R;
+                hy = r < R ? r : r + g.H;
+            } else {
+                const int cc = c - 2 * R * g.W, r = cc / (2 * R), s = cc - r * (2 * R);
+                hx = s < R ? s : s + g.W;
+                hy = r + R;
+            }
+            cell[i] = hy * P + hx;
+            const int off = wrapi(y0 - R + hy, g.ny) * g.nx + wrapi(x0 - R + hx, g.nx);
+#pragma unroll
+            for (int k = 0; k < KZ; ++k) halo[i][k] = ld(pz[k + R] + off);
+        }
+    }
+    const int ctr = (ly + R) * P + lx + R;
+    if (act) {
+#pragma unroll
+        for (int k = 0; k < KZ; ++k) buf[k * SL + ctr] = q[k + R];
+    }
+#pragma unroll
+    for (int i = 0; i < kBrickRing; ++i)
+        if (cell[i] >= 0) {
+#pragma unroll
+            for (int k = 0; k < KZ; ++k) buf[k * SL + cell[i]] = halo[i][k];
+        }
+    if (valid) {
+#pragma unroll
+        for (int k = 0; k < KZ; ++k)
+            if (z0 + k < g.nz) ep.pre(k, pz[k + R] + own);
+    }
+    __syncthreads();
+    if (valid) {
+#pragma unroll
+        for (int k = 0; k < KZ; ++k) {
+            if (z0 + k < g.nz) {
+                const T *row = buf + k * SL + ctr;
+                const T c = q[k + R];
+                T sacc = V::mul(w.c0, c);
+#pragma unroll
+                for (int p = 1; p <= R; ++p) {
+                    sacc = V::fma(w.wx[p], V::add(row[p], row[-p]), sacc);
+                    sacc = V::fma(w.wy[p], V::add(row[p * P], row[-p * P]), sacc);
+                    sacc = V::fma(w.wz[p], V::add(q[k + R + p], q[k + R - p]), sacc);
+                }
+                ep.point(k, pz[k + R] + own, c, sacc);
+            }
+        }
+    }
+}
+
+template <typename T, int KZ, class Load, class Epi>
+__global__ void __launch_bounds__(kBrickThreads)
+stencil_brick_kernel(BrickGeom g, Coef<typename VT<T>::S> w, Load ld, Epi ep) {
+    extern __shared__ __align__(16) unsigned char brick_lds[];
+    __shared__ double red_scratch[64];
+    if (ep.skip()) return;
+    ld.prepare();
+    epi_prepare(ep, 0);
+    stencil_brick<T, KZ>(g, w, ld, ep, xcd_remap(blockIdx.x, g.nblocks), reinterpret_cast<T *>(brick_lds));
+    ep.finish(blockIdx.x, g.nblocks, red_scratch);
+}
+
 // ---- plain loaders / epilogues -------------------------------------------
 template <typename T>
 struct LoadPlain {

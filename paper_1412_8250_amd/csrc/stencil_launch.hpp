@@ -41,10 +41,32 @@ inline int launch_stencil_shape(const ofdft_grid &g, int zlen, const Coef<typena
     return OFDFT_OK;
 }
 
+template <typename T, int KZ, class Load, class Epi>
+inline int launch_stencil_brick(const ofdft_grid &g, const Coef<typename VT<T>::S> &c, const Load &ld,
+                                const Epi &ep, hipStream_t s) {
+    const BrickGeom b = make_brick_geom(g, KZ);
+    hipLaunchKernelGGL((stencil_brick_kernel<T, KZ, Load, Epi>), dim3(b.nblocks), dim3(kBrickThreads),
+                       brick_lds_bytes(b, KZ, sizeof(T)), s, b, c, ld, ep);
+    OFDFT_CHECK_HIP(hipGetLastError());
+    return OFDFT_OK;
+}
+
+// Arrays a loader reads per stencil point (kArrays member; 1 without).
+template <class Load, class = void>
+struct LoadArrays {
+    static constexpr int value = 1;
+};
+template <class Load>
+struct LoadArrays<Load, std::void_t<decltype(Load::kArrays)>> {
+    static constexpr int value = Load::kArrays;
+};
+
 template <typename T, class Load, class Epi>
 inline int launch_stencil(const ofdft_grid &g, const Coef<typename VT<T>::S> &c, const Load &ld,
                           const Epi &ep, hipStream_t s, int family = FAMILY_PASS) {
-    const StencilCfg cfg = pick_stencil_cfg(g, sizeof(T), family);
+    const StencilCfg cfg = pick_stencil_cfg(g, sizeof(T), family, LoadArrays<Load>::value);
+    if (cfg.shape == SHAPE_BRICK)
+        return cfg.zlen == 1 ? launch_stencil_brick<T, 1>(g, c, ld, ep, s) : launch_stencil_brick<T, 4>(g, c, ld, ep, s);
     return dispatch_shape(cfg.shape, [&](auto sh) {
         using S = decltype(sh);
         return launch_stencil_shape<T, S::TX, S::TYT, S::RY>(g, cfg.zlen, c, ld, ep, s);

@@ -10,7 +10,8 @@
 //     the residual and density-update passes share its entry (FP64, FP32).
 // The configuration the library would use untuned is always a candidate and
 // keeps its place unless another one is more than 2% faster, so noise does
-// not flip the choice.  All candidates compute the same operator (the tests
+// not flip the choice (where that is the brick kernel, the grid is left without
+// an entry and the tile heuristic's shape is reported).  All candidates compute the same operator (the tests
 // check every shape against the oracle); only the reduction order of the
 // fused passes changes with the tiling.
 #include <algorithm>
@@ -147,8 +148,14 @@ extern "C" int ofdft_tune_stencil(const ofdft_grid *grid, int radius, ofdft_dtyp
     double best = -1.0, def_ms = -1.0;
     Candidate pick{def.shape, def.zlen};
     int rc = OFDFT_OK;
+    // on small grids the untuned library runs the brick kernel, which is no
+    // table entry: it is timed with the grid's entry erased (shape < 0)
+    StencilCfg bk;
+    const bool brick = brick_stencil(g, eb, family == FAMILY_PASS ? 2 : 1, bk);
+    if (brick) cand.push_back({-1, 0});
     for (const Candidate &k : cand) {
-        record_stencil_cfg(g, eb, family, StencilCfg{k.shape, k.zlen});
+        if (k.shape < 0) erase_stencil_cfg(g, eb, family);
+        else record_stencil_cfg(g, eb, family, StencilCfg{k.shape, k.zlen});
         if ((rc = launch()) != OFDFT_OK) break;                        // warm-up
         if (hipEventRecord(e0, s) != hipSuccess) { rc = OFDFT_HIP_ERROR; break; }
         for (int r = 0; r < reps && rc == OFDFT_OK; ++r) rc = launch();
@@ -160,7 +167,8 @@ extern "C" int ofdft_tune_stencil(const ofdft_grid *grid, int radius, ofdft_dtyp
             break;
         }
         const double t = ms / reps;
-        if (k.shape == def.shape && k.zlen == def.zlen) def_ms = t;
+        if (brick ? k.shape < 0 : k.shape == def.shape && k.zlen == def.zlen) def_ms = t;
+        if (k.shape < 0) continue;                                     // wins below or not at all
         if (best < 0.0 || t < best) {
             best = t;
             pick = k;
@@ -176,8 +184,11 @@ extern "C" int ofdft_tune_stencil(const ofdft_grid *grid, int radius, ofdft_dtyp
     if (def_ms > 0.0 && best > 0.98 * def_ms) {
         pick = Candidate{def.shape, def.zlen};
         best = def_ms;
+        if (brick) erase_stencil_cfg(g, eb, family);
+        else record_stencil_cfg(g, eb, family, StencilCfg{pick.shape, pick.zlen});
+    } else {
+        record_stencil_cfg(g, eb, family, StencilCfg{pick.shape, pick.zlen});
     }
-    record_stencil_cfg(g, eb, family, StencilCfg{pick.shape, pick.zlen});
     OFDFT_CHECK_HIP(hipStreamSynchronize(s));
     if (out) {
         *out = ofdft_tune_result{};

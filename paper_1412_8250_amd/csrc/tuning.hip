@@ -5,6 +5,7 @@
 #include <tuple>
 #include <vector>
 
+#include "stencil_core.hpp"
 #include "tuning.hpp"
 
 namespace ofdft {
@@ -63,7 +64,27 @@ StencilCfg default_stencil_cfg(const ofdft_grid &g, int elem_bytes, int family) 
     return c;
 }
 
-StencilCfg pick_stencil_cfg(const ofdft_grid &g, int elem_bytes, int family) {
+// Measured on MI355X (back-to-back applies, march / brick, us; the call itself
+// takes 8.5 on the host): FP32 110x75x91 10.9 / 8.7, 128^3 11.2 / 11.2, 160^3
+// 16.9 / 17.6; FP64 48^3 13.1 / 8.7, 110x75x91 15.1 / 8.9, 128^3 20.9 / 14.3,
+// 160^3 27.4 / 24.9, 192^3 35.7 / 42.3; complex128 96^3 15.5 / 13.8, 110x75x91
+// 13.7 / 11.6, 128^3 22.5 / 29.8.  Passes that read two arrays per stencil point
+// load twice as much through L1 and cross earlier (CG iteration, FP64 80^3
+// 27.5 / 23.4, 96^3 30.8 / 30.2; FP32 96^3 27.1 / 26.0).  One plane per brick up
+// to 2^17 points (CG iteration at 16^3 14.3 against 15.7 with four), else four.
+bool brick_stencil(const ofdft_grid &g, int elem_bytes, int arrays, StencilCfg &c) {
+    if (g.nx < kBrickMinAxis || g.ny < kBrickMinAxis || g.nz < kBrickMinAxis) return false;
+    const int64_t n = npoints(g);
+    const int64_t limit = arrays > 1 ? (int64_t)900000
+                          : elem_bytes == 4 ? (int64_t)1500000 : elem_bytes == 8 ? (int64_t)4500000 : (int64_t)1000000;
+    if (n > limit) return false;
+    const int kz = n <= (1 << 17) ? 1 : 4;
+    if (make_brick_geom(g, kz).nblocks > kRedSlots) return false;
+    c = StencilCfg{SHAPE_BRICK, kz};
+    return true;
+}
+
+StencilCfg pick_stencil_cfg(const ofdft_grid &g, int elem_bytes, int family, int arrays) {
     {
         std::lock_guard<std::mutex> lk(g_mu);
         auto it = g_table.find(std::make_tuple(g.nx, g.ny, g.nz, elem_bytes, family));
@@ -71,6 +92,8 @@ StencilCfg pick_stencil_cfg(const ofdft_grid &g, int elem_bytes, int family) {
         it = g_table.find(std::make_tuple(g.nx, g.ny, g.nz, elem_bytes, (int)FAMILY_ALL));
         if (it != g_table.end()) return it->second;
     }
+    StencilCfg brick;
+    if (brick_stencil(g, elem_bytes, arrays, brick)) return brick;
     return default_stencil_cfg(g, elem_bytes, family);
 }
 

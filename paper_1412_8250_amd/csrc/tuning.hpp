@@ -19,7 +19,9 @@ enum StencilShape {
     SHAPE_64x8x1 = 4,    // 64 x 8 tile, 512 threads
     SHAPE_64x8x4 = 5,    // 64 x 32 tile, 512 threads: the plain FP64 and FP32 applies only
                          // (fused kernels given this id run 64 x 8 x 2)
-    SHAPE_COUNT = 6
+    SHAPE_COUNT = 6,
+    SHAPE_BRICK = SHAPE_COUNT    // no marched tile: the brick kernel (chosen by pick_stencil_cfg on
+                                 // small grids without a table entry; never an entry itself)
 };
 
 template <int TX_, int TYT_, int RY_>
@@ -64,7 +66,11 @@ inline void shape_extent(int shape, int &tx, int &ty) {
 // every family without an entry of its own.
 enum TuneFamily { FAMILY_ALL = -1, FAMILY_APPLY = 0, FAMILY_PASS = 1, FAMILY_COUNT = 2 };
 
-StencilCfg pick_stencil_cfg(const ofdft_grid &g, int elem_bytes, int family);
+// Without a table entry: the brick kernel where it wins (zlen: its planes, 1 or
+// 4), else the tile heuristic.  `arrays`: arrays the pass's loader reads per
+// stencil point.
+StencilCfg pick_stencil_cfg(const ofdft_grid &g, int elem_bytes, int family, int arrays = 1);
+bool brick_stencil(const ofdft_grid &g, int elem_bytes, int arrays, StencilCfg &c);
 // The heuristic alone (no table).
 StencilCfg default_stencil_cfg(const ofdft_grid &g, int elem_bytes, int family);
 void record_stencil_cfg(const ofdft_grid &g, int elem_bytes, int family, StencilCfg c);
