@@ -246,7 +246,7 @@ int ofdft_batch_apply_preconditioner(ofdft_batch *b, int j, const double *kappa,
  * rel_tol |f|.  No preconditioner (a shift-dependent preconditioner breaks the
  * shared Krylov space: use ofdft_batch_set_preconditioner for that).
  * ofdft_multishift_create: one grid, radius 1..6, up to max_shifts (1..16)
- *   shifts per solve.  Allocates 4 + max(max_shifts - 1, 1) complex128 vectors of
+ *   shifts per solve.  Allocates 9 + max_shifts complex128 vectors of
  *   the grid and the solve's device scalars, so a context serves one solve
  *   at a time (solves on one context must not overlap on different streams).
  *   INVALID_ARG or NO_MEMORY.

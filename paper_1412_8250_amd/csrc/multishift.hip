@@ -17,21 +17,27 @@
 // (-L_h + kappa_r) e = f - (-L_h + kappa_r) x_r by a one-shift sequence from
 // zero, x_r += e, until the true residual meets the tolerance.
 //
-// Two launches per iteration:
+// Two launches per iteration, and one more every kMsBlock iterations:
 //  * stencil phase: the stencil runs on r alone; the seed direction and its
 //    image follow point by point, p = r + beta p_old and q = A r + beta q_old
 //    (A linear; q updated in place), p^T q is reduced; the last workgroup
 //    sets alpha_k and every running shift's pi_{k+1} and alpha_k^(r);
-//  * vector phase: every running shift forms p^(r) = r / pi^(r) + beta^(r)
-//    p^(r) (the seed's was written by the stencil phase) and x^(r) +=
-//    alpha^(r) p^(r); r -= alpha q; r^T r and |r|^2 are reduced and the last
-//    workgroup sets beta_k, the next beta^(r), advances pi and freezes the
-//    converged shifts.
+//  * residual phase: r_{k+1} = r_k - alpha q into the next of kMsBlock
+//    residual buffers; r^T r and |r|^2 are reduced and the last workgroup
+//    sets beta_k, the next beta^(r), advances pi and freezes the converged
+//    shifts;
+//  * iterate phase: the shifts' directions and iterates enter nothing until
+//    the end, so they are brought up to date kMsBlock iterations at a time
+//    from the kept residuals and the recorded coefficients: p^(r) = r_i /
+//    pi_i^(r) + beta_i^(r) p^(r), x^(r) += alpha_i^(r) p^(r) for the pending
+//    i in order (the seed is a shift with pi = 1), the same operations per
+//    point as one iteration at a time, with p and x read and written once.
 // Per point and iteration this moves 5 complex128 vectors in the stencil
-// phase and 3 + 3 (seed) + 4 per other running shift in the vector phase,
-// against 11 per system for separate COCG solves.  The scalars live on the
-// device; the host reads the status every few iterations, and launches made
-// after the end exit at once.
+// phase, 3 in the residual phase and 1 + 4 / kMsBlock per running shift in the
+// iterate phase (the residuals are read once for all shifts), where updating
+// every shift in every iteration moved 3 + 4 per shift; separate COCG solves
+// move 11 per system.  The scalars live on the device; the host reads the
+// status every few iterations, and launches made after the end exit at once.
 #include <algorithm>
 #include <cmath>
 #include <new>
@@ -44,19 +50,27 @@ namespace {
 
 constexpr int kMsMax = 16;          // shifts per solve
 constexpr int kMsThreads = 256;     // vector-phase workgroup
-constexpr int kMsMaxVBlocks = 4096;
+constexpr int kMsMaxVBlocks = 1024;
 constexpr int kMsPoll = 8;          // iterations between status reads
+// Iterations whose iterate updates run together (a divisor of kMsPoll).  With
+// four shifts the phases move 128 + (4 x 64 + 4 x 16) / 4 = 208 B per point and
+// iteration against 320 one at a time; eight would save 40 more and keep four
+// more residuals.
+constexpr int kMsBlock = 4;
+static_assert(kMsPoll % kMsBlock == 0, "whole blocks between status reads");
 
 struct MsShift {
-    double2 *x, *p;              // iterate (caller's array); direction (unused for the seed)
+    double2 *x, *p;              // iterate (caller's array); direction
     double sre, sim;             // sigma = kappa_r - kappa_seed
     double pi_re, pi_im;         // pi_k
     double pp_re, pp_im;         // pi_{k-1}
     double pn_re, pn_im;         // pi_{k+1} (set by the stencil phase)
     double ir_re, ir_im;         // 1 / pi_k
-    double al_re, al_im;         // alpha_k^(r)
     double be_re, be_im;         // beta_{k-1}^(r)
-    int run, stat, iters, pad;   // run: updated this iteration; stat: HDone code
+    double2 c_ir[kMsBlock], c_be[kMsBlock], c_al[kMsBlock];   // pending iterations' 1 / pi, beta, alpha
+    int run, stat, iters;        // run: updated this iteration; stat: HDone code
+    int pend;                    // pending iterations (the first `pend` slots of the block)
+    int have_p, pad;             // p holds a direction (the first update reads none)
 };
 
 struct MsState {
@@ -73,7 +87,14 @@ __device__ inline double2 csub(double2 a, double2 b) { return make_double2(a.x -
 __device__ inline double cabs2(double2 a) { return a.x * a.x + a.y * a.y; }
 __device__ inline bool cfinite(double2 a) { return isfinite(a.x) && isfinite(a.y); }
 
-// r = f, every iterate zero; {f^T f re, im, |f|^2}.
+// The residual buffers: r_k is in slot k mod (kMsBlock + 1), so the block's
+// residuals r_k .. r_{k + kMsBlock - 1} and the next one are distinct.
+constexpr int kMsRing = kMsBlock + 1;
+struct MsRing {
+    double2 *r[kMsRing];
+};
+
+// r_0 = f, every iterate zero; {f^T f re, im, |f|^2}.
 __global__ void __launch_bounds__(kMsThreads)
 ms_init(MsState *st, const MsShift *sh, const double2 *f, double2 *r, int64_t n, double tol,
         double *part, unsigned int *ctr) {
@@ -123,7 +144,7 @@ struct MsEpiQ {
     GPtr<double2> p_old, p_out, q;
     double2 kappa, beta;
     double acc[2];
-    double2 po[2], qo[2];
+    double2 po[4], qo[4];
     __device__ void pre(int r, int64_t i) {
         if constexpr (!First) {
             po[r] = p_old[i];
@@ -144,14 +165,36 @@ struct MsEpiQ {
     }
 };
 
+// One tile of a stencil pass of this solver by the march (shape tag) or, for
+// the brick tag, by the brick kernel; nthreads and nblocks of the launch.
+template <int TX_, int TYT_, int RY_>
+struct MsMarch {
+    static constexpr int kThreads = TX_ * TYT_;
+    using Geom = TileGeom;
+    template <class Load, class Epi>
+    __device__ static void run(const Geom &g, const Coef<double> &c, const Load &ld, Epi &ep, int lb) {
+        __shared__ double2 lds[StencilLds<double2, TX_, TYT_, RY_>::kElems];
+        stencil_tile<double2, TX_, TYT_, RY_>(g, c, ld, ep, lb, lds);
+    }
+};
+template <int KZ>
+struct MsBrick {
+    static constexpr int kThreads = kBrickThreads;
+    using Geom = BrickGeom;
+    template <class Load, class Epi>
+    __device__ static void run(const Geom &g, const Coef<double> &c, const Load &ld, Epi &ep, int lb) {
+        extern __shared__ __align__(16) unsigned char brick_lds[];
+        stencil_brick<double2, KZ>(g, c, ld, ep, lb, reinterpret_cast<double2 *>(brick_lds));
+    }
+};
+
 // First: iteration 0 (launched as the first stencil phase after ms_init).
-template <int TX, int TYT, int RY, bool First>
-__global__ void __launch_bounds__(TX * TYT)
-ms_stencil(TileGeom tg, Coef<double> coef, double kre, double kim, MsState *st, MsShift *sh,
+// slot: the block's pending slot of this iteration (iteration mod kMsBlock).
+template <class Tile, bool First>
+__global__ void __launch_bounds__(Tile::kThreads)
+ms_stencil(typename Tile::Geom tg, Coef<double> coef, double kre, double kim, MsState *st, MsShift *sh, int slot,
            const double2 *r, double2 *pA, double2 *pB, double2 *q, double *part, unsigned int *ctr) {
-    using SLd = StencilLds<double2, TX, TYT, RY>;
-    __shared__ double2 lds[SLd::kElems];
-    __shared__ double scratch[2 * (TX * TYT / 64)];
+    __shared__ double scratch[2 * (Tile::kThreads / 64)];
     if (st->done != H_RUNNING) return;
     const int total = tg.nblocks;
     const int lb = xcd_remap(blockIdx.x, total);
@@ -161,7 +204,7 @@ ms_stencil(TileGeom tg, Coef<double> coef, double kre, double kim, MsState *st, 
     MsLoadR ld{GPtr<double2>(r)};
     MsEpiQ<First> ep{GPtr<double2>(p_old), GPtr<double2>(p_new), GPtr<double2>(q), c2(kre, kim),
                      c2(st->be_re, st->be_im), {0.0, 0.0}, {}, {}};
-    stencil_tile<double2, TX, TYT, RY>(tg, coef, ld, ep, lb, lds);
+    Tile::run(tg, coef, ld, ep, lb);
     double acc[2] = {ep.acc[0], ep.acc[1]};
     block_sum<2>(acc, scratch);
     double t[2];
@@ -194,56 +237,27 @@ ms_stencil(TileGeom tg, Coef<double> coef, double kre, double kim, MsState *st, 
             s.iters = st->iter;
             continue;
         }
-        const double2 aj = cdiv(cmul(al, pi), pn);
-        s.al_re = aj.x;
-        s.al_im = aj.y;
+        s.c_ir[slot] = c2(s.ir_re, s.ir_im);
+        s.c_be[slot] = c2(s.be_re, s.be_im);
+        s.c_al[slot] = cdiv(cmul(al, pi), pn);
+        s.pend = slot + 1;
     }
 }
 
+// Residual phase: r_{k+1} = r_k - alpha q.
 __global__ void __launch_bounds__(kMsThreads)
-ms_update(MsState *st, MsShift *sh, double2 *r, const double2 *q, const double2 *pA, const double2 *pB,
-          int64_t n, double *part, unsigned int *ctr) {
+ms_residual_step(MsState *st, MsShift *sh, const double2 *r, double2 *rnext, const double2 *q, int64_t n,
+                 double *part, unsigned int *ctr) {
     __shared__ double scratch[3 * (kMsThreads / 64)];
-    __shared__ double2 *s_x[kMsMax];
-    __shared__ double2 *s_p[kMsMax];
-    __shared__ double2 s_ir[kMsMax], s_be[kMsMax], s_al[kMsMax];
-    __shared__ int s_run[kMsMax];
     if (st->done != H_RUNNING) return;
-    const int S = st->nshift, seed = st->seed;
-    const bool first = st->iter == 0;
-    if ((int)threadIdx.x < S) {
-        const MsShift &s = sh[threadIdx.x];
-        s_x[threadIdx.x] = s.x;
-        s_p[threadIdx.x] = (int)threadIdx.x == seed ? nullptr : s.p;
-        s_ir[threadIdx.x] = c2(s.ir_re, s.ir_im);
-        s_be[threadIdx.x] = c2(s.be_re, s.be_im);
-        s_al[threadIdx.x] = c2(s.al_re, s.al_im);
-        s_run[threadIdx.x] = s.run;
-    }
-    __syncthreads();
-    const GPtr<double2> R(r), Q(q), PS(st->parity ? pA : pB);   // the seed direction just written
+    const int S = st->nshift;
+    const GPtr<double2> R(r), Q(q), N(rnext);
     const double2 nal = c2(-st->al_re, -st->al_im);
     double acc[3] = {0.0, 0.0, 0.0};
     const int64_t stride = (int64_t)gridDim.x * kMsThreads;
     for (int64_t i = (int64_t)blockIdx.x * kMsThreads + threadIdx.x; i < n; i += stride) {
-        const double2 rv = R[i];
-        const double2 qv = Q[i];
-        for (int j = 0; j < S; ++j) {
-            if (!s_run[j]) continue;
-            double2 pj;
-            if (j == seed) {
-                pj = PS[i];
-            } else {
-                const GPtr<double2> P(s_p[j]);
-                pj = cmul(rv, s_ir[j]);
-                if (!first) pj = cfma(s_be[j], P[i], pj);
-                P.st(i, pj);
-            }
-            const GPtr<double2> X(s_x[j]);
-            X.st(i, cfma(s_al[j], pj, X[i]));
-        }
-        const double2 rn = cfma(nal, qv, rv);
-        R.st(i, rn);
+        const double2 rn = cfma(nal, Q[i], R[i]);
+        N.st(i, rn);
         acc[0] += rn.x * rn.x - rn.y * rn.y;
         acc[1] += 2.0 * rn.x * rn.y;
         acc[2] += rn.x * rn.x + rn.y * rn.y;
@@ -303,6 +317,68 @@ ms_update(MsState *st, MsShift *sh, double2 *r, const double2 *q, const double2 
     st->done = d;
 }
 
+// Iterate phase: the pending iterations of every shift (see the head of the
+// file); `it0` is the block's first iteration.  A shift that froze inside the
+// block has fewer pending iterations; launches with none pending move nothing.
+__global__ void __launch_bounds__(kMsThreads)
+ms_iterates(MsShift *sh, int S, int it0, MsRing ring, int64_t n) {
+    __shared__ double2 s_ir[kMsMax][kMsBlock], s_be[kMsMax][kMsBlock], s_al[kMsMax][kMsBlock];
+    __shared__ double2 *s_x[kMsMax], *s_p[kMsMax];
+    __shared__ int s_pend[kMsMax], s_have[kMsMax], s_most;
+    if (threadIdx.x == 0) {
+        int most = 0;
+        for (int j = 0; j < S; ++j) most = max(most, sh[j].pend);
+        s_most = most;
+    }
+    if ((int)threadIdx.x < S) {
+        const MsShift &s = sh[threadIdx.x];
+        s_x[threadIdx.x] = s.x;
+        s_p[threadIdx.x] = s.p;
+        s_pend[threadIdx.x] = s.pend;
+        s_have[threadIdx.x] = s.have_p;
+        for (int k = 0; k < kMsBlock; ++k) {
+            s_ir[threadIdx.x][k] = s.c_ir[k];
+            s_be[threadIdx.x][k] = s.c_be[k];
+            s_al[threadIdx.x][k] = s.c_al[k];
+        }
+    }
+    __syncthreads();
+    const int most = s_most;
+    if (most == 0) return;
+    const int64_t stride = (int64_t)gridDim.x * kMsThreads;
+    for (int64_t i = (int64_t)blockIdx.x * kMsThreads + threadIdx.x; i < n; i += stride) {
+        double2 rv[kMsBlock];
+#pragma unroll
+        for (int k = 0; k < kMsBlock; ++k)
+            if (k < most) rv[k] = GPtr<double2>(ring.r[(it0 + k) % kMsRing])[i];
+        for (int j = 0; j < S; ++j) {
+            const int pend = s_pend[j];
+            if (pend == 0) continue;
+            const GPtr<double2> X(s_x[j]), P(s_p[j]);
+            double2 xv = X[i], pj = s_have[j] ? P[i] : c2(0.0, 0.0);
+#pragma unroll
+            for (int k = 0; k < kMsBlock; ++k)
+                if (k < pend) {
+                    double2 pn = cmul(rv[k], s_ir[j][k]);
+                    if (k > 0 || s_have[j]) pn = cfma(s_be[j][k], pj, pn);
+                    pj = pn;
+                    xv = cfma(s_al[j][k], pj, xv);
+                }
+            P.st(i, pj);
+            X.st(i, xv);
+        }
+    }
+}
+
+// The pending slots are free again (after ms_iterates).
+__global__ void ms_block_done(MsShift *sh, int S) {
+    const int j = threadIdx.x;
+    if (j < S && sh[j].pend) {
+        sh[j].pend = 0;
+        sh[j].have_p = 1;
+    }
+}
+
 struct MsLoadX {
     GPtr<double2> x;
     __device__ double2 operator()(int64_t i) const { return x[i]; }
@@ -312,7 +388,7 @@ struct MsEpiRes {        // acc |f - (-L x + kappa x)|^2
     GPtr<double2> f;
     double2 kappa;
     double acc[1];
-    double2 fo[2];
+    double2 fo[4];
     __device__ void pre(int r, int64_t i) { fo[r] = f[i]; }
     __device__ void point(int r, int64_t, double2 c, double2 s) {
         const double2 a = cfma(kappa, c, c2(-s.x, -s.y));
@@ -321,18 +397,16 @@ struct MsEpiRes {        // acc |f - (-L x + kappa x)|^2
     }
 };
 
-template <int TX, int TYT, int RY>
-__global__ void __launch_bounds__(TX * TYT)
-ms_residual(TileGeom tg, Coef<double> coef, double kre, double kim, const double2 *x, const double2 *f,
+template <class Tile>
+__global__ void __launch_bounds__(Tile::kThreads)
+ms_residual(typename Tile::Geom tg, Coef<double> coef, double kre, double kim, const double2 *x, const double2 *f,
             double *part, unsigned int *ctr, double *out) {
-    using SLd = StencilLds<double2, TX, TYT, RY>;
-    __shared__ double2 lds[SLd::kElems];
-    __shared__ double scratch[TX * TYT / 64];
+    __shared__ double scratch[Tile::kThreads / 64];
     const int total = tg.nblocks;
     const int lb = xcd_remap(blockIdx.x, total);
     MsLoadX ld{GPtr<double2>(x)};
     MsEpiRes ep{GPtr<double2>(f), c2(kre, kim), {0.0}, {}};
-    stencil_tile<double2, TX, TYT, RY>(tg, coef, ld, ep, lb, lds);
+    Tile::run(tg, coef, ld, ep, lb);
     double acc[1] = {ep.acc[0]};
     block_sum<1>(acc, scratch);
     double t[1];
@@ -343,7 +417,7 @@ struct MsEpiResVec {     // d = f - (-L x + kappa x) written; acc |d|^2
     GPtr<double2> f, d;
     double2 kappa;
     double acc[1];
-    double2 fo[2];
+    double2 fo[4];
     __device__ void pre(int r, int64_t i) { fo[r] = f[i]; }
     __device__ void point(int r, int64_t i, double2 c, double2 s) {
         const double2 a = cfma(kappa, c, c2(-s.x, -s.y));
@@ -353,18 +427,16 @@ struct MsEpiResVec {     // d = f - (-L x + kappa x) written; acc |d|^2
     }
 };
 
-template <int TX, int TYT, int RY>
-__global__ void __launch_bounds__(TX * TYT)
-ms_resvec(TileGeom tg, Coef<double> coef, double kre, double kim, const double2 *x, const double2 *f,
+template <class Tile>
+__global__ void __launch_bounds__(Tile::kThreads)
+ms_resvec(typename Tile::Geom tg, Coef<double> coef, double kre, double kim, const double2 *x, const double2 *f,
           double2 *d, double *part, unsigned int *ctr, double *out) {
-    using SLd = StencilLds<double2, TX, TYT, RY>;
-    __shared__ double2 lds[SLd::kElems];
-    __shared__ double scratch[TX * TYT / 64];
+    __shared__ double scratch[Tile::kThreads / 64];
     const int total = tg.nblocks;
     const int lb = xcd_remap(blockIdx.x, total);
     MsLoadX ld{GPtr<double2>(x)};
     MsEpiResVec ep{GPtr<double2>(f), GPtr<double2>(d), c2(kre, kim), {0.0}, {}};
-    stencil_tile<double2, TX, TYT, RY>(tg, coef, ld, ep, lb, lds);
+    Tile::run(tg, coef, ld, ep, lb);
     double acc[1] = {ep.acc[0]};
     block_sum<1>(acc, scratch);
     double t[1];
@@ -400,14 +472,16 @@ struct ofdft_multishift {
     ofdft_grid grid{};
     int radius = 0;
     int max_shifts = 0;
-    int shape = 0;               // effective complex128 tile shape
+    int shape = 0;               // effective complex128 tile shape, or SHAPE_BRICK
     TileGeom tg{};
+    BrickGeom bg{};
     Coef<double> coef{};
     int64_t n = 0;
     int vblocks = 0;
-    double2 *r = nullptr, *q = nullptr, *pA = nullptr, *pB = nullptr;
-    std::vector<double2 *> p;    // directions of non-seed shifts (max_shifts - 1, at least
-                                 // one: p[0] holds the correction of the finishing solves)
+    MsRing ring{};               // residuals
+    double2 *q = nullptr, *pA = nullptr, *pB = nullptr;
+    double2 *e = nullptr;        // correction of the finishing solves
+    std::vector<double2 *> p;    // directions of the shifts
     MsState *d_state = nullptr;
     MsShift *d_shift = nullptr;
     double *d_part = nullptr;
@@ -419,7 +493,9 @@ struct ofdft_multishift {
 namespace {
 
 void ms_free(ofdft_multishift *m) {
-    for (void *p : {(void *)m->r, (void *)m->q, (void *)m->pA, (void *)m->pB, (void *)m->d_state,
+    for (double2 *p : m->ring.r)
+        if (p) (void)hipFree(p);
+    for (void *p : {(void *)m->e, (void *)m->q, (void *)m->pA, (void *)m->pB, (void *)m->d_state,
                     (void *)m->d_shift, (void *)m->d_part, (void *)m->d_ctr, (void *)m->d_res})
         if (p) (void)hipFree(p);
     for (double2 *p : m->p)
@@ -440,11 +516,15 @@ int ms_alloc(P_ **p, size_t bytes) {
     return OFDFT_OK;
 }
 
-// The two complex128 tiles the solver uses (32 x 8 for small grids).
+// Calls f(tile tag, geometry, blocks, threads, LDS bytes) for the context's
+// stencil passes: bricks of four planes where they win, else one of the two
+// marched complex128 tiles (32 x 16 points for narrow grids).
 template <class F>
-int ms_dispatch(int shape, F &&f) {
-    if (shape == SHAPE_32x8x2) return f(ShapeTag<32, 8, 2>{});
-    return f(ShapeTag<64, 8, 1>{});
+int ms_dispatch(const ofdft_multishift *m, F &&f) {
+    if (m->shape == SHAPE_BRICK)
+        return f(MsBrick<4>{}, m->bg, m->bg.nblocks, dim3(kBrickThreads), brick_lds_bytes(m->bg, 4, sizeof(double2)));
+    if (m->shape == SHAPE_32x8x2) return f(MsMarch<32, 8, 2>{}, m->tg, m->tg.nblocks, dim3(32, 8), (size_t)0);
+    return f(MsMarch<64, 8, 1>{}, m->tg, m->tg.nblocks, dim3(64, 8), (size_t)0);
 }
 
 }  // namespace
@@ -468,25 +548,33 @@ extern "C" int ofdft_multishift_create(const ofdft_grid *grid, int radius, int m
     m->max_shifts = max_shifts;
     m->n = npoints(*grid);
     m->coef = make_coef(*grid, radius);
-    m->shape = cocg_shape<double2>(grid->nx <= 40 ? SHAPE_32x8x2 : SHAPE_64x8x1);
-    const int zl = stepped_zlen(*grid, false, m->shape);
-    ms_dispatch(m->shape, [&](auto sh) {
-        using S = decltype(sh);
-        m->tg = make_tile_geom<S::TX, S::TYT, S::RY>(*grid, zl);
-        return 0;
-    });
+    StencilCfg bk;
+    if (brick_stencil(*grid, sizeof(double2), 1, bk)) {
+        m->shape = SHAPE_BRICK;
+        m->bg = make_brick_geom(*grid, 4);
+    } else {
+        m->shape = cocg_shape<double2>(grid->nx <= 40 ? SHAPE_32x8x2 : SHAPE_64x8x1);
+        // one 512- or 256-thread workgroup per CU at a time: chunks that fill
+        // the chip in whole waves
+        int tx, ty;
+        shape_extent(m->shape, tx, ty);
+        const int zl = zlen_auto(*grid, tx, ty, 256);
+        m->tg = m->shape == SHAPE_32x8x2 ? make_tile_geom<32, 8, 2>(*grid, zl) : make_tile_geom<64, 8, 1>(*grid, zl);
+    }
     m->vblocks = (int)std::min<int64_t>(kMsMaxVBlocks, (m->n + kMsThreads - 1) / kMsThreads);
     const size_t vb = sizeof(double2) * (size_t)m->n;
-    const size_t nslots = (size_t)std::max(m->tg.nblocks, m->vblocks);
-    m->p.assign(std::max(max_shifts - 1, 1), nullptr);
+    const size_t nslots = (size_t)std::max(std::max(m->tg.nblocks, m->bg.nblocks), m->vblocks);
+    m->p.assign(max_shifts, nullptr);
     int st = OFDFT_OK;
-    if ((st = ms_alloc(&m->r, vb)) || (st = ms_alloc(&m->q, vb)) || (st = ms_alloc(&m->pA, vb)) ||
+    if ((st = ms_alloc(&m->e, vb)) || (st = ms_alloc(&m->q, vb)) || (st = ms_alloc(&m->pA, vb)) ||
         (st = ms_alloc(&m->pB, vb)) || (st = ms_alloc(&m->d_state, sizeof(MsState))) ||
         (st = ms_alloc(&m->d_shift, sizeof(MsShift) * kMsMax)) ||
         (st = ms_alloc(&m->d_part, sizeof(double) * 3 * nslots)) ||
         (st = ms_alloc(&m->d_ctr, sizeof(unsigned int) * kArriveWords)) || (st = ms_alloc(&m->d_res, sizeof(double) * kMsMax)))
         return fail(st);
     for (auto &p : m->p)
+        if ((st = ms_alloc(&p, vb))) return fail(st);
+    for (auto &p : m->ring.r)
         if ((st = ms_alloc(&p, vb))) return fail(st);
     if (hipMemset(m->d_ctr, 0, sizeof(unsigned int) * kArriveWords) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
         set_error("ofdft_multishift_create: clearing the reduction counter failed");
@@ -520,11 +608,10 @@ int ms_iterate(ofdft_multishift *m, int S, const double *kappa, int seed, const 
     hst.seed = seed;
     hst.done = H_RUNNING;
     hsh.assign(kMsMax, MsShift{});
-    int pi = 0;
     for (int j = 0; j < S; ++j) {
         MsShift &h = hsh[j];
         h.x = x[j];
-        h.p = j == seed ? nullptr : m->p[pi++];
+        h.p = m->p[j];
         h.sre = kappa[2 * j] - kappa[2 * seed];
         h.sim = kappa[2 * j + 1] - kappa[2 * seed + 1];
         h.pi_re = h.pp_re = h.ir_re = 1.0;
@@ -537,7 +624,7 @@ int ms_iterate(ofdft_multishift *m, int S, const double *kappa, int seed, const 
     {
         ProfScope ps(K_POINTWISE, n * e * (2.0 + S), s);
         hipLaunchKernelGGL(ms_init, dim3(m->vblocks), dim3(kMsThreads), 0, s, m->d_state, m->d_shift, f,
-                           m->r, m->n, tol, m->d_part, m->d_ctr);
+                           m->ring.r[0], m->n, tol, m->d_part, m->d_ctr);
         OFDFT_CHECK_HIP(hipGetLastError());
     }
     const double kre = kappa[2 * seed], kim = kappa[2 * seed + 1];
@@ -547,22 +634,28 @@ int ms_iterate(ofdft_multishift *m, int S, const double *kappa, int seed, const 
         OFDFT_CHECK_HIP(hipStreamSynchronize(s));
         if (hst.done != H_RUNNING) break;
         for (int c = 0; c < kMsPoll; ++c) {
-            int st = ms_dispatch(m->shape, [&](auto sh) {
-                using Sh = decltype(sh);
+            const int it = round * kMsPoll + c, slot = it % kMsBlock;     // iteration of this launch, if still running
+            const double2 *r = m->ring.r[it % kMsRing];
+            OFDFT_TRY(ms_dispatch(m, [&](auto tag, const auto &geom, int blocks, dim3 threads, size_t lds) {
+                using Tile = decltype(tag);
                 ProfScope ps(K_MS_STENCIL, 0.0, s);
-                // the first launch after ms_init is iteration 0
-                auto kern = round == 0 && c == 0 ? ms_stencil<Sh::TX, Sh::TYT, Sh::RY, true>
-                                                 : ms_stencil<Sh::TX, Sh::TYT, Sh::RY, false>;
-                hipLaunchKernelGGL(kern, dim3(m->tg.nblocks), dim3(Sh::TX, Sh::TYT), 0, s, m->tg, m->coef, kre,
-                                   kim, m->d_state, m->d_shift, m->r, m->pA, m->pB, m->q, m->d_part, m->d_ctr);
+                auto kern = it == 0 ? ms_stencil<Tile, true> : ms_stencil<Tile, false>;
+                hipLaunchKernelGGL(kern, dim3(blocks), threads, lds, s, geom, m->coef, kre, kim, m->d_state,
+                                   m->d_shift, slot, r, m->pA, m->pB, m->q, m->d_part, m->d_ctr);
                 OFDFT_CHECK_HIP(hipGetLastError());
                 return OFDFT_OK;
-            });
-            OFDFT_TRY(st);
+            }));
             ProfScope ps(K_MS_UPDATE, 0.0, s);
-            hipLaunchKernelGGL(ms_update, dim3(m->vblocks), dim3(kMsThreads), 0, s, m->d_state, m->d_shift,
-                               m->r, m->q, m->pA, m->pB, m->n, m->d_part, m->d_ctr);
+            hipLaunchKernelGGL(ms_residual_step, dim3(m->vblocks), dim3(kMsThreads), 0, s, m->d_state, m->d_shift, r,
+                               m->ring.r[(it + 1) % kMsRing], m->q, m->n, m->d_part, m->d_ctr);
             OFDFT_CHECK_HIP(hipGetLastError());
+            if (slot == kMsBlock - 1) {
+                hipLaunchKernelGGL(ms_iterates, dim3(m->vblocks), dim3(kMsThreads), 0, s, m->d_shift, S,
+                                   it - slot, m->ring, m->n);
+                OFDFT_CHECK_HIP(hipGetLastError());
+                hipLaunchKernelGGL(ms_block_done, dim3(1), dim3(kMsMax), 0, s, m->d_shift, S);
+                OFDFT_CHECK_HIP(hipGetLastError());
+            }
         }
     }
     OFDFT_CHECK_HIP(hipMemcpyAsync(&hst, m->d_state, sizeof(MsState), hipMemcpyDeviceToHost, s));
@@ -573,17 +666,18 @@ int ms_iterate(ofdft_multishift *m, int S, const double *kappa, int seed, const 
         return OFDFT_HIP_ERROR;
     }
     // Algorithmic bytes of the iterations taken: the stencil phase reads r,
-    // p_old and q_old (r only in the first iteration) and writes p and q; the vector
-    // phase reads r, q and writes r, plus 3 vectors for the seed (p, x read,
-    // x written) and 4 for every other shift (p, x read and written; 3 in the
-    // first iteration) while the shift runs.
+    // p_old and q_old (r only in the first iteration) and writes p and q; the
+    // residual phase reads r, q and writes r; the iterate phase reads each
+    // residual once and, per block and running shift, p and x (x alone the
+    // first time) and writes both.
     const int steps = hst.iter;
     if (steps > 0) {
         prof_add(K_MS_STENCIL, n * e * (5.0 * steps - 2.0), 0);
-        double upd = 3.0 * steps;
+        double upd = 4.0 * steps;
         for (int j = 0; j < S; ++j) {
             const int it = hsh[j].stat == H_RUNNING ? steps : hsh[j].iters;
-            upd += j == seed ? 3.0 * it : (it > 0 ? 4.0 * it - 1.0 : 0.0);
+            const int blocks = (it + kMsBlock - 1) / kMsBlock;
+            upd += it > 0 ? 4.0 * blocks - 1.0 : 0.0;
         }
         prof_add(K_MS_UPDATE, n * e * upd, 0);
     }
@@ -594,16 +688,16 @@ int ms_iterate(ofdft_multishift *m, int S, const double *kappa, int seed, const 
 int ms_true_residual(ofdft_multishift *m, const double *kap, const double2 *x, const double2 *f, double2 *d,
                      double *d_out, hipStream_t s) {
     const double e = sizeof(double2), n = (double)m->n;
-    return ms_dispatch(m->shape, [&](auto sh) {
-        using Sh = decltype(sh);
+    return ms_dispatch(m, [&](auto tag, const auto &geom, int blocks, dim3 threads, size_t lds) {
+        using Tile = decltype(tag);
         if (d) {
             ProfScope ps(K_RESIDUAL, n * e * 3.0, s);
-            hipLaunchKernelGGL((ms_resvec<Sh::TX, Sh::TYT, Sh::RY>), dim3(m->tg.nblocks), dim3(Sh::TX, Sh::TYT),
-                               0, s, m->tg, m->coef, kap[0], kap[1], x, f, d, m->d_part, m->d_ctr, d_out);
+            hipLaunchKernelGGL(ms_resvec<Tile>, dim3(blocks), threads, lds, s, geom, m->coef, kap[0], kap[1], x, f, d,
+                               m->d_part, m->d_ctr, d_out);
         } else {
             ProfScope ps(K_RESIDUAL, n * e * 2.0, s);
-            hipLaunchKernelGGL((ms_residual<Sh::TX, Sh::TYT, Sh::RY>), dim3(m->tg.nblocks), dim3(Sh::TX, Sh::TYT),
-                               0, s, m->tg, m->coef, kap[0], kap[1], x, f, m->d_part, m->d_ctr, d_out);
+            hipLaunchKernelGGL(ms_residual<Tile>, dim3(blocks), threads, lds, s, geom, m->coef, kap[0], kap[1], x, f,
+                               m->d_part, m->d_ctr, d_out);
         }
         OFDFT_CHECK_HIP(hipGetLastError());
         return OFDFT_OK;
@@ -638,12 +732,12 @@ int ms_solve(ofdft_multishift *m, int S, const double *kappa, int seed, const do
             default: code = OFDFT_NOT_CONVERGED; break;
         }
         // A converged shift whose true residual drifted above the tolerance:
-        // correction solves d = f - A x (into r), A e = d from zero (e in p[0],
+        // correction solves d = f - A x (into r_0's buffer), A e = d from zero (a
         // one-shift sequence, target tol |f| / |d| with a margin), x += e.
         if (h.stat == H_CONVERGED && code == OFDFT_NOT_CONVERGED && std::isfinite(rel)) {
             int budget = std::max(maxit - steps, 0);
             for (int round = 0; round < kMsFixRounds && rel > tol && budget > 0; ++round) {
-                OFDFT_TRY(ms_true_residual(m, kappa + 2 * j, x[j], f, m->r, m->d_res + j, s));
+                OFDFT_TRY(ms_true_residual(m, kappa + 2 * j, x[j], f, m->ring.r[0], m->d_res + j, s));
                 double d2 = 0.0;
                 OFDFT_CHECK_HIP(hipMemcpyAsync(&d2, m->d_res + j, sizeof(double), hipMemcpyDeviceToHost, s));
                 OFDFT_CHECK_HIP(hipStreamSynchronize(s));
@@ -651,12 +745,12 @@ int ms_solve(ofdft_multishift *m, int S, const double *kappa, int seed, const do
                 const double tc = std::min(0.5, 0.5 * tol * std::sqrt(fn2 / d2));
                 MsState cst{};
                 std::vector<MsShift> csh;
-                double2 *ex[1] = {m->p[0]};
-                OFDFT_TRY(ms_iterate(m, 1, kappa + 2 * j, 0, m->r, ex, tc, budget, cst, csh, s));
+                double2 *ex[1] = {m->e};
+                OFDFT_TRY(ms_iterate(m, 1, kappa + 2 * j, 0, m->ring.r[0], ex, tc, budget, cst, csh, s));
                 extra_it[j] += cst.iter;
                 budget -= cst.iter;
                 if (cst.done == H_NONFINITE || cst.done == H_BREAKDOWN) break;
-                hipLaunchKernelGGL(ms_axpy, dim3(m->vblocks), dim3(kMsThreads), 0, s, x[j], m->p[0], m->n);
+                hipLaunchKernelGGL(ms_axpy, dim3(m->vblocks), dim3(kMsThreads), 0, s, x[j], m->e, m->n);
                 OFDFT_CHECK_HIP(hipGetLastError());
                 prof_add(K_POINTWISE, (double)m->n * sizeof(double2) * 3.0, 1);
                 OFDFT_TRY(ms_true_residual(m, kappa + 2 * j, x[j], f, nullptr, m->d_res + j, s));

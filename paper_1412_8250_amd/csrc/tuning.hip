@@ -75,8 +75,12 @@ StencilCfg default_stencil_cfg(const ofdft_grid &g, int elem_bytes, int family) 
 bool brick_stencil(const ofdft_grid &g, int elem_bytes, int arrays, StencilCfg &c) {
     if (g.nx < kBrickMinAxis || g.ny < kBrickMinAxis || g.nz < kBrickMinAxis) return false;
     const int64_t n = npoints(g);
+    // complex128 to twice the size where 64-wide tiles would be over 20% idle (130x110x125 29.5 / 26.2)
+    const bool idle = 5 * ((g.nx + 63) / 64 * 64) > 6 * g.nx;
     const int64_t limit = arrays > 1 ? (int64_t)900000
-                          : elem_bytes == 4 ? (int64_t)1500000 : elem_bytes == 8 ? (int64_t)4500000 : (int64_t)1000000;
+                          : elem_bytes == 4 ? (int64_t)1500000
+                          : elem_bytes == 8 ? (int64_t)4500000
+                                            : (int64_t)(idle ? 2000000 : 1000000);
     if (n > limit) return false;
     const int kz = n <= (1 << 17) ? 1 : 4;
     if (make_brick_geom(g, kz).nblocks > kRedSlots) return false;
