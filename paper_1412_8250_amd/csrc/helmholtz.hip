@@ -29,6 +29,7 @@
 #include <vector>
 
 #include "helmholtz.hpp"
+#include "stencil_launch.hpp"
 
 namespace ofdft {
 
@@ -437,6 +438,13 @@ int residual_c128(ofdft_batch *b, int j, const double2 *f, const double2 *x, dou
                   double kre, double kim, double *totals, hipStream_t s) {
     const ofdft_grid &g = b->grids[j];
     const Coef<double> c = make_coef(g, b->radius);
+    StencilCfg bk;
+    if (brick_stencil(g, sizeof(double2), 1, bk)) {
+        ProfScope ps(K_RESIDUAL, (double)npoints(g) * (r ? 48 : 32), s);
+        return launch_stencil_brick<double2, 4>(
+            g, c, LoadPlain<double2>{x},
+            EpiHRes<double2>{f, r, make_double2(kre, kim), totals, b->rb.partials, b->rb.counter, 0.0, 0.0, {}}, s);
+    }
     TileGeom tg = make_tile_geom<64, 4, 2>(g, zlen_for_blocks(g, SHAPE_64x4x2, 512));
     LoadPlain<double2> ld{x};
     EpiHRes<double2> ep{f, r, make_double2(kre, kim), totals, b->rb.partials, b->rb.counter, 0.0, 0.0};
@@ -521,7 +529,12 @@ int upload_systems(ofdft_batch *b, const double *kappa, const std::vector<const 
             h.tg = make_tile_geom<S::TX, S::TYT, S::RY>(g, zl);
             return 0;
         });
-        h.nunits = h.tg.nblocks;
+        // untuned stepped batches run small grids on bricks, system by system
+        // (so a system's reduction order does not depend on the others)
+        StencilCfg bk;
+        h.brick = stepped && b->shape < 0 && brick_stencil(g, c64 ? 8 : 16, 1, bk) ? 1 : 0;
+        if (h.brick) h.bg = make_brick_geom(g, 4);
+        h.nunits = h.brick ? h.bg.nblocks : h.tg.nblocks;
         h.n = npoints(g);
         h.coef = make_coef(g, b->radius);
         h.coef32 = to_float(h.coef);
@@ -670,15 +683,20 @@ extern "C" int ofdft_batch_tune(ofdft_batch *b, const double *kappa, const void 
         int shape, P, planes;
     };
     const bool c64 = b->dtype == OFDFT_C64;
-    const Cand def{default_shape(b), 0, kStepPlanes};
+    // untuned: bricks for the grids that take them (shape -1), else the default tile
+    StencilCfg bk;
+    const bool brick = std::any_of(b->grids.begin(), b->grids.end(),
+                                   [&](const ofdft_grid &g) { return brick_stencil(g, c64 ? 8 : 16, 1, bk); });
+    const Cand def{brick ? -1 : default_shape(b), 0, kStepPlanes};
     std::vector<Cand> cand;
+    if (brick) cand.push_back(def);
     const std::vector<int> shapes = c64 ? std::vector<int>{SHAPE_64x4x2, SHAPE_64x4x4, SHAPE_32x8x2, SHAPE_64x8x2,
                                                            SHAPE_64x8x1}
                                         : std::vector<int>{SHAPE_64x8x1, SHAPE_64x4x2, SHAPE_32x8x2};
     for (int sh : shapes)
         for (int planes : {40, kStepPlanes, 160}) cand.push_back({sh, 0, planes});
     if (!b->precond)
-        for (int P : {16, 64}) cand.push_back({def.shape, P, kStepPlanes});
+        for (int P : {16, 64}) cand.push_back({default_shape(b), P, kStepPlanes});
     const int keep_shape = b->shape, keep_P = b->P, keep_planes = b->zplanes;
     std::vector<ofdft_solve_stats> st(nsys);
     double best = -1.0, def_ms = -1.0;
@@ -722,7 +740,7 @@ extern "C" int ofdft_batch_tune(ofdft_batch *b, const double *kappa, const void 
     b->zplanes = pick.planes;
     if (out) {
         *out = ofdft_tune_result{};
-        out->shape = pick.shape;
+        out->shape = pick.shape >= 0 ? pick.shape : default_shape(b);
         out->zlen = pick.planes;
         out->group = pick.P;
         out->candidates = (int)cand.size();

@@ -21,7 +21,9 @@ enum HDone { H_RUNNING = 0, H_CONVERGED = 1, H_BREAKDOWN = 2, H_NONFINITE = 3, H
 struct HSys {
     int nx, ny, nz;
     int nunits;
+    int brick, pad;           // stepped stencil phases: 1 = bricks (bg), 0 = marched tiles (tg)
     TileGeom tg;
+    BrickGeom bg;
     int64_t n;
     Coef<double> coef;
     Coef<float> coef32;
@@ -114,15 +116,18 @@ struct ofdft_batch {
     // stepped schedule
     ofdft::StepState *d_step = nullptr, *h_step = nullptr;   // per system (host copy pinned)
     int *d_ublk = nullptr, *d_vblk = nullptr;                 // block prefix sums (nsys + 1)
-    int *d_xpre = nullptr;       // per XCD: prefix sums of its share of every system's tiles (8 x (nsys + 1))
-    int step_grid = 0;           // stencil-phase workgroups: 8 x the longest XCD share
+    // marched systems, then systems on bricks; per XCD: prefix sums of its share of
+    // every system's tiles (2 x 8 x (nsys + 1); none of the other class)
+    int *d_xpre = nullptr;
+    int step_grid[2] = {0, 0};   // stencil-phase workgroups of each class: 8 x the longest XCD share
+    size_t step_lds = 0;         // LDS bytes of the brick launches
     unsigned int *d_ctr = nullptr;                           // per-system arrival counters
     double *d_spart = nullptr;                               // per-system partial slots
     int step_shape = -1, step_units = 0, step_vblocks = 0;
-    std::vector<int> h_ublk, h_vblk;
+    std::vector<int> h_ublk, h_vblk, h_brick;
     hipGraphExec_t step_graph = nullptr;
     hipStream_t step_cap = nullptr;
-    int step_graph_key[4] = {-1, -1, -1, -1};
+    int step_graph_key[5] = {-1, -1, -1, -1, -1};
     // preconditioner (OFDFT_PRECOND_*): z = M r per system
     int precond = 0;
     double *d_kap = nullptr;      // {Re, Im} for ofdft_batch_apply_preconditioner

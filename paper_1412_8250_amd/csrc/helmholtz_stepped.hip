@@ -127,15 +127,34 @@ struct StepEpiPAp {
 
 enum StepPhase { PH_INIT = 0, PH_PAP = 1, PH_PAP_FIRST = 2 };
 
+// A system's tile by the march or, for small grids, by the brick kernel.
+template <typename T, int TX, int TYT, int RY>
+struct StepMarch {
+    static constexpr int kThreads = TX * TYT;
+    template <class Load, class Epi>
+    __device__ static void run(const HSys &h, const Load &ld, Epi &ep, int unit) {
+        __shared__ T lds[StencilLds<T, TX, TYT, RY>::kElems];
+        stencil_tile<T, TX, TYT, RY>(h.tg, coef_of<T>(h), ld, ep, unit, lds);
+    }
+};
+template <typename T>
+struct StepBrick {
+    static constexpr int kThreads = kBrickThreads;
+    template <class Load, class Epi>
+    __device__ static void run(const HSys &h, const Load &ld, Epi &ep, int unit) {
+        extern __shared__ __align__(16) unsigned char brick_lds[];
+        stencil_brick<T, 4>(h.bg, coef_of<T>(h), ld, ep, unit, reinterpret_cast<T *>(brick_lds));
+    }
+};
+
 // Stencil phases.  part: 4 slots per unit, system j's region starts at
 // 4 * ublk[j] and is laid out [k][unit].
-template <typename T, int TX, int TYT, int RY, int Phase>
-__global__ void __launch_bounds__(TX * TYT)
+template <typename T, class Tile, int Phase>
+__global__ void __launch_bounds__(Tile::kThreads)
 step_stencil(const HSys *sys, StepState *st, const int *ublk, const int *xpre, int nsys,
              unsigned int *ctr, double *part, double tol) {
     using CT = CX<T>;
-    __shared__ T lds[StencilLds<T, TX, TYT, RY>::kElems];
-    __shared__ double scratch[4 * (TX * TYT / 64)];
+    __shared__ double scratch[4 * (Tile::kThreads / 64)];
     // workgroup b runs on XCD b % 8; that XCD's list holds, system after
     // system, the tiles [n x / 8, n (x + 1) / 8) of each system of n tiles
     constexpr int kXcd = 8;
@@ -154,7 +173,7 @@ step_stencil(const HSys *sys, StepState *st, const int *ublk, const int *xpre, i
     if constexpr (Phase == PH_INIT) {
         StepLoadX<T> ld{GPtr<T>(h.x)};
         StepEpiInit<T> ep{GPtr<T>(h.f), GPtr<T>(h.r), kappa, {0, 0, 0, 0}, {}};
-        stencil_tile<T, TX, TYT, RY>(h.tg, coef_of<T>(h), ld, ep, unit, lds);
+        Tile::run(h, ld, ep, unit);
         double acc[4] = {ep.acc[0], ep.acc[1], ep.acc[2], ep.acc[3]};
         block_sum<4>(acc, scratch);
         double t[4];
@@ -182,7 +201,7 @@ step_stencil(const HSys *sys, StepState *st, const int *ublk, const int *xpre, i
         StepEpiPAp<T, Phase == PH_PAP_FIRST> ep{GPtr<T>(p_old), GPtr<T>(p_new), GPtr<T>(h.Ap), GPtr<T>(h.x),
                                                 kappa, CT::mk(sj->be_re, sj->be_im),
                                                 CT::mk(sj->al_re, sj->al_im), {0, 0}, {}, {}, {}};
-        stencil_tile<T, TX, TYT, RY>(h.tg, coef_of<T>(h), ld, ep, unit, lds);
+        Tile::run(h, ld, ep, unit);
         double acc[2] = {ep.acc[0], ep.acc[1]};
         block_sum<2>(acc, scratch);
         double t[2];
@@ -317,24 +336,28 @@ step_dot(const HSys *sys, StepState *st, const int *vblk, int nsys, unsigned int
     }
 }
 
-template <typename T, int TX, int TYT, int RY>
-int launch_phase(ofdft_batch *b, int phase, double tol, hipStream_t s) {
-    const int grid = b->step_grid;
-    auto kern = phase == PH_INIT ? step_stencil<T, TX, TYT, RY, PH_INIT>
-                : phase == PH_PAP_FIRST ? step_stencil<T, TX, TYT, RY, PH_PAP_FIRST>
-                : step_stencil<T, TX, TYT, RY, PH_PAP>;
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(TX, TYT), 0, s, b->d_sys, b->d_step, b->d_ublk, b->d_xpre,
-                       b->nsys, b->d_ctr, b->d_spart, tol);
+template <typename T, class Tile>
+int launch_phase(ofdft_batch *b, int cls, int phase, dim3 threads, size_t lds, double tol, hipStream_t s) {
+    auto kern = phase == PH_INIT ? step_stencil<T, Tile, PH_INIT>
+                : phase == PH_PAP_FIRST ? step_stencil<T, Tile, PH_PAP_FIRST>
+                : step_stencil<T, Tile, PH_PAP>;
+    hipLaunchKernelGGL(kern, dim3(b->step_grid[cls]), threads, lds, s, b->d_sys, b->d_step, b->d_ublk,
+                       b->d_xpre + cls * 8 * (b->nsys + 1), b->nsys, b->d_ctr, b->d_spart, tol);
     OFDFT_CHECK_HIP(hipGetLastError());
     return OFDFT_OK;
 }
 
+// One launch per class of systems present (marched tiles, bricks).
 template <typename T>
 int launch_stencil_phase(ofdft_batch *b, int shape, int phase, double tol, hipStream_t s) {
-    return dispatch_cocg_shape<T>(shape, [&](auto sh) {
-        using S = decltype(sh);
-        return launch_phase<T, S::TX, S::TYT, S::RY>(b, phase, tol, s);
-    });
+    if (b->step_grid[0])
+        OFDFT_TRY(dispatch_cocg_shape<T>(shape, [&](auto sh) {
+            using S = decltype(sh);
+            return launch_phase<T, StepMarch<T, S::TX, S::TYT, S::RY>>(b, 0, phase, dim3(S::TX, S::TYT), 0, tol, s);
+        }));
+    if (b->step_grid[1])
+        OFDFT_TRY((launch_phase<T, StepBrick<T>>(b, 1, phase, dim3(kBrickThreads), b->step_lds, tol, s)));
+    return OFDFT_OK;
 }
 
 template <typename T>
@@ -436,8 +459,8 @@ int first_iteration(ofdft_batch *b, int shape, hipStream_t s, bool timed) {
 
 template <typename T>
 int graph_get(ofdft_batch *b, int shape) {
-    const int key[4] = {shape, (int)sizeof(T), b->step_units, b->precond};
-    if (b->step_graph && std::equal(key, key + 4, b->step_graph_key)) return OFDFT_OK;
+    const int key[5] = {shape, (int)sizeof(T), b->step_units, b->precond, b->step_grid[1]};
+    if (b->step_graph && std::equal(key, key + 5, b->step_graph_key)) return OFDFT_OK;
     if (b->step_graph) {
         (void)hipGraphExecDestroy(b->step_graph);
         b->step_graph = nullptr;
@@ -455,39 +478,46 @@ int graph_get(ofdft_batch *b, int shape) {
     const hipError_t ei = hipGraphInstantiate(&b->step_graph, graph, nullptr, nullptr, 0);
     (void)hipGraphDestroy(graph);
     OFDFT_CHECK_HIP(ei);
-    for (int i = 0; i < 4; ++i) b->step_graph_key[i] = key[i];
+    for (int i = 0; i < 5; ++i) b->step_graph_key[i] = key[i];
     return OFDFT_OK;
 }
 
 // Block tables of the current system table (units from the uploaded tile
 // geometries, vector blocks from the sizes) and the partial-slot buffer.
-int prepare_layout(ofdft_batch *b, const std::vector<HSys> &hs, hipStream_t s) {
+int prepare_layout(ofdft_batch *b, const std::vector<HSys> &hs, size_t elem, hipStream_t s) {
     const int nsys = b->nsys;
-    std::vector<int> ublk(nsys + 1, 0), vblk(nsys + 1, 0);
+    std::vector<int> ublk(nsys + 1, 0), vblk(nsys + 1, 0), brick(nsys, 0);
+    size_t lds = 0;
     for (int j = 0; j < nsys; ++j) {
-        ublk[j + 1] = ublk[j] + hs[j].tg.nblocks;
+        brick[j] = hs[j].brick;
+        if (brick[j]) lds = std::max(lds, brick_lds_bytes(hs[j].bg, 4, elem));
+        ublk[j + 1] = ublk[j] + hs[j].nunits;
         const int64_t want = (hs[j].n + 8 * kVecThreadsStep - 1) / (8 * kVecThreadsStep);
         vblk[j + 1] = vblk[j] + (int)std::max<int64_t>(1, std::min<int64_t>(want, kVecMaxBlocks));
     }
-    if (ublk == b->h_ublk && vblk == b->h_vblk) return OFDFT_OK;
+    b->step_lds = lds;
+    if (ublk == b->h_ublk && vblk == b->h_vblk && brick == b->h_brick) return OFDFT_OK;
     if (b->step_graph) {                    // captured with the old tables
         OFDFT_CHECK_HIP(hipStreamSynchronize(s));
         (void)hipGraphExecDestroy(b->step_graph);
         b->step_graph = nullptr;
     }
-    // per-XCD shares of every system's tiles (see step_stencil)
-    std::vector<int> xpre(8 * (size_t)(nsys + 1), 0);
-    int longest = 0;
-    for (int x = 0; x < 8; ++x) {
-        int *xp = xpre.data() + x * (nsys + 1);
-        for (int j = 0; j < nsys; ++j) {
-            const int64_t nu = ublk[j + 1] - ublk[j];
-            xp[j + 1] = xp[j] + (int)(nu * (x + 1) / 8 - nu * x / 8);
+    // per-XCD shares of every system's tiles (see step_stencil), class by class
+    std::vector<int> xpre(2 * 8 * (size_t)(nsys + 1), 0);
+    for (int cls = 0; cls < 2; ++cls) {
+        int longest = 0;
+        for (int x = 0; x < 8; ++x) {
+            int *xp = xpre.data() + (cls * 8 + x) * (nsys + 1);
+            for (int j = 0; j < nsys; ++j) {
+                const int64_t nu = brick[j] == cls ? ublk[j + 1] - ublk[j] : 0;
+                xp[j + 1] = xp[j] + (int)(nu * (x + 1) / 8 - nu * x / 8);
+            }
+            longest = std::max(longest, xp[nsys]);
         }
-        longest = std::max(longest, xp[nsys]);
+        b->step_grid[cls] = 8 * longest;
     }
     if (!b->d_ublk) {
-        OFDFT_CHECK_HIP(hipMalloc(&b->d_xpre, sizeof(int) * 8 * (nsys + 1)));
+        OFDFT_CHECK_HIP(hipMalloc(&b->d_xpre, sizeof(int) * 16 * (nsys + 1)));
         OFDFT_CHECK_HIP(hipMalloc(&b->d_ublk, sizeof(int) * (nsys + 1)));
         OFDFT_CHECK_HIP(hipMalloc(&b->d_vblk, sizeof(int) * (nsys + 1)));
         OFDFT_CHECK_HIP(hipMalloc(&b->d_ctr, sizeof(unsigned int) * kArriveWords * nsys));
@@ -509,8 +539,8 @@ int prepare_layout(ofdft_batch *b, const std::vector<HSys> &hs, hipStream_t s) {
     OFDFT_CHECK_HIP(hipStreamSynchronize(s));
     b->h_ublk = ublk;
     b->h_vblk = vblk;
+    b->h_brick = brick;
     b->step_units = ublk[nsys];
-    b->step_grid = 8 * std::max(longest, 1);
     b->step_vblocks = vblk[nsys];
     return OFDFT_OK;
 }
@@ -618,7 +648,7 @@ int stepped_run(ofdft_batch *b, bool c64, int shape, const std::vector<HSys> &hs
                 const std::vector<int> &which, const std::vector<int> &maxit, double tol,
                 std::vector<int> &iters, std::vector<int> &done, hipStream_t s) {
     if (b->precond && c64) return OFDFT_INVALID_ARG;
-    OFDFT_TRY(prepare_layout(b, hs, s));
+    OFDFT_TRY(prepare_layout(b, hs, c64 ? sizeof(float2) : sizeof(double2), s));
     if (c64) return run_t<float2>(b, shape, hs, which, maxit, tol, iters, done, s);
     return run_t<double2>(b, shape, hs, which, maxit, tol, iters, done, s);
 }
