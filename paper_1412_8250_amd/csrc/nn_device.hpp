@@ -17,136 +17,116 @@ namespace nn {
 
 // Bricks of the convolution and weight-gradient kernels: 16 x 4 x 4 points,
 // staged in LDS with a one-point halo.
-constexpr int kWbX = 16, kWbY = 4, kWbZ = 4, kWbZg = 4;
+constexpr int kWbX = 16, kWbY = 4, kWbZ = 4;
 constexpr int kWbTX = kWbX + 2, kWbTY = kWbY + 2, kWbTZ = kWbZ + 2;
 constexpr int kWbHalo = kWbTX * kWbTY * kWbTZ;      // 648 points
 constexpr int kWbPts = kWbX * kWbY * kWbZ;          // 256 points
 constexpr int kWbStride = 20;                       // LDS elements per point (16 + pad: no bank conflicts)
 
-__device__ inline int wrap_any(int i, int n) {
+// Periodic image of -1 <= i <= n + 16 (a brick and its halo): one conditional
+// step on axes longer than a brick, the remainder on shorter ones.
+__device__ inline int wrap_brick(int i, int n) {
+    if (n > 17) return wrapc(i, n);
     const int r = i % n;
     return r < 0 ? r + n : r;
 }
 
 // ---------------------------------------------------------------------------
-// Convolution, C_in a multiple of 16.  Block = 4 waves, each 16 points.
-// Weights Wt: [27][NTILE*16][Cin] (BF16, or FP32 in the FP32 mode; zero rows
-// for co >= Cout).  Output: activation type A (with or without ReLU) or FP32
-// (no ReLU), channels-last Cout.
-//
-// One 16-channel chunk of one tap is one v_mfma_f32_16x16x16 bf16 (lane
-// (m, kq) supplies channels 4 kq .. 4 kq + 3 of point m and of output m) or,
-// in the FP32 mode, four v_mfma_f32_16x16x4 f32 with the same loads: step j
-// takes channel 4 kq + j from every lane, so its K = 4 values are channels
-// j, 4 + j, 8 + j, 12 + j -- a permutation of the chunk's channels, applied
-// to A and B alike.
-template <int NTILE, typename A>
-__global__ void __launch_bounds__(256)
-conv_k16(InDescT<A> in, Geo g, const A *__restrict__ Wt, int cin, int cout, A *out_a,
-         float *out_f32, int relu) {
-    using V = typename Vec4<A>::type;
-    using Raw = typename Vec4<A>::raw;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int p0 = (blockIdx.x * 4 + wave) * 16;
-    if (p0 >= g.npts) return;
-    const int m = lane & 15, kq = lane >> 4;
-    int p = p0 + m;
-    if (p >= g.npts) p = p0;
-    const int x = p % g.nx, y = (p / g.nx) % g.ny, z = p / (g.nx * g.ny);
-    const int xs[3] = {wrapc(x - 1, g.nx), x, wrapc(x + 1, g.nx)};
-    const int ys[3] = {wrapc(y - 1, g.ny), y, wrapc(y + 1, g.ny)};
-    const int zs[3] = {wrapc(z - 1, g.nz), z, wrapc(z + 1, g.nz)};
-    f32x4 acc[NTILE];
-#pragma unroll
-    for (int nt = 0; nt < NTILE; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    constexpr int CO = NTILE * 16;
-    for (int t = 0; t < 27; ++t) {
-        const int xx = xs[t % 3], yy = ys[(t / 3) % 3], zz = zs[t / 9];
-        const A *wt = Wt + (size_t)t * CO * cin;
-        for (int c0 = 0; c0 < cin; c0 += 16) {
-            const V a = fetch4<A>(in, xx, yy, zz, c0 + 4 * kq, g);
-#pragma unroll
-            for (int nt = 0; nt < NTILE; ++nt) {
-                const Raw raw = *reinterpret_cast<const Raw *>(wt + (size_t)(nt * 16 + m) * cin + c0 + 4 * kq);
-                const V b = __builtin_bit_cast(V, raw);
-                if constexpr (sizeof(A) == 2) {
-                    acc[nt] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc[nt], 0, 0, 0);
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        acc[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], acc[nt], 0, 0, 0);
-                }
-            }
-        }
-    }
-#pragma unroll
-    for (int nt = 0; nt < NTILE; ++nt) {
-        const int co = nt * 16 + m;
-        if (co >= cout) continue;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int q = p0 + 4 * kq + i;
-            if (q >= g.npts) continue;
-            float v = acc[nt][i];
-            if (relu) v = fmaxf(v, 0.f);
-            if (out_f32) out_f32[(size_t)q * cout + co] = v;
-            else out_a[(size_t)q * cout + co] = Act<A>::from(v);
-        }
-    }
-}
-
 // Convolution on bricks, C_in a multiple of 16: one block (4 waves) owns a
-// brick of 16 x 4 x 4 points and NTB output tiles of 16 channels (tile group
-// blockIdx.y).  Per 16-channel input chunk the brick's input with its
-// one-point halo (18 x 6 x 6 points) is staged in LDS once (periodic images,
-// upsampled / concatenated / masked sources as in fetch4); then wave w runs
-// the 27 taps over the 4 rows of brick plane z0 + w: per tap it loads the
-// weights of its NTB tiles once (lane (m, kq): ci 4 kq .. 4 kq + 3 of output
-// channel m) and, per row, the 16 points' shifted input (lane (m, kq): point
-// m, channels 4 kq .. 4 kq + 3, one 8-byte LDS read) -- one MFMA K step per
-// (tap, chunk, row, tile).  Each input value is read from memory once per
-// brick and chunk instead of once per tap.  wgt layout as for conv_k16.
-template <int NTB, typename A>
+// brick of 16 x B x B points (B = 4: four rows per wave; B = 2: one) and NTB
+// output tiles of 16 channels (tile group blockIdx.y).  Per 16-channel input
+// chunk the brick's input with its one-point halo (periodic images, upsampled
+// / concatenated / masked sources as in fetch4) and the chunk's weights of
+// those tiles stand in LDS; the next chunk's are fetched into registers
+// meanwhile.  Wave w runs the 27 taps over its rows: per tap one weight read
+// per tile (lane (m, kq): ci 4 kq .. 4 kq + 3 of output channel m) and, per
+// row, one read of the 16 points' shifted input (lane (m, kq): point m,
+// channels 4 kq .. 4 kq + 3) -- one MFMA K step per (tap, chunk, row, tile), in
+// that order for every B and NTB.  Weights Wt: [27][padded C_out][C_in] (BF16,
+// or FP32 in the FP32 mode; zero rows for co >= C_out).  Output: activation
+// type A (with or without ReLU) or FP32 (no ReLU), channels-last C_out.
+//
+// One 16-channel chunk of one tap is one v_mfma_f32_16x16x16 bf16 or, in the
+// FP32 mode, four v_mfma_f32_16x16x4 f32 with the same loads: step j takes
+// channel 4 kq + j from every lane, so its K = 4 values are channels j, 4 + j,
+// 8 + j, 12 + j -- a permutation of the chunk's channels, applied to A and B
+// alike.
+//
+// Bound by LDS reads (16 bytes per lane and K step of one tile and row), and on
+// the coarse levels by too few workgroups: those take the small brick and one
+// tile per block, so that a 16^3 level gives 256 workgroups instead of 16.
+// Weights read from L2 in every tap left each wave waiting for them: one
+// application at 64^3 took 751 us, 278 so.
+template <int NTB, int B, typename A>
 __global__ void __launch_bounds__(256)
 conv_brick(InDescT<A> in, Geo g, const A *__restrict__ Wt, int cin, int cout, A *out_a, float *out_f32,
            int relu, int nbx, int nby) {
     using V = typename Vec4<A>::type;
     using Raw = typename Vec4<A>::raw;
-    __shared__ __align__(16) A xs[kWbHalo * kWbStride];
+    constexpr int TY = B + 2, TZ = B + 2, HALO = kWbTX * TY * TZ, ROWS = B * B / 4;
+    constexpr int NX = (HALO * 4 + 255) / 256, NW = (27 * 16 * NTB * 4 + 255) / 256;
+    __shared__ __align__(16) A xs[HALO * kWbStride];
+    __shared__ __align__(16) A ws[27 * 16 * NTB * kWbStride];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, m = lane & 15, kq = lane >> 4;
     int b = blockIdx.x;
     const int bxi = b % nbx;
     b /= nbx;
     const int byi = b % nby;
     const int bzi = b / nby;
-    const int x0 = bxi * kWbX, y0 = byi * kWbY, z0 = bzi * kWbZ;
+    const int x0 = bxi * kWbX, y0 = byi * B, z0 = bzi * B;
     const int cop = ((cout + 15) / 16) * 16;          // padded rows of the weight layout
     const int cob = blockIdx.y * NTB * 16;            // first output channel of the block
-    f32x4 acc[kWbY][NTB];
+    f32x4 acc[ROWS][NTB];
 #pragma unroll
-    for (int r = 0; r < kWbY; ++r)
+    for (int r = 0; r < ROWS; ++r)
 #pragma unroll
         for (int nt = 0; nt < NTB; ++nt) acc[r][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    V xv[NX];
+    Raw wv[NW];
+    auto fetch = [&](int c0) {
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+            const int e = min(tid + i * 256, HALO * 4 - 1), q = e >> 2, c4 = e & 3;
+            const int lx = q % kWbTX, ly = (q / kWbTX) % TY, lz = q / (kWbTX * TY);
+            xv[i] = fetch4<A>(in, wrap_brick(x0 - 1 + lx, g.nx), wrap_brick(y0 - 1 + ly, g.ny),
+                              wrap_brick(z0 - 1 + lz, g.nz), c0 + 4 * c4, g);
+        }
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {                // rows (tap, output channel of the block)
+            const int e = min(tid + i * 256, 27 * 16 * NTB * 4 - 1), q = e >> 2, c4 = e & 3;
+            const int t = q / (16 * NTB), co = q - t * 16 * NTB;
+            wv[i] = *reinterpret_cast<const Raw *>(Wt + ((size_t)t * cop + cob + co) * cin + c0 + 4 * c4);
+        }
+    };
+    fetch(0);
     for (int c0 = 0; c0 < cin; c0 += 16) {
         __syncthreads();
-        for (int e = tid; e < kWbHalo * 4; e += 256) {
-            const int q = e >> 2, c4 = e & 3;
-            const int lx = q % kWbTX, ly = (q / kWbTX) % kWbTY, lz = q / (kWbTX * kWbTY);
-            const V v = fetch4<A>(in, wrap_any(x0 - 1 + lx, g.nx), wrap_any(y0 - 1 + ly, g.ny),
-                                  wrap_any(z0 - 1 + lz, g.nz), c0 + 4 * c4, g);
-            *reinterpret_cast<Raw *>(xs + q * kWbStride + 4 * c4) = __builtin_bit_cast(Raw, v);
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+            const int e = tid + i * 256;
+            if (e < HALO * 4)
+                *reinterpret_cast<Raw *>(xs + (e >> 2) * kWbStride + 4 * (e & 3)) = __builtin_bit_cast(Raw, xv[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            const int e = tid + i * 256;
+            if (e < 27 * 16 * NTB * 4) *reinterpret_cast<Raw *>(ws + (e >> 2) * kWbStride + 4 * (e & 3)) = wv[i];
         }
         __syncthreads();
+        if (c0 + 16 < cin) fetch(c0 + 16);
+        // wave's rows: B = 4: plane `wave`, rows 0 .. 3; B = 2: plane wave / 2, row wave % 2
+        const int wz = B == 4 ? wave : wave >> 1, wy = B == 4 ? 0 : wave & 1;
+#pragma unroll 9
         for (int t = 0; t < 27; ++t) {
             const int dx = t % 3, dyo = (t / 3) % 3, dz = t / 9;      // shift + 1
-            const A *wt = Wt + ((size_t)t * cop + cob + m) * cin + c0 + 4 * kq;
             V bw[NTB];
 #pragma unroll
             for (int nt = 0; nt < NTB; ++nt)
-                bw[nt] = __builtin_bit_cast(V, *reinterpret_cast<const Raw *>(wt + (size_t)nt * 16 * cin));
+                bw[nt] = __builtin_bit_cast(
+                    V, *reinterpret_cast<const Raw *>(ws + ((t * NTB + nt) * 16 + m) * kWbStride + 4 * kq));
 #pragma unroll
-            for (int r = 0; r < kWbY; ++r) {
-                const A *xr = xs + (((wave + dz) * kWbTY + (r + dyo)) * kWbTX + m + dx) * kWbStride + 4 * kq;
+            for (int r = 0; r < ROWS; ++r) {
+                const A *xr = xs + (((wz + dz) * TY + (wy + r + dyo)) * kWbTX + m + dx) * kWbStride + 4 * kq;
                 const V a = __builtin_bit_cast(V, *reinterpret_cast<const Raw *>(xr));
 #pragma unroll
                 for (int nt = 0; nt < NTB; ++nt) {
@@ -162,10 +142,10 @@ conv_brick(InDescT<A> in, Geo g, const A *__restrict__ Wt, int cin, int cout, A 
         }
     }
     // lane holds D[point 4 kq + i][channel m] of each row and tile
-    const int z = z0 + wave;
+    const int z = z0 + (B == 4 ? wave : wave >> 1);
 #pragma unroll
-    for (int r = 0; r < kWbY; ++r) {
-        const int y = y0 + r;
+    for (int r = 0; r < ROWS; ++r) {
+        const int y = y0 + (B == 4 ? r : wave & 1);
 #pragma unroll
         for (int nt = 0; nt < NTB; ++nt) {
             const int co = cob + nt * 16 + m;
@@ -239,7 +219,7 @@ conv_c1(InDescT<A> in, Geo g, const A *__restrict__ W1, int cout, A *out_a, floa
 }
 
 // Weight gradient on bricks: one block (4 waves) owns a (16 ci x 16 co) tile
-// pair and a column of kWbZg bricks of 16 x 4 x 4 points along z.  Per brick
+// pair and a column of zg bricks of 16 x 4 x 4 points along z.  Per brick
 // the input tile with its one-point halo (18 x 6 x 6 points, the ci tile)
 // and the masked output gradient (256 points, the co tile) are staged in LDS
 // once; every wave then runs its taps (t = wave + 4u) over the brick's 16
@@ -248,21 +228,35 @@ conv_c1(InDescT<A> in, Geo g, const A *__restrict__ W1, int cout, A *out_a, floa
 // and dY[row point 4 kq + j][co m] (zero outside the grid), so each input
 // value is read from memory once per brick instead of once per tap.
 // part[chunk][t][ci][co], chunk = block column; summed by wgrad_reduce.
+//
+// Bound by LDS reads: the K index of both operands runs over points while LDS
+// holds channels side by side, so a lane's four values lie in four rows.  The
+// bf16 form reads them with the transposing ds_read_b64_tr_b16 (within 16
+// lanes, lane 4 j + c fetches channels 4 c .. 4 c + 3 of point 4 kq + j and
+// lane m receives channel m of the four points), one LDS instruction per
+// operand where four 2-byte reads and their packing were (mean launch of a
+// 64^3 training pair 70 -> 25 us).
 
-inline int wb_chunks(const Geo &g, int &nbx, int &nby, int &ngz) {
+// z bricks per block: long columns amortise the partial's write, but a level
+// with few bricks needs its blocks (at least 512 where the bricks allow it).
+inline int wb_chunks(const Geo &g, int pairs, int &nbx, int &nby, int &ngz, int &zg) {
     nbx = (g.nx + kWbX - 1) / kWbX;
     nby = (g.ny + kWbY - 1) / kWbY;
     const int nbz = (g.nz + kWbZ - 1) / kWbZ;
-    ngz = (nbz + kWbZg - 1) / kWbZg;
+    for (zg = 4; zg > 1; zg /= 2)
+        if (nbx * nby * ((nbz + zg - 1) / zg) * pairs >= 512) break;
+    ngz = (nbz + zg - 1) / zg;
     return nbx * nby * ngz;
 }
 
 template <typename A>
 __global__ void __launch_bounds__(256)
 conv_wgrad_brick(InDescT<A> x_in, Geo g, const A *__restrict__ dy, const A *__restrict__ ymask, int cin,
-                 int cout, int nbx, int nby, float *__restrict__ part) {
-    __shared__ A xs[kWbHalo * kWbStride];
-    __shared__ A ys[kWbPts * kWbStride];
+                 int cout, int nbx, int nby, int zg, float *__restrict__ part) {
+    using V = typename Vec4<A>::type;
+    using Raw = typename Vec4<A>::raw;
+    __shared__ __align__(16) A xs[kWbHalo * kWbStride];
+    __shared__ __align__(16) A ys[kWbPts * kWbStride];
     const int cot = (cout + 15) / 16;
     const int cit = blockIdx.y / cot, co_t = blockIdx.y % cot;
     int b = blockIdx.x;
@@ -277,68 +271,89 @@ conv_wgrad_brick(InDescT<A> x_in, Geo g, const A *__restrict__ dy, const A *__re
     f32x4 acc[7];
 #pragma unroll
     for (int u = 0; u < 7; ++u) acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int bz = gz * kWbZg; bz < min((gz + 1) * kWbZg, nbz); ++bz) {
+    for (int bz = gz * zg; bz < min((gz + 1) * zg, nbz); ++bz) {
         const int z0 = bz * kWbZ;
         __syncthreads();                      // the previous brick's readers are done
         // input tile with halo, channels [ci0, ci0 + 16), periodic images
         if (cin >= 16) {
+#pragma unroll 4
             for (int e = tid; e < kWbHalo * 4; e += 256) {
                 const int q = e >> 2, c4 = e & 3;
                 const int lx = q % kWbTX, ly = (q / kWbTX) % kWbTY, lz = q / (kWbTX * kWbTY);
-                const typename Vec4<A>::type v =
-                    fetch4<A>(x_in, wrap_any(x0 - 1 + lx, g.nx), wrap_any(y0 - 1 + ly, g.ny),
-                              wrap_any(z0 - 1 + lz, g.nz), ci0 + 4 * c4, g);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) xs[q * kWbStride + 4 * c4 + j] = static_cast<A>(v[j]);   // same bits: short -> u16, float -> float
+                const V v = fetch4<A>(x_in, wrap_brick(x0 - 1 + lx, g.nx), wrap_brick(y0 - 1 + ly, g.ny),
+                                      wrap_brick(z0 - 1 + lz, g.nz), ci0 + 4 * c4, g);
+                *reinterpret_cast<Raw *>(xs + q * kWbStride + 4 * c4) = __builtin_bit_cast(Raw, v);
             }
         } else {                              // one input channel
             for (int q = tid; q < kWbHalo; q += 256) {
                 const int lx = q % kWbTX, ly = (q / kWbTX) % kWbTY, lz = q / (kWbTX * kWbTY);
-                xs[q * kWbStride] = fetch1<A>(x_in, wrap_any(x0 - 1 + lx, g.nx), wrap_any(y0 - 1 + ly, g.ny),
-                                              wrap_any(z0 - 1 + lz, g.nz), 0, g);
+                xs[q * kWbStride] = fetch1<A>(x_in, wrap_brick(x0 - 1 + lx, g.nx), wrap_brick(y0 - 1 + ly, g.ny),
+                                              wrap_brick(z0 - 1 + lz, g.nz), 0, g);
 #pragma unroll
                 for (int c = 1; c < 16; ++c) xs[q * kWbStride + c] = A(0);
             }
         }
         // masked output gradient of the brick's points, channels [co0, co0 + 16)
-        for (int e = tid; e < kWbPts * 16; e += 256) {
-            const int q = e >> 4, c = e & 15;
-            const int lx = q % kWbX, ly = (q / kWbX) % kWbY, lz = q / (kWbX * kWbY);
-            const int x = x0 + lx, y = y0 + ly, z = z0 + lz, co = co0 + c;
-            A d = A(0);
-            if (x < g.nx && y < g.ny && z < g.nz && co < cout) {
-                const size_t i = (size_t)pidx(x, y, z, g) * cout + co;
-                d = dy[i];
-                if (ymask && !Act<A>::pos(ymask[i])) d = A(0);
+        if (cout >= 16) {                     // whole groups of four channels (cout % 16 == 0)
+            for (int e = tid; e < kWbPts * 4; e += 256) {
+                const int q = e >> 2, c4 = e & 3;
+                const int lx = q % kWbX, ly = (q / kWbX) % kWbY, lz = q / (kWbX * kWbY);
+                const int x = x0 + lx, y = y0 + ly, z = z0 + lz;
+                V v = V{};
+                if (x < g.nx && y < g.ny && z < g.nz) {
+                    const size_t i = (size_t)pidx(x, y, z, g) * cout + co0 + 4 * c4;
+                    v = __builtin_bit_cast(V, *reinterpret_cast<const Raw *>(dy + i));
+                    if (ymask) {
+                        const V mk = __builtin_bit_cast(V, *reinterpret_cast<const Raw *>(ymask + i));
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            if (!(mk[j] > 0)) v[j] = 0;
+                    }
+                }
+                *reinterpret_cast<Raw *>(ys + q * kWbStride + 4 * c4) = __builtin_bit_cast(Raw, v);
             }
-            ys[q * kWbStride + c] = d;
+        } else {
+            for (int e = tid; e < kWbPts * 16; e += 256) {
+                const int q = e >> 4, c = e & 15;
+                const int lx = q % kWbX, ly = (q / kWbX) % kWbY, lz = q / (kWbX * kWbY);
+                const int x = x0 + lx, y = y0 + ly, z = z0 + lz, co = co0 + c;
+                A d = A(0);
+                if (x < g.nx && y < g.ny && z < g.nz && co < cout) {
+                    const size_t i = (size_t)pidx(x, y, z, g) * cout + co;
+                    d = dy[i];
+                    if (ymask && !Act<A>::pos(ymask[i])) d = A(0);
+                }
+                ys[q * kWbStride + c] = d;
+            }
         }
         __syncthreads();
+        // the lane's part of a transposing read: row point 4 kq + (lane / 4) % 4, channels 4 (lane % 4) ..
+        const int tr = (4 * kq + ((lane >> 2) & 3)) * kWbStride + 4 * (lane & 3);
         for (int r = 0; r < kWbY * kWbZ; ++r) {
             const int ly = r % kWbY, lz = r / kWbY;
-            A bv[4];
+            const A *yrow = ys + (lz * kWbY + ly) * kWbX * kWbStride;
+            V bv;
+            if constexpr (sizeof(A) == 2) {
+                bv = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) V *)(yrow + tr));
+            } else {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) bv[j] = ys[((lz * kWbY + ly) * kWbX + 4 * kq + j) * kWbStride + m];
+                for (int j = 0; j < 4; ++j) bv[j] = yrow[(4 * kq + j) * kWbStride + m];
+            }
 #pragma unroll
             for (int u = 0; u < 7; ++u) {
                 const int t = wave + 4 * u;
                 if (t >= 27) break;
                 const int dx = t % 3, dyo = (t / 3) % 3, dz = t / 9;      // shift + 1
-                const A *xr = xs + (((lz + dz) * kWbTY + (ly + dyo)) * kWbTX + 4 * kq + dx) * kWbStride + m;
-                A av[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) av[j] = xr[j * kWbStride];
+                const A *xrow = xs + (((lz + dz) * kWbTY + (ly + dyo)) * kWbTX + dx) * kWbStride;
                 if constexpr (sizeof(A) == 2) {
-                    s16x4 a, bb;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        a[j] = (short)av[j];
-                        bb[j] = (short)bv[j];
-                    }
-                    acc[u] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, bb, acc[u], 0, 0, 0);
+                    const V av =
+                        __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) V *)(xrow + tr));
+                    acc[u] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, bv, acc[u], 0, 0, 0);
                 } else {
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[j], bv[j], acc[u], 0, 0, 0);
+                    for (int j = 0; j < 4; ++j)
+                        acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(xrow[(4 * kq + j) * kWbStride + m], bv[j], acc[u],
+                                                                      0, 0, 0);
                 }
             }
         }
@@ -358,29 +373,27 @@ conv_wgrad_brick(InDescT<A> x_in, Geo g, const A *__restrict__ dy, const A *__re
     }
 }
 
-// First stage of the chunk sum: slice s of `slices` sums chunks
-// [s * per, (s + 1) * per) in order into tmp[s][i] (per = ceil(chunks /
-// slices)), so that many blocks share the work; wgrad_reduce then sums the
-// slices in order.  The result does not depend on timing.
-__global__ void wgrad_reduce_slices(const float *__restrict__ part, int chunks, int count, int slices,
-                                    float *__restrict__ tmp) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    const int sl = blockIdx.y;
-    if (i >= count) return;
-    const int per = (chunks + slices - 1) / slices;
-    const int c0 = sl * per, c1 = min(c0 + per, chunks);
+// dW[i] = sum over chunks of part[chunk][i], 64 values and kWgradLanes runs of
+// chunks per block: run y sums chunks y, y + kWgradLanes, ... in order, then the
+// runs are added in order.  The result does not depend on timing.
+constexpr int kWgradLanes = 16;
+__global__ void __launch_bounds__(64 * kWgradLanes)
+wgrad_reduce(const float *__restrict__ part, int chunks, int count, float *__restrict__ dw) {
+    __shared__ float run[kWgradLanes][64];
+    const int i = blockIdx.x * 64 + threadIdx.x;
     float s = 0.f;
-    for (int c = c0; c < c1; ++c) s += part[(size_t)c * count + i];
-    tmp[(size_t)sl * count + i] = s;
-}
-
-// dW[i] = sum over chunks (fixed order) of part[chunk][i]
-__global__ void wgrad_reduce(const float *__restrict__ part, int chunks, int count, float *__restrict__ dw) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= count) return;
-    float s = 0.f;
-    for (int c = 0; c < chunks; ++c) s += part[(size_t)c * count + i];
-    dw[i] = s;
+    if (i < count) {
+#pragma unroll 4
+        for (int c = threadIdx.y; c < chunks; c += kWgradLanes) s += part[(size_t)c * count + i];
+    }
+    run[threadIdx.y][threadIdx.x] = s;
+    __syncthreads();
+    if (threadIdx.y == 0 && i < count) {
+        float t = 0.f;
+#pragma unroll
+        for (int y = 0; y < kWgradLanes; ++y) t += run[y][threadIdx.x];
+        dw[i] = t;
+    }
 }
 
 // 2x2x2 average pooling (fine grid g, C channels).

@@ -35,7 +35,6 @@ const int kBufCh[NBUF] = {1, 16, 16, 16, 16, 16, 32, 32, 32, 32, 32, 64, 64, 64,
                           64, 64, 64};
 
 int ntile(int c) { return (c + 15) / 16; }
-constexpr int kWgradSlices = 32;    // first-stage slices of the weight-gradient chunk sum
 
 Geo geo_of(const ofdft_nn *net, int level) {
     Geo g;
@@ -93,20 +92,29 @@ int conv(const InDescT<A> &in, const Geo &g, const A *w, int cin, int cout, void
             default: hipLaunchKernelGGL((conv_c1<4, A>), dim3(blocks), dim3(256), 0, s, in, g, w, cout, oa, out_f32, r); break;
         }
     } else {
-        // bricks of 16 x 4 x 4 points; at most 4 output tiles per block
-        const int nbx = (g.nx + kWbX - 1) / kWbX, nby = (g.ny + kWbY - 1) / kWbY, nbz = (g.nz + kWbZ - 1) / kWbZ;
+        // 16 x 4 x 4 bricks with up to three output tiles per block where that
+        // gives every CU two workgroups; else 16 x 2 x 2 bricks, one tile each
+        // (64 to 64 channels at 16^3: 75 us on 16 workgroups, 15 on 256)
         const int nt = ntile(cout);
-        const int ntb = nt <= 4 ? nt : (nt % 4 == 0 ? 4 : 3);
+        const int nbx = (g.nx + kWbX - 1) / kWbX;
+        const int ntb = nt == 1 || nt == 3 ? nt : 2;
         if (nt % ntb) {
             set_error("network: unsupported channel count %d", cout);
             return OFDFT_INVALID_ARG;
         }
-        const dim3 grid(nbx * nby * nbz, nt / ntb);
-        switch (ntb) {
-            case 1: hipLaunchKernelGGL((conv_brick<1, A>), grid, dim3(256), 0, s, in, g, w, cin, cout, oa, out_f32, r, nbx, nby); break;
-            case 2: hipLaunchKernelGGL((conv_brick<2, A>), grid, dim3(256), 0, s, in, g, w, cin, cout, oa, out_f32, r, nbx, nby); break;
-            case 3: hipLaunchKernelGGL((conv_brick<3, A>), grid, dim3(256), 0, s, in, g, w, cin, cout, oa, out_f32, r, nbx, nby); break;
-            default: hipLaunchKernelGGL((conv_brick<4, A>), grid, dim3(256), 0, s, in, g, w, cin, cout, oa, out_f32, r, nbx, nby); break;
+        const int nb4 = nbx * ((g.ny + 3) / 4) * ((g.nz + 3) / 4);
+        if (nb4 * (nt / ntb) >= 512) {
+            const dim3 grid(nb4, nt / ntb);
+            const int nby = (g.ny + 3) / 4;
+            switch (ntb) {
+                case 1: hipLaunchKernelGGL((conv_brick<1, 4, A>), grid, dim3(256), 0, s, in, g, w, cin, cout, oa, out_f32, r, nbx, nby); break;
+                case 2: hipLaunchKernelGGL((conv_brick<2, 4, A>), grid, dim3(256), 0, s, in, g, w, cin, cout, oa, out_f32, r, nbx, nby); break;
+                default: hipLaunchKernelGGL((conv_brick<3, 4, A>), grid, dim3(256), 0, s, in, g, w, cin, cout, oa, out_f32, r, nbx, nby); break;
+            }
+        } else {
+            const int nby = (g.ny + 1) / 2, nbz = (g.nz + 1) / 2;
+            hipLaunchKernelGGL((conv_brick<1, 2, A>), dim3(nbx * nby * nbz, nt), dim3(256), 0, s, in, g, w, cin, cout,
+                               oa, out_f32, r, nbx, nby);
         }
     }
     OFDFT_CHECK_HIP(hipGetLastError());
@@ -117,24 +125,20 @@ template <typename A>
 int wgrad(ofdft_nn *net, int layer, const InDescT<A> &x, const Geo &g, const void *dy, const void *ymask,
           hipStream_t s) {
     const int cin = kDefs[layer].cin, cout = kDefs[layer].cout;
-    int nbx, nby, ngz;
-    const int chunks = wb_chunks(g, nbx, nby, ngz);
+    const int pairs = ntile(cin) * ntile(cout);
+    int nbx, nby, ngz, zg;
+    const int chunks = wb_chunks(g, pairs, nbx, nby, ngz, zg);
     const size_t count = (size_t)27 * cin * cout;
     if ((size_t)chunks * count > net->part_cap) {
         set_error("network: weight-gradient scratch too small");
         return OFDFT_INVALID_ARG;
     }
     ProfScope ps(K_NN, (double)g.npts * sizeof(A) * (cin + cout), s);
-    hipLaunchKernelGGL(conv_wgrad_brick<A>, dim3(chunks, ntile(cin) * ntile(cout)), dim3(256), 0, s, x, g,
-                       (const A *)dy, (const A *)ymask, cin, cout, nbx, nby, net->part);
+    hipLaunchKernelGGL(conv_wgrad_brick<A>, dim3(chunks, pairs), dim3(256), 0, s, x, g, (const A *)dy,
+                       (const A *)ymask, cin, cout, nbx, nby, zg, net->part);
     OFDFT_CHECK_HIP(hipGetLastError());
-    // the chunk sum in two fixed-order stages (slices of chunks, then the slices)
-    const int slices = std::min(kWgradSlices, chunks);
-    hipLaunchKernelGGL(wgrad_reduce_slices, dim3((unsigned)((count + 255) / 256), slices), dim3(256), 0, s,
-                       net->part, chunks, (int)count, slices, net->part2);
-    OFDFT_CHECK_HIP(hipGetLastError());
-    hipLaunchKernelGGL(wgrad_reduce, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, s, net->part2,
-                       slices, (int)count, net->gr[layer]);
+    hipLaunchKernelGGL(wgrad_reduce, dim3((unsigned)((count + 63) / 64)), dim3(64, kWgradLanes), 0, s, net->part,
+                       chunks, (int)count, net->gr[layer]);
     OFDFT_CHECK_HIP(hipGetLastError());
     return OFDFT_OK;
 }
@@ -167,15 +171,13 @@ int net_reserve(ofdft_nn *net, const ofdft_grid &g) {
         // layer l runs on the level of its output
         static const int lvl[kLayers] = {0, 0, 1, 1, 2, 2, 3, 3, 2, 2, 1, 1, 0, 0, 0};
         const Geo gg = geo_of(net, lvl[l]);
-        int nbx, nby, ngz;
-        const size_t chunks = (size_t)wb_chunks(gg, nbx, nby, ngz);
+        int nbx, nby, ngz, zg;
+        const size_t chunks =
+            (size_t)wb_chunks(gg, ntile(kDefs[l].cin) * ntile(kDefs[l].cout), nbx, nby, ngz, zg);
         cap = std::max(cap, chunks * 27 * kDefs[l].cin * kDefs[l].cout);
     }
     OFDFT_TRY(nalloc(net, &net->part, sizeof(float) * cap, net->ws));
     net->part_cap = cap;
-    size_t cmax = 0;
-    for (int l = 0; l < kLayers; ++l) cmax = std::max(cmax, (size_t)27 * kDefs[l].cin * kDefs[l].cout);
-    OFDFT_TRY(nalloc(net, &net->part2, sizeof(float) * cmax * kWgradSlices, net->ws));
     return OFDFT_OK;
 }
 
@@ -379,15 +381,23 @@ extern "C" int ofdft_nn_create(uint64_t seed, ofdft_nn **out) {
         return st;
     };
     std::mt19937_64 rng(seed);
+    // weights, Adam moments and gradients: the layers of each one after another
+    // in one array, the order of the host arrays
+    int st;
+    size_t off = 0;
+    const size_t all = sizeof(float) * ofdft_nn_param_count();
+    if ((st = nalloc(net, &net->w[0], all, net->allocs)) || (st = nalloc(net, &net->m[0], all, net->allocs)) ||
+        (st = nalloc(net, &net->v[0], all, net->allocs)) || (st = nalloc(net, &net->gr[0], all, net->allocs)))
+        return fail(st);
     for (int l = 0; l < kLayers; ++l) {
         const int cin = kDefs[l].cin, cout = kDefs[l].cout;
         const size_t cnt = (size_t)27 * cin * cout;
-        int st;
-        if ((st = nalloc(net, &net->w[l], sizeof(float) * cnt, net->allocs)) ||
-            (st = nalloc(net, &net->m[l], sizeof(float) * cnt, net->allocs)) ||
-            (st = nalloc(net, &net->v[l], sizeof(float) * cnt, net->allocs)) ||
-            (st = nalloc(net, &net->gr[l], sizeof(float) * cnt, net->allocs)) ||
-            (st = nalloc(net, &net->wf[l], sizeof(u16) * (cin == 1 ? ntile(cout) * 16 * 32 : 27 * ntile(cout) * 16 * cin), net->allocs)) ||
+        net->w[l] = net->w[0] + off;
+        net->m[l] = net->m[0] + off;
+        net->v[l] = net->v[0] + off;
+        net->gr[l] = net->gr[0] + off;
+        off += cnt;
+        if ((st = nalloc(net, &net->wf[l], sizeof(u16) * (cin == 1 ? ntile(cout) * 16 * 32 : 27 * ntile(cout) * 16 * cin), net->allocs)) ||
             (st = nalloc(net, &net->wb[l], sizeof(u16) * (cout == 1 ? ntile(cin) * 16 * 32 : 27 * ntile(cin) * 16 * cout), net->allocs)) ||
             (st = nalloc(net, &net->wf32[l], sizeof(float) * (cin == 1 ? ntile(cout) * 16 * 32 : 27 * ntile(cout) * 16 * cin), net->allocs)) ||
             (st = nalloc(net, &net->wb32[l], sizeof(float) * (cout == 1 ? ntile(cin) * 16 * 32 : 27 * ntile(cin) * 16 * cout), net->allocs)))
@@ -401,7 +411,6 @@ extern "C" int ofdft_nn_create(uint64_t seed, ofdft_nn **out) {
             hipMemset(net->v[l], 0, sizeof(float) * cnt) != hipSuccess)
             return fail(OFDFT_HIP_ERROR);
     }
-    int st;
     if ((st = nalloc(net, &net->totals, sizeof(double) * 16, net->allocs)) || (st = redbuf_alloc(net->rb)))
         return fail(st);
     if ((st = pack_all(net, nullptr))) return fail(st);
@@ -424,12 +433,7 @@ extern "C" int ofdft_nn_set_weights(ofdft_nn *net, const float *w, size_t count)
         set_error("ofdft_nn_set_weights: expected %zu values", ofdft_nn_param_count());
         return OFDFT_INVALID_ARG;
     }
-    size_t off = 0;
-    for (int l = 0; l < kLayers; ++l) {
-        const size_t cnt = (size_t)27 * kDefs[l].cin * kDefs[l].cout;
-        OFDFT_CHECK_HIP(hipMemcpy(net->w[l], w + off, sizeof(float) * cnt, hipMemcpyHostToDevice));
-        off += cnt;
-    }
+    OFDFT_CHECK_HIP(hipMemcpy(net->w[0], w, sizeof(float) * count, hipMemcpyHostToDevice));
     OFDFT_TRY(pack_all(net, nullptr));
     OFDFT_CHECK_HIP(hipDeviceSynchronize());
     net->adam_t = 0;
@@ -442,13 +446,7 @@ extern "C" int ofdft_nn_get_weights(ofdft_nn *net, float *w, size_t count, int g
         return OFDFT_INVALID_ARG;
     }
     OFDFT_CHECK_HIP(hipDeviceSynchronize());
-    size_t off = 0;
-    for (int l = 0; l < kLayers; ++l) {
-        const size_t cnt = (size_t)27 * kDefs[l].cin * kDefs[l].cout;
-        OFDFT_CHECK_HIP(hipMemcpy(w + off, gradients ? net->gr[l] : net->w[l], sizeof(float) * cnt,
-                                  hipMemcpyDeviceToHost));
-        off += cnt;
-    }
+    OFDFT_CHECK_HIP(hipMemcpy(w, gradients ? net->gr[0] : net->w[0], sizeof(float) * count, hipMemcpyDeviceToHost));
     return OFDFT_OK;
 }
 
