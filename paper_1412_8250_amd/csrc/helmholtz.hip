@@ -202,7 +202,7 @@ __device__ void cocg_solve_one(const HSys &s, HState *st, GroupCtl *c, double (*
     if (done == H_RUNNING && maxit <= 0) done = H_MAXIT;
     int iter = 0;
     double be_re = 0.0, be_im = 0.0;
-    GPtr<T> p_old(s.pA), p_new(s.pB);
+    GPtr<T> p_old(s.p), p_new(s.q[1]);
     __syncthreads();
 
     while (done == H_RUNNING) {
@@ -542,18 +542,13 @@ int upload_systems(ofdft_batch *b, const double *kappa, const std::vector<const 
         h.kim = kappa[2 * j + 1];
         h.x = x[j];
         h.f = f[j];
-        h.z = b->precond ? b->z[j] : nullptr;
-        if (c64) {
-            h.r = b->r[j];
-            h.pA = b->pA[j];
-            h.pB = b->pB[j];
-            h.Ap = b->Ap[j];
-        } else {
-            h.r = b->r[j];
-            h.pA = b->pA[j];
-            h.pB = b->pB[j];
-            h.Ap = b->Ap[j];
-        }
+        h.r = b->r[j];
+        h.p = b->p[j];
+        h.Ap = b->Ap[j];
+        h.ring = b->ring;
+        h.precond = b->precond != OFDFT_PRECOND_NONE;
+        h.q[0] = h.precond ? b->z[j] : b->r[j];
+        for (int k = 1; k < b->ring; ++k) h.q[k] = b->slot[k][j];
     }
     OFDFT_CHECK_HIP(hipMemcpyAsync(b->d_sys, hs.data(), sizeof(HSys) * b->nsys, hipMemcpyHostToDevice, s));
     OFDFT_CHECK_HIP(hipStreamSynchronize(s));
@@ -590,8 +585,17 @@ extern "C" int ofdft_batch_create(int nsys, const ofdft_grid *grids, int radius,
     const bool c64 = dtype == OFDFT_C64;
     const size_t e = c64 ? sizeof(float2) : sizeof(double2);
     b->r.resize(nsys);
-    b->pA.resize(nsys);
-    b->pB.resize(nsys);
+    b->p.resize(nsys);
+    // four ring slots, or two where the vectors would then take more than an
+    // eighth of the card's memory (no more than a schedule without the ring)
+    double bytes = 0.0;
+    for (int j = 0; j < nsys; ++j) bytes += (double)npoints(grids[j]) * e * (2 + kRingMax);
+    int dev = 0, cus = 0;
+    size_t mem_total = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceTotalMem(&mem_total, dev) != hipSuccess)
+        return fail(OFDFT_HIP_ERROR);
+    b->ring = bytes <= (double)mem_total / 8 ? kRingMax : 2;
+    for (int k = 1; k < b->ring; ++k) b->slot[k].resize(nsys);
     b->Ap.resize(nsys);
     b->r128.resize(nsys);
     b->f32.resize(nsys);
@@ -599,18 +603,18 @@ extern "C" int ofdft_batch_create(int nsys, const ofdft_grid *grids, int radius,
     for (int j = 0; j < nsys; ++j) {
         const size_t n = (size_t)npoints(grids[j]);
         int st = OFDFT_OK;
-        if ((st = dalloc(b, &b->r[j], n * e)) || (st = dalloc(b, &b->pA[j], n * e)) ||
-            (st = dalloc(b, &b->pB[j], n * e)) || (st = dalloc(b, &b->Ap[j], n * e)))
+        if ((st = dalloc(b, &b->r[j], n * e)) || (st = dalloc(b, &b->p[j], n * e)) ||
+            (st = dalloc(b, &b->Ap[j], n * e)))
             return fail(st);
+        if ((st = dalloc(b, &b->slot[1][j], (b->ring - 1) * n * e))) return fail(st);
+        for (int k = 2; k < b->ring; ++k) b->slot[k][j] = (char *)b->slot[1][j] + (k - 1) * n * e;
         if (c64) {
             if ((st = dalloc(b, &b->r128[j], n * sizeof(double2))) ||
                 (st = dalloc(b, &b->f32[j], n * e)) || (st = dalloc(b, &b->x32[j], n * e)))
                 return fail(st);
         }
     }
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         return fail(OFDFT_HIP_ERROR);
     b->groups_cap = std::max(1, cus * 8);
     int st = OFDFT_OK;
@@ -843,13 +847,15 @@ extern "C" int ofdft_batch_set_preconditioner(ofdft_batch *b, int kind) {
             set_error("ofdft_batch_set_preconditioner: out of device memory");
             return undo(OFDFT_NO_MEMORY);
         }
-        if (hipMalloc(&ztab, sizeof(void *) * b->nsys) != hipSuccess) {
+        std::vector<void *> zt(z);
+        for (int k = 1; k < b->ring; ++k) zt.insert(zt.end(), b->slot[k].begin(), b->slot[k].end());
+        if (hipMalloc(&ztab, sizeof(void *) * zt.size()) != hipSuccess) {
             ztab = nullptr;
             set_error("ofdft_batch_set_preconditioner: out of device memory");
             return undo(OFDFT_NO_MEMORY);
         }
         if (hipMemcpy(rtab, rt.data(), sizeof(void *) * b->nsys, hipMemcpyHostToDevice) != hipSuccess ||
-            hipMemcpy(ztab, z.data(), sizeof(void *) * b->nsys, hipMemcpyHostToDevice) != hipSuccess)
+            hipMemcpy(ztab, zt.data(), sizeof(void *) * zt.size(), hipMemcpyHostToDevice) != hipSuccess)
             return undo(OFDFT_HIP_ERROR);
     }
     OFDFT_CHECK_HIP(hipDeviceSynchronize());
@@ -919,13 +925,16 @@ static int batch_solve(ofdft_batch *b, const double *kappa, const void *const *r
             for (int j : which) {
                 iters[j] += it_pass[j];
                 done[j] = done_pass[j];
-                // init: read x, f, write r; stencil phase: read r (z), p_old,
-                // Ap_old, x, write p, Ap, x (the first one reads r only and
-                // writes p, Ap); vector phase: read r, Ap, write r (the last
-                // direction's x update is accounted by the run itself)
+                // init: read x, f, write r; stencil phase: read r (z), Ap_old,
+                // write Ap (the first one reads no Ap_old); vector phase: read
+                // r, Ap, write r; every ring-th one also reads the other slots,
+                // p and x and writes p and x, the first of these reads no p
+                // (what a stopped system still owes is accounted by the run)
                 const double n = (double)npoints(b->grids[j]);
-                bs += n * e * (3.0 + (it_pass[j] > 0 ? 7.0 * it_pass[j] - 4.0 : 0.0));
+                const int flushes = it_pass[j] / b->ring;
+                bs += n * e * (3.0 + (it_pass[j] > 0 ? 3.0 * it_pass[j] - 1.0 : 0.0));
                 bu += n * e * 3.0 * it_pass[j];
+                if (flushes > 0) bu += n * e * ((b->ring + (b->precond ? 4.0 : 3.0)) * flushes - 1.0);
                 if (b->precond) {
                     // one cycle and one dot phase (read r, z) after the init
                     // phase and after each iteration but the last

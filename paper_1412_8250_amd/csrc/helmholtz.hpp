@@ -18,6 +18,9 @@ namespace ofdft {
 // H_IDLE marks systems that do not take part in a pass.
 enum HDone { H_RUNNING = 0, H_CONVERGED = 1, H_BREAKDOWN = 2, H_NONFINITE = 3, H_MAXIT = 4, H_IDLE = 5 };
 
+// Slots of the stepped schedule's ring (see helmholtz_stepped.hip): 4 or 2.
+constexpr int kRingMax = 4;
+
 struct HSys {
     int nx, ny, nz;
     int nunits;
@@ -28,8 +31,13 @@ struct HSys {
     Coef<double> coef;
     Coef<float> coef32;
     double kre, kim;          // adjacent: the multigrid cycle reads them as {Re, Im}
-    void *x, *r, *pA, *pB, *Ap;
-    void *z;                  // preconditioned residual M r (nullptr: no preconditioner)
+    void *x, *r, *p, *Ap;
+    // stepped schedule: the vectors the directions are built from (residuals, or
+    // z = M r with a preconditioner) of the iterations whose p and x are still
+    // to be brought up to date; iteration k's in slot k % ring.  Without a
+    // preconditioner slot 0 is r.  The persistent schedule's second p is slot 1.
+    void *q[kRingMax];
+    int ring, precond;
     const void *f;
 };
 
@@ -97,8 +105,10 @@ struct ofdft_batch {
     ofdft_dtype dtype = OFDFT_C128;
     std::vector<ofdft_grid> grids;
     std::vector<void *> allocs;
-    // per system workspaces (complex128: r, pA, pB, Ap; complex64 adds r128, f32, x32)
-    std::vector<void *> r, pA, pB, Ap, r128, f32, x32;
+    // per system workspaces (complex128: r, p, ring slots 1 .. ring - 1, Ap; complex64 adds r128, f32, x32)
+    std::vector<void *> r, p, Ap, r128, f32, x32;
+    std::vector<void *> slot[ofdft::kRingMax];   // slot[0] unused
+    int ring = 2;
     ofdft::HSys *d_sys = nullptr;
     ofdft::HState *d_st = nullptr;
     int *d_order = nullptr;
@@ -131,14 +141,14 @@ struct ofdft_batch {
     // preconditioner (OFDFT_PRECOND_*): z = M r per system
     int precond = 0;
     double *d_kap = nullptr;      // {Re, Im} for ofdft_batch_apply_preconditioner
-    std::vector<void *> z;
+    std::vector<void *> z;        // ring slot 0 of the preconditioned iteration
     std::vector<ofdft::Multigrid *> mg_of, mg_own;
     // consecutive systems on one grid form a group: one hierarchy holds their
     // level arrays (system j is member mg_q[j]) and one launch per kernel runs
     // their cycles; groups as (first system, count)
     std::vector<int> mg_q;
     std::vector<std::pair<int, int>> mg_groups;
-    void **d_rtab = nullptr, **d_ztab = nullptr;   // r[j], z[j] (device tables)
+    void **d_rtab = nullptr, **d_ztab = nullptr;   // device tables: r[j]; ring slot k of system j at [k nsys + j]
     // the groups' cycles run on kMgLanes side streams (group g on lane
     // g % lanes), forked from and joined back into the solve's stream, so
     // the latency-bound coarse levels of different groups overlap

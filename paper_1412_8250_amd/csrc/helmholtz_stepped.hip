@@ -5,15 +5,25 @@
 //
 // Each COCG phase is ONE launch over all running systems of the batch:
 //  * stencil phase: the stencil runs on r alone (A r = -L r + kappa r); the
-//    new direction and its image follow point by point from the previous
-//    ones, p = r + beta p_old and Ap = A r + beta Ap_old (A is linear), so
-//    only one array is read with a halo; p^T Ap is reduced;  the grid holds
+//    image of the new direction p = r + beta p_old follows point by point from
+//    the previous one, Ap = A r + beta Ap_old (A is linear), so only one array
+//    is read with a halo, and p itself isn't needed: p^T A p = r^T A p +
+//    beta p_old^T A p, where p_old^T A p = Ap_old^T r + beta p_old^T Ap_old is
+//    zero but for rounding (with a single-precision cycle as preconditioner
+//    that isn't small: left out, the solutions moved 5 times further).  The
+//    two products r^T A p and Ap_old^T r are reduced.  The grid holds
 //    the stencil tiles of every system, so eight 320^3 systems give
 //    thousands of workgroups per launch.  Each XCD takes one contiguous
 //    eighth of every system's tiles (neighbouring tiles share their halos
 //    in that XCD's L2, and the systems still running keep every XCD busy
 //    when the others have converged);
-//  * vector phase: x += alpha p, r -= alpha Ap, r^T r and |r|^2 reduced.
+//  * vector phase: r -= alpha Ap into the next slot of a ring of residuals,
+//    r^T r and |r|^2 reduced.  Every ring-th vector phase (ring = 4; 2 for
+//    batches that fill the card's memory) brings p and x up to date from the
+//    ring and the kept alphas and betas: p = r_k + beta_k p, x += alpha_k p.
+// Per iteration that moves 6 vectors and (ring + 3) / ring for p and x: 7.75
+// in place of the 10 that the update of p and x in each iteration takes
+// (6 cells of 24 to 96 points an axis, 8 shifts each, to 1e-10: 66 -> 62 ms).
 // The scalars of every system (alpha, beta, r^T r, status) live on the
 // device: the last workgroup of a system to finish a phase combines that
 // system's partial sums (fixed order, so results do not depend on timing or
@@ -26,7 +36,8 @@
 // symmetric) the iteration is preconditioned COCG: after the vector phase
 // z = M r is formed by the cycle's own launches, a dot phase reduces
 // rho = r^T z and sets beta = rho_new / rho, and the stencil phase runs on z:
-// p = z + beta p_old, Ap = A z + beta Ap_old.
+// p = z + beta p_old, Ap = A z + beta Ap_old, and so for p^T A p.  The ring
+// then holds z; r is updated in place.
 #include <algorithm>
 #include <cmath>
 
@@ -36,16 +47,17 @@ namespace ofdft {
 
 struct StepState {
     double rr_re, rr_im;     // r^T r (preconditioned: r^T z) of the current residual
-    double al_re, al_im;     // alpha of the current iteration
-    double be_re, be_im;     // beta of the next direction
+    double al[kRingMax][2];  // alpha and beta {re, im} of the iterations in the ring
+    double be[kRingMax][2];  // (slot iter % ring)
+    double pa[2];            // p^T A p of the last direction
     double rn2, fn2, tol2;   // |r|^2, |f|^2, tol^2 |f|^2
-    int iter, done, maxit, parity;   // parity: 0 -> p_old in pA, 1 -> p_old in pB
-    int xpend, pad;          // x += alpha p of the last direction still to apply
+    int iter, done, maxit, pad;      // iter % ring directions are still to be applied to x
 };
 
 namespace {
 
 constexpr int kStepIters = 4;          // iterations per captured graph
+static_assert(kStepIters % kRingMax == 0 && kStepIters % 2 == 0, "a captured block ends at its first ring slot");
 constexpr int kVecThreadsStep = 256;
 constexpr int kVecMaxBlocks = 1024;    // per system
 
@@ -87,41 +99,31 @@ struct StepEpiInit {     // r = f - (-L x + kappa x); acc {r^T r re, im, |r|^2, 
     }
 };
 
-// Centre = r (z when preconditioned), s = L r.  p = r + beta p_old and
-// Ap = (-L r + kappa r) + beta Ap_old, Ap updated in place (each point is read
-// and written by the same thread); the previous iteration's x += alpha p_old
-// is applied here too, where p_old is read anyway (the vector phase then
-// moves r and Ap only; the last direction's update is left to step_finish).
-// The first iteration (beta = 0, no previous direction) reads neither p_old,
-// Ap_old nor x.  acc {p^T Ap re, im}.  The first iteration is
-// a kernel of its own: with a run-time flag the loads and their use sit in
-// branches, and the compiler then waits for the halo fetches of the previous
-// plane before it reuses the registers of these loads.
+// Centre = r (z when preconditioned), s = L r.  Ap = (-L r + kappa r) +
+// beta Ap_old, updated in place (each point is read and written by the same
+// thread).  acc {r^T Ap re, im, r^T Ap_old re, im}.  The first iteration (beta = 0, no previous
+// image) reads no Ap_old and is a kernel of its own: with a run-time flag the
+// loads and their use sit in branches, and the compiler then waits for the
+// halo fetches of the previous plane before it reuses their registers.
 template <typename T, bool First>
 struct StepEpiPAp {
-    GPtr<T> p_old, p_out, Ap, x;
-    T kappa, beta, alpha;
-    double acc[2];
-    T po[4], ao[4], xo[4];
+    GPtr<T> Ap;
+    T kappa, beta;
+    double acc[4];
+    T ao[4];
     __device__ void pre(int q, int64_t i) {
-        if constexpr (!First) {
-            po[q] = p_old[i];
-            ao[q] = Ap[i];
-            xo[q] = x[i];
-        }
+        if constexpr (!First) ao[q] = Ap[i];
     }
     __device__ void point(int q, int64_t i, T c, T s) {
         T a = cfma(kappa, c, T{-s.x, -s.y});
-        T p = c;
         if constexpr (!First) {
-            x.st(i, cfma(alpha, po[q], xo[q]));
-            p = cfma(beta, po[q], c);
             a = cfma(beta, ao[q], a);
+            acc[2] += (double)c.x * ao[q].x - (double)c.y * ao[q].y;
+            acc[3] += (double)c.x * ao[q].y + (double)c.y * ao[q].x;
         }
-        p_out.st(i, p);
         Ap.st(i, a);
-        acc[0] += (double)p.x * a.x - (double)p.y * a.y;
-        acc[1] += (double)p.x * a.y + (double)p.y * a.x;
+        acc[0] += (double)c.x * a.x - (double)c.y * a.y;
+        acc[1] += (double)c.x * a.y + (double)c.y * a.x;
     }
 };
 
@@ -152,7 +154,7 @@ struct StepBrick {
 template <typename T, class Tile, int Phase>
 __global__ void __launch_bounds__(Tile::kThreads)
 step_stencil(const HSys *sys, StepState *st, const int *ublk, const int *xpre, int nsys,
-             unsigned int *ctr, double *part, double tol) {
+             unsigned int *ctr, double *part, double tol, int slot) {
     using CT = CX<T>;
     __shared__ double scratch[4 * (Tile::kThreads / 64)];
     // workgroup b runs on XCD b % 8; that XCD's list holds, system after
@@ -184,7 +186,6 @@ step_stencil(const HSys *sys, StepState *st, const int *ublk, const int *xpre, i
             sj->fn2 = t[3];
             sj->tol2 = tol * tol * t[3];
             sj->iter = 0;
-            sj->parity = 0;
             int d = !isfinite(t[2]) ? H_NONFINITE : (t[2] <= sj->tol2 ? H_CONVERGED : H_RUNNING);
             if (d == H_RUNNING && sj->maxit <= 0) d = H_MAXIT;
             sj->done = d;
@@ -192,43 +193,58 @@ step_stencil(const HSys *sys, StepState *st, const int *ublk, const int *xpre, i
     } else {
         // PH_PAP_FIRST runs iteration 0 of every running system, PH_PAP the
         // later ones (the host launches the first right after the init phase)
-        const void *p_old = sj->parity ? h.pB : h.pA;
-        const void *p_new = sj->parity ? h.pA : h.pB;
-        const void *base = h.z ? h.z : h.r;
-        StepLoadX<T> ld{GPtr<T>(base)};
-        // alpha of the previous iteration: the last workgroup below sets this
-        // iteration's only after every workgroup has arrived
-        StepEpiPAp<T, Phase == PH_PAP_FIRST> ep{GPtr<T>(p_old), GPtr<T>(p_new), GPtr<T>(h.Ap), GPtr<T>(h.x),
-                                                kappa, CT::mk(sj->be_re, sj->be_im),
-                                                CT::mk(sj->al_re, sj->al_im), {0, 0}, {}, {}, {}};
+        StepLoadX<T> ld{GPtr<T>(h.q[slot])};
+        StepEpiPAp<T, Phase == PH_PAP_FIRST> ep{GPtr<T>(h.Ap), kappa, CT::mk(sj->be[slot][0], sj->be[slot][1]),
+                                                {0, 0, 0, 0}, {}};
         Tile::run(h, ld, ep, unit);
-        double acc[2] = {ep.acc[0], ep.acc[1]};
-        block_sum<2>(acc, scratch);
-        double t[2];
-        if (reduce_grid<2>(acc, pj, nunits, unit, ctr + (size_t)j * kArriveWords, scratch, t)) {
+        constexpr int kSums = Phase == PH_PAP_FIRST ? 2 : 4;
+        double acc[kSums];
+        for (int k = 0; k < kSums; ++k) acc[k] = ep.acc[k];
+        block_sum<kSums>(acc, scratch);
+        double t[kSums];
+        if (reduce_grid<kSums>(acc, pj, nunits, unit, ctr + (size_t)j * kArriveWords, scratch, t)) {
+            if constexpr (kSums == 4) {         // + beta (Ap_old^T r + beta p_old^T Ap_old)
+                const double be_re = sj->be[slot][0], be_im = sj->be[slot][1];
+                const double u = t[2] + (be_re * sj->pa[0] - be_im * sj->pa[1]);
+                const double v = t[3] + (be_re * sj->pa[1] + be_im * sj->pa[0]);
+                t[0] += be_re * u - be_im * v;
+                t[1] += be_re * v + be_im * u;
+            }
+            sj->pa[0] = t[0];
+            sj->pa[1] = t[1];
             const double den = t[0] * t[0] + t[1] * t[1];
-            // the previous direction's x update is applied by now
-            sj->xpend = 0;
             if (!isfinite(den)) {
                 sj->done = H_NONFINITE;
             } else if (den == 0.0) {
                 sj->done = H_BREAKDOWN;
             } else {
-                sj->al_re = (sj->rr_re * t[0] + sj->rr_im * t[1]) / den;
-                sj->al_im = (sj->rr_im * t[0] - sj->rr_re * t[1]) / den;
-                sj->xpend = 1;
+                sj->al[slot][0] = (sj->rr_re * t[0] + sj->rr_im * t[1]) / den;
+                sj->al[slot][1] = (sj->rr_im * t[0] - sj->rr_re * t[1]) / den;
             }
         }
     }
 }
 
-// Vector phase: r -= alpha Ap (x follows in the next stencil phase or in
-// step_finish); then beta (unpreconditioned) and status.  part region of system j starts at 4 * vblk[j] (the caller
-// offsets part past the stencil slots).
+// p and x of one point brought up to date by the ring's first `cnt` directions.
 template <typename T>
+__device__ inline void ring_point(const T (&q)[kRingMax], int cnt, const T *al, const T *be, T &p, T &x) {
+#pragma unroll
+    for (int k = 0; k < kRingMax; ++k)
+        if (k < cnt) {
+            p = cfma(be[k], p, q[k]);
+            x = cfma(al[k], p, x);
+        }
+}
+
+// Vector phase of the iteration in ring slot `slot`: r -= alpha Ap (into the
+// next slot; in place when preconditioned), with Ring > 0 (the last slot of a
+// ring of Ring) also p and x; then beta (unpreconditioned) and status.  part
+// region of system j starts at 4 * vblk[j] (the caller offsets part past the
+// stencil slots).
+template <typename T, int Ring>
 __global__ void __launch_bounds__(kVecThreadsStep)
 step_update(const HSys *sys, StepState *st, const int *vblk, int nsys, unsigned int *ctr,
-            double *part) {
+            double *part, int slot) {
     using CT = CX<T>;
     __shared__ double scratch[3 * (kVecThreadsStep / 64)];
     const int b = blockIdx.x;
@@ -237,34 +253,58 @@ step_update(const HSys *sys, StepState *st, const int *vblk, int nsys, unsigned 
     if (sj->done != H_RUNNING) return;
     const HSys &h = sys[j];
     const int lb = b - vblk[j], nb = vblk[j + 1] - vblk[j];
-    const GPtr<T> r(h.r), Ap(h.Ap);
-    const T nal = CT::mk(-sj->al_re, -sj->al_im);
+    const bool pre = h.precond != 0;            // rho and beta come from the dot phase
+    const int next = Ring ? 0 : slot + 1;
+    const GPtr<T> r(pre ? h.r : h.q[slot]), rn(pre ? h.r : h.q[next]), Ap(h.Ap);
+    const T nal = CT::mk(-sj->al[slot][0], -sj->al[slot][1]);
     double acc[3] = {0.0, 0.0, 0.0};
     const int64_t stride = (int64_t)nb * kVecThreadsStep;
-    for (int64_t i = (int64_t)lb * kVecThreadsStep + threadIdx.x; i < h.n; i += stride) {
-        const T rv = cfma(nal, Ap[i], r[i]);
-        r.st(i, rv);
+    auto residual = [&](int64_t i, T rv) {
+        rn.st(i, rv);
         const double a = rv.x, c = rv.y;
         acc[0] += a * a - c * c;
         acc[1] += 2.0 * a * c;
         acc[2] += a * a + c * c;
+    };
+    if constexpr (Ring > 0) {
+        const GPtr<T> x(h.x), p(h.p);
+        T al[kRingMax], be[kRingMax];
+        GPtr<T> q[kRingMax];
+        for (int k = 0; k < Ring; ++k) {
+            al[k] = CT::mk(sj->al[k][0], sj->al[k][1]);
+            be[k] = CT::mk(sj->be[k][0], sj->be[k][1]);
+            q[k] = GPtr<T>(h.q[k]);
+        }
+        const bool have = sj->iter >= Ring;     // p holds a direction
+        for (int64_t i = (int64_t)lb * kVecThreadsStep + threadIdx.x; i < h.n; i += stride) {
+            T qv[kRingMax];
+            for (int k = 0; k < Ring; ++k) qv[k] = q[k][i];
+            const T rv = pre ? r[i] : qv[Ring - 1];
+            T pv{0, 0}, xv = x[i];
+            if (have) pv = p[i];
+            residual(i, cfma(nal, Ap[i], rv));
+            ring_point<T>(qv, Ring, al, be, pv, xv);
+            p.st(i, pv);
+            x.st(i, xv);
+        }
+    } else {
+        for (int64_t i = (int64_t)lb * kVecThreadsStep + threadIdx.x; i < h.n; i += stride)
+            residual(i, cfma(nal, Ap[i], r[i]));
     }
     block_sum<3>(acc, scratch);
     double t[3];
     if (reduce_grid<3>(acc, part + 4 * (size_t)vblk[j], nb, lb, ctr + (size_t)j * kArriveWords, scratch, t)) {
-        const bool pre = h.z != nullptr;        // rho and beta come from the dot phase
         if (!pre) {
             const double rr_re = sj->rr_re, rr_im = sj->rr_im;
             const double d2 = rr_re * rr_re + rr_im * rr_im;
-            sj->be_re = (t[0] * rr_re + t[1] * rr_im) / d2;
-            sj->be_im = (t[1] * rr_re - t[0] * rr_im) / d2;
+            sj->be[next][0] = (t[0] * rr_re + t[1] * rr_im) / d2;
+            sj->be[next][1] = (t[1] * rr_re - t[0] * rr_im) / d2;
             sj->rr_re = t[0];
             sj->rr_im = t[1];
         }
         sj->rn2 = t[2];
         const int iter = sj->iter + 1;
         sj->iter = iter;
-        sj->parity ^= 1;
         int d = H_RUNNING;
         if (!isfinite(t[2])) d = H_NONFINITE;
         else if (t[2] <= sj->tol2) d = H_CONVERGED;
@@ -274,9 +314,8 @@ step_update(const HSys *sys, StepState *st, const int *vblk, int nsys, unsigned 
     }
 }
 
-// x += alpha p of the last direction of every system whose update is still
-// pending (the stencil phase applies each direction's update one iteration
-// late, so a converged, capped or stopped system owes its last one).
+// x of every system that stopped between two updates of x: the directions in
+// the ring, iter % ring of them.
 template <typename T>
 __global__ void __launch_bounds__(kVecThreadsStep)
 step_finish(const HSys *sys, const StepState *st, const int *vblk, int nsys) {
@@ -284,15 +323,31 @@ step_finish(const HSys *sys, const StepState *st, const int *vblk, int nsys) {
     const int b = blockIdx.x;
     const int j = find_sys(vblk, nsys, b);
     const StepState *sj = st + j;
-    if (!sj->xpend) return;
     const HSys &h = sys[j];
+    const int cnt = sj->iter % h.ring;
+    if (!cnt) return;
     const int lb = b - vblk[j], nb = vblk[j + 1] - vblk[j];
-    // the direction written by the last stencil phase (parity has flipped since)
-    const GPtr<T> x(h.x), p(sj->parity ? h.pB : h.pA);
-    const T al = CT::mk(sj->al_re, sj->al_im);
+    const GPtr<T> x(h.x), p(h.p);
+    T al[kRingMax], be[kRingMax];
+    GPtr<T> q[kRingMax];
+#pragma unroll
+    for (int k = 0; k < kRingMax; ++k) {
+        al[k] = CT::mk(sj->al[k][0], sj->al[k][1]);
+        be[k] = CT::mk(sj->be[k][0], sj->be[k][1]);
+        q[k] = GPtr<T>(h.q[k < cnt ? k : 0]);
+    }
+    const bool have = sj->iter >= h.ring;
     const int64_t stride = (int64_t)nb * kVecThreadsStep;
-    for (int64_t i = (int64_t)lb * kVecThreadsStep + threadIdx.x; i < h.n; i += stride)
-        x.st(i, cfma(al, p[i], x[i]));
+    for (int64_t i = (int64_t)lb * kVecThreadsStep + threadIdx.x; i < h.n; i += stride) {
+        T qv[kRingMax];
+#pragma unroll
+        for (int k = 0; k < kRingMax; ++k)
+            if (k < cnt) qv[k] = q[k][i];
+        T pv{0, 0}, xv = x[i];
+        if (have) pv = p[i];
+        ring_point<T>(qv, cnt, al, be, pv, xv);
+        x.st(i, xv);
+    }
 }
 
 // Dot phase of the preconditioned iteration: rho = r^T z, |z|^2; first call
@@ -305,9 +360,9 @@ step_dot(const HSys *sys, StepState *st, const int *vblk, int nsys, unsigned int
     const int j = find_sys(vblk, nsys, b);
     StepState *sj = st + j;
     const HSys &h = sys[j];
-    if (sj->done != H_RUNNING || !h.z) return;
+    if (sj->done != H_RUNNING || !h.precond) return;
     const int lb = b - vblk[j], nb = vblk[j + 1] - vblk[j];
-    const GPtr<T> r(h.r), z(h.z);
+    const GPtr<T> r(h.r), z(h.q[sj->iter % h.ring]);
     double acc[3] = {0.0, 0.0, 0.0};
     const int64_t stride = (int64_t)nb * kVecThreadsStep;
     for (int64_t i = (int64_t)lb * kVecThreadsStep + threadIdx.x; i < h.n; i += stride) {
@@ -327,8 +382,9 @@ step_dot(const HSys *sys, StepState *st, const int *vblk, int nsys, unsigned int
             if (sj->iter > 0) {
                 const double rr_re = sj->rr_re, rr_im = sj->rr_im;
                 const double d2 = rr_re * rr_re + rr_im * rr_im;
-                sj->be_re = (t[0] * rr_re + t[1] * rr_im) / d2;
-                sj->be_im = (t[1] * rr_re - t[0] * rr_im) / d2;
+                double *be = sj->be[sj->iter % h.ring];
+                be[0] = (t[0] * rr_re + t[1] * rr_im) / d2;
+                be[1] = (t[1] * rr_re - t[0] * rr_im) / d2;
             }
             sj->rr_re = t[0];
             sj->rr_im = t[1];
@@ -337,45 +393,47 @@ step_dot(const HSys *sys, StepState *st, const int *vblk, int nsys, unsigned int
 }
 
 template <typename T, class Tile>
-int launch_phase(ofdft_batch *b, int cls, int phase, dim3 threads, size_t lds, double tol, hipStream_t s) {
+int launch_phase(ofdft_batch *b, int cls, int phase, dim3 threads, size_t lds, double tol, int slot, hipStream_t s) {
     auto kern = phase == PH_INIT ? step_stencil<T, Tile, PH_INIT>
                 : phase == PH_PAP_FIRST ? step_stencil<T, Tile, PH_PAP_FIRST>
                 : step_stencil<T, Tile, PH_PAP>;
     hipLaunchKernelGGL(kern, dim3(b->step_grid[cls]), threads, lds, s, b->d_sys, b->d_step, b->d_ublk,
-                       b->d_xpre + cls * 8 * (b->nsys + 1), b->nsys, b->d_ctr, b->d_spart, tol);
+                       b->d_xpre + cls * 8 * (b->nsys + 1), b->nsys, b->d_ctr, b->d_spart, tol, slot);
     OFDFT_CHECK_HIP(hipGetLastError());
     return OFDFT_OK;
 }
 
 // One launch per class of systems present (marched tiles, bricks).
 template <typename T>
-int launch_stencil_phase(ofdft_batch *b, int shape, int phase, double tol, hipStream_t s) {
+int launch_stencil_phase(ofdft_batch *b, int shape, int phase, double tol, int slot, hipStream_t s) {
     if (b->step_grid[0])
         OFDFT_TRY(dispatch_cocg_shape<T>(shape, [&](auto sh) {
             using S = decltype(sh);
-            return launch_phase<T, StepMarch<T, S::TX, S::TYT, S::RY>>(b, 0, phase, dim3(S::TX, S::TYT), 0, tol, s);
+            return launch_phase<T, StepMarch<T, S::TX, S::TYT, S::RY>>(b, 0, phase, dim3(S::TX, S::TYT), 0, tol, slot,
+                                                                       s);
         }));
     if (b->step_grid[1])
-        OFDFT_TRY((launch_phase<T, StepBrick<T>>(b, 1, phase, dim3(kBrickThreads), b->step_lds, tol, s)));
+        OFDFT_TRY((launch_phase<T, StepBrick<T>>(b, 1, phase, dim3(kBrickThreads), b->step_lds, tol, slot, s)));
     return OFDFT_OK;
 }
 
 template <typename T>
-int launch_update(ofdft_batch *b, hipStream_t s) {
-    hipLaunchKernelGGL(step_update<T>, dim3(b->step_vblocks), dim3(kVecThreadsStep), 0, s, b->d_sys,
-                       b->d_step, b->d_vblk, b->nsys, b->d_ctr, b->d_spart + 4 * (size_t)b->step_units);
+int launch_update(ofdft_batch *b, int slot, hipStream_t s) {
+    auto kern = slot < b->ring - 1 ? step_update<T, 0> : b->ring == 2 ? step_update<T, 2> : step_update<T, kRingMax>;
+    hipLaunchKernelGGL(kern, dim3(b->step_vblocks), dim3(kVecThreadsStep), 0, s, b->d_sys,
+                       b->d_step, b->d_vblk, b->nsys, b->d_ctr, b->d_spart + 4 * (size_t)b->step_units, slot);
     OFDFT_CHECK_HIP(hipGetLastError());
     return OFDFT_OK;
 }
 
-// z = M r of every preconditioned system, then rho = r^T z (and beta).
+// z = M r (into ring slot `slot`) of every preconditioned system, then rho = r^T z (and beta).
 // Systems that are not running skip both inside the kernels.  The cycles run
 // on the batch's side streams (forked from s and joined back; inside a graph
 // capture this makes parallel branches).  Timed: the host reads the
 // statuses first and launches (and times) only the cycles of running
 // systems, one after another on s, so each cycle's duration is its own;
 // otherwise the caller accounts them.
-int precondition(ofdft_batch *b, hipStream_t s, bool timed) {
+int precondition(ofdft_batch *b, int slot, hipStream_t s, bool timed) {
     if (timed) {
         OFDFT_CHECK_HIP(hipMemcpyAsync(b->h_step, b->d_step, sizeof(StepState) * b->nsys, hipMemcpyDeviceToHost, s));
         OFDFT_CHECK_HIP(hipStreamSynchronize(s));
@@ -391,8 +449,8 @@ int precondition(ofdft_batch *b, hipStream_t s, bool timed) {
             if (b->h_step[j].done != H_RUNNING) continue;
             // bytes are added after the pass from the iteration counts
             ProfScope ps(K_MULTIGRID_C, 0.0, s);
-            OFDFT_TRY(mg_apply_shifted(*b->mg_of[j], b->mg_q[j], (const double2 *)b->r[j], (double2 *)b->z[j],
-                                       &b->d_sys[j].kre, &b->d_step[j].done, s));
+            OFDFT_TRY(mg_apply_shifted(*b->mg_of[j], b->mg_q[j], (const double2 *)b->r[j],
+                                       (double2 *)(slot ? b->slot[slot][j] : b->z[j]), &b->d_sys[j].kre, &b->d_step[j].done, s));
         }
     } else {
         // one grouped cycle per group: shift {kre, kim} and status of system j
@@ -401,7 +459,7 @@ int precondition(ofdft_batch *b, hipStream_t s, bool timed) {
             const int j0 = b->mg_groups[g].first, cnt = b->mg_groups[g].second;
             hipStream_t q = lanes ? b->mg_lane[g % lanes] : s;
             OFDFT_TRY(mg_apply_shifted_group(*b->mg_of[j0], cnt, (const double2 *const *)(b->d_rtab + j0),
-                                             (double2 *const *)(b->d_ztab + j0), &b->d_sys[j0].kre,
+                                             (double2 *const *)(b->d_ztab + (size_t)slot * b->nsys + j0), &b->d_sys[j0].kre,
                                              (int)(sizeof(HSys) / sizeof(double)), &b->d_step[j0].done,
                                              (int)(sizeof(StepState) / sizeof(int)), q));
         }
@@ -417,20 +475,22 @@ int precondition(ofdft_batch *b, hipStream_t s, bool timed) {
     return OFDFT_OK;
 }
 
-// `iters` iterations of all phases.  Timed: each launch is accounted and
+// `iters` iterations of all phases after the first one (ring slots 1, 2, ..;
+// a multiple of the ring).  Timed: each launch is accounted and
 // timed on its own; otherwise (graph capture) the caller accounts replays.
 template <typename T>
 int step_iterations(ofdft_batch *b, int shape, int iters, hipStream_t s, bool timed) {
     for (int k = 0; k < iters; ++k) {
+        const int slot = (k + 1) % b->ring;
         {
             ProfScope ps(K_COCG, 0.0, s, timed);
-            OFDFT_TRY(launch_stencil_phase<T>(b, shape, PH_PAP, 0.0, s));
+            OFDFT_TRY(launch_stencil_phase<T>(b, shape, PH_PAP, 0.0, slot, s));
         }
         {
             ProfScope ps(K_COCG_UPDATE, 0.0, s, timed);
-            OFDFT_TRY(launch_update<T>(b, s));
+            OFDFT_TRY(launch_update<T>(b, slot, s));
         }
-        if (b->precond) OFDFT_TRY(precondition(b, s, timed));
+        if (b->precond) OFDFT_TRY(precondition(b, (slot + 1) % b->ring, s, timed));
     }
     return OFDFT_OK;
 }
@@ -441,14 +501,14 @@ template <typename T>
 int first_iteration(ofdft_batch *b, int shape, hipStream_t s, bool timed) {
     {
         ProfScope ps(K_COCG, 0.0, s);
-        OFDFT_TRY(launch_stencil_phase<T>(b, shape, PH_PAP_FIRST, 0.0, s));
+        OFDFT_TRY(launch_stencil_phase<T>(b, shape, PH_PAP_FIRST, 0.0, 0, s));
     }
     {
         ProfScope ps(K_COCG_UPDATE, 0.0, s);
-        OFDFT_TRY(launch_update<T>(b, s));
+        OFDFT_TRY(launch_update<T>(b, 0, s));
     }
     if (b->precond) {
-        OFDFT_TRY(precondition(b, s, timed));
+        OFDFT_TRY(precondition(b, 1, s, timed));
         if (!timed) {
             prof_add(K_COCG_UPDATE, 0.0, 1);
             prof_add(K_MULTIGRID_C, 0.0, b->nsys);
@@ -560,10 +620,10 @@ int run_t(ofdft_batch *b, int shape, const std::vector<HSys> &hs, const std::vec
                        (b->precond && prof_timed(K_MULTIGRID_C));
     {
         ProfScope ps(K_COCG, 0.0, s);
-        OFDFT_TRY(launch_stencil_phase<T>(b, shape, PH_INIT, tol, s));
+        OFDFT_TRY(launch_stencil_phase<T>(b, shape, PH_INIT, tol, 0, s));
     }
     if (b->precond) {
-        OFDFT_TRY(precondition(b, s, timed));
+        OFDFT_TRY(precondition(b, 0, s, timed));
         if (!timed) {
             prof_add(K_COCG_UPDATE, 0.0, 1);
             prof_add(K_MULTIGRID_C, 0.0, nsys);
@@ -610,10 +670,11 @@ int run_t(ofdft_batch *b, int shape, const std::vector<HSys> &hs, const std::vec
             if (b->precond) prof_add(K_MULTIGRID_C, 0.0, (int64_t)reps * kStepIters * nsys);
         }
     }
-    // the last directions' x updates (read x, p; write x)
+    // the directions still in the ring (read them, x and p; write x)
     double fin = 0.0;
     for (int j : which)
-        if (b->h_step[j].xpend) fin += 3.0 * sizeof(T) * (double)hs[j].n;
+        if (const int cnt = b->h_step[j].iter % b->ring)
+            fin += (cnt + (b->h_step[j].iter >= b->ring ? 3.0 : 2.0)) * sizeof(T) * (double)hs[j].n;
     if (fin > 0.0) {
         ProfScope ps(K_COCG_UPDATE, fin, s);
         hipLaunchKernelGGL(step_finish<T>, dim3(b->step_vblocks), dim3(kVecThreadsStep), 0, s, b->d_sys, b->d_step,
