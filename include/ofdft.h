@@ -132,6 +132,8 @@ int fd_gradient_apply(const ofdft_grid *grid, int radius, const double *x, doubl
  *         prolongation; exact DFT solve on the coarsest grid), a fixed
  *         symmetric positive definite approximation of the inverse of
  *         -L_h, so the iteration count does not grow with the grid.
+ *         Two of its vectors are allocated only where eight are at most
+ *         an eighth of the card's memory.
  * cg_poisson_solve:
  *   rhs      device FP64 array g (not modified)
  *   x        device FP64 array: initial guess on entry (warm start), solution on
@@ -191,7 +193,9 @@ int ofdft_poisson_set_refinement(ofdft_poisson *s, double inner_min, double inne
  *
  * ofdft_batch_create: nsys systems, grids[j] (host array), one radius, dtype
  *   OFDFT_C128 or OFDFT_C64 (C64 runs COCG in complex64 inside complex128
- *   residual refinement).  Allocates all workspaces.
+ *   residual refinement).  Allocates all workspaces: six vectors per system
+ *   (four where six of each would be more than an eighth of the card's
+ *   memory), C64 three more.
  * cg_helmholtz_solve_batched:
  *   kappa    host array of 2*nsys doubles (re, im) per system; kappa != 0
  *   rhs      host array of nsys device pointers to complex128 arrays f_j

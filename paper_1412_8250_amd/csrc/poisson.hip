@@ -311,7 +311,7 @@ void poisson_free(ofdft_poisson *s) {
         delete s->mg;
     }
     void *dev[] = {s->gp, s->r, s->pA, s->pB, s->Ap, s->r32, s->d32, s->qA, s->qB, s->Aq, s->st,
-                   s->totals, s->z, s->xbest};
+                   s->totals, s->z, s->xbest, s->mg_z[2]};
     for (void *p : dev)
         if (p) (void)hipFree(p);
     if (s->st_host) (void)hipHostFree(s->st_host);
@@ -477,6 +477,23 @@ extern "C" int ofdft_poisson_create(const ofdft_grid *grid, int radius, int mode
         if (st == OFDFT_OK && hipMalloc(&s->z, sizeof(double) * npoints(*grid)) != hipSuccess) {
             set_error("ofdft_poisson_create: out of device memory");
             st = OFDFT_NO_MEMORY;
+        }
+        // four ring slots, or two (the vectors there are anyway) where eight
+        // vectors are more than an eighth of the card's memory
+        int dev = 0;
+        size_t mem_total = 0;
+        if (st == OFDFT_OK && (hipGetDevice(&dev) != hipSuccess || hipDeviceTotalMem(&mem_total, dev) != hipSuccess))
+            st = OFDFT_HIP_ERROR;
+        const size_t bytes = sizeof(double) * npoints(*grid);
+        s->mg_z[0] = s->z;
+        s->mg_z[1] = s->pB;
+        if (st == OFDFT_OK && 8 * bytes <= mem_total / 8) {
+            s->mg_ring = 4;
+            if (hipMalloc(&s->mg_z[2], 2 * bytes) != hipSuccess) {
+                set_error("ofdft_poisson_create: out of device memory");
+                st = OFDFT_NO_MEMORY;
+            }
+            s->mg_z[3] = s->mg_z[2] + npoints(*grid);
         }
     }
     if (st != OFDFT_OK) {

@@ -32,6 +32,9 @@ struct ofdft_poisson {
     // multigrid form; its iteration state on the device (and a pinned host
     // copy) and the captured block of iterations
     ofdft::Multigrid *mg = nullptr;
+    // the last mg_ring preconditioned residuals (slot 0 is z, slot 1 pB)
+    double *mg_z[4] = {};
+    int mg_ring = 2;
     void *pdev = nullptr, *pdev_h = nullptr;
     hipGraphExec_t mggraph = nullptr;
     hipStream_t mgcap = nullptr;
