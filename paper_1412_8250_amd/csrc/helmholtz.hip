@@ -546,7 +546,7 @@ int upload_systems(ofdft_batch *b, const double *kappa, const std::vector<const 
         h.p = b->p[j];
         h.Ap = b->Ap[j];
         h.ring = b->ring;
-        h.precond = b->precond != OFDFT_PRECOND_NONE;
+        h.precond = !b->precond ? 0 : mg_forms_dots(*b->mg_of[j]) ? kPrecondCycle : kPrecondDots;
         h.q[0] = h.precond ? b->z[j] : b->r[j];
         for (int k = 1; k < b->ring; ++k) h.q[k] = b->slot[k][j];
     }
@@ -936,11 +936,11 @@ static int batch_solve(ofdft_batch *b, const double *kappa, const void *const *r
                 bu += n * e * 3.0 * it_pass[j];
                 if (flushes > 0) bu += n * e * ((b->ring + (b->precond ? 4.0 : 3.0)) * flushes - 1.0);
                 if (b->precond) {
-                    // one cycle and one dot phase (read r, z) after the init
-                    // phase and after each iteration but the last
+                    // one cycle with its products (a dot phase reads r, z)
+                    // after the init phase and after each iteration but the last
                     const int cycles = it_pass[j];
-                    bu += n * e * 2.0 * cycles;
-                    prof_add(K_MULTIGRID_C, mg_cycle_bytes(*b->mg_of[j]) * cycles, 0);
+                    if (!mg_forms_dots(*b->mg_of[j])) bu += n * e * 2.0 * cycles;
+                    prof_add(K_MULTIGRID_C, mg_cycle_bytes(*b->mg_of[j], true) * cycles, 0);
                 }
             }
             prof_add(K_COCG, bs, 0);

@@ -20,6 +20,8 @@ enum HDone { H_RUNNING = 0, H_CONVERGED = 1, H_BREAKDOWN = 2, H_NONFINITE = 3, H
 
 // Slots of the stepped schedule's ring (see helmholtz_stepped.hip): 4 or 2.
 constexpr int kRingMax = 4;
+// A cycle that forms rho itself; one (a single level) that leaves it to the dot phase.
+enum { kPrecondCycle = 1, kPrecondDots = 2 };
 
 struct HSys {
     int nx, ny, nz;
@@ -37,13 +39,56 @@ struct HSys {
     // to be brought up to date; iteration k's in slot k % ring.  Without a
     // preconditioner slot 0 is r.  The persistent schedule's second p is slot 1.
     void *q[kRingMax];
-    int ring, precond;
+    int ring, precond;        // precond: 0, kPrecondCycle or kPrecondDots
     const void *f;
 };
 
 struct HState;
 struct GroupCtl;
-struct StepState;
+
+// Device state of a system in the stepped schedule.
+struct StepState {
+    double rr_re, rr_im;     // r^T r (preconditioned: r^T z) of the current residual
+    double al[kRingMax][2];  // alpha and beta {re, im} of the iterations in the ring
+    double be[kRingMax][2];  // (slot iter % ring)
+    double pa[2];            // p^T A p of the last direction
+    double rn2, fn2, tol2;   // |r|^2, |f|^2, tol^2 |f|^2
+    int iter, done, maxit, pad;      // iter % ring directions are still to be applied to x
+};
+
+// rho = r^T z and |z|^2 of the preconditioned iteration and what follows from
+// them: the first call of a solve (iter 0) sets rho, later ones
+// beta = rho_new / rho and rho.  st: the first system of the launch.
+struct StepRho {
+    static constexpr int kSums = 3;
+    static constexpr bool kExtra = false;
+    StepState *st;
+    int ring;
+    __device__ static void point(double (&acc)[3], double2 z, double2 r, double2 = {}) {
+        acc[0] += r.x * z.x - r.y * z.y;
+        acc[1] += r.x * z.y + r.y * z.x;
+        acc[2] += z.x * z.x + z.y * z.y;
+    }
+    __device__ double2 extra(int64_t) const { return make_double2(0.0, 0.0); }
+    __device__ void finish(int q, const double (&t)[3]) const {
+        StepState *sj = st + q;
+        if (!isfinite(t[0]) || !isfinite(t[1]) || !isfinite(t[2])) {
+            sj->done = H_NONFINITE;
+        } else if (t[0] * t[0] + t[1] * t[1] <= 1e-60 * sj->rn2 * t[2]) {
+            sj->done = H_BREAKDOWN;
+        } else {
+            if (sj->iter > 0) {
+                const double rr_re = sj->rr_re, rr_im = sj->rr_im;
+                const double d2 = rr_re * rr_re + rr_im * rr_im;
+                double *be = sj->be[sj->iter % ring];
+                be[0] = (t[0] * rr_re + t[1] * rr_im) / d2;
+                be[1] = (t[1] * rr_re - t[0] * rr_im) / d2;
+            }
+            sj->rr_re = t[0];
+            sj->rr_im = t[1];
+        }
+    }
+};
 
 template <typename T> struct CX;
 template <> struct CX<double2> {

@@ -34,8 +34,9 @@
 //
 // With a preconditioner M (one multigrid cycle per system, complex
 // symmetric) the iteration is preconditioned COCG: after the vector phase
-// z = M r is formed by the cycle's own launches, a dot phase reduces
-// rho = r^T z and sets beta = rho_new / rho, and the stencil phase runs on z:
+// z = M r is formed by the cycle's own launches, the last of which also
+// reduces rho = r^T z and sets beta = rho_new / rho, and the stencil phase runs
+// on z:
 // p = z + beta p_old, Ap = A z + beta Ap_old, and so for p^T A p.  The ring
 // then holds z; r is updated in place.
 #include <algorithm>
@@ -44,15 +45,6 @@
 #include "helmholtz.hpp"
 
 namespace ofdft {
-
-struct StepState {
-    double rr_re, rr_im;     // r^T r (preconditioned: r^T z) of the current residual
-    double al[kRingMax][2];  // alpha and beta {re, im} of the iterations in the ring
-    double be[kRingMax][2];  // (slot iter % ring)
-    double pa[2];            // p^T A p of the last direction
-    double rn2, fn2, tol2;   // |r|^2, |f|^2, tol^2 |f|^2
-    int iter, done, maxit, pad;      // iter % ring directions are still to be applied to x
-};
 
 namespace {
 
@@ -350,9 +342,8 @@ step_finish(const HSys *sys, const StepState *st, const int *vblk, int nsys) {
     }
 }
 
-// Dot phase of the preconditioned iteration: rho = r^T z, |z|^2; first call
-// of a solve (iter 0) sets rho, later ones beta = rho_new / rho and rho.
-template <typename T>
+// Dot phase of the preconditioned iteration for systems whose grid is itself
+// the coarsest one (longer cycles form rho in their last kernel).
 __global__ void __launch_bounds__(kVecThreadsStep)
 step_dot(const HSys *sys, StepState *st, const int *vblk, int nsys, unsigned int *ctr, double *part) {
     __shared__ double scratch[3 * (kVecThreadsStep / 64)];
@@ -360,36 +351,18 @@ step_dot(const HSys *sys, StepState *st, const int *vblk, int nsys, unsigned int
     const int j = find_sys(vblk, nsys, b);
     StepState *sj = st + j;
     const HSys &h = sys[j];
-    if (sj->done != H_RUNNING || !h.precond) return;
+    if (sj->done != H_RUNNING || h.precond != kPrecondDots) return;
     const int lb = b - vblk[j], nb = vblk[j + 1] - vblk[j];
-    const GPtr<T> r(h.r), z(h.q[sj->iter % h.ring]);
+    const GPtr<double2> r(h.r), z(h.q[sj->iter % h.ring]);
     double acc[3] = {0.0, 0.0, 0.0};
     const int64_t stride = (int64_t)nb * kVecThreadsStep;
     for (int64_t i = (int64_t)lb * kVecThreadsStep + threadIdx.x; i < h.n; i += stride) {
-        const T a = r[i], c = z[i];
-        acc[0] += (double)a.x * c.x - (double)a.y * c.y;
-        acc[1] += (double)a.x * c.y + (double)a.y * c.x;
-        acc[2] += (double)c.x * c.x + (double)c.y * c.y;
+        StepRho::point(acc, z[i], r[i]);
     }
     block_sum<3>(acc, scratch);
     double t[3];
-    if (reduce_grid<3>(acc, part + 4 * (size_t)vblk[j], nb, lb, ctr + (size_t)j * kArriveWords, scratch, t)) {
-        if (!isfinite(t[0]) || !isfinite(t[1]) || !isfinite(t[2])) {
-            sj->done = H_NONFINITE;
-        } else if (t[0] * t[0] + t[1] * t[1] <= 1e-60 * sj->rn2 * t[2]) {
-            sj->done = H_BREAKDOWN;
-        } else {
-            if (sj->iter > 0) {
-                const double rr_re = sj->rr_re, rr_im = sj->rr_im;
-                const double d2 = rr_re * rr_re + rr_im * rr_im;
-                double *be = sj->be[sj->iter % h.ring];
-                be[0] = (t[0] * rr_re + t[1] * rr_im) / d2;
-                be[1] = (t[1] * rr_re - t[0] * rr_im) / d2;
-            }
-            sj->rr_re = t[0];
-            sj->rr_im = t[1];
-        }
-    }
+    if (reduce_grid<3>(acc, part + 4 * (size_t)vblk[j], nb, lb, ctr + (size_t)j * kArriveWords, scratch, t))
+        StepRho{st, h.ring}.finish(j, t);
 }
 
 template <typename T, class Tile>
@@ -426,6 +399,11 @@ int launch_update(ofdft_batch *b, int slot, hipStream_t s) {
     return OFDFT_OK;
 }
 
+// Whether a system of the batch needs the dot phase.
+bool dot_phase(const ofdft_batch *b) {
+    return std::any_of(b->mg_own.begin(), b->mg_own.end(), [](const Multigrid *mg) { return !mg_forms_dots(*mg); });
+}
+
 // z = M r (into ring slot `slot`) of every preconditioned system, then rho = r^T z (and beta).
 // Systems that are not running skip both inside the kernels.  The cycles run
 // on the batch's side streams (forked from s and joined back; inside a graph
@@ -450,7 +428,7 @@ int precondition(ofdft_batch *b, int slot, hipStream_t s, bool timed) {
             // bytes are added after the pass from the iteration counts
             ProfScope ps(K_MULTIGRID_C, 0.0, s);
             OFDFT_TRY(mg_apply_shifted(*b->mg_of[j], b->mg_q[j], (const double2 *)b->r[j],
-                                       (double2 *)(slot ? b->slot[slot][j] : b->z[j]), &b->d_sys[j].kre, &b->d_step[j].done, s));
+                                       (double2 *)(slot ? b->slot[slot][j] : b->z[j]), StepRho{b->d_step + j, b->ring}, &b->d_sys[j].kre, &b->d_step[j].done, s));
         }
     } else {
         // one grouped cycle per group: shift {kre, kim} and status of system j
@@ -459,7 +437,8 @@ int precondition(ofdft_batch *b, int slot, hipStream_t s, bool timed) {
             const int j0 = b->mg_groups[g].first, cnt = b->mg_groups[g].second;
             hipStream_t q = lanes ? b->mg_lane[g % lanes] : s;
             OFDFT_TRY(mg_apply_shifted_group(*b->mg_of[j0], cnt, (const double2 *const *)(b->d_rtab + j0),
-                                             (double2 *const *)(b->d_ztab + (size_t)slot * b->nsys + j0), &b->d_sys[j0].kre,
+                                             (double2 *const *)(b->d_ztab + (size_t)slot * b->nsys + j0),
+                                             StepRho{b->d_step + j0, b->ring}, &b->d_sys[j0].kre,
                                              (int)(sizeof(HSys) / sizeof(double)), &b->d_step[j0].done,
                                              (int)(sizeof(StepState) / sizeof(int)), q));
         }
@@ -468,8 +447,9 @@ int precondition(ofdft_batch *b, int slot, hipStream_t s, bool timed) {
         OFDFT_CHECK_HIP(hipEventRecord(b->mg_join[k], b->mg_lane[k]));
         OFDFT_CHECK_HIP(hipStreamWaitEvent(s, b->mg_join[k], 0));
     }
+    if (!dot_phase(b)) return OFDFT_OK;
     ProfScope ps(K_COCG_UPDATE, 0.0, s, timed);
-    hipLaunchKernelGGL(step_dot<double2>, dim3(b->step_vblocks), dim3(kVecThreadsStep), 0, s, b->d_sys,
+    hipLaunchKernelGGL(step_dot, dim3(b->step_vblocks), dim3(kVecThreadsStep), 0, s, b->d_sys,
                        b->d_step, b->d_vblk, b->nsys, b->d_ctr, b->d_spart + 4 * (size_t)b->step_units);
     OFDFT_CHECK_HIP(hipGetLastError());
     return OFDFT_OK;
@@ -510,7 +490,7 @@ int first_iteration(ofdft_batch *b, int shape, hipStream_t s, bool timed) {
     if (b->precond) {
         OFDFT_TRY(precondition(b, 1, s, timed));
         if (!timed) {
-            prof_add(K_COCG_UPDATE, 0.0, 1);
+            if (dot_phase(b)) prof_add(K_COCG_UPDATE, 0.0, 1);
             prof_add(K_MULTIGRID_C, 0.0, b->nsys);
         }
     }
@@ -625,7 +605,7 @@ int run_t(ofdft_batch *b, int shape, const std::vector<HSys> &hs, const std::vec
     if (b->precond) {
         OFDFT_TRY(precondition(b, 0, s, timed));
         if (!timed) {
-            prof_add(K_COCG_UPDATE, 0.0, 1);
+            if (dot_phase(b)) prof_add(K_COCG_UPDATE, 0.0, 1);
             prof_add(K_MULTIGRID_C, 0.0, nsys);
         }
     }
@@ -666,7 +646,7 @@ int run_t(ofdft_batch *b, int shape, const std::vector<HSys> &hs, const std::vec
             OFDFT_TRY(graph_get<T>(b, shape));
             for (int k = 0; k < reps; ++k) OFDFT_CHECK_HIP(hipGraphLaunch(b->step_graph, s));
             prof_add(K_COCG, 0.0, reps * kStepIters);
-            prof_add(K_COCG_UPDATE, 0.0, reps * kStepIters * (b->precond ? 2 : 1));
+            prof_add(K_COCG_UPDATE, 0.0, reps * kStepIters * (b->precond && dot_phase(b) ? 2 : 1));
             if (b->precond) prof_add(K_MULTIGRID_C, 0.0, (int64_t)reps * kStepIters * nsys);
         }
     }

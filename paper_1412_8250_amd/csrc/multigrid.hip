@@ -5,6 +5,7 @@
 #include <utility>
 
 #include "fcg.hpp"
+#include "helmholtz.hpp"
 #include "multigrid.hpp"
 #include "profile.hpp"
 
@@ -166,11 +167,12 @@ __device__ __forceinline__ S mg_op(const MgDims &d, C kap, S c, S xp, S xm, S yp
 
 // Tile of the workgroup: origin, planes [z0, z0 + zl) and system.
 struct MgWhere {
-    int x0, y0, z0, zl, q;
+    int x0, y0, z0, zl, q, b;      // b: the workgroup's number in its system
 };
 __device__ inline MgWhere mg_where(const MgTile &tl, int nz) {
     int b = xcd_remap(blockIdx.x, gridDim.x);
     MgWhere m;
+    m.b = b % (tl.tx * tl.ty * tl.tz);
     m.x0 = (b % tl.tx) * tl.W;
     b /= tl.tx;
     m.y0 = (b % tl.ty) * tl.H;
@@ -180,6 +182,50 @@ __device__ inline MgWhere mg_where(const MgTile &tl, int nz) {
     m.zl = min(tl.zl, nz - m.z0);
     return m;
 }
+
+// Products formed by the upward half of level 0: kSums sums of point(z, r,
+// extra) per system, handed to finish(system, sums) by the last workgroup.
+struct MgNoDot {
+    static constexpr int kSums = 0;
+    static constexpr bool kExtra = false;
+};
+template <class Dot>
+struct MgDot {
+    Dot dot;
+    double *part;              // 3 cap slots per system
+    unsigned int *ctr;         // kArriveWords per system
+    int cap;
+};
+
+// State of the preconditioned CG below, on the device.
+constexpr int kPcgRing = 4;
+struct PDev {
+    double *x;
+    double rz, pAp, zAp, r2, tol2;
+    double a[kPcgRing], b[kPcgRing];     // of the iterations in the ring
+    int iters, maxit, done;
+    int n_ap, n_step, n_dots;
+};
+
+struct PcgRho {          // {<z, Ap>, <r, z>}: beta and the next rho
+    static constexpr int kSums = 2;
+    static constexpr bool kExtra = true;
+    const double *Ap;
+    PDev *D;
+    int slot, next;
+    __device__ double extra(int64_t i) const { return GPtr<double>(Ap)[i]; }
+    __device__ static void point(double (&acc)[2], double z, double r, double ap) {
+        acc[0] = ::fma(z, ap, acc[0]);
+        acc[1] = ::fma(r, z, acc[1]);
+    }
+    __device__ void finish(int, const double (&t)[2]) const {
+        const double b = -D->a[slot] * t[0] / D->rz;
+        D->b[next] = isfinite(b) ? b : 0.0;
+        D->zAp = t[0];
+        D->rz = t[1];
+        D->n_dots += 1;
+    }
+};
 
 // Downward half of a level, one pass over f: the two pre-smoothing sweeps from
 // u = 0 (with the Jacobi factor s = omega / (diag + kappa), u1 = s f and
@@ -318,9 +364,19 @@ __global__ void __launch_bounds__(NT) mg_down(MgDims d, MgDims cd, MgTile tl, do
 // step of plane p.  A column keeps the (x, y)-interpolated coarse value of the
 // two coarse planes around it; the next one's corners are fetched a step
 // ahead.
-template <typename TF, typename S, typename TO, int NT, int SL>
+//
+// With a Dot (level 0 inside a Krylov loop) the products of z with r = f (and
+// with A p) that the loop takes next are reduced here, from the z at hand and
+// r re-read through the caches; f is then the caller's FP64 array also with
+// FP32 levels (its FP32 copy would be stored and read in addition).  Bytes per
+// point of FP64 vectors with FP32 levels, cycle and products, where a pass of
+// its own read r and z: 49 -> 41 (with A p 57 -> 49).  Measured, whole solves:
+// Poisson 96^3 1.61 -> 1.55 ms, 320^3 15.2 -> 15.1; eight shifted systems of
+// 96^3 6.7 -> 6.4; an SCF step of 320^3 226 -> 212.
+template <typename TF, typename S, typename TO, int NT, int SL, class Dot>
 __global__ void __launch_bounds__(NT) mg_up(MgDims d, MgDims cd, MgTile tl, double w, MgArr<const TF> fa,
-                                            MgArr<const S> ua, MgArr<const S> uca, MgArr<TO> za, MgShift sh) {
+                                            MgArr<const S> ua, MgArr<const S> uca, MgArr<TO> za, MgShift sh,
+                                            MgDot<Dot> dot) {
     using V = VT<S>;
     using R = typename MgT<S>::R;
     using C = typename MgT<S>::C;
@@ -380,6 +436,7 @@ __global__ void __launch_bounds__(NT) mg_up(MgDims d, MgDims cd, MgTile tl, doub
         ca[i] = V::add(V::add(cn[0][i], cn[1][i]), V::add(cn[2][i], cn[3][i]));
         f0[i] = f1[i] = v0[i] = v1[i] = t0[i] = t1[i] = V::zero();
     }
+    [[maybe_unused]] double acc[Dot::kSums ? Dot::kSums : 1] = {};
     auto step = [&](int t, auto pc) __attribute__((always_inline)) {
         constexpr int B = decltype(pc)::value, Q = B ^ 1;
         S f2[SL], v2[SL];
@@ -418,9 +475,19 @@ __global__ void __launch_bounds__(NT) mg_up(MgDims d, MgDims cd, MgTile tl, doub
                 tb[B][c] = tn;
             }
             if (t >= 4 && co.own[i]) {
+                [[maybe_unused]] TO dr{}, de{};
+                if constexpr (Dot::kSums > 0) {
+                    dr = f[zo + co.off[i]];
+                    if constexpr (Dot::kExtra) de = dot.dot.extra(zo + co.off[i]);
+                }
                 const S at = mg_op<S>(d, kap, t1[i], tb[Q][c + 1], tb[Q][c - 1], tb[Q][c + RW], tb[Q][c - RW],
                                       t0[i], tn);
-                z.st(zo + co.off[i], cv<TO>(V::add(t1[i], mg_scale(s, V::sub(f0[i], at)))));
+                const TO zv = cv<TO>(V::add(t1[i], mg_scale(s, V::sub(f0[i], at))));
+                z.st(zo + co.off[i], zv);
+                if constexpr (Dot::kSums > 0) {
+                    if constexpr (Dot::kExtra) Dot::point(acc, zv, dr, de);
+                    else Dot::point(acc, zv, dr);
+                }
             }
             f0[i] = f1[i];
             f1[i] = f2[i];
@@ -435,6 +502,15 @@ __global__ void __launch_bounds__(NT) mg_up(MgDims d, MgDims cd, MgTile tl, doub
     for (int t = 0; t <= m.zl + 3; t += 2) {       // zl is even
         step(t, std::integral_constant<int, 0>{});
         step(t + 1, std::integral_constant<int, 1>{});
+    }
+    if constexpr (Dot::kSums > 0) {
+        constexpr int K = Dot::kSums;
+        __shared__ double scratch[K * (NT / 64)];
+        block_sum<K>(acc, scratch);
+        double tot[K];
+        if (reduce_grid<K>(acc, dot.part + (int64_t)m.q * K * dot.cap, tl.tx * tl.ty * tl.tz, m.b,
+                           dot.ctr + (int64_t)m.q * kArriveWords, scratch, tot))
+            dot.dot.finish(m.q, tot);
     }
 }
 
@@ -622,6 +698,10 @@ MgTile mg_pick_tile(const MgLevel &L, int count, size_t elem, int halo, int warm
     return best;
 }
 
+// Systems of a launch for which the tile of a kernel with products is picked:
+// four shifted systems on a grid (the density functional's batches), one real one.
+constexpr int mg_dot_systems(size_t elem) { return elem == 16 ? 4 : 1; }
+
 template <typename TF, typename S>
 int launch_down(const MgLevel &L, const MgLevel &C, int count, double2 kappa, double omega, MgArr<const TF> f,
                 MgArr<S> u, MgArr<S> fl, MgArr<S> cf, MgShift sh, hipStream_t s) {
@@ -641,20 +721,23 @@ int launch_down(const MgLevel &L, const MgLevel &C, int count, double2 kappa, do
     return OFDFT_OK;
 }
 
-template <typename TF, typename S, typename TO>
+template <class Dot, typename TF, typename S, typename TO>
 int launch_up(const MgLevel &L, const MgLevel &C, int count, double2 kappa, double omega, MgArr<const TF> f,
-              MgArr<const S> u, MgArr<const S> cu, MgArr<TO> z, MgShift sh, hipStream_t s) {
+              MgArr<const S> u, MgArr<const S> cu, MgArr<TO> z, MgShift sh, MgDot<Dot> dot, hipStream_t s) {
     int cap;
-    const MgTile t = mg_pick_tile(L, count, sizeof(S), 4, 4, 4, cap);
+    // a system's products are summed in an order of its own, whatever it shares the launch with
+    const int pick = Dot::kSums ? mg_dot_systems(sizeof(TO)) : count;
+    const MgTile t = mg_pick_tile(L, pick, sizeof(S), 4, 4, 4, cap);
+    if (Dot::kSums && t.blocks() > dot.cap) return OFDFT_INVALID_ARG;     // sized by mg_create
     const MgDims d = dims_of(L, kappa), cd = dims_of(C, kappa);
     const dim3 grid(t.blocks() * count);
     switch (cap) {
-        case 256: hipLaunchKernelGGL((mg_up<TF, S, TO, 256, 1>), grid, dim3(256), 0, s, d, cd, t, omega, f, u, cu, z, sh); break;
-        case 512: hipLaunchKernelGGL((mg_up<TF, S, TO, 256, 2>), grid, dim3(256), 0, s, d, cd, t, omega, f, u, cu, z, sh); break;
-        case 1024: hipLaunchKernelGGL((mg_up<TF, S, TO, 512, 2>), grid, dim3(512), 0, s, d, cd, t, omega, f, u, cu, z, sh); break;
+        case 256: hipLaunchKernelGGL((mg_up<TF, S, TO, 256, 1, Dot>), grid, dim3(256), 0, s, d, cd, t, omega, f, u, cu, z, sh, dot); break;
+        case 512: hipLaunchKernelGGL((mg_up<TF, S, TO, 256, 2, Dot>), grid, dim3(256), 0, s, d, cd, t, omega, f, u, cu, z, sh, dot); break;
+        case 1024: hipLaunchKernelGGL((mg_up<TF, S, TO, 512, 2, Dot>), grid, dim3(512), 0, s, d, cd, t, omega, f, u, cu, z, sh, dot); break;
         default:
             if constexpr (sizeof(S) <= 8)
-                hipLaunchKernelGGL((mg_up<TF, S, TO, 512, 4>), grid, dim3(512), 0, s, d, cd, t, omega, f, u, cu, z, sh);
+                hipLaunchKernelGGL((mg_up<TF, S, TO, 512, 4, Dot>), grid, dim3(512), 0, s, d, cd, t, omega, f, u, cu, z, sh, dot);
     }
     OFDFT_CHECK_HIP(hipGetLastError());
     return OFDFT_OK;
@@ -678,17 +761,18 @@ int vcycle_coarse(Multigrid &mg, int l, int q0, int count, double2 kappa, MgShif
     OFDFT_TRY((launch_down<S, S>(L, C, count, kappa, mg.omega, f, u, none, lvl<S>(C.f, C, q0), sh, s)));
     OFDFT_TRY(vcycle_coarse<S>(mg, l + 1, q0, count, kappa, sh, s));
     const MgArr<const S> ct{(const S *)C.t + (int64_t)q0 * C.n, C.n, nullptr};
-    return launch_up<S, S, S>(L, C, count, kappa, mg.omega, f, uc, ct, t, sh, s);
+    return launch_up<MgNoDot, S, S, S>(L, C, count, kappa, mg.omega, f, uc, ct, t, sh, {}, s);
 }
 
 // The whole cycle z = M f for `count` systems from q0 of the hierarchy: level
 // 0 reads f and writes z in FP64 (TIO), its work arrays are S.  V(2,2), two
 // kernels per level.  With S narrower than TIO the downward half also stores
 // f in S (level 0's f array), which the upward half reads instead of the FP64
-// input.  f, z and sh address system q0 first.
-template <typename TIO, typename S>
+// input, unless that half forms products (see mg_up; a one-level cycle forms
+// none).  f, z, sh and dot address system q0 first.
+template <typename TIO, typename S, class Dot = MgNoDot>
 int vcycle(Multigrid &mg, int q0, int count, MgArr<const TIO> f, MgArr<TIO> z, double2 kappa, MgShift sh,
-           hipStream_t s) {
+           hipStream_t s, Dot prod = {}) {
     MgLevel &L = mg.lv[0];
     if (mg.lv.size() == 1) {
         const MgDims d = dims_of(L, kappa);
@@ -701,17 +785,19 @@ int vcycle(Multigrid &mg, int q0, int count, MgArr<const TIO> f, MgArr<TIO> z, d
     MgLevel &C = mg.lv[1];
     const MgArr<S> cf = lvl<S>(C.f, C, q0);
     const MgArr<const S> ct{(const S *)C.t + (int64_t)q0 * C.n, C.n, nullptr};
-    if constexpr (sizeof(S) < sizeof(TIO)) {
+    if constexpr (sizeof(S) < sizeof(TIO) && Dot::kSums == 0) {
         const MgArr<S> fl = lvl<S>(L.f, L, q0);
         const MgArr<const S> flc{fl.base, fl.stride, nullptr};
         OFDFT_TRY((launch_down<TIO, S>(L, C, count, kappa, mg.omega, f, u, fl, cf, sh, s)));
         OFDFT_TRY(vcycle_coarse<S>(mg, 1, q0, count, kappa, sh, s));
-        return launch_up<S, S, TIO>(L, C, count, kappa, mg.omega, flc, uc, ct, z, sh, s);
+        return launch_up<MgNoDot, S, S, TIO>(L, C, count, kappa, mg.omega, flc, uc, ct, z, sh, {}, s);
     } else {
         const MgArr<S> none{nullptr, 0, nullptr};
         OFDFT_TRY((launch_down<TIO, S>(L, C, count, kappa, mg.omega, f, u, none, cf, sh, s)));
         OFDFT_TRY(vcycle_coarse<S>(mg, 1, q0, count, kappa, sh, s));
-        return launch_up<TIO, S, TIO>(L, C, count, kappa, mg.omega, f, uc, ct, z, sh, s);
+        const MgDot<Dot> dot{prod, mg.dpart + (int64_t)q0 * 3 * mg.dot_cap, mg.dctr + (int64_t)q0 * kArriveWords,
+                             mg.dot_cap};
+        return launch_up<Dot, TIO, S, TIO>(L, C, count, kappa, mg.omega, f, uc, ct, z, sh, dot, s);
     }
 }
 
@@ -781,6 +867,21 @@ int mg_create(Multigrid &mg, const ofdft_grid &g, int elem_bytes, bool fp32, int
             *own[k] = p;
         }
     }
+    if (nlev > 1) {              // reductions of the products in level 0's last kernel
+        int cap;
+        mg.dot_cap = mg_pick_tile(mg.lv[0], mg_dot_systems((size_t)elem_bytes), es, 4, 4, 4, cap).blocks();
+        const size_t bp = sizeof(double) * 3 * (size_t)mg.dot_cap * groups, bc = sizeof(unsigned int) * kArriveWords * (size_t)groups;
+        void *p = nullptr;
+        if (hipMalloc(&p, bp + bc) != hipSuccess) {
+            mg_free(mg);
+            set_error("multigrid: out of device memory");
+            return OFDFT_NO_MEMORY;
+        }
+        mg.allocs.push_back(p);
+        mg.dpart = (double *)p;
+        mg.dctr = (unsigned int *)((char *)p + bp);
+        OFDFT_CHECK_HIP(hipMemset(mg.dctr, 0, bc));
+    }
     // tables of the coarsest grid's exact solve
     const MgLevel &B = mg.lv.back();
     std::vector<double> tab(6 * kMgTab + 3 * kMgCoarseMax, 0.0);
@@ -818,6 +919,9 @@ void mg_free(Multigrid &mg) {
     mg.allocs.clear();
     mg.lv.clear();
     mg.tab = nullptr;
+    mg.dpart = nullptr;
+    mg.dctr = nullptr;
+    mg.dot_cap = 0;
 }
 
 int mg_apply(Multigrid &mg, const double *r, double *z, hipStream_t s, double kappa) {
@@ -853,7 +957,18 @@ int mg_apply_shifted(Multigrid &mg, int q, const double2 *r, double2 *z, const d
                    : vcycle<double2, double2>(mg, q, 1, f, o, k, sh, s);
 }
 
-int mg_apply_shifted_group(Multigrid &mg, int count, const double2 *const *r, double2 *const *z,
+int mg_apply_shifted(Multigrid &mg, int q, const double2 *r, double2 *z, const StepRho &rho, const double *kappa,
+                     const int *run, hipStream_t s) {
+    if (mg.lv.empty() || mg.elem != 16 || !kappa || q < 0 || q >= mg.groups) return OFDFT_INVALID_ARG;
+    const double2 k = make_double2(0.0, 0.0);
+    const MgShift sh{kappa, run, 0, 0};
+    const MgArr<const double2> f{r, 0, nullptr};
+    const MgArr<double2> o{z, 0, nullptr};
+    return mg.fp32 ? vcycle<double2, float2>(mg, q, 1, f, o, k, sh, s, rho)
+                   : vcycle<double2, double2>(mg, q, 1, f, o, k, sh, s, rho);
+}
+
+int mg_apply_shifted_group(Multigrid &mg, int count, const double2 *const *r, double2 *const *z, const StepRho &rho,
                            const double *kappa, int kstride, const int *run, int rstride, hipStream_t s) {
     if (mg.lv.empty() || mg.elem != 16 || !kappa || !r || !z || count < 1 || count > mg.groups)
         return OFDFT_INVALID_ARG;
@@ -861,22 +976,23 @@ int mg_apply_shifted_group(Multigrid &mg, int count, const double2 *const *r, do
     const MgShift sh{kappa, run, kstride, rstride};
     const MgArr<const double2> f{nullptr, 0, r};
     const MgArr<double2> o{nullptr, 0, z};
-    return mg.fp32 ? vcycle<double2, float2>(mg, 0, count, f, o, k, sh, s)
-                   : vcycle<double2, double2>(mg, 0, count, f, o, k, sh, s);
+    return mg.fp32 ? vcycle<double2, float2>(mg, 0, count, f, o, k, sh, s, rho)
+                   : vcycle<double2, double2>(mg, 0, count, f, o, k, sh, s, rho);
 }
 
 // Algorithmic bytes of one cycle.  Fine level, FP64 levels: the downward half
 // reads f and writes u and an eighth of an element (the restricted residual),
 // the upward half reads f, u and an eighth (the coarse correction) and writes
 // z: 5.25 elements per point.  FP32 levels: f (FP64) is read once and stored
-// as FP32, which the upward half reads.  Each coarser level moves 5.25
+// as FP32, which the upward half reads, unless that half forms products: it
+// then reads f.  Each coarser level moves 5.25
 // elements per point, and they hold 1/7 of the fine points in all.
-double mg_cycle_bytes(const Multigrid &mg) {
+double mg_cycle_bytes(const Multigrid &mg, bool dots) {
     if (mg.lv.empty()) return 0.0;
     const double E = (double)mg.elem, e = mg.fp32 ? E / 2 : E;
     const double n = (double)mg.lv[0].n;
     if (mg.lv.size() == 1) return 2.0 * n * E;
-    const double fine = mg.fp32 ? 2.0 * E + 4.25 * e : 3.0 * E + 2.25 * e;
+    const double fine = mg.fp32 && !dots ? 2.0 * E + 4.25 * e : 3.0 * E + 2.25 * e;
     return n * fine + n / 7.0 * 5.25 * e;
 }
 
@@ -904,17 +1020,8 @@ double mg_cycle_bytes(const Multigrid &mg) {
 namespace {
 
 constexpr int kPcgBlock = 4;
-constexpr int kPcgRing = 4;
 static_assert(kPcgBlock % kPcgRing == 0, "a captured block ends where the ring does (2 divides it, too)");
 enum { P_RUN = 0, P_OK = 1, P_NONFINITE = 2, P_BREAKDOWN = 3, P_MAXIT = 4 };
-
-struct PDev {
-    double *x;
-    double rz, pAp, zAp, r2, tol2;
-    double a[kPcgRing], b[kPcgRing];     // of the iterations in the ring
-    int iters, maxit, done;
-    int n_ap, n_step, n_dots;
-};
 
 struct EpiZAp {          // centre z: Ap = -L z + b Ap_old, <z, Ap>; p^T A p and alpha into the state
     double *__restrict__ Ap;
@@ -1028,29 +1135,18 @@ struct PcgFinishOp {     // x of a solve that stopped between two updates of x: 
     }
 };
 
-struct PcgDotsOp {       // {<z, Ap>, <r, z>}: beta and the next rho
+struct PcgDotsOp {       // PcgRho's sums after a one-level cycle
     static constexpr int kClass = K_CG_UPDATE;
     static constexpr int kBytes = 0;
-    const double *z, *r, *Ap;
-    PDev *D;
-    __device__ bool skip() const { return D->done != P_RUN; }
+    const double *z, *r;
+    PcgRho rho;
+    __device__ bool skip() const { return rho.D->done != P_RUN; }
     __device__ void prepare() {}
-    __device__ void operator()(int64_t i, double (&acc)[2]) const {
-        const double zi = z[i];
-        acc[0] = ::fma(zi, Ap[i], acc[0]);
-        acc[1] = ::fma(r[i], zi, acc[1]);
-    }
+    __device__ void operator()(int64_t i, double (&acc)[2]) const { PcgRho::point(acc, z[i], r[i], rho.Ap[i]); }
 };
 struct PcgDotsFin {
-    PDev *D;
-    int slot, next;
-    __device__ void operator()(const double (&t)[2]) const {
-        const double b = -D->a[slot] * t[0] / D->rz;
-        D->b[next] = isfinite(b) ? b : 0.0;
-        D->zAp = t[0];
-        D->rz = t[1];
-        D->n_dots += 1;
-    }
+    PcgRho rho;
+    __device__ void operator()(const double (&t)[2]) const { rho.finish(0, t); }
 };
 
 // One iteration, its z in ring slot `slot`.
@@ -1074,9 +1170,18 @@ int pcg_iteration(ofdft_poisson *s, int slot, hipStream_t st) {
         OFDFT_TRY((launch_reduce<1>(n, PcgStepOp<4>{r, Ap, p, {z[0], z[1], z[2], z[3]}, D, slot}, FinStepP{D},
                                     s->rb, st)));
     }
-    OFDFT_TRY(mg_apply_run(*s->mg, r, z[next], st, 0.0, &D->done));
-    OFDFT_TRY((launch_reduce<2>(n, PcgDotsOp{z[next], r, Ap, D}, PcgDotsFin{D, slot, next}, s->rb, st)));
-    return OFDFT_OK;
+    const PcgRho rho{Ap, D, slot, next};
+    if (!mg_forms_dots(*s->mg)) {
+        OFDFT_TRY(mg_apply_run(*s->mg, r, z[next], st, 0.0, &D->done));
+        return launch_reduce<2>(n, PcgDotsOp{z[next], r, rho}, PcgDotsFin{rho}, s->rb, st);
+    }
+    ProfScope ps(K_MULTIGRID, 0.0, st);      // bytes: counted with the cycles that ran
+    const MgShift sh{nullptr, &D->done, 0, 0};
+    const MgArr<const double> f{r, 0, nullptr};
+    const MgArr<double> o{z[next], 0, nullptr};
+    const double2 k0 = make_double2(0.0, 0.0);
+    return s->mg->fp32 ? vcycle<double, float>(*s->mg, 0, 1, f, o, k0, sh, st, rho)
+                       : vcycle<double, double>(*s->mg, 0, 1, f, o, k0, sh, st, rho);
 }
 
 int pcg_graph(ofdft_poisson *s) {
@@ -1171,11 +1276,12 @@ int poisson_solve_mg(ofdft_poisson *s, double *x, double rel_tol, int max_iter, 
     }
     // stencil: read z, Ap_old, write Ap; update: read r, Ap, write r, every
     // ring-th one reads the ring, p, x and writes p, x (the first reads no p);
-    // products: read z, r, Ap
+    // products: Ap in the cycle, after a one-level one z, r, Ap
     prof_add(K_CG_STENCIL, nd * 24.0 * Dh->n_ap, eager ? 0 : Dh->n_ap);
-    prof_add(K_CG_UPDATE, nd * 8.0 * (3.0 * Dh->n_step + 3.0 * Dh->n_dots + (flushes ? (ring + 4.0) * flushes - 1.0 : 0.0)),
-             eager ? 0 : Dh->n_step + Dh->n_dots);
-    prof_add(K_MULTIGRID, mg_cycle_bytes(*s->mg) * Dh->n_dots, eager ? 0 : Dh->n_dots);
+    prof_add(K_CG_UPDATE, nd * 8.0 * (3.0 * Dh->n_step + (mg_forms_dots(*s->mg) ? 0.0 : 3.0) * Dh->n_dots + (flushes ? (ring + 4.0) * flushes - 1.0 : 0.0)),
+             eager ? 0 : Dh->n_step + (mg_forms_dots(*s->mg) ? 0 : Dh->n_dots));
+    const double extra = mg_forms_dots(*s->mg) ? 8.0 * nd : 0.0;
+    prof_add(K_MULTIGRID, (mg_cycle_bytes(*s->mg, true) + extra) * Dh->n_dots, eager ? 0 : Dh->n_dots);
     stats.iters = Dh->iters;
     switch (Dh->done) {
         case P_OK: return OFDFT_OK;

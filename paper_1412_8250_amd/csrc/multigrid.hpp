@@ -18,6 +18,8 @@
 
 namespace ofdft {
 
+struct StepRho;
+
 struct MgLevel {
     int nx = 0, ny = 0, nz = 0;
     double cx = 0, cy = 0, cz = 0;   // 1 / h_a^2
@@ -32,6 +34,9 @@ struct Multigrid {
     int elem = 8;                // input / output element bytes: 8 (FP64) or 16 (complex128)
     bool fp32 = true;            // level arrays and their arithmetic in FP32 (else FP64)
     int groups = 1;              // systems whose level arrays the hierarchy holds (same grid)
+    double *dpart = nullptr;     // partial sums (dot_cap per sum and system) and arrival counters of the products
+    unsigned int *dctr = nullptr;
+    int dot_cap = 0;
     const double *tab = nullptr; // coarsest grid: basis matrices and eigenvalues (device)
     std::vector<void *> allocs;
 };
@@ -64,13 +69,19 @@ int mg_apply_run(Multigrid &mg, const double *r, double *z, hipStream_t s, doubl
 // System q of the hierarchy's group does the cycle.
 int mg_apply_shifted(Multigrid &mg, int q, const double2 *r, double2 *z, const double *kappa, const int *run,
                      hipStream_t s);
+// The same, the last kernel also reducing the products of rho (if
+// mg_forms_dots; else they are the caller's).
+int mg_apply_shifted(Multigrid &mg, int q, const double2 *r, double2 *z, const StepRho &rho, const double *kappa,
+                     const int *run, hipStream_t s);
+// Whether the cycle's last kernel can form products of z: a hierarchy of more than one level.
+inline bool mg_forms_dots(const Multigrid &mg) { return mg.lv.size() > 1; }
 // The cycles of systems 0 .. count-1 of the group in one launch per kernel:
 // system q reads r[q], writes z[q] (device tables of device pointers), its
 // shift at kappa + q kstride and its run flag at run + q rstride (run may be
-// null).  Not accounted in the profile.
-int mg_apply_shifted_group(Multigrid &mg, int count, const double2 *const *r, double2 *const *z,
+// null); rho as above, of system 0.  Not accounted in the profile.
+int mg_apply_shifted_group(Multigrid &mg, int count, const double2 *const *r, double2 *const *z, const StepRho &rho,
                            const double *kappa, int kstride, const int *run, int rstride, hipStream_t s);
-// Algorithmic HBM bytes of one cycle.
-double mg_cycle_bytes(const Multigrid &mg);
+// Algorithmic HBM bytes of one cycle (dots: one that forms products of r and z).
+double mg_cycle_bytes(const Multigrid &mg, bool dots = false);
 
 }  // namespace ofdft
