@@ -371,8 +371,9 @@ __global__ void __launch_bounds__(NT) mg_down(MgDims d, MgDims cd, MgTile tl, do
 // FP32 levels (its FP32 copy would be stored and read in addition).  Bytes per
 // point of FP64 vectors with FP32 levels, cycle and products, where a pass of
 // its own read r and z: 49 -> 41 (with A p 57 -> 49).  Measured, whole solves:
-// Poisson 96^3 1.61 -> 1.55 ms, 320^3 15.2 -> 15.1; eight shifted systems of
-// 96^3 6.7 -> 6.4; an SCF step of 320^3 226 -> 212.
+// Poisson 96^3 1.61 -> 1.52 ms, 320^3 15.2 -> 14.1 (15.1 with the real
+// operands loaded where they are used); eight shifted systems of 96^3 6.7 -> 6.4;
+// an SCF step of 320^3 226 -> 212.
 template <typename TF, typename S, typename TO, int NT, int SL, class Dot>
 __global__ void __launch_bounds__(NT) mg_up(MgDims d, MgDims cd, MgTile tl, double w, MgArr<const TF> fa,
                                             MgArr<const S> ua, MgArr<const S> uca, MgArr<TO> za, MgShift sh,
@@ -437,6 +438,11 @@ __global__ void __launch_bounds__(NT) mg_up(MgDims d, MgDims cd, MgTile tl, doub
         f0[i] = f1[i] = v0[i] = v1[i] = t0[i] = t1[i] = V::zero();
     }
     [[maybe_unused]] double acc[Dot::kSums ? Dot::kSums : 1] = {};
+    // the products' operands, a step ahead where they are real (complex ones
+    // would spill): issued before the step's fetches, so that waiting for them
+    // leaves those in flight
+    constexpr bool kAhead = Dot::kSums > 0 && sizeof(TO) == 8;
+    [[maybe_unused]] TO dr[SL] = {}, de[SL] = {};
     auto step = [&](int t, auto pc) __attribute__((always_inline)) {
         constexpr int B = decltype(pc)::value, Q = B ^ 1;
         S f2[SL], v2[SL];
@@ -453,6 +459,19 @@ __global__ void __launch_bounds__(NT) mg_up(MgDims d, MgDims cd, MgTile tl, doub
             }
             v2[i] = V::add(un[B][i], corr);
         }
+        const int64_t zo = (int64_t)(m.z0 + t - 4) * nxy;
+        [[maybe_unused]] TO rv[SL], ev[SL];
+        if constexpr (kAhead) {
+#pragma unroll
+            for (int i = 0; i < SL; ++i) {
+                rv[i] = dr[i];
+                ev[i] = de[i];
+                if (t >= 3 && t < m.zl + 3 && co.own[i]) {
+                    dr[i] = f[zo + nxy + co.off[i]];
+                    if constexpr (Dot::kExtra) de[i] = dot.dot.extra(zo + nxy + co.off[i]);
+                }
+            }
+        }
         if constexpr (B == 0) corners((p >> 1) + 1 == cd.nz ? 0 : (p >> 1) + 1);
         if (t + 2 <= m.zl + 3) {
 #pragma unroll
@@ -462,7 +481,6 @@ __global__ void __launch_bounds__(NT) mg_up(MgDims d, MgDims cd, MgTile tl, doub
             }
             kf = kf + 1 == d.nz ? 0 : kf + 1;
         }
-        const int64_t zo = (int64_t)(m.z0 + t - 4) * nxy;
 #pragma unroll
         for (int i = 0; i < SL; ++i) {
             const int c = tid + i * NT;
@@ -475,18 +493,17 @@ __global__ void __launch_bounds__(NT) mg_up(MgDims d, MgDims cd, MgTile tl, doub
                 tb[B][c] = tn;
             }
             if (t >= 4 && co.own[i]) {
-                [[maybe_unused]] TO dr{}, de{};
-                if constexpr (Dot::kSums > 0) {
-                    dr = f[zo + co.off[i]];
-                    if constexpr (Dot::kExtra) de = dot.dot.extra(zo + co.off[i]);
+                if constexpr (Dot::kSums > 0 && !kAhead) {
+                    rv[i] = f[zo + co.off[i]];
+                    if constexpr (Dot::kExtra) ev[i] = dot.dot.extra(zo + co.off[i]);
                 }
                 const S at = mg_op<S>(d, kap, t1[i], tb[Q][c + 1], tb[Q][c - 1], tb[Q][c + RW], tb[Q][c - RW],
                                       t0[i], tn);
                 const TO zv = cv<TO>(V::add(t1[i], mg_scale(s, V::sub(f0[i], at))));
                 z.st(zo + co.off[i], zv);
                 if constexpr (Dot::kSums > 0) {
-                    if constexpr (Dot::kExtra) Dot::point(acc, zv, dr, de);
-                    else Dot::point(acc, zv, dr);
+                    if constexpr (Dot::kExtra) Dot::point(acc, zv, rv[i], ev[i]);
+                    else Dot::point(acc, zv, rv[i]);
                 }
             }
             f0[i] = f1[i];
