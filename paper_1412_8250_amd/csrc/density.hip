@@ -787,8 +787,13 @@ int u_iteration(ofdft_scf *s, const double *v, double *u, int parity, const UPar
     OFDFT_CHECK_HIP(hipGetLastError());
     const double *base = r_cur;
     if (P.pre) {
-        OFDFT_TRY(mg_apply_run(*s->umg, r_cur, s->z, st, s->u_kappa, &U->done));
-        OFDFT_TRY((launch_reduce<5>(n, DotsOpD{u, s->z, r_cur, r_prev, U, 0}, FinDots{U}, s->rb, st)));
+        if (mg_forms_dots(*s->umg)) {
+            const MgUpdateDots dots{u, r_prev, &U->q, U->dots, &U->n_dots, false};
+            OFDFT_TRY(mg_apply_run(*s->umg, r_cur, s->z, st, s->u_kappa, &U->done, dots));
+        } else {
+            OFDFT_TRY(mg_apply_run(*s->umg, r_cur, s->z, st, s->u_kappa, &U->done));
+            OFDFT_TRY((launch_reduce<5>(n, DotsOpD{u, s->z, r_cur, r_prev, U, 0}, FinDots{U}, s->rb, st)));
+        }
         base = s->z;
     }
     hipLaunchKernelGGL(u_direction, dim3(1), dim3(1), 0, st, U, P);
@@ -891,11 +896,16 @@ int density_update_dev(ofdft_scf *s, const double *v, double *u, int &iters, dou
     }
     // algorithmic bytes of the passes that did work (the early exits move none)
     const double nd = (double)s->n;
-    const int64_t nst = Uh->n_ka + Uh->n_kd, nvec = Uh->n_kb + Uh->n_dots + Uh->n_eval + Uh->n_step;
+    // the cycle's products read u and r_prev beside it; a one-level cycle leaves them to a pass (u, z, r, r_prev)
+    const bool fused = P.pre && mg_forms_dots(*s->umg);
+    const int64_t ndots = fused ? 0 : Uh->n_dots;
+    const int64_t nst = Uh->n_ka + Uh->n_kd, nvec = Uh->n_kb + ndots + Uh->n_eval + Uh->n_step;
     prof_add(K_U_STENCIL, nd * (24.0 * Uh->n_ka + 40.0 * Uh->n_kd), eager ? 0 : nst);
-    prof_add(K_U_VECTOR, nd * (32.0 * Uh->n_kb + 32.0 * Uh->n_dots + 24.0 * Uh->n_eval + 24.0 * Uh->n_step),
+    prof_add(K_U_VECTOR, nd * (32.0 * Uh->n_kb + 32.0 * ndots + 24.0 * Uh->n_eval + 24.0 * Uh->n_step),
              eager ? 0 : nvec);
-    if (P.pre) prof_add(K_MULTIGRID, mg_cycle_bytes(*s->umg) * Uh->n_dots, eager ? 0 : Uh->n_dots);
+    if (P.pre)
+        prof_add(K_MULTIGRID, (mg_cycle_bytes(*s->umg, fused) + (fused ? 16.0 * nd : 0.0)) * Uh->n_dots,
+                 eager ? 0 : Uh->n_dots);
     s->s_prev = Uh->s_prev;
     iters = Uh->q;
     res = Uh->res;

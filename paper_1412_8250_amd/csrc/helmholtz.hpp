@@ -62,14 +62,15 @@ struct StepState {
 struct StepRho {
     static constexpr int kSums = 3;
     static constexpr bool kExtra = false;
+    using Extra = double2;
     StepState *st;
     int ring;
-    __device__ static void point(double (&acc)[3], double2 z, double2 r, double2 = {}) {
+    __device__ void prepare() {}
+    __device__ static void point(double (&acc)[3], double2 z, double2 r) {
         acc[0] += r.x * z.x - r.y * z.y;
         acc[1] += r.x * z.y + r.y * z.x;
         acc[2] += z.x * z.x + z.y * z.y;
     }
-    __device__ double2 extra(int64_t) const { return make_double2(0.0, 0.0); }
     __device__ void finish(int q, const double (&t)[3]) const {
         StepState *sj = st + q;
         if (!isfinite(t[0]) || !isfinite(t[1]) || !isfinite(t[2])) {

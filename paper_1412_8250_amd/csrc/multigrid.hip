@@ -188,11 +188,12 @@ __device__ inline MgWhere mg_where(const MgTile &tl, int nz) {
 struct MgNoDot {
     static constexpr int kSums = 0;
     static constexpr bool kExtra = false;
+    using Extra = double;
 };
 template <class Dot>
 struct MgDot {
     Dot dot;
-    double *part;              // 3 cap slots per system
+    double *part;              // Multigrid::kDotSums cap slots per system
     unsigned int *ctr;         // kArriveWords per system
     int cap;
 };
@@ -210,9 +211,11 @@ struct PDev {
 struct PcgRho {          // {<z, Ap>, <r, z>}: beta and the next rho
     static constexpr int kSums = 2;
     static constexpr bool kExtra = true;
+    using Extra = double;
     const double *Ap;
     PDev *D;
     int slot, next;
+    __device__ void prepare() {}
     __device__ double extra(int64_t i) const { return GPtr<double>(Ap)[i]; }
     __device__ static void point(double (&acc)[2], double z, double r, double ap) {
         acc[0] = ::fma(z, ap, acc[0]);
@@ -438,11 +441,13 @@ __global__ void __launch_bounds__(NT) mg_up(MgDims d, MgDims cd, MgTile tl, doub
         f0[i] = f1[i] = v0[i] = v1[i] = t0[i] = t1[i] = V::zero();
     }
     [[maybe_unused]] double acc[Dot::kSums ? Dot::kSums : 1] = {};
-    // the products' operands, a step ahead where they are real (complex ones
-    // would spill): issued before the step's fetches, so that waiting for them
+    // the products' operands, a step ahead where that spills nothing (not
+    // complex ones): issued before the step's fetches, so that waiting for them
     // leaves those in flight
-    constexpr bool kAhead = Dot::kSums > 0 && sizeof(TO) == 8;
-    [[maybe_unused]] TO dr[SL] = {}, de[SL] = {};
+    constexpr bool kAhead = Dot::kSums > 0 && sizeof(TO) == 8 && (sizeof(S) == 4 || SL < 4);
+    [[maybe_unused]] TO dr[SL] = {};
+    [[maybe_unused]] typename Dot::Extra de[SL] = {};
+    if constexpr (Dot::kSums > 0) dot.dot.prepare();
     auto step = [&](int t, auto pc) __attribute__((always_inline)) {
         constexpr int B = decltype(pc)::value, Q = B ^ 1;
         S f2[SL], v2[SL];
@@ -460,7 +465,8 @@ __global__ void __launch_bounds__(NT) mg_up(MgDims d, MgDims cd, MgTile tl, doub
             v2[i] = V::add(un[B][i], corr);
         }
         const int64_t zo = (int64_t)(m.z0 + t - 4) * nxy;
-        [[maybe_unused]] TO rv[SL], ev[SL];
+        [[maybe_unused]] TO rv[SL];
+        [[maybe_unused]] typename Dot::Extra ev[SL];
         if constexpr (kAhead) {
 #pragma unroll
             for (int i = 0; i < SL; ++i) {
@@ -525,7 +531,7 @@ __global__ void __launch_bounds__(NT) mg_up(MgDims d, MgDims cd, MgTile tl, doub
         __shared__ double scratch[K * (NT / 64)];
         block_sum<K>(acc, scratch);
         double tot[K];
-        if (reduce_grid<K>(acc, dot.part + (int64_t)m.q * K * dot.cap, tl.tx * tl.ty * tl.tz, m.b,
+        if (reduce_grid<K>(acc, dot.part + (int64_t)m.q * Multigrid::kDotSums * dot.cap, tl.tx * tl.ty * tl.tz, m.b,
                            dot.ctr + (int64_t)m.q * kArriveWords, scratch, tot))
             dot.dot.finish(m.q, tot);
     }
@@ -812,7 +818,7 @@ int vcycle(Multigrid &mg, int q0, int count, MgArr<const TIO> f, MgArr<TIO> z, d
         const MgArr<S> none{nullptr, 0, nullptr};
         OFDFT_TRY((launch_down<TIO, S>(L, C, count, kappa, mg.omega, f, u, none, cf, sh, s)));
         OFDFT_TRY(vcycle_coarse<S>(mg, 1, q0, count, kappa, sh, s));
-        const MgDot<Dot> dot{prod, mg.dpart + (int64_t)q0 * 3 * mg.dot_cap, mg.dctr + (int64_t)q0 * kArriveWords,
+        const MgDot<Dot> dot{prod, mg.dpart + (int64_t)q0 * Multigrid::kDotSums * mg.dot_cap, mg.dctr + (int64_t)q0 * kArriveWords,
                              mg.dot_cap};
         return launch_up<Dot, TIO, S, TIO>(L, C, count, kappa, mg.omega, f, uc, ct, z, sh, dot, s);
     }
@@ -887,7 +893,7 @@ int mg_create(Multigrid &mg, const ofdft_grid &g, int elem_bytes, bool fp32, int
     if (nlev > 1) {              // reductions of the products in level 0's last kernel
         int cap;
         mg.dot_cap = mg_pick_tile(mg.lv[0], mg_dot_systems((size_t)elem_bytes), es, 4, 4, 4, cap).blocks();
-        const size_t bp = sizeof(double) * 3 * (size_t)mg.dot_cap * groups, bc = sizeof(unsigned int) * kArriveWords * (size_t)groups;
+        const size_t bp = sizeof(double) * Multigrid::kDotSums * (size_t)mg.dot_cap * groups, bc = sizeof(unsigned int) * kArriveWords * (size_t)groups;
         void *p = nullptr;
         if (hipMalloc(&p, bp + bc) != hipSuccess) {
             mg_free(mg);
@@ -961,6 +967,18 @@ int mg_apply_run(Multigrid &mg, const double *r, double *z, hipStream_t s, doubl
     const MgArr<double> o{z, 0, nullptr};
     return mg.fp32 ? vcycle<double, float>(mg, 0, 1, f, o, k, sh, s)
                    : vcycle<double, double>(mg, 0, 1, f, o, k, sh, s);
+}
+
+int mg_apply_run(Multigrid &mg, const double *r, double *z, hipStream_t s, double kappa, const int *run,
+                 const MgUpdateDots &dots) {
+    if (mg.lv.empty() || mg.elem != 8) return OFDFT_INVALID_ARG;
+    ProfScope ps(K_MULTIGRID, 0.0, s);
+    const double2 k = make_double2(kappa, 0.0);
+    const MgShift sh{nullptr, run, 0, 0};
+    const MgArr<const double> f{r, 0, nullptr};
+    const MgArr<double> o{z, 0, nullptr};
+    return mg.fp32 ? vcycle<double, float>(mg, 0, 1, f, o, k, sh, s, dots)
+                   : vcycle<double, double>(mg, 0, 1, f, o, k, sh, s, dots);
 }
 
 int mg_apply_shifted(Multigrid &mg, int q, const double2 *r, double2 *z, const double *kappa, const int *run,

@@ -34,11 +34,12 @@ struct Multigrid {
     int elem = 8;                // input / output element bytes: 8 (FP64) or 16 (complex128)
     bool fp32 = true;            // level arrays and their arithmetic in FP32 (else FP64)
     int groups = 1;              // systems whose level arrays the hierarchy holds (same grid)
-    double *dpart = nullptr;     // partial sums (dot_cap per sum and system) and arrival counters of the products
+    double *dpart = nullptr;     // partial sums (kDotSums dot_cap per system) and arrival counters of the products
     unsigned int *dctr = nullptr;
     int dot_cap = 0;
     const double *tab = nullptr; // coarsest grid: basis matrices and eigenvalues (device)
     std::vector<void *> allocs;
+    static constexpr int kDotSums = 5;   // products per launch at most
 };
 
 constexpr int kMgCoarseMax = 16;     // coarsest grid: at most this many points per axis
@@ -61,6 +62,36 @@ int mg_apply(Multigrid &mg, const double *r, double *z, hipStream_t s, double ka
 // The same cycle, every kernel returning at once while *run != 0 (device
 // flag, for cycles inside captured blocks of an iteration that may be over).
 int mg_apply_run(Multigrid &mg, const double *r, double *z, hipStream_t s, double kappa, const int *run);
+// The same with the density update's products <u,z>, <r,z>, <r_prev,z>, <u,r>,
+// <u,r_prev> (the third and the last 0 while *q is 0) reduced into dots[0..4]
+// by the last kernel, which then adds 1 to *count (if mg_forms_dots).
+struct MgUpdateDots {
+    static constexpr int kSums = 5;
+    static constexpr bool kExtra = true;
+    using Extra = double2;
+    const double *u, *r_prev;
+    const int *q;
+    double *dots;
+    int *count;
+    bool have;
+    __device__ void prepare() { have = *q > 0; }
+    __device__ double2 extra(int64_t i) const {
+        return make_double2(GPtr<double>(u)[i], have ? GPtr<double>(r_prev)[i] : 0.0);
+    }
+    __device__ static void point(double (&acc)[5], double z, double r, double2 e) {
+        acc[0] = ::fma(e.x, z, acc[0]);
+        acc[1] = ::fma(r, z, acc[1]);
+        acc[2] = ::fma(e.y, z, acc[2]);
+        acc[3] = ::fma(e.x, r, acc[3]);
+        acc[4] = ::fma(e.x, e.y, acc[4]);
+    }
+    __device__ void finish(int, const double (&t)[5]) const {
+        for (int k = 0; k < 5; ++k) dots[k] = t[k];
+        *count += 1;
+    }
+};
+int mg_apply_run(Multigrid &mg, const double *r, double *z, hipStream_t s, double kappa, const int *run,
+                 const MgUpdateDots &dots);
 // z = M r for -Delta + kappa (complex128 arrays).  kappa points to device
 // memory holding {Re, Im} and is read by every launch, so a captured launch
 // sequence follows later changes of the shift; if `run` is given, every
