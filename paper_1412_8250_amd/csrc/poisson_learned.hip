@@ -83,7 +83,7 @@ int poisson_solve_learned(ofdft_poisson *s, double *x, double rel_tol, int max_i
     }
     double best = r2;
     OFDFT_TRY((launch_reduce<1>(n, CopyOp2{xb, x}, NoFin{}, s->rb, st)));
-    const double r2_start = r2;
+    double r2_mark = r2;
     bool fall_back = !std::isfinite(r2);
     if (!fall_back && r2 > tol2) {
         OFDFT_TRY(nn::net_apply(s->net, g, r, z, h2, true, st));
@@ -115,9 +115,12 @@ int poisson_solve_learned(ofdft_poisson *s, double *x, double rel_tol, int max_i
                 OFDFT_TRY((launch_reduce<1>(n, CopyOp2{xb, x}, NoFin{}, s->rb, st)));
             }
             if (r2 <= tol2) break;
-            if (iters >= 20 && best > 0.01 * r2_start) {   // less than 10x in residual norm
-                fall_back = true;
-                break;
+            if (iters % 20 == 0) {      // less than 10x in residual norm since the last look
+                if (best > 0.01 * r2_mark) {
+                    fall_back = true;
+                    break;
+                }
+                r2_mark = best;
             }
             OFDFT_TRY(nn::net_apply(s->net, g, r, z, h2, true, st));
             ++applies;
