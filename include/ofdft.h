@@ -250,10 +250,16 @@ int ofdft_batch_apply_preconditioner(ofdft_batch *b, int j, const double *kappa,
  * rel_tol |f|.  No preconditioner (a shift-dependent preconditioner breaks the
  * shared Krylov space: use ofdft_batch_set_preconditioner for that).
  * ofdft_multishift_create: one grid, radius 1..6, up to max_shifts (1..16)
- *   shifts per solve.  Allocates 9 + max_shifts complex128 vectors of
- *   the grid and the solve's device scalars, so a context serves one solve
- *   at a time (solves on one context must not overlap on different streams).
- *   INVALID_ARG or NO_MEMORY.
+ *   shifts per solve.  Allocates 4 + max(max_shifts - 1, 1) complex128 vectors
+ *   of the grid and, where all then take at most an eighth of the card's memory
+ *   and fit into what is free, six more (five with one shift) that make the
+ *   iterations cheaper; and the solve's device scalars, so a context serves one
+ *   solve at a time (solves on one context must not overlap on different
+ *   streams).  INVALID_ARG or NO_MEMORY.
+ * ofdft_multishift_set_compact: 1 gives the six vectors back, 0 takes them
+ *   (again); not while a solve runs.  Solutions are the same bit for bit.
+ *   INVALID_ARG or NO_MEMORY (stays compact).  ofdft_multishift_compact: the
+ *   present form (1 or 0; -1 for NULL).
  * cocg_multishift_solve:
  *   kappa    host array of 2*nshift doubles (re, im); each kappa_r != 0
  *   seed     index of the seed system, or -1: the shift expected to converge
@@ -279,6 +285,8 @@ int ofdft_batch_apply_preconditioner(ofdft_batch *b, int j, const double *kappa,
 typedef struct ofdft_multishift ofdft_multishift;
 int ofdft_multishift_create(const ofdft_grid *grid, int radius, int max_shifts, ofdft_multishift **out);
 int ofdft_multishift_destroy(ofdft_multishift *m);
+int ofdft_multishift_set_compact(ofdft_multishift *m, int compact);
+int ofdft_multishift_compact(const ofdft_multishift *m);
 int cocg_multishift_solve(ofdft_multishift *m, int nshift, const double *kappa, int seed, const void *rhs,
                           void *const *x, double rel_tol, int max_iter, ofdft_solve_stats *stats,
                           int *seed_used, void *stream);

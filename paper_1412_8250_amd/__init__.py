@@ -116,6 +116,8 @@ def _declare(l):
         "ofdft_batch_apply_preconditioner": (_I, [_V, _I, ctypes.POINTER(_D), _V, _V, _V]),
         "ofdft_multishift_create": (_I, [ctypes.POINTER(Grid), _I, _I, ctypes.POINTER(_V)]),
         "ofdft_multishift_destroy": (_I, [_V]),
+        "ofdft_multishift_set_compact": (_I, [_V, _I]),
+        "ofdft_multishift_compact": (_I, [_V]),
         "cocg_multishift_solve": (_I, [_V, _I, ctypes.POINTER(_D), _I, _V, ctypes.POINTER(_V), _D, _I,
                                        _SP, ctypes.POINTER(_I), _V]),
         "ofdft_nn_create": (_I, [ctypes.c_uint64, ctypes.POINTER(_V)]),
@@ -449,6 +451,16 @@ class MultiShift:
         self._h = ctypes.c_void_p()
         _check(lib().ofdft_multishift_create(ctypes.byref(self._grid), int(radius), self.max_shifts,
                                              ctypes.byref(self._h)))
+
+    @property
+    def compact(self) -> bool:
+        """Whether the context does without the vectors that only make the
+        iterations cheaper (set to give them back or take them again)."""
+        return lib().ofdft_multishift_compact(self._h) == 1
+
+    @compact.setter
+    def compact(self, on: bool):
+        _check(lib().ofdft_multishift_set_compact(self._h, 1 if on else 0))
 
     def solve(self, kappas, rhs, xs, rel_tol: float = 1e-8, max_iter: int = 100000, seed: int = -1,
               stream=None, allow_not_converged: bool = False):

@@ -38,6 +38,14 @@
 // every shift in every iteration moved 3 + 4 per shift; separate COCG solves
 // move 11 per system.  The scalars live on the device; the host reads the
 // status every few iterations, and launches made after the end exit at once.
+//
+// A compact context keeps no residuals: the iterate phase runs in every
+// iteration, between the other two, so r is updated in place, and the seed's
+// direction is the stencil phase's (no copy among the shifts').  The operations
+// per point are the same, so are the results, bit for bit; it holds six
+// vectors less and moves more (128 + 64 per shift but the seed + 48 B per point
+// and iteration).  Contexts are compact where the other form would take more
+// than an eighth of the card's memory, or does not fit into what is free.
 #include <algorithm>
 #include <cmath>
 #include <new>
@@ -54,8 +62,9 @@ constexpr int kMsMaxVBlocks = 1024;
 constexpr int kMsPoll = 8;          // iterations between status reads
 // Iterations whose iterate updates run together (a divisor of kMsPoll).  With
 // four shifts the phases move 128 + (4 x 64 + 4 x 16) / 4 = 208 B per point and
-// iteration against 320 one at a time; eight would save 40 more and keep four
-// more residuals.
+// iteration against 368 one at a time (the seed's 48 and 64 for each of the
+// others beside the 128); eight would save 32 more and keep four more
+// residuals.
 constexpr int kMsBlock = 4;
 static_assert(kMsPoll % kMsBlock == 0, "whole blocks between status reads");
 
@@ -320,8 +329,11 @@ ms_residual_step(MsState *st, MsShift *sh, const double2 *r, double2 *rnext, con
 // Iterate phase: the pending iterations of every shift (see the head of the
 // file); `it0` is the block's first iteration.  A shift that froze inside the
 // block has fewer pending iterations; launches with none pending move nothing.
+// Compact: the one pending iteration, before the residual phase; the seed (no
+// p of its own) takes the direction the stencil phase has just written.
 __global__ void __launch_bounds__(kMsThreads)
-ms_iterates(MsShift *sh, int S, int it0, MsRing ring, int64_t n) {
+ms_iterates(const MsState *st, MsShift *sh, int S, int it0, MsRing ring, const double2 *pA, const double2 *pB,
+            int64_t n) {
     __shared__ double2 s_ir[kMsMax][kMsBlock], s_be[kMsMax][kMsBlock], s_al[kMsMax][kMsBlock];
     __shared__ double2 *s_x[kMsMax], *s_p[kMsMax];
     __shared__ int s_pend[kMsMax], s_have[kMsMax], s_most;
@@ -345,6 +357,7 @@ ms_iterates(MsShift *sh, int S, int it0, MsRing ring, int64_t n) {
     __syncthreads();
     const int most = s_most;
     if (most == 0) return;
+    const GPtr<double2> PS(st->parity ? pA : pB);
     const int64_t stride = (int64_t)gridDim.x * kMsThreads;
     for (int64_t i = (int64_t)blockIdx.x * kMsThreads + threadIdx.x; i < n; i += stride) {
         double2 rv[kMsBlock];
@@ -355,6 +368,10 @@ ms_iterates(MsShift *sh, int S, int it0, MsRing ring, int64_t n) {
             const int pend = s_pend[j];
             if (pend == 0) continue;
             const GPtr<double2> X(s_x[j]), P(s_p[j]);
+            if (!s_p[j]) {
+                X.st(i, cfma(s_al[j][0], PS[i], X[i]));
+                continue;
+            }
             double2 xv = X[i], pj = s_have[j] ? P[i] : c2(0.0, 0.0);
 #pragma unroll
             for (int k = 0; k < kMsBlock; ++k)
@@ -478,10 +495,23 @@ struct ofdft_multishift {
     Coef<double> coef{};
     int64_t n = 0;
     int vblocks = 0;
-    MsRing ring{};               // residuals
-    double2 *q = nullptr, *pA = nullptr, *pB = nullptr;
-    double2 *e = nullptr;        // correction of the finishing solves
-    std::vector<double2 *> p;    // directions of the shifts
+    double2 *r = nullptr, *q = nullptr, *pA = nullptr, *pB = nullptr;
+    std::vector<double2 *> p;    // directions of the shifts but one (at least one vector)
+    // the other residuals, the last shift's direction and the correction of the
+    // finishing solves; none: the context is compact
+    std::vector<double2 *> extra;
+    bool compact() const { return extra.empty(); }
+    MsRing ring() const {        // residuals (compact: all in r)
+        MsRing g;
+        for (int k = 0; k < kMsRing; ++k) g.r[k] = k == 0 || compact() ? r : extra[k - 1];
+        return g;
+    }
+    // Direction of shift j; compact: of the k-th shift but the seed.
+    double2 *dir(int j) const { return j < (int)p.size() ? p[j] : extra[kMsRing - 1]; }
+    // Correction vector: the one-shift sequences that fill it use no direction
+    // in a compact context and p[0] in another.
+    double2 *corr() const { return compact() ? p[0] : extra.back(); }
+    size_t extras() const { return kMsRing - 1 + (max_shifts > 1 ? 2 : 1); }
     MsState *d_state = nullptr;
     MsShift *d_shift = nullptr;
     double *d_part = nullptr;
@@ -493,9 +523,9 @@ struct ofdft_multishift {
 namespace {
 
 void ms_free(ofdft_multishift *m) {
-    for (double2 *p : m->ring.r)
-        if (p) (void)hipFree(p);
-    for (void *p : {(void *)m->e, (void *)m->q, (void *)m->pA, (void *)m->pB, (void *)m->d_state,
+    for (double2 *p : m->extra) (void)hipFree(p);
+    m->extra.clear();
+    for (void *p : {(void *)m->r, (void *)m->q, (void *)m->pA, (void *)m->pB, (void *)m->d_state,
                     (void *)m->d_shift, (void *)m->d_part, (void *)m->d_ctr, (void *)m->d_res})
         if (p) (void)hipFree(p);
     for (double2 *p : m->p)
@@ -513,6 +543,21 @@ int ms_alloc(P_ **p, size_t bytes) {
         set_error("multi-shift COCG: device allocation of %zu bytes failed", bytes);
         return OFDFT_NO_MEMORY;
     }
+    return OFDFT_OK;
+}
+
+// Leaves the compact form; NO_MEMORY (nothing changed) if the vectors do not fit.
+int ms_extend(ofdft_multishift *m) {
+    std::vector<double2 *> v;
+    for (size_t k = 0; k < m->extras(); ++k) {
+        double2 *p = nullptr;
+        if (const int st = ms_alloc(&p, sizeof(double2) * (size_t)m->n)) {
+            for (double2 *q : v) (void)hipFree(q);
+            return st;
+        }
+        v.push_back(p);
+    }
+    m->extra = v;
     return OFDFT_OK;
 }
 
@@ -564,9 +609,9 @@ extern "C" int ofdft_multishift_create(const ofdft_grid *grid, int radius, int m
     m->vblocks = (int)std::min<int64_t>(kMsMaxVBlocks, (m->n + kMsThreads - 1) / kMsThreads);
     const size_t vb = sizeof(double2) * (size_t)m->n;
     const size_t nslots = (size_t)std::max(std::max(m->tg.nblocks, m->bg.nblocks), m->vblocks);
-    m->p.assign(max_shifts, nullptr);
+    m->p.assign(std::max(max_shifts - 1, 1), nullptr);
     int st = OFDFT_OK;
-    if ((st = ms_alloc(&m->e, vb)) || (st = ms_alloc(&m->q, vb)) || (st = ms_alloc(&m->pA, vb)) ||
+    if ((st = ms_alloc(&m->r, vb)) || (st = ms_alloc(&m->q, vb)) || (st = ms_alloc(&m->pA, vb)) ||
         (st = ms_alloc(&m->pB, vb)) || (st = ms_alloc(&m->d_state, sizeof(MsState))) ||
         (st = ms_alloc(&m->d_shift, sizeof(MsShift) * kMsMax)) ||
         (st = ms_alloc(&m->d_part, sizeof(double) * 3 * nslots)) ||
@@ -574,17 +619,36 @@ extern "C" int ofdft_multishift_create(const ofdft_grid *grid, int radius, int m
         return fail(st);
     for (auto &p : m->p)
         if ((st = ms_alloc(&p, vb))) return fail(st);
-    for (auto &p : m->ring.r)
-        if ((st = ms_alloc(&p, vb))) return fail(st);
     if (hipMemset(m->d_ctr, 0, sizeof(unsigned int) * kArriveWords) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
         set_error("ofdft_multishift_create: clearing the reduction counter failed");
         return fail(OFDFT_HIP_ERROR);
     }
     if (hipEventCreate(&m->ev0) != hipSuccess || hipEventCreate(&m->ev1) != hipSuccess)
         return fail(OFDFT_HIP_ERROR);
+    // the vectors that can be done without come last
+    int dev = 0;
+    size_t mem_total = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceTotalMem(&mem_total, dev) != hipSuccess)
+        return fail(OFDFT_HIP_ERROR);
+    if ((4 + m->p.size() + m->extras()) * vb <= mem_total / 8) (void)ms_extend(m);
     *out = m;
     return OFDFT_OK;
 }
+
+extern "C" int ofdft_multishift_set_compact(ofdft_multishift *m, int compact) {
+    if (!m || compact < 0 || compact > 1) {
+        set_error("ofdft_multishift_set_compact: context and 0/1 expected");
+        return OFDFT_INVALID_ARG;
+    }
+    if (compact) {                              // no solve is under way: solves synchronise their stream
+        for (double2 *p : m->extra) (void)hipFree(p);
+        m->extra.clear();
+        return OFDFT_OK;
+    }
+    return m->compact() ? ms_extend(m) : OFDFT_OK;
+}
+
+extern "C" int ofdft_multishift_compact(const ofdft_multishift *m) { return m ? (m->compact() ? 1 : 0) : -1; }
 
 extern "C" int ofdft_multishift_destroy(ofdft_multishift *m) {
     if (!m) return OFDFT_OK;
@@ -608,10 +672,12 @@ int ms_iterate(ofdft_multishift *m, int S, const double *kappa, int seed, const 
     hst.seed = seed;
     hst.done = H_RUNNING;
     hsh.assign(kMsMax, MsShift{});
-    for (int j = 0; j < S; ++j) {
+    const bool compact = m->compact();
+    const MsRing ring = m->ring();
+    for (int j = 0, dirs = 0; j < S; ++j) {
         MsShift &h = hsh[j];
         h.x = x[j];
-        h.p = m->p[j];
+        h.p = compact && j == seed ? nullptr : m->dir(dirs++);
         h.sre = kappa[2 * j] - kappa[2 * seed];
         h.sim = kappa[2 * j + 1] - kappa[2 * seed + 1];
         h.pi_re = h.pp_re = h.ir_re = 1.0;
@@ -624,7 +690,7 @@ int ms_iterate(ofdft_multishift *m, int S, const double *kappa, int seed, const 
     {
         ProfScope ps(K_POINTWISE, n * e * (2.0 + S), s);
         hipLaunchKernelGGL(ms_init, dim3(m->vblocks), dim3(kMsThreads), 0, s, m->d_state, m->d_shift, f,
-                           m->ring.r[0], m->n, tol, m->d_part, m->d_ctr);
+                           ring.r[0], m->n, tol, m->d_part, m->d_ctr);
         OFDFT_CHECK_HIP(hipGetLastError());
     }
     const double kre = kappa[2 * seed], kim = kappa[2 * seed + 1];
@@ -634,8 +700,9 @@ int ms_iterate(ofdft_multishift *m, int S, const double *kappa, int seed, const 
         OFDFT_CHECK_HIP(hipStreamSynchronize(s));
         if (hst.done != H_RUNNING) break;
         for (int c = 0; c < kMsPoll; ++c) {
-            const int it = round * kMsPoll + c, slot = it % kMsBlock;     // iteration of this launch, if still running
-            const double2 *r = m->ring.r[it % kMsRing];
+            const int it = round * kMsPoll + c;                 // iteration of this launch, if still running
+            const int slot = compact ? 0 : it % kMsBlock;
+            const double2 *r = ring.r[it % kMsRing];
             OFDFT_TRY(ms_dispatch(m, [&](auto tag, const auto &geom, int blocks, dim3 threads, size_t lds) {
                 using Tile = decltype(tag);
                 ProfScope ps(K_MS_STENCIL, 0.0, s);
@@ -646,16 +713,19 @@ int ms_iterate(ofdft_multishift *m, int S, const double *kappa, int seed, const 
                 return OFDFT_OK;
             }));
             ProfScope ps(K_MS_UPDATE, 0.0, s);
-            hipLaunchKernelGGL(ms_residual_step, dim3(m->vblocks), dim3(kMsThreads), 0, s, m->d_state, m->d_shift, r,
-                               m->ring.r[(it + 1) % kMsRing], m->q, m->n, m->d_part, m->d_ctr);
-            OFDFT_CHECK_HIP(hipGetLastError());
-            if (slot == kMsBlock - 1) {
-                hipLaunchKernelGGL(ms_iterates, dim3(m->vblocks), dim3(kMsThreads), 0, s, m->d_shift, S,
-                                   it - slot, m->ring, m->n);
+            auto iterates = [&]() -> int {
+                hipLaunchKernelGGL(ms_iterates, dim3(m->vblocks), dim3(kMsThreads), 0, s, m->d_state, m->d_shift, S,
+                                   it - slot, ring, m->pA, m->pB, m->n);
                 OFDFT_CHECK_HIP(hipGetLastError());
                 hipLaunchKernelGGL(ms_block_done, dim3(1), dim3(kMsMax), 0, s, m->d_shift, S);
                 OFDFT_CHECK_HIP(hipGetLastError());
-            }
+                return OFDFT_OK;
+            };
+            if (compact) OFDFT_TRY(iterates());
+            hipLaunchKernelGGL(ms_residual_step, dim3(m->vblocks), dim3(kMsThreads), 0, s, m->d_state, m->d_shift, r,
+                               ring.r[(it + 1) % kMsRing], m->q, m->n, m->d_part, m->d_ctr);
+            OFDFT_CHECK_HIP(hipGetLastError());
+            if (!compact && slot == kMsBlock - 1) OFDFT_TRY(iterates());
         }
     }
     OFDFT_CHECK_HIP(hipMemcpyAsync(&hst, m->d_state, sizeof(MsState), hipMemcpyDeviceToHost, s));
@@ -669,15 +739,16 @@ int ms_iterate(ofdft_multishift *m, int S, const double *kappa, int seed, const 
     // p_old and q_old (r only in the first iteration) and writes p and q; the
     // residual phase reads r, q and writes r; the iterate phase reads each
     // residual once and, per block and running shift, p and x (x alone the
-    // first time) and writes both.
+    // first time) and writes both (compact: of the seed p is not written).
     const int steps = hst.iter;
     if (steps > 0) {
         prof_add(K_MS_STENCIL, n * e * (5.0 * steps - 2.0), 0);
         double upd = 4.0 * steps;
         for (int j = 0; j < S; ++j) {
             const int it = hsh[j].stat == H_RUNNING ? steps : hsh[j].iters;
-            const int blocks = (it + kMsBlock - 1) / kMsBlock;
-            upd += it > 0 ? 4.0 * blocks - 1.0 : 0.0;
+            const int blocks = compact ? it : (it + kMsBlock - 1) / kMsBlock;
+            if (compact && j == seed) upd += 3.0 * it;
+            else upd += it > 0 ? 4.0 * blocks - 1.0 : 0.0;
         }
         prof_add(K_MS_UPDATE, n * e * upd, 0);
     }
@@ -737,7 +808,7 @@ int ms_solve(ofdft_multishift *m, int S, const double *kappa, int seed, const do
         if (h.stat == H_CONVERGED && code == OFDFT_NOT_CONVERGED && std::isfinite(rel)) {
             int budget = std::max(maxit - steps, 0);
             for (int round = 0; round < kMsFixRounds && rel > tol && budget > 0; ++round) {
-                OFDFT_TRY(ms_true_residual(m, kappa + 2 * j, x[j], f, m->ring.r[0], m->d_res + j, s));
+                OFDFT_TRY(ms_true_residual(m, kappa + 2 * j, x[j], f, m->r, m->d_res + j, s));
                 double d2 = 0.0;
                 OFDFT_CHECK_HIP(hipMemcpyAsync(&d2, m->d_res + j, sizeof(double), hipMemcpyDeviceToHost, s));
                 OFDFT_CHECK_HIP(hipStreamSynchronize(s));
@@ -745,12 +816,12 @@ int ms_solve(ofdft_multishift *m, int S, const double *kappa, int seed, const do
                 const double tc = std::min(0.5, 0.5 * tol * std::sqrt(fn2 / d2));
                 MsState cst{};
                 std::vector<MsShift> csh;
-                double2 *ex[1] = {m->e};
-                OFDFT_TRY(ms_iterate(m, 1, kappa + 2 * j, 0, m->ring.r[0], ex, tc, budget, cst, csh, s));
+                double2 *ex[1] = {m->corr()};
+                OFDFT_TRY(ms_iterate(m, 1, kappa + 2 * j, 0, m->r, ex, tc, budget, cst, csh, s));
                 extra_it[j] += cst.iter;
                 budget -= cst.iter;
                 if (cst.done == H_NONFINITE || cst.done == H_BREAKDOWN) break;
-                hipLaunchKernelGGL(ms_axpy, dim3(m->vblocks), dim3(kMsThreads), 0, s, x[j], m->e, m->n);
+                hipLaunchKernelGGL(ms_axpy, dim3(m->vblocks), dim3(kMsThreads), 0, s, x[j], m->corr(), m->n);
                 OFDFT_CHECK_HIP(hipGetLastError());
                 prof_add(K_POINTWISE, (double)m->n * sizeof(double2) * 3.0, 1);
                 OFDFT_TRY(ms_true_residual(m, kappa + 2 * j, x[j], f, nullptr, m->d_res + j, s));
