@@ -193,9 +193,14 @@ int ofdft_poisson_set_refinement(ofdft_poisson *s, double inner_min, double inne
  *
  * ofdft_batch_create: nsys systems, grids[j] (host array), one radius, dtype
  *   OFDFT_C128 or OFDFT_C64 (C64 runs COCG in complex64 inside complex128
- *   residual refinement).  Allocates all workspaces: six vectors per system
- *   (four where six of each would be more than an eighth of the card's
- *   memory), C64 three more.
+ *   residual refinement).  Allocates all workspaces: four vectors per system,
+ *   C64 three more, and two more per system that make the iterations cheaper
+ *   where six of each are at most an eighth of the card's memory and fit into
+ *   what is free.
+ * ofdft_batch_set_compact: 1 gives those two back, 0 takes them (again); not
+ *   while a solve runs.  Solutions are the same bit for bit.  INVALID_ARG or
+ *   NO_MEMORY (stays compact).  ofdft_batch_compact: the present form (1 or 0;
+ *   -1 for NULL).
  * cg_helmholtz_solve_batched:
  *   kappa    host array of 2*nsys doubles (re, im) per system; kappa != 0
  *   rhs      host array of nsys device pointers to complex128 arrays f_j
@@ -217,6 +222,7 @@ int ofdft_poisson_set_refinement(ofdft_poisson *s, double inner_min, double inne
  *   Allocates one complex128 vector per system and multigrid level arrays
  *   per system (about 1.3 fine-grid vectors); consecutive systems on one
  *   grid (up to 64) form a group whose cycles run as one launch per kernel.
+ *   A batch becomes compact where they would not fit otherwise.
  *   INVALID_ARG (nothing changed) or NO_MEMORY.
  * ------------------------------------------------------------------------ */
 typedef enum {
@@ -229,6 +235,8 @@ typedef struct ofdft_batch ofdft_batch;
 int ofdft_batch_create(int nsys, const ofdft_grid *grids, int radius, ofdft_dtype dtype,
                        ofdft_batch **out);
 int ofdft_batch_destroy(ofdft_batch *b);
+int ofdft_batch_set_compact(ofdft_batch *b, int compact);
+int ofdft_batch_compact(const ofdft_batch *b);
 int cg_helmholtz_solve_batched(ofdft_batch *b, const double *kappa, const void *const *rhs,
                                void *const *x, double rel_tol, int max_iter,
                                ofdft_solve_stats *stats, void *stream);

@@ -109,6 +109,8 @@ def _declare(l):
         "ofdft_stencil_set_config": (_I, [_I, _I, _I, _I, _I, _I]),
         "ofdft_batch_set_config": (_I, [_V, _I, _I]),
         "ofdft_batch_set_preconditioner": (_I, [_V, _I]),
+        "ofdft_batch_set_compact": (_I, [_V, _I]),
+        "ofdft_batch_compact": (_I, [_V]),
         "ofdft_scf_energy": (_I, [_V, ctypes.POINTER(GaussAtoms), ctypes.POINTER(_D), _V]),
         "ofdft_scf_energy_paper_form": (_I, [_V, ctypes.POINTER(GaussAtoms), _D, ctypes.POINTER(_D), _V]),
         "ofdft_scf_forces_paper_form": (_I, [_V, ctypes.POINTER(GaussAtoms), _D, ctypes.POINTER(_D), _V]),
@@ -377,6 +379,16 @@ class HelmholtzBatch:
         self._grids = grids
         self._h = ctypes.c_void_p()
         _check(lib().ofdft_batch_create(self.n, grids, int(radius), int(dtype), ctypes.byref(self._h)))
+
+    @property
+    def compact(self) -> bool:
+        """Whether the batch does without the vectors that only make the
+        iterations cheaper (set to give them back or take them again)."""
+        return lib().ofdft_batch_compact(self._h) == 1
+
+    @compact.setter
+    def compact(self, on: bool):
+        _check(lib().ofdft_batch_set_compact(self._h, 1 if on else 0))
 
     def set_config(self, shape_id: int, group: int):
         _check(lib().ofdft_batch_set_config(self._h, int(shape_id), int(group)))

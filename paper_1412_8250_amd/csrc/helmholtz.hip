@@ -487,9 +487,54 @@ void precond_free(ofdft_batch *b) {
     b->precond = OFDFT_PRECOND_NONE;
 }
 
+// Back to two ring slots.  No solve is under way (solves synchronise their stream).
+void batch_compact(ofdft_batch *b) {
+    if (b->step_graph) {                         // captured with the other slots
+        (void)hipGraphExecDestroy(b->step_graph);
+        b->step_graph = nullptr;
+    }
+    for (int k = 2; k < kRingMax; ++k) {
+        for (void *p : b->slot[k])
+            if (p) (void)hipFree(p);
+        b->slot[k].clear();
+    }
+    b->ring = 2;
+}
+
+// z, then slots 1 .. ring - 1 of every system: the device table of the cycles' outputs.
+int upload_ztab(ofdft_batch *b) {
+    std::vector<void *> zt(b->z);
+    for (int k = 1; k < b->ring; ++k) zt.insert(zt.end(), b->slot[k].begin(), b->slot[k].end());
+    OFDFT_CHECK_HIP(hipMemcpy(b->d_ztab, zt.data(), sizeof(void *) * zt.size(), hipMemcpyHostToDevice));
+    return OFDFT_OK;
+}
+
+// From two ring slots to four; NO_MEMORY (nothing changed) if they do not fit.
+int batch_extend(ofdft_batch *b) {
+    const size_t e = b->dtype == OFDFT_C64 ? sizeof(float2) : sizeof(double2);
+    for (int k = 2; k < kRingMax; ++k) {
+        b->slot[k].assign(b->nsys, nullptr);
+        for (int j = 0; j < b->nsys; ++j)
+            if (hipMalloc(&b->slot[k][j], (size_t)npoints(b->grids[j]) * e) != hipSuccess) {
+                (void)hipGetLastError();
+                b->slot[k][j] = nullptr;
+                batch_compact(b);
+                set_error("ofdft_batch: out of device memory");
+                return OFDFT_NO_MEMORY;
+            }
+    }
+    if (b->step_graph) {
+        (void)hipGraphExecDestroy(b->step_graph);
+        b->step_graph = nullptr;
+    }
+    b->ring = kRingMax;
+    return b->d_ztab ? upload_ztab(b) : OFDFT_OK;
+}
+
 void batch_free(ofdft_batch *b) {
     stepped_free(b);
     precond_free(b);
+    batch_compact(b);
     for (void *p : b->allocs)
         if (p) (void)hipFree(p);
     b->allocs.clear();
@@ -502,6 +547,7 @@ template <typename P_>
 int dalloc(ofdft_batch *b, P_ **p, size_t bytes) {
     void *q = nullptr;
     if (hipMalloc(&q, bytes) != hipSuccess) {
+        (void)hipGetLastError();
         set_error("ofdft_batch: out of device memory (%zu bytes)", bytes);
         return OFDFT_NO_MEMORY;
     }
@@ -586,16 +632,7 @@ extern "C" int ofdft_batch_create(int nsys, const ofdft_grid *grids, int radius,
     const size_t e = c64 ? sizeof(float2) : sizeof(double2);
     b->r.resize(nsys);
     b->p.resize(nsys);
-    // four ring slots, or two where the vectors would then take more than an
-    // eighth of the card's memory (no more than a schedule without the ring)
-    double bytes = 0.0;
-    for (int j = 0; j < nsys; ++j) bytes += (double)npoints(grids[j]) * e * (2 + kRingMax);
-    int dev = 0, cus = 0;
-    size_t mem_total = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceTotalMem(&mem_total, dev) != hipSuccess)
-        return fail(OFDFT_HIP_ERROR);
-    b->ring = bytes <= (double)mem_total / 8 ? kRingMax : 2;
-    for (int k = 1; k < b->ring; ++k) b->slot[k].resize(nsys);
+    b->slot[1].resize(nsys);
     b->Ap.resize(nsys);
     b->r128.resize(nsys);
     b->f32.resize(nsys);
@@ -604,17 +641,18 @@ extern "C" int ofdft_batch_create(int nsys, const ofdft_grid *grids, int radius,
         const size_t n = (size_t)npoints(grids[j]);
         int st = OFDFT_OK;
         if ((st = dalloc(b, &b->r[j], n * e)) || (st = dalloc(b, &b->p[j], n * e)) ||
-            (st = dalloc(b, &b->Ap[j], n * e)))
+            (st = dalloc(b, &b->slot[1][j], n * e)) || (st = dalloc(b, &b->Ap[j], n * e)))
             return fail(st);
-        if ((st = dalloc(b, &b->slot[1][j], (b->ring - 1) * n * e))) return fail(st);
-        for (int k = 2; k < b->ring; ++k) b->slot[k][j] = (char *)b->slot[1][j] + (k - 1) * n * e;
         if (c64) {
             if ((st = dalloc(b, &b->r128[j], n * sizeof(double2))) ||
                 (st = dalloc(b, &b->f32[j], n * e)) || (st = dalloc(b, &b->x32[j], n * e)))
                 return fail(st);
         }
     }
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    int dev = 0, cus = 0;
+    size_t mem_total = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceTotalMem(&mem_total, dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         return fail(OFDFT_HIP_ERROR);
     b->groups_cap = std::max(1, cus * 8);
     int st = OFDFT_OK;
@@ -629,9 +667,29 @@ extern "C" int ofdft_batch_create(int nsys, const ofdft_grid *grids, int radius,
     if ((st = redbuf_alloc(b->rb))) return fail(st);
     if (hipEventCreate(&b->ev0) != hipSuccess || hipEventCreate(&b->ev1) != hipSuccess)
         return fail(OFDFT_HIP_ERROR);
+    // four ring slots, or two (no more memory than a schedule without the ring)
+    // where the vectors would then take more than an eighth of the card's memory
+    // or do not fit into what is free: the slots that can be done without come last
+    double bytes = 0.0;
+    for (int j = 0; j < nsys; ++j) bytes += (double)npoints(grids[j]) * e * (2 + kRingMax);
+    if (bytes <= (double)mem_total / 8) (void)batch_extend(b);
     *out = b;
     return OFDFT_OK;
 }
+
+extern "C" int ofdft_batch_set_compact(ofdft_batch *b, int compact) {
+    if (!b || compact < 0 || compact > 1) {
+        set_error("ofdft_batch_set_compact: batch and 0/1 expected");
+        return OFDFT_INVALID_ARG;
+    }
+    if (compact) {
+        batch_compact(b);
+        return OFDFT_OK;
+    }
+    return b->ring == 2 ? batch_extend(b) : OFDFT_OK;
+}
+
+extern "C" int ofdft_batch_compact(const ofdft_batch *b) { return b ? (b->ring == 2 ? 1 : 0) : -1; }
 
 extern "C" int ofdft_batch_destroy(ofdft_batch *b) {
     if (!b) return OFDFT_OK;
@@ -676,8 +734,16 @@ extern "C" int ofdft_batch_tune(ofdft_batch *b, const double *kappa, const void 
             set_error("ofdft_batch_tune: NULL array for system %d", j);
             return OFDFT_INVALID_ARG;
         }
-        if (hipMalloc(&tmp[j], sizeof(double2) * npoints(b->grids[j])) != hipSuccess) {
+        const size_t bytes = sizeof(double2) * npoints(b->grids[j]);
+        bool ok = hipMalloc(&tmp[j], bytes) == hipSuccess;
+        if (!ok && b->ring > 2) {                // the scratch before the slots that can be done without
             (void)hipGetLastError();
+            batch_compact(b);
+            ok = hipMalloc(&tmp[j], bytes) == hipSuccess;
+        }
+        if (!ok) {
+            (void)hipGetLastError();
+            tmp[j] = nullptr;
             release();
             set_error("ofdft_batch_tune: out of device memory");
             return OFDFT_NO_MEMORY;
@@ -754,7 +820,9 @@ extern "C" int ofdft_batch_tune(ofdft_batch *b, const double *kappa, const void 
     return OFDFT_OK;
 }
 
-extern "C" int ofdft_batch_set_preconditioner(ofdft_batch *b, int kind) {
+namespace {
+
+int set_preconditioner(ofdft_batch *b, int kind) {
     if (!b || (kind != OFDFT_PRECOND_NONE && kind != OFDFT_PRECOND_MULTIGRID &&
                kind != OFDFT_PRECOND_MULTIGRID_F64)) {
         set_error("ofdft_batch_set_preconditioner: unknown kind %d", kind);
@@ -762,7 +830,7 @@ extern "C" int ofdft_batch_set_preconditioner(ofdft_batch *b, int kind) {
     }
     if (kind == b->precond) return OFDFT_OK;
     if (b->precond != OFDFT_PRECOND_NONE && kind != OFDFT_PRECOND_NONE) {     // switch precision
-        const int st = ofdft_batch_set_preconditioner(b, OFDFT_PRECOND_NONE);
+        const int st = set_preconditioner(b, OFDFT_PRECOND_NONE);
         if (st != OFDFT_OK) return st;
     }
     if (kind == OFDFT_PRECOND_NONE) {
@@ -810,6 +878,7 @@ extern "C" int ofdft_batch_set_preconditioner(ofdft_batch *b, int kind) {
     }
     if (hipEventCreateWithFlags(&fork, hipEventDisableTiming) != hipSuccess) return undo(OFDFT_HIP_ERROR);
     if (hipMalloc(&kap, 2 * sizeof(double)) != hipSuccess) {
+        (void)hipGetLastError();
         kap = nullptr;
         set_error("ofdft_batch_set_preconditioner: out of device memory");
         return undo(OFDFT_NO_MEMORY);
@@ -835,6 +904,7 @@ extern "C" int ofdft_batch_set_preconditioner(ofdft_batch *b, int kind) {
     for (int j = 0; j < b->nsys; ++j) {
         const ofdft_grid &g = b->grids[j];
         if (hipMalloc(&z[j], sizeof(double2) * (size_t)npoints(g)) != hipSuccess) {
+            (void)hipGetLastError();
             z[j] = nullptr;
             set_error("ofdft_batch_set_preconditioner: out of device memory");
             return undo(OFDFT_NO_MEMORY);
@@ -843,19 +913,18 @@ extern "C" int ofdft_batch_set_preconditioner(ofdft_batch *b, int kind) {
     {
         std::vector<void *> rt(b->r.begin(), b->r.begin() + b->nsys);
         if (hipMalloc(&rtab, sizeof(void *) * b->nsys) != hipSuccess) {
+            (void)hipGetLastError();
             rtab = nullptr;
             set_error("ofdft_batch_set_preconditioner: out of device memory");
             return undo(OFDFT_NO_MEMORY);
         }
-        std::vector<void *> zt(z);
-        for (int k = 1; k < b->ring; ++k) zt.insert(zt.end(), b->slot[k].begin(), b->slot[k].end());
-        if (hipMalloc(&ztab, sizeof(void *) * zt.size()) != hipSuccess) {
+        if (hipMalloc(&ztab, sizeof(void *) * b->nsys * kRingMax) != hipSuccess) {
+            (void)hipGetLastError();
             ztab = nullptr;
             set_error("ofdft_batch_set_preconditioner: out of device memory");
             return undo(OFDFT_NO_MEMORY);
         }
-        if (hipMemcpy(rtab, rt.data(), sizeof(void *) * b->nsys, hipMemcpyHostToDevice) != hipSuccess ||
-            hipMemcpy(ztab, zt.data(), sizeof(void *) * zt.size(), hipMemcpyHostToDevice) != hipSuccess)
+        if (hipMemcpy(rtab, rt.data(), sizeof(void *) * b->nsys, hipMemcpyHostToDevice) != hipSuccess)
             return undo(OFDFT_HIP_ERROR);
     }
     OFDFT_CHECK_HIP(hipDeviceSynchronize());
@@ -872,7 +941,18 @@ extern "C" int ofdft_batch_set_preconditioner(ofdft_batch *b, int kind) {
     b->mg_join = join;
     b->mg_fork = fork;
     b->precond = kind;
-    return OFDFT_OK;
+    return upload_ztab(b);
+}
+
+}  // namespace
+
+extern "C" int ofdft_batch_set_preconditioner(ofdft_batch *b, int kind) {
+    int st = set_preconditioner(b, kind);
+    if (st == OFDFT_NO_MEMORY && b->ring > 2) {  // the hierarchies before the slots that can be done without
+        batch_compact(b);
+        st = set_preconditioner(b, kind);
+    }
+    return st;
 }
 
 extern "C" int ofdft_batch_apply_preconditioner(ofdft_batch *b, int j, const double *kappa, const void *r,

@@ -154,7 +154,7 @@ struct ofdft_batch {
     // per system workspaces (complex128: r, p, ring slots 1 .. ring - 1, Ap; complex64 adds r128, f32, x32)
     std::vector<void *> r, p, Ap, r128, f32, x32;
     std::vector<void *> slot[ofdft::kRingMax];   // slot[0] unused
-    int ring = 2;
+    int ring = 2;                                // 2 (compact) or 4: slots in use
     ofdft::HSys *d_sys = nullptr;
     ofdft::HState *d_st = nullptr;
     int *d_order = nullptr;

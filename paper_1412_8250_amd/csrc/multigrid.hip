@@ -882,6 +882,7 @@ int mg_create(Multigrid &mg, const ofdft_grid &g, int elem_bytes, bool fp32, int
         for (int k = 0; k < count; ++k) {
             void *p = nullptr;
             if (hipMalloc(&p, b) != hipSuccess) {
+                (void)hipGetLastError();
                 mg_free(mg);
                 set_error("multigrid: out of device memory");
                 return OFDFT_NO_MEMORY;
@@ -896,6 +897,7 @@ int mg_create(Multigrid &mg, const ofdft_grid &g, int elem_bytes, bool fp32, int
         const size_t bp = sizeof(double) * Multigrid::kDotSums * (size_t)mg.dot_cap * groups, bc = sizeof(unsigned int) * kArriveWords * (size_t)groups;
         void *p = nullptr;
         if (hipMalloc(&p, bp + bc) != hipSuccess) {
+            (void)hipGetLastError();
             mg_free(mg);
             set_error("multigrid: out of device memory");
             return OFDFT_NO_MEMORY;
@@ -923,6 +925,7 @@ int mg_create(Multigrid &mg, const ofdft_grid &g, int elem_bytes, bool fp32, int
     }
     void *p = nullptr;
     if (hipMalloc(&p, sizeof(double) * tab.size()) != hipSuccess) {
+        (void)hipGetLastError();
         mg_free(mg);
         set_error("multigrid: out of device memory");
         return OFDFT_NO_MEMORY;
