@@ -132,8 +132,9 @@ int fd_gradient_apply(const ofdft_grid *grid, int radius, const double *x, doubl
  *         prolongation; exact DFT solve on the coarsest grid), a fixed
  *         symmetric positive definite approximation of the inverse of
  *         -L_h, so the iteration count does not grow with the grid.
- *         Two of its vectors are allocated only where eight are at most
- *         an eighth of the card's memory.
+ *         Two of its vectors only make the iterations cheaper; they are
+ *         allocated where eight are at most an eighth of the card's memory
+ *         and they fit into what is free (see ofdft_poisson_set_compact).
  * cg_poisson_solve:
  *   rhs      device FP64 array g (not modified)
  *   x        device FP64 array: initial guess on entry (warm start), solution on
@@ -177,6 +178,13 @@ int cg_poisson_solve_noalloc(const ofdft_grid *grid, int radius, const double *r
  * stream) and replayed; kernels leave early once converged.  enable = 0 turns
  * this off for the solver (results are bitwise identical either way). */
 int ofdft_poisson_set_graphs(ofdft_poisson *s, int enable);
+/* Multigrid form: 1 gives the two vectors back that only make the iterations
+ * cheaper, 0 takes them (again); not while a solve runs.  Solutions are the
+ * same bit for bit.  INVALID_ARG (also for the other forms) or NO_MEMORY (stays
+ * compact).  ofdft_poisson_compact: the present form (1 or 0; -1 for other
+ * solvers and NULL). */
+int ofdft_poisson_set_compact(ofdft_poisson *s, int compact);
+int ofdft_poisson_compact(const ofdft_poisson *s);
 /* Refined form: each FP32 inner solve targets 0.3 x (remaining reduction),
  * clamped to [inner_min, inner_max] (defaults 1e-5, 1e-1).  INVALID_ARG unless
  * 0 < inner_min <= inner_max < 1. */

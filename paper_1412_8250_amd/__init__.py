@@ -133,6 +133,8 @@ def _declare(l):
         "ofdft_nn_train_step": (_I, [_V, _GP, _V, _V, _D, ctypes.POINTER(_D), _V]),
         "ofdft_poisson_set_network": (_I, [_V, _V]),
         "ofdft_poisson_set_graphs": (_I, [_V, _I]),
+        "ofdft_poisson_set_compact": (_I, [_V, _I]),
+        "ofdft_poisson_compact": (_I, [_V]),
         "ofdft_poisson_set_refinement": (_I, [_V, _D, _D]),
         "ofdft_poisson_set_learned_mode": (_I, [_V, _I]),
         "ofdft_poisson_apply_preconditioner": (_I, [_V, _V, _V, _V]),
@@ -328,6 +330,16 @@ class PoissonSolver:
 
     def set_graphs(self, enable: bool):
         _check(lib().ofdft_poisson_set_graphs(self._h, 1 if enable else 0))
+
+    @property
+    def compact(self) -> bool:
+        """Whether a multigrid solver does without the vectors that only make
+        the iterations cheaper (set to give them back or take them again)."""
+        return lib().ofdft_poisson_compact(self._h) == 1
+
+    @compact.setter
+    def compact(self, on: bool):
+        _check(lib().ofdft_poisson_set_compact(self._h, 1 if on else 0))
 
     def set_network(self, net):
         """Attach a Network (learned mode only); the solver keeps a reference."""

@@ -450,6 +450,32 @@ int poisson_solve(ofdft_poisson *s, const double *rhs, double *x, double rel_tol
 
 using namespace ofdft;
 
+namespace {
+
+// The captured block of iterations goes with the ring slots it was captured with.
+void drop_mg_graph(ofdft_poisson *s) {
+    if (s->mggraph) (void)hipGraphExecDestroy(s->mggraph);
+    s->mggraph = nullptr;
+}
+
+// Multigrid form: from two ring slots to four; NO_MEMORY (nothing changed) if they do not fit.
+int poisson_extend(ofdft_poisson *s) {
+    const int64_t n = npoints(s->g);
+    double *p = nullptr;
+    if (hipMalloc(&p, 2 * sizeof(double) * n) != hipSuccess) {
+        (void)hipGetLastError();
+        set_error("ofdft_poisson: out of device memory");
+        return OFDFT_NO_MEMORY;
+    }
+    drop_mg_graph(s);
+    s->mg_z[2] = p;
+    s->mg_z[3] = p + n;
+    s->mg_ring = 4;
+    return OFDFT_OK;
+}
+
+}  // namespace
+
 extern "C" int ofdft_poisson_create(const ofdft_grid *grid, int radius, int mode,
                                     ofdft_poisson **out) {
     OFDFT_TRY(check_grid(grid, radius));
@@ -475,26 +501,21 @@ extern "C" int ofdft_poisson_create(const ofdft_grid *grid, int radius, int mode
         if (!s->mg) st = OFDFT_NO_MEMORY;
         else st = mg_create(*s->mg, *grid, 8, mode == OFDFT_MULTIGRID);
         if (st == OFDFT_OK && hipMalloc(&s->z, sizeof(double) * npoints(*grid)) != hipSuccess) {
+            (void)hipGetLastError();
+            s->z = nullptr;
             set_error("ofdft_poisson_create: out of device memory");
             st = OFDFT_NO_MEMORY;
         }
         // four ring slots, or two (the vectors there are anyway) where eight
-        // vectors are more than an eighth of the card's memory
+        // vectors are more than an eighth of the card's memory or the slots do not
+        // fit into what is free
         int dev = 0;
         size_t mem_total = 0;
         if (st == OFDFT_OK && (hipGetDevice(&dev) != hipSuccess || hipDeviceTotalMem(&mem_total, dev) != hipSuccess))
             st = OFDFT_HIP_ERROR;
-        const size_t bytes = sizeof(double) * npoints(*grid);
         s->mg_z[0] = s->z;
         s->mg_z[1] = s->pB;
-        if (st == OFDFT_OK && 8 * bytes <= mem_total / 8) {
-            s->mg_ring = 4;
-            if (hipMalloc(&s->mg_z[2], 2 * bytes) != hipSuccess) {
-                set_error("ofdft_poisson_create: out of device memory");
-                st = OFDFT_NO_MEMORY;
-            }
-            s->mg_z[3] = s->mg_z[2] + npoints(*grid);
-        }
+        if (st == OFDFT_OK && 8 * sizeof(double) * npoints(*grid) <= mem_total / 8) (void)poisson_extend(s);
     }
     if (st != OFDFT_OK) {
         poisson_free(s);
@@ -511,6 +532,23 @@ extern "C" int ofdft_poisson_destroy(ofdft_poisson *s) {
     delete s;
     return OFDFT_OK;
 }
+
+extern "C" int ofdft_poisson_set_compact(ofdft_poisson *s, int compact) {
+    if (!s || !s->mg || compact < 0 || compact > 1) {
+        set_error("ofdft_poisson_set_compact: multigrid solver and 0/1 expected");
+        return OFDFT_INVALID_ARG;
+    }
+    if (!compact) return s->mg_ring == 2 ? poisson_extend(s) : OFDFT_OK;
+    if (s->mg_ring > 2) {                       // no solve is under way: solves synchronise their stream
+        drop_mg_graph(s);
+        (void)hipFree(s->mg_z[2]);
+        s->mg_z[2] = s->mg_z[3] = nullptr;
+        s->mg_ring = 2;
+    }
+    return OFDFT_OK;
+}
+
+extern "C" int ofdft_poisson_compact(const ofdft_poisson *s) { return s && s->mg ? (s->mg_ring == 2 ? 1 : 0) : -1; }
 
 // Bounds of the FP32 inner tolerance of the refined form (defaults 1e-5, 1e-1).
 extern "C" int ofdft_poisson_set_refinement(ofdft_poisson *s, double inner_min, double inner_max) {
