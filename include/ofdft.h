@@ -134,7 +134,7 @@ int fd_gradient_apply(const ofdft_grid *grid, int radius, const double *x, doubl
  *         -L_h, so the iteration count does not grow with the grid.
  *         Two of its vectors only make the iterations cheaper; they are
  *         allocated where eight are at most an eighth of the card's memory
- *         and they fit into what is free (see ofdft_poisson_set_compact).
+ *         and a sixteenth of it stays free (see ofdft_poisson_set_compact).
  * cg_poisson_solve:
  *   rhs      device FP64 array g (not modified)
  *   x        device FP64 array: initial guess on entry (warm start), solution on
@@ -203,8 +203,8 @@ int ofdft_poisson_set_refinement(ofdft_poisson *s, double inner_min, double inne
  *   OFDFT_C128 or OFDFT_C64 (C64 runs COCG in complex64 inside complex128
  *   residual refinement).  Allocates all workspaces: four vectors per system,
  *   C64 three more, and two more per system that make the iterations cheaper
- *   where six of each are at most an eighth of the card's memory and fit into
- *   what is free.
+ *   where six of each are at most an eighth of the card's memory and a
+ *   sixteenth of it stays free.
  * ofdft_batch_set_compact: 1 gives those two back, 0 takes them (again); not
  *   while a solve runs.  Solutions are the same bit for bit.  INVALID_ARG or
  *   NO_MEMORY (stays compact).  ofdft_batch_compact: the present form (1 or 0;
@@ -268,9 +268,9 @@ int ofdft_batch_apply_preconditioner(ofdft_batch *b, int j, const double *kappa,
  * ofdft_multishift_create: one grid, radius 1..6, up to max_shifts (1..16)
  *   shifts per solve.  Allocates 4 + max(max_shifts - 1, 1) complex128 vectors
  *   of the grid and, where all then take at most an eighth of the card's memory
- *   and fit into what is free, six more (five with one shift) that make the
- *   iterations cheaper; and the solve's device scalars, so a context serves one
- *   solve at a time (solves on one context must not overlap on different
+ *   and a sixteenth of it stays free, six more (five with one shift) that make
+ *   the iterations cheaper; and the solve's device scalars, so a context serves
+ *   one solve at a time (solves on one context must not overlap on different
  *   streams).  INVALID_ARG or NO_MEMORY.
  * ofdft_multishift_set_compact: 1 gives the six vectors back, 0 takes them
  *   (again); not while a solve runs.  Solutions are the same bit for bit.
@@ -424,7 +424,9 @@ typedef struct ofdft_scf ofdft_scf;
  * when U(v) stopped above u_tol (u_max_iter reached, or no descent direction
  * left at FP64 precision) or a Poisson or shifted solve missed its tolerance
  * within max_iter; errors of any part are returned at once (create then
- * frees everything and leaves *out unset). */
+ * frees everything and leaves *out unset).  Create makes the solver contexts
+ * compact (see their set_compact) where less than a sixteenth of the card's
+ * memory would stay free. */
 int ofdft_scf_create(const ofdft_scf_params *p, const double *b, const double *u0,
                      ofdft_scf **out, void *stream);
 int ofdft_scf_destroy(ofdft_scf *s);

@@ -82,6 +82,15 @@ int check_grid(const ofdft_grid *g, int radius) {
     return OFDFT_OK;
 }
 
+bool optional_room(double all, double extra) {
+    size_t free_bytes = 0, total = 0;
+    if (hipMemGetInfo(&free_bytes, &total) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return all <= (double)total / 8 && extra + (double)total / 16 <= (double)free_bytes;
+}
+
 int redbuf_alloc(RedBuf &rb) {
     OFDFT_CHECK_HIP(hipMalloc(&rb.partials, sizeof(double) * kRedSlots * kRedMaxK));
     OFDFT_CHECK_HIP(hipMalloc(&rb.counter, sizeof(unsigned int) * kArriveWords));

@@ -53,6 +53,13 @@ Coef<float> to_float(const Coef<double> &c);
 
 int check_grid(const ofdft_grid *g, int radius);
 
+// Whether a context of `all` bytes takes `extra` of them that it can do without:
+// it is at most an eighth of the card's memory, and a sixteenth of the card
+// stays free for what is allocated afterwards (other contexts, and the scratch
+// that the runtime takes at a kernel's first launch, up to 1 GB, without which
+// the queue aborts).
+bool optional_room(double all, double extra);
+
 // Checkpoint files: device arrays written and read through a host staging
 // buffer (blocking copies).  Each returns OFDFT_OK, or an error with the
 // message set (INVALID_ARG for a short or failed file operation).

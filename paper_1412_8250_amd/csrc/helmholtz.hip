@@ -650,8 +650,7 @@ extern "C" int ofdft_batch_create(int nsys, const ofdft_grid *grids, int radius,
         }
     }
     int dev = 0, cus = 0;
-    size_t mem_total = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceTotalMem(&mem_total, dev) != hipSuccess ||
+    if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         return fail(OFDFT_HIP_ERROR);
     b->groups_cap = std::max(1, cus * 8);
@@ -668,11 +667,10 @@ extern "C" int ofdft_batch_create(int nsys, const ofdft_grid *grids, int radius,
     if (hipEventCreate(&b->ev0) != hipSuccess || hipEventCreate(&b->ev1) != hipSuccess)
         return fail(OFDFT_HIP_ERROR);
     // four ring slots, or two (no more memory than a schedule without the ring)
-    // where the vectors would then take more than an eighth of the card's memory
-    // or do not fit into what is free: the slots that can be done without come last
-    double bytes = 0.0;
-    for (int j = 0; j < nsys; ++j) bytes += (double)npoints(grids[j]) * e * (2 + kRingMax);
-    if (bytes <= (double)mem_total / 8) (void)batch_extend(b);
+    // where there is no room for them: those that can be done without come last
+    double vec = 0.0;
+    for (int j = 0; j < nsys; ++j) vec += (double)npoints(grids[j]) * e;
+    if (optional_room(vec * (2 + kRingMax), vec * (kRingMax - 2))) (void)batch_extend(b);
     *out = b;
     return OFDFT_OK;
 }

@@ -44,8 +44,8 @@
 // direction is the stencil phase's (no copy among the shifts').  The operations
 // per point are the same, so are the results, bit for bit; it holds six
 // vectors less and moves more (128 + 64 per shift but the seed + 48 B per point
-// and iteration).  Contexts are compact where the other form would take more
-// than an eighth of the card's memory, or does not fit into what is free.
+// and iteration).  Contexts are compact where the others are no option
+// (optional_room) or do not fit.
 #include <algorithm>
 #include <cmath>
 #include <new>
@@ -626,11 +626,8 @@ extern "C" int ofdft_multishift_create(const ofdft_grid *grid, int radius, int m
     if (hipEventCreate(&m->ev0) != hipSuccess || hipEventCreate(&m->ev1) != hipSuccess)
         return fail(OFDFT_HIP_ERROR);
     // the vectors that can be done without come last
-    int dev = 0;
-    size_t mem_total = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceTotalMem(&mem_total, dev) != hipSuccess)
-        return fail(OFDFT_HIP_ERROR);
-    if ((4 + m->p.size() + m->extras()) * vb <= mem_total / 8) (void)ms_extend(m);
+    const double extra = (double)m->extras() * vb;
+    if (optional_room((4.0 + m->p.size()) * vb + extra, extra)) (void)ms_extend(m);
     *out = m;
     return OFDFT_OK;
 }

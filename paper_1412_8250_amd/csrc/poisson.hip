@@ -506,16 +506,12 @@ extern "C" int ofdft_poisson_create(const ofdft_grid *grid, int radius, int mode
             set_error("ofdft_poisson_create: out of device memory");
             st = OFDFT_NO_MEMORY;
         }
-        // four ring slots, or two (the vectors there are anyway) where eight
-        // vectors are more than an eighth of the card's memory or the slots do not
-        // fit into what is free
-        int dev = 0;
-        size_t mem_total = 0;
-        if (st == OFDFT_OK && (hipGetDevice(&dev) != hipSuccess || hipDeviceTotalMem(&mem_total, dev) != hipSuccess))
-            st = OFDFT_HIP_ERROR;
+        // four ring slots, or two (the vectors there are anyway) where there is no
+        // room for them
         s->mg_z[0] = s->z;
         s->mg_z[1] = s->pB;
-        if (st == OFDFT_OK && 8 * sizeof(double) * npoints(*grid) <= mem_total / 8) (void)poisson_extend(s);
+        const double vec = sizeof(double) * (double)npoints(*grid);
+        if (st == OFDFT_OK && optional_room(8 * vec, 2 * vec)) (void)poisson_extend(s);
     }
     if (st != OFDFT_OK) {
         poisson_free(s);

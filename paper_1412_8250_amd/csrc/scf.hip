@@ -608,14 +608,9 @@ int potential_map(ofdft_scf *s, hipStream_t st, double &pois_res, int &pois_it, 
     return worst;
 }
 
-}  // namespace
-
-}  // namespace ofdft
-
-using namespace ofdft;
-
-extern "C" int ofdft_scf_create(const ofdft_scf_params *p, const double *b, const double *u0,
-                                ofdft_scf **out, void *stream) {
+// compact: the solvers' contexts without the vectors that only make them faster.
+int scf_create(const ofdft_scf_params *p, const double *b, const double *u0, ofdft_scf **out, void *stream,
+               bool compact) {
     if (!p || !b || !u0 || !out) {
         set_error("ofdft_scf_create: NULL argument");
         return OFDFT_INVALID_ARG;
@@ -715,10 +710,13 @@ extern "C" int ofdft_scf_create(const ofdft_scf_params *p, const double *b, cons
                 s->lr_groups[g].push_back(j);
                 gmax = std::max(gmax, (int)s->lr_groups[g].size());
             }
-            if ((rc = ofdft_multishift_create(&p->grid, p->radius, gmax, &s->ms))) return fail(rc);
+            if ((rc = ofdft_multishift_create(&p->grid, p->radius, gmax, &s->ms)) ||
+                (compact && (rc = ofdft_multishift_set_compact(s->ms, 1))))
+                return fail(rc);
         }
         if ((rc = ofdft_batch_create(kLrRound, grids, p->radius,
-                                     p->helmholtz_dtype == OFDFT_C64 ? OFDFT_C64 : OFDFT_C128, &s->batch)))
+                                     p->helmholtz_dtype == OFDFT_C64 ? OFDFT_C64 : OFDFT_C128, &s->batch)) ||
+            (compact && (rc = ofdft_batch_set_compact(s->batch, 1))))
             return fail(rc);
         if (p->helmholtz_precond != OFDFT_PRECOND_NONE &&
             (rc = ofdft_batch_set_preconditioner(s->batch, p->helmholtz_precond)))
@@ -739,10 +737,12 @@ extern "C" int ofdft_scf_create(const ofdft_scf_params *p, const double *b, cons
         }
         ofdft_grid grids[4];
         for (int q = 0; q < 4; ++q) grids[q] = p->grid;
-        if (p->helmholtz_multishift && (rc = ofdft_multishift_create(&p->grid, p->radius, 2, &s->ms)))
+        if (p->helmholtz_multishift && ((rc = ofdft_multishift_create(&p->grid, p->radius, 2, &s->ms)) ||
+                                        (compact && (rc = ofdft_multishift_set_compact(s->ms, 1)))))
             return fail(rc);
         if ((rc = ofdft_batch_create(4, grids, p->radius,
-                                     p->helmholtz_dtype == OFDFT_C64 ? OFDFT_C64 : OFDFT_C128, &s->batch)))
+                                     p->helmholtz_dtype == OFDFT_C64 ? OFDFT_C64 : OFDFT_C128, &s->batch)) ||
+            (compact && (rc = ofdft_batch_set_compact(s->batch, 1))))
             return fail(rc);
         if (p->helmholtz_precond != OFDFT_PRECOND_NONE &&
             (rc = ofdft_batch_set_preconditioner(s->batch, p->helmholtz_precond)))
@@ -754,8 +754,16 @@ extern "C" int ofdft_scf_create(const ofdft_scf_params *p, const double *b, cons
                        p->poisson_mode == OFDFT_MULTIGRID_F64)
                           ? p->poisson_mode
                           : OFDFT_PLAIN_F64;
-    if ((rc = ofdft_poisson_create(&p->grid, p->radius, pmode, &s->pois))) return fail(rc);
+    if ((rc = ofdft_poisson_create(&p->grid, p->radius, pmode, &s->pois)) ||
+        (compact && s->pois->mg && (rc = ofdft_poisson_set_compact(s->pois, 1))))
+        return fail(rc);
     if ((rc = ofdft_anderson_create(s->n, p->history, p->zeta, &s->mix))) return fail(rc);
+    // what the solvers took and can do without goes back if little else is left
+    if (!optional_room(0.0, 0.0) &&
+        ((s->ms && (rc = ofdft_multishift_set_compact(s->ms, 1))) ||
+         (s->batch && (rc = ofdft_batch_set_compact(s->batch, 1))) ||
+         (s->pois->mg && (rc = ofdft_poisson_set_compact(s->pois, 1)))))
+        return fail(rc);
     if (hipMemcpyAsync(s->b, b, b8, hipMemcpyDeviceToDevice, st) != hipSuccess ||
         hipMemcpyAsync(s->u, u0, b8, hipMemcpyDeviceToDevice, st) != hipSuccess ||
         hipMemsetAsync(s->phi, 0, b8, st) != hipSuccess || hipMemsetAsync(s->vlr, 0, b8, st) != hipSuccess ||
@@ -798,6 +806,23 @@ extern "C" int ofdft_scf_create(const ofdft_scf_params *p, const double *b, cons
     if (hipStreamSynchronize(st) != hipSuccess) return fail(OFDFT_HIP_ERROR);
     *out = s;
     return mst;         // NOT_CONVERGED if a solve of v_0 missed its tolerance
+}
+
+}  // namespace
+
+}  // namespace ofdft
+
+using namespace ofdft;
+
+extern "C" int ofdft_scf_create(const ofdft_scf_params *p, const double *b, const double *u0,
+                                ofdft_scf **out, void *stream) {
+    const int st = scf_create(p, b, u0, out, stream, false);
+    // where a later part of the context lacks what an earlier one took, all do
+    // without the vectors that only make them faster
+    const bool full = st == OFDFT_NO_MEMORY || (st == OFDFT_HIP_ERROR && hipPeekAtLastError() == hipErrorOutOfMemory);
+    if (!full) return st;
+    (void)hipGetLastError();
+    return scf_create(p, b, u0, out, stream, true);
 }
 
 extern "C" int ofdft_scf_destroy(ofdft_scf *s) {

@@ -78,7 +78,7 @@ def test_same_solutions(precond, timed):
 def test_two_slots_where_four_do_not_fit():
     """A system holds 4 vectors at least and 6 with four slots; 5 are free."""
     torch = torch_cuda()
-    shape, vec = (320, 400, 500), 16 * 320 * 400 * 500
+    shape, vec = (512, 512, 512), 16 * 512 ** 3
     announce("batch compact by memory", shape)
     f = torch.ones(shape, dtype=torch.complex128, device="cuda")
     x = torch.zeros_like(f)
@@ -99,14 +99,15 @@ def test_two_slots_where_four_do_not_fit():
 def test_preconditioner_takes_the_room_of_two_slots():
     """The batch holds 6 vectors with four slots and 4 with two, z and the levels
     (complex64: 16 B per point and 24 on an eighth of it, and so on) 2.2 more:
-    with 6.7 free the preconditioner fits only beside two slots."""
+    with 7.2 free the preconditioner fits only beside two slots."""
     torch = torch_cuda()
-    shape, vec = (384, 384, 384), 16 * 384 ** 3
+    shape, vec = (512, 512, 512), 16 * 512 ** 3
     announce("batch preconditioner by memory", shape)
     f = torch.ones(shape, dtype=torch.complex128, device="cuda")
     x = torch.zeros_like(f)
-    with free_bytes(int(6.7 * vec)):
+    with free_bytes(int(7.2 * vec)):
         b = ofd.HelmholtzBatch([shape], [(0.4,) * 3])
+        b.compact = False
         assert not b.compact
         b.set_preconditioner(ofd.PRECOND_MULTIGRID)
         assert b.compact
@@ -114,3 +115,16 @@ def test_preconditioner_takes_the_room_of_two_slots():
     b.close()
     x -= 1.0 / (40.0 + 3.0j)
     assert float(torch.view_as_real(x).abs().max()) <= 1e-10 / 40.0
+
+
+def test_room_for_others_stays_free():
+    """Four slots would leave less than a sixteenth of the card free."""
+    torch = torch_cuda()
+    total = torch.cuda.mem_get_info()[1]
+    shape, vec = (256, 256, 256), 16 * 256 ** 3
+    announce("batch leaves room", shape)
+    for free, compact in ((total // 16 + 5 * vec, True), (total // 16 + 7 * vec, False)):
+        with free_bytes(free):
+            b = ofd.HelmholtzBatch([shape], [(0.4,) * 3])
+            assert b.compact == compact
+            b.close()
