@@ -554,8 +554,6 @@ def main():
         # re-running the stencil tuner reports what it chose (same table entries)
         tuned = {fam: ofd.tune_stencil(shape, h, ofd.F64, code, reps=5)
                  for fam, code in (("pass_f64", ofd.TUNE_PASS), ("apply_f64", ofd.TUNE_APPLY))}
-        for v in tuned.values():
-            v["shape_name"] = ofd.SHAPE_NAMES[v["shape"]]
         log("autotuned launch configuration:", tuned)
 
     # Every step (warm-up and timed) is the first fixed-point step from the same
@@ -642,13 +640,11 @@ def main():
             at = {}
             for name, code in (("f32", ofd.F32), ("c128", ofd.C128)):
                 r = ofd.tune_stencil(shape, h, code, ofd.TUNE_APPLY, reps=5)
-                r["shape_name"] = ofd.SHAPE_NAMES[r["shape"]]
                 at[f"apply_{name}_320"] = r
             for n in (24, 48, 64, 96, 112, 192):
                 hh = (0.4,) * 3
                 for fam, code in (("apply", ofd.TUNE_APPLY), ("pass", ofd.TUNE_PASS)):
                     r = ofd.tune_stencil((n, n, n), hh, ofd.F64, code, reps=5)
-                    r["shape_name"] = ofd.SHAPE_NAMES[r["shape"]]
                     at[f"{fam}_f64_{n}"] = r
             extras["autotune_grids"] = at
         if not args.no_autotune:

@@ -644,8 +644,10 @@ int ofdft_stencil_set_config(int nx, int ny, int nz, int elem_bytes, int shape, 
  *   OFDFT_TUNE_PASS: the fused single-pass stencil kernels (CG, residual and
  *   density-update passes), timed on the CG stencil pass, dtype F64 or F32.
  *   The untuned configuration is a candidate and is kept unless another is
- *   more than 2% faster.  Synchronises the stream.  INVALID_ARG, NO_MEMORY,
- *   HIP_ERROR.
+ *   more than 2% faster; where it is the brick kernel (grids that stay in the
+ *   caches) the family then has no entry, and a shape set by hand for every
+ *   family remains for the other one.  Synchronises the stream.  INVALID_ARG,
+ *   NO_MEMORY, HIP_ERROR.
  * ofdft_batch_tune: times `iters` COCG iterations of the batch's systems
  *   (kappa, rhs as for cg_helmholtz_solve_batched; x = starting guesses, read
  *   only: the runs use copies) for each stepped-schedule tile shape and
@@ -653,8 +655,11 @@ int ofdft_stencil_set_config(int nx, int ny, int nz, int elem_bytes, int shape, 
  *   persistent schedule with 16 and 64 workgroups per group; sets the
  *   fastest as the batch's configuration.
  * out (optional): shape id, zlen (z-chunk length; for a batch the z-chunk
- *   target, planes), group (batch: persistent group size, 0 = stepped),
- *   candidates timed, best_ms and default_ms (per launch; per solve of
+ *   target, planes), group (batch: persistent group size, 0 = stepped; else
+ *   the planes of a brick, 1 or 4, where the brick kernel stays, and 0 where a
+ *   tile of the march runs: with bricks, shape and zlen are what the march
+ *   would run untuned; a batch whose untuned configuration stays runs the grids
+ *   that take bricks on them, the others as shape and zlen say), candidates timed, best_ms and default_ms (per launch; per solve of
  *   `iters` iterations for a batch) of the choice and of the untuned
  *   configuration.
  * ofdft_tune_save / ofdft_tune_load: the launch table as text (one entry per

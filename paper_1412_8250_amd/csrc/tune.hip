@@ -10,9 +10,11 @@
 //     the residual and density-update passes share its entry (FP64, FP32).
 // The configuration the library would use untuned is always a candidate and
 // keeps its place unless another one is more than 2% faster, so noise does
-// not flip the choice (where that is the brick kernel, the grid is left without
-// an entry and the tile heuristic's shape is reported).  All candidates compute the same operator (the tests
-// check every shape against the oracle); only the reduction order of the
+// not flip the choice.  Where that is the brick kernel, which is no table entry,
+// the family is left without one, also where a hand-set shape stood for every
+// family (the others then keep that shape as their own), and the result names
+// the bricks by their planes.  All candidates compute the same operator (the
+// tests check every shape against the oracle); only the reduction order of the
 // fused passes changes with the tiling.
 #include <algorithm>
 #include <vector>
@@ -148,14 +150,13 @@ extern "C" int ofdft_tune_stencil(const ofdft_grid *grid, int radius, ofdft_dtyp
     double best = -1.0, def_ms = -1.0;
     Candidate pick{def.shape, def.zlen};
     int rc = OFDFT_OK;
-    // on small grids the untuned library runs the brick kernel, which is no
-    // table entry: it is timed with the grid's entry erased (shape < 0)
+    // on small grids the untuned library runs the brick kernel: an entry while it
+    // is timed, so that no hand-set one stands in its way
     StencilCfg bk;
     const bool brick = brick_stencil(g, eb, family == FAMILY_PASS ? 2 : 1, bk);
-    if (brick) cand.push_back({-1, 0});
+    if (brick) cand.push_back({bk.shape, bk.zlen});
     for (const Candidate &k : cand) {
-        if (k.shape < 0) erase_stencil_cfg(g, eb, family);
-        else record_stencil_cfg(g, eb, family, StencilCfg{k.shape, k.zlen});
+        record_stencil_cfg(g, eb, family, StencilCfg{k.shape, k.zlen});
         if ((rc = launch()) != OFDFT_OK) break;                        // warm-up
         if (hipEventRecord(e0, s) != hipSuccess) { rc = OFDFT_HIP_ERROR; break; }
         for (int r = 0; r < reps && rc == OFDFT_OK; ++r) rc = launch();
@@ -167,8 +168,9 @@ extern "C" int ofdft_tune_stencil(const ofdft_grid *grid, int radius, ofdft_dtyp
             break;
         }
         const double t = ms / reps;
-        if (brick ? k.shape < 0 : k.shape == def.shape && k.zlen == def.zlen) def_ms = t;
-        if (k.shape < 0) continue;                                     // wins below or not at all
+        const bool is_brick = k.shape == SHAPE_BRICK;
+        if (brick ? is_brick : k.shape == def.shape && k.zlen == def.zlen) def_ms = t;
+        if (is_brick) continue;                                        // wins below or not at all
         if (best < 0.0 || t < best) {
             best = t;
             pick = k;
@@ -181,20 +183,20 @@ extern "C" int ofdft_tune_stencil(const ofdft_grid *grid, int radius, ofdft_dtyp
         return rc;
     }
     // the untuned configuration stays unless beaten by more than 2%
+    bool bricks = false;
     if (def_ms > 0.0 && best > 0.98 * def_ms) {
         pick = Candidate{def.shape, def.zlen};
         best = def_ms;
-        if (brick) erase_stencil_cfg(g, eb, family);
-        else record_stencil_cfg(g, eb, family, StencilCfg{pick.shape, pick.zlen});
-    } else {
-        record_stencil_cfg(g, eb, family, StencilCfg{pick.shape, pick.zlen});
+        bricks = brick;
     }
+    if (bricks) untune_stencil_cfg(g, eb, family);
+    else record_stencil_cfg(g, eb, family, StencilCfg{pick.shape, pick.zlen});
     OFDFT_CHECK_HIP(hipStreamSynchronize(s));
     if (out) {
         *out = ofdft_tune_result{};
         out->shape = pick.shape;
         out->zlen = pick.zlen;
-        out->group = 0;
+        out->group = bricks ? bk.zlen : 0;
         out->candidates = (int)cand.size();
         out->best_ms = best;
         out->default_ms = def_ms;

@@ -111,6 +111,18 @@ void erase_stencil_cfg(const ofdft_grid &g, int elem_bytes, int family) {
     g_table.erase(std::make_tuple(g.nx, g.ny, g.nz, elem_bytes, family));
 }
 
+void untune_stencil_cfg(const ofdft_grid &g, int elem_bytes, int family) {
+    std::lock_guard<std::mutex> lk(g_mu);
+    auto key = [&](int f) { return std::make_tuple(g.nx, g.ny, g.nz, elem_bytes, f); };
+    g_table.erase(key(family));
+    const auto all = g_table.find(key(FAMILY_ALL));
+    if (all == g_table.end()) return;
+    const StencilCfg c = all->second;
+    for (int f = 0; f < FAMILY_COUNT; ++f)
+        if (f != family) g_table.emplace(key(f), c);      // keeps an entry that is there
+    g_table.erase(key(FAMILY_ALL));
+}
+
 // Text form of the table, one entry per line: family nx ny nz bytes shape zlen.
 int table_save(const char *path) {
     std::lock_guard<std::mutex> lk(g_mu);
@@ -122,6 +134,7 @@ int table_save(const char *path) {
     std::fprintf(f, "# ofdft stencil launch table: family nx ny nz elem_bytes shape zlen\n");
     for (const auto &kv : g_table) {
         const auto &k = kv.first;
+        if (kv.second.shape >= SHAPE_COUNT) continue;     // being timed
         std::fprintf(f, "%d %d %d %d %d %d %d\n", std::get<4>(k), std::get<0>(k), std::get<1>(k), std::get<2>(k),
                      std::get<3>(k), kv.second.shape, kv.second.zlen);
     }

@@ -2,8 +2,9 @@
 // size, element bytes, kernel family) is consulted first; its entries are
 // written by the library's autotuner (ofdft_tune_stencil, which times every
 // legal shape and z-chunk length of a family on the grid) or set by hand
-// (ofdft_stencil_set_config, for every family at once); without an entry a
-// fixed heuristic measured at 320^3 decides.
+// (ofdft_stencil_set_config, for every family at once); without an entry grids
+// that stay in the caches run the brick kernel (brick_stencil) and larger ones
+// the march with the tile of a heuristic measured at 320^3 (default_stencil_cfg).
 #pragma once
 
 #include "common.hpp"
@@ -21,7 +22,8 @@ enum StencilShape {
                          // (fused kernels given this id run 64 x 8 x 2)
     SHAPE_COUNT = 6,
     SHAPE_BRICK = SHAPE_COUNT    // no marched tile: the brick kernel (chosen by pick_stencil_cfg on
-                                 // small grids without a table entry; never an entry itself)
+                                 // small grids without a table entry; an entry itself only while
+                                 // the tuner times it)
 };
 
 template <int TX_, int TYT_, int RY_>
@@ -75,6 +77,9 @@ bool brick_stencil(const ofdft_grid &g, int elem_bytes, int arrays, StencilCfg &
 StencilCfg default_stencil_cfg(const ofdft_grid &g, int elem_bytes, int family);
 void record_stencil_cfg(const ofdft_grid &g, int elem_bytes, int family, StencilCfg c);
 void erase_stencil_cfg(const ofdft_grid &g, int elem_bytes, int family);
+// The family runs untuned: without an entry of its own, and a hand-set one of
+// every family becomes the other families' own.
+void untune_stencil_cfg(const ofdft_grid &g, int elem_bytes, int family);
 int zlen_for_blocks(const ofdft_grid &g, int shape, int target_blocks);
 // z-chunk length minimising (waves of workgroups) x (chunk planes + warm-up)
 // for `resident` workgroups in flight; tiles of tx x ty points.
