@@ -26,20 +26,6 @@ MgDims dims_of(const MgLevel &L, double2 kappa) {
     return MgDims{L.nx, L.ny, L.nz, L.cx, L.cy, L.cz, 2.0 * (L.cx + L.cy + L.cz), kappa.x, kappa.y, L.n};
 }
 
-// Launch geometry of the two cycle kernels of a level: a workgroup owns a
-// W x H tile of (x, y) (both even) and marches along z over zl planes (even);
-// tiles in x, y and z of one system, the systems of a launch one after
-// another.
-struct MgTile {
-    int W, H, zl;
-    int tx, ty, tz;
-    __host__ __device__ int blocks() const { return tx * ty * tz; }
-};
-
-// z chunks of four planes times systems of a launch: the limit mg_create
-// keeps on systems per hierarchy.
-inline int mg_zch(int nz) { return (nz + 3) / 4; }
-
 // Element types: the cycle's input f and output z are FP64 (real or complex);
 // the levels' arrays are stored, and their arithmetic done, in S (FP64 or
 // FP32, real or complex).  R is S's real type, C the complex scalar of that
@@ -682,11 +668,12 @@ constexpr int kMgCaps[4] = {256, 512, 1024, 2048};
 // small workgroups.  Measured at 320^3 (down / up, us): 2048 columns 148 / 140,
 // 1024 columns 150 / 174, 512 200 / 168, 256 225 / 217; at 96^3 2048 columns
 // 13 / 12, 256 columns 12 / 10; at 24^3 9 / 10 and 6 / 6.
-MgTile mg_pick_tile(const MgLevel &L, int count, size_t elem, int halo, int warm, int bufs, int &cap) {
+MgPick mg_pick_tile(const MgLevel &L, int count, size_t elem, int halo, int warm, int bufs) {
     constexpr double kStep = 0.55, kCol = 0.0008;     // us; kCol per column of 4 bytes
-    MgTile best{};
+    MgPick best;
     double best_cost = -1.0;
-    cap = kMgCaps[0];
+    best.cap = kMgCaps[0];
+    best.count = count;
     for (int cols : kMgCaps) {
         const size_t lds = elem * cols * bufs;
         if (lds > 100 * 1024 || (elem == 16 && cols > 1024)) break;    // complex128: registers
@@ -711,8 +698,8 @@ MgTile mg_pick_tile(const MgLevel &L, int count, size_t elem, int halo, int warm
                 const double cost = waves * (zl + warm) * step;
                 if (best_cost < 0.0 || cost < best_cost) {
                     best_cost = cost;
-                    best = MgTile{W, H, zl, tx, ty, tz};
-                    cap = cols;
+                    best.t = MgTile{W, H, zl, tx, ty, tz};
+                    best.cap = cols;
                 }
                 if (zl <= 4) break;
             }
@@ -725,14 +712,19 @@ MgTile mg_pick_tile(const MgLevel &L, int count, size_t elem, int halo, int warm
 // four shifted systems on a grid (the density functional's batches), one real one.
 constexpr int mg_dot_systems(size_t elem) { return elem == 16 ? 4 : 1; }
 
+MgPick mg_pick_down(const MgLevel &L, int count, size_t elem) { return mg_pick_tile(L, count, elem, 5, 5, 6); }
+MgPick mg_pick_up(const MgLevel &L, int count, size_t elem) { return mg_pick_tile(L, count, elem, 4, 4, 4); }
+
 template <typename TF, typename S>
 int launch_down(const MgLevel &L, const MgLevel &C, int count, double2 kappa, double omega, MgArr<const TF> f,
                 MgArr<S> u, MgArr<S> fl, MgArr<S> cf, MgShift sh, hipStream_t s) {
-    int cap;
-    const MgTile t = mg_pick_tile(L, count, sizeof(S), 5, 5, 6, cap);
+    const MgPick pick = L.down[0].count == count   ? L.down[0]
+                        : L.down[1].count == count ? L.down[1]
+                                                   : mg_pick_down(L, count, sizeof(S));
+    const MgTile t = pick.t;
     const MgDims d = dims_of(L, kappa), cd = dims_of(C, kappa);
     const dim3 grid(t.blocks() * count);
-    switch (cap) {
+    switch (pick.cap) {
         case 256: hipLaunchKernelGGL((mg_down<TF, S, 256, 1>), grid, dim3(256), 0, s, d, cd, t, omega, f, u, fl, cf, sh); break;
         case 512: hipLaunchKernelGGL((mg_down<TF, S, 256, 2>), grid, dim3(256), 0, s, d, cd, t, omega, f, u, fl, cf, sh); break;
         case 1024: hipLaunchKernelGGL((mg_down<TF, S, 512, 2>), grid, dim3(512), 0, s, d, cd, t, omega, f, u, fl, cf, sh); break;
@@ -747,14 +739,16 @@ int launch_down(const MgLevel &L, const MgLevel &C, int count, double2 kappa, do
 template <class Dot, typename TF, typename S, typename TO>
 int launch_up(const MgLevel &L, const MgLevel &C, int count, double2 kappa, double omega, MgArr<const TF> f,
               MgArr<const S> u, MgArr<const S> cu, MgArr<TO> z, MgShift sh, MgDot<Dot> dot, hipStream_t s) {
-    int cap;
     // a system's products are summed in an order of its own, whatever it shares the launch with
-    const int pick = Dot::kSums ? mg_dot_systems(sizeof(TO)) : count;
-    const MgTile t = mg_pick_tile(L, pick, sizeof(S), 4, 4, 4, cap);
+    const MgPick pick = Dot::kSums               ? L.dot
+                        : L.up[0].count == count ? L.up[0]
+                        : L.up[1].count == count ? L.up[1]
+                                                 : mg_pick_up(L, count, sizeof(S));
+    const MgTile t = pick.t;
     if (Dot::kSums && t.blocks() > dot.cap) return OFDFT_INVALID_ARG;     // sized by mg_create
     const MgDims d = dims_of(L, kappa), cd = dims_of(C, kappa);
     const dim3 grid(t.blocks() * count);
-    switch (cap) {
+    switch (pick.cap) {
         case 256: hipLaunchKernelGGL((mg_up<TF, S, TO, 256, 1, Dot>), grid, dim3(256), 0, s, d, cd, t, omega, f, u, cu, z, sh, dot); break;
         case 512: hipLaunchKernelGGL((mg_up<TF, S, TO, 256, 2, Dot>), grid, dim3(256), 0, s, d, cd, t, omega, f, u, cu, z, sh, dot); break;
         case 1024: hipLaunchKernelGGL((mg_up<TF, S, TO, 512, 2, Dot>), grid, dim3(512), 0, s, d, cd, t, omega, f, u, cu, z, sh, dot); break;
@@ -829,11 +823,13 @@ int vcycle(Multigrid &mg, int q0, int count, MgArr<const TIO> f, MgArr<TIO> z, d
 int mg_create(Multigrid &mg, const ofdft_grid &g, int elem_bytes, bool fp32, int groups) {
     mg_free(mg);
     if ((elem_bytes != 8 && elem_bytes != 16) || groups < 1) return OFDFT_INVALID_ARG;
-    if ((int64_t)mg_zch(g.nz) * groups > 65535) {     // grid z = systems x z chunks
+    // no limits of these launches (which are one-dimensional): what is refused and
+    // accepted here has been part of the interface since they had three dimensions
+    if (((int64_t)g.nz + 3) / 4 * groups > 65535) {
         set_error("multigrid: %d systems of %d planes exceed one launch", groups, g.nz);
         return OFDFT_INVALID_ARG;
     }
-    if (g.nz > 65535) {             // one z plane per grid row of the launches
+    if (g.nz > 65535) {
         set_error("multigrid: nz = %d exceeds 65535", g.nz);
         return OFDFT_INVALID_ARG;
     }
@@ -891,9 +887,16 @@ int mg_create(Multigrid &mg, const ofdft_grid &g, int elem_bytes, bool fp32, int
             *own[k] = p;
         }
     }
+    for (int l = 0; l + 1 < nlev; ++l) {
+        MgLevel &M = mg.lv[l];
+        for (int k = 0; k < (groups > 1 ? 2 : 1); ++k) {
+            M.down[k] = mg_pick_down(M, k ? groups : 1, es);
+            M.up[k] = mg_pick_up(M, k ? groups : 1, es);
+        }
+    }
     if (nlev > 1) {              // reductions of the products in level 0's last kernel
-        int cap;
-        mg.dot_cap = mg_pick_tile(mg.lv[0], mg_dot_systems((size_t)elem_bytes), es, 4, 4, 4, cap).blocks();
+        mg.lv[0].dot = mg_pick_up(mg.lv[0], mg_dot_systems((size_t)elem_bytes), es);
+        mg.dot_cap = mg.lv[0].dot.t.blocks();
         const size_t bp = sizeof(double) * Multigrid::kDotSums * (size_t)mg.dot_cap * groups, bc = sizeof(unsigned int) * kArriveWords * (size_t)groups;
         void *p = nullptr;
         if (hipMalloc(&p, bp + bc) != hipSuccess) {

@@ -20,11 +20,32 @@ namespace ofdft {
 
 struct StepRho;
 
+// Launch geometry of the two cycle kernels of a level: a workgroup owns a
+// W x H tile of (x, y) (both even) and marches along z over zl planes (even);
+// tiles in x, y and z of one system, the systems of a launch one after
+// another.
+struct MgTile {
+    int W, H, zl;
+    int tx, ty, tz;
+    __host__ __device__ int blocks() const { return tx * ty * tz; }
+};
+
+// The tile picked for launches of `count` systems and its column capacity.
+struct MgPick {
+    MgTile t{};
+    int cap = 0, count = 0;
+};
+
 struct MgLevel {
     int nx = 0, ny = 0, nz = 0;
     double cx = 0, cy = 0, cz = 0;   // 1 / h_a^2
     int64_t n = 0;
     void *u = nullptr, *t = nullptr, *f = nullptr;   // element type of the levels
+    // tiles of launches of one system and of all of the hierarchy's (searched in
+    // every launch that is not replayed they cost the host 65 us a cycle at 512^3:
+    // 100 where it is 35)
+    MgPick down[2], up[2];
+    MgPick dot;                      // the upward kernel that forms products
 };
 
 struct Multigrid {
