@@ -9,7 +9,9 @@
 // of p carry a 6-wide periodic halo in x, so x neighbours are constant offsets,
 // y offsets are computed once per solve, and z values are read once per column.
 // Measured at 16^3, FP64, to 1e-10: 0.92 ms with two launches per iteration,
-// 0.48 so (5.4 us per iteration).
+// 0.48 so (5.4 us per iteration).  A launch runs kTinyIters iterations at most
+// and p is kept for the next, so that no solve, also one whose tolerance cannot
+// be met, holds the stream for longer than some milliseconds.
 #pragma once
 
 #include "cg.hpp"
@@ -19,6 +21,7 @@ namespace ofdft {
 constexpr int kTinyThreads = 1024;
 constexpr int kTinyMinAxis = 6;          // one periodic wrap per offset
 constexpr size_t kTinyLds = 140 * 1024;
+constexpr int kTinyIters = 512;          // per launch: 3 ms at 16^3, 5 ms at most
 
 // Planes per thread (4 or 8) if the grid fits one workgroup, else 0.
 inline int tiny_planes(const ofdft_grid &g, size_t elem) {
@@ -44,7 +47,8 @@ __device__ inline double tiny_sum(double x, double *scratch) {
 
 template <typename T, int KZ>
 __global__ void __launch_bounds__(kTinyThreads)
-cg_tiny_kernel(int nx, int ny, int nz, Coef<typename VT<T>::S> w, T *__restrict__ x, T *__restrict__ r, CgState *st) {
+cg_tiny_kernel(int nx, int ny, int nz, Coef<typename VT<T>::S> w, T *__restrict__ x, T *__restrict__ r,
+               T *__restrict__ pkeep, CgState *st) {
     using S = typename VT<T>::S;
     constexpr int R = kMaxRadius;
     extern __shared__ __align__(16) unsigned char tiny_lds[];
@@ -74,11 +78,11 @@ cg_tiny_kernel(int nx, int ny, int nz, Coef<typename VT<T>::S> w, T *__restrict_
         const int64_t i = (int64_t)(z0 + k) * nxy + col;
         xv[k] = own ? x[i] : T(0);
         rv[k] = own ? r[i] : T(0);
-        pv[k] = T(0);
+        pv[k] = own && !s.first ? pkeep[i] : T(0);
         av[k] = T(0);
     }
-    S beta = S(0);
-    while (s.done == CG_RUNNING) {
+    S beta = (S)s.beta;
+    for (int left = kTinyIters; s.done == CG_RUNNING && left > 0; --left) {
         // p = r + beta p_old (first iteration: p = r)
 #pragma unroll
         for (int k = 0; k < KZ; ++k)
@@ -152,18 +156,19 @@ cg_tiny_kernel(int nx, int ny, int nz, Coef<typename VT<T>::S> w, T *__restrict_
             const int64_t i = (int64_t)(z0 + k) * nxy + col;
             x[i] = xv[k];
             r[i] = rv[k];
+            pkeep[i] = pv[k];
         }
     if (threadIdx.x == 0) *st = s;
 }
 
 template <typename T>
-inline int launch_cg_tiny(const ofdft_grid &g, int kz, const Coef<typename VT<T>::S> &c, T *x, T *r, CgState *st,
-                          hipStream_t s) {
+inline int launch_cg_tiny(const ofdft_grid &g, int kz, const Coef<typename VT<T>::S> &c, T *x, T *r, T *p,
+                          CgState *st, hipStream_t s) {
     const size_t lds = (size_t)(g.nx + 2 * kMaxRadius) * g.ny * g.nz * sizeof(T);
     if (kz == 4)
-        hipLaunchKernelGGL((cg_tiny_kernel<T, 4>), dim3(1), dim3(kTinyThreads), lds, s, g.nx, g.ny, g.nz, c, x, r, st);
+        hipLaunchKernelGGL((cg_tiny_kernel<T, 4>), dim3(1), dim3(kTinyThreads), lds, s, g.nx, g.ny, g.nz, c, x, r, p, st);
     else
-        hipLaunchKernelGGL((cg_tiny_kernel<T, 8>), dim3(1), dim3(kTinyThreads), lds, s, g.nx, g.ny, g.nz, c, x, r, st);
+        hipLaunchKernelGGL((cg_tiny_kernel<T, 8>), dim3(1), dim3(kTinyThreads), lds, s, g.nx, g.ny, g.nz, c, x, r, p, st);
     OFDFT_CHECK_HIP(hipGetLastError());
     return OFDFT_OK;
 }

@@ -209,14 +209,16 @@ template <typename T>
 int cg_iterate(const ofdft_grid &g, const Coef<typename VT<T>::S> &c, T *x, T *r, T *pA, T *pB,
                T *Ap, CgState *st, CgState *st_host, const RedBuf &rb, hipStream_t s, int &iters,
                int &done, CgGraph *graph) {
-    // a grid of one workgroup: every iteration in one launch
+    // a grid of one workgroup: many iterations in one launch
     if (const int kz = tiny_planes(g, sizeof(T))) {
-        {
-            ProfScope ps(K_CG_STENCIL, 0.0, s);
-            OFDFT_TRY(launch_cg_tiny<T>(g, kz, c, x, r, st, s));
-        }
-        OFDFT_CHECK_HIP(hipMemcpyAsync(st_host, st, sizeof(CgState), hipMemcpyDeviceToHost, s));
-        OFDFT_CHECK_HIP(hipStreamSynchronize(s));
+        do {
+            {
+                ProfScope ps(K_CG_STENCIL, 0.0, s);
+                OFDFT_TRY(launch_cg_tiny<T>(g, kz, c, x, r, pA, st, s));
+            }
+            OFDFT_CHECK_HIP(hipMemcpyAsync(st_host, st, sizeof(CgState), hipMemcpyDeviceToHost, s));
+            OFDFT_CHECK_HIP(hipStreamSynchronize(s));
+        } while (st_host->done == CG_RUNNING);
         iters = st_host->iter;
         done = st_host->done;
         prof_add(K_CG_STENCIL, (double)npoints(g) * sizeof(T) * 10 * iters, 0);
