@@ -439,7 +439,7 @@ int residual_c128(ofdft_batch *b, int j, const double2 *f, const double2 *x, dou
     const ofdft_grid &g = b->grids[j];
     const Coef<double> c = make_coef(g, b->radius);
     StencilCfg bk;
-    if (brick_stencil(g, sizeof(double2), 1, bk)) {
+    if (brick_system(g, sizeof(double2), bk)) {
         ProfScope ps(K_RESIDUAL, (double)npoints(g) * (r ? 48 : 32), s);
         return launch_stencil_brick<double2, 4>(
             g, c, LoadPlain<double2>{x},
@@ -578,7 +578,7 @@ int upload_systems(ofdft_batch *b, const double *kappa, const std::vector<const 
         // untuned stepped batches run small grids on bricks, system by system
         // (so a system's reduction order does not depend on the others)
         StencilCfg bk;
-        h.brick = stepped && b->shape < 0 && brick_stencil(g, c64 ? 8 : 16, 1, bk) ? 1 : 0;
+        h.brick = stepped && b->shape < 0 && brick_system(g, c64 ? 8 : 16, bk) ? 1 : 0;
         if (h.brick) h.bg = make_brick_geom(g, 4);
         h.nunits = h.brick ? h.bg.nblocks : h.tg.nblocks;
         h.n = npoints(g);
@@ -754,7 +754,7 @@ extern "C" int ofdft_batch_tune(ofdft_batch *b, const double *kappa, const void 
     // untuned: bricks for the grids that take them (shape -1), else the default tile
     StencilCfg bk;
     const bool brick = std::any_of(b->grids.begin(), b->grids.end(),
-                                   [&](const ofdft_grid &g) { return brick_stencil(g, c64 ? 8 : 16, 1, bk); });
+                                   [&](const ofdft_grid &g) { return brick_system(g, c64 ? 8 : 16, bk); });
     const Cand def{brick ? -1 : default_shape(b), 0, kStepPlanes};
     std::vector<Cand> cand;
     if (brick) cand.push_back(def);

@@ -66,6 +66,11 @@ constexpr int kMsPoll = 8;          // iterations between status reads
 // others beside the 128); eight would save 32 more and keep four more
 // residuals.
 constexpr int kMsBlock = 4;
+// Bricks up to this many points.  An iteration with four shifts on bricks over
+// one on the march, widths of 40 to 260: 0.73 to 0.81 at 0.05 M points, 0.95 to
+// 1.03 at 0.6 M, 0.99 to 1.08 at 0.75 M, 1.02 to 1.09 at 0.9 M, 1.05 to 1.15 at
+// 2 M (130 x 110 x 125: 107 us against 97).
+constexpr int64_t kMsBrickPoints = 700000;
 static_assert(kMsPoll % kMsBlock == 0, "whole blocks between status reads");
 
 struct MsShift {
@@ -594,7 +599,7 @@ extern "C" int ofdft_multishift_create(const ofdft_grid *grid, int radius, int m
     m->n = npoints(*grid);
     m->coef = make_coef(*grid, radius);
     StencilCfg bk;
-    if (brick_stencil(*grid, sizeof(double2), 1, bk)) {
+    if (brick_fits(*grid, kMsBrickPoints, bk)) {
         m->shape = SHAPE_BRICK;
         m->bg = make_brick_geom(*grid, 4);
     } else {

@@ -64,28 +64,52 @@ StencilCfg default_stencil_cfg(const ofdft_grid &g, int elem_bytes, int family) 
     return c;
 }
 
-// Measured on MI355X (back-to-back applies, march / brick, us; the call itself
-// takes 8.5 on the host): FP32 110x75x91 10.9 / 8.7, 128^3 11.2 / 11.2, 160^3
-// 16.9 / 17.6; FP64 48^3 13.1 / 8.7, 110x75x91 15.1 / 8.9, 128^3 20.9 / 14.3,
-// 160^3 27.4 / 24.9, 192^3 35.7 / 42.3; complex128 96^3 15.5 / 13.8, 110x75x91
-// 13.7 / 11.6, 128^3 22.5 / 29.8.  Passes that read two arrays per stencil point
-// load twice as much through L1 and cross earlier (CG iteration, FP64 80^3
-// 27.5 / 23.4, 96^3 30.8 / 30.2; FP32 96^3 27.1 / 26.0).  One plane per brick up
-// to 2^17 points (CG iteration at 16^3 14.3 against 15.7 with four), else four.
-bool brick_stencil(const ofdft_grid &g, int elem_bytes, int arrays, StencilCfg &c) {
+// Which of the two kernels wins depends on the points and, for complex128, on
+// the tile the march would run.  Measured on MI355X, time of the bricks over
+// that of the march, over widths nx of 24 to 330 (ny = nz):
+//   applies, FP32: 0.64 to 0.99 up to 1.5 M points, 0.64 to 1.04 at 1.8 M;
+//   applies, FP64: 0.50 to 0.98 at 1.5 to 2.5 M, 0.59 to 1.10 at 4.4 M, 0.54 to
+//     1.05 at 5 M, the worst of them where 64-wide tiles fit (nx = 192, 300);
+//   applies, complex128, where the march runs 32-wide tiles (nx = 24 to 40, 80,
+//     96, 144, 160, 208, 224): 0.52 to 0.87 up to 1 M; where 64-wide tiles would
+//     idle over 20% besides, 0.66 to 1.01 up to 2 M;
+//   applies, complex128, with 64-wide tiles: 0.67 to 0.94 at 0.4 to 0.7 M, 0.91 to
+//     1.12 (1.01 on average) at 0.8 M, 0.86 to 1.11 at 1 M and up to 1.30 at 2 M,
+//     except where the one tile idles by a third (nx = 48): 0.89 to 0.96;
+//   CG iterations (two arrays per point), FP64: 0.68 to 0.92 at 0.3 to 0.5 M, 0.82
+//     to 1.06 at 0.9 M, 0.90 to 1.09 at 1.1 M; FP32 0.70 to 1.07 at 0.9 M.
+// Shifted systems of a batch run bricks up to 1 M points (2 M where 64-wide tiles
+// would idle), whatever else is in the batch: at 0.75 M points an iteration of one
+// system takes 0.44 to 0.77 of the march's time, of 4 or 16 systems, which fill
+// the chip with marched tiles, 0.82 to 1.13; in complex64 0.6 to 0.9.
+// One plane per brick up to 2^17 points (CG iteration at 16^3 14.3 us against
+// 15.7 with four), else four.
+bool brick_fits(const ofdft_grid &g, int64_t limit, StencilCfg &c) {
     if (g.nx < kBrickMinAxis || g.ny < kBrickMinAxis || g.nz < kBrickMinAxis) return false;
     const int64_t n = npoints(g);
-    // complex128 to twice the size where 64-wide tiles would be over 20% idle (130x110x125 29.5 / 26.2)
-    const bool idle = 5 * ((g.nx + 63) / 64 * 64) > 6 * g.nx;
-    const int64_t limit = arrays > 1 ? (int64_t)900000
-                          : elem_bytes == 4 ? (int64_t)1500000
-                          : elem_bytes == 8 ? (int64_t)4500000
-                                            : (int64_t)(idle ? 2000000 : 1000000);
     if (n > limit) return false;
     const int kz = n <= (1 << 17) ? 1 : 4;
     if (make_brick_geom(g, kz).nblocks > kRedSlots) return false;
     c = StencilCfg{SHAPE_BRICK, kz};
     return true;
+}
+
+bool brick_stencil(const ofdft_grid &g, int elem_bytes, int arrays, StencilCfg &c) {
+    const int wide = (g.nx + 63) / 64 * 64;               // 64-wide tiles over a row
+    int64_t limit;
+    if (arrays > 1) limit = 900000;
+    else if (elem_bytes == 4) limit = 1500000;
+    else if (elem_bytes == 8) limit = 4500000;
+    else if (default_stencil_cfg(g, elem_bytes, FAMILY_APPLY).shape == SHAPE_32x8x2)
+        limit = 5 * wide > 6 * g.nx ? 2000000 : 1000000;
+    else
+        limit = 3 * wide >= 4 * g.nx ? 2000000 : 800000;
+    return brick_fits(g, limit, c);
+}
+
+bool brick_system(const ofdft_grid &g, int elem_bytes, StencilCfg &c) {
+    const int wide = (g.nx + 63) / 64 * 64;
+    return brick_fits(g, elem_bytes == 8 ? 4500000 : 5 * wide > 6 * g.nx ? 2000000 : 1000000, c);
 }
 
 StencilCfg pick_stencil_cfg(const ofdft_grid &g, int elem_bytes, int family, int arrays) {

@@ -73,6 +73,9 @@ enum TuneFamily { FAMILY_ALL = -1, FAMILY_APPLY = 0, FAMILY_PASS = 1, FAMILY_COU
 // stencil point.
 StencilCfg pick_stencil_cfg(const ofdft_grid &g, int elem_bytes, int family, int arrays = 1);
 bool brick_stencil(const ofdft_grid &g, int elem_bytes, int arrays, StencilCfg &c);
+// The same for the shifted systems of a batch, and the rule with another limit of points.
+bool brick_system(const ofdft_grid &g, int elem_bytes, StencilCfg &c);
+bool brick_fits(const ofdft_grid &g, int64_t limit, StencilCfg &c);
 // The heuristic alone (no table).
 StencilCfg default_stencil_cfg(const ofdft_grid &g, int elem_bytes, int family);
 void record_stencil_cfg(const ofdft_grid &g, int elem_bytes, int family, StencilCfg c);
