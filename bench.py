@@ -294,15 +294,14 @@ def profile_kernel(which, shape, h, reps=5):
 # 348 instead of 418 vector passes, the same minimiser to the 1e-8 tolerance.
 LINE_SLOPE_TOL = 1e-2
 
-# Kernel classes whose every launch is one kernel (the multigrid cycles and
-# the density-update passes are several kernels each).
-SINGLE_KERNEL_CLASSES = ("apply", "cg_stencil", "cg_update", "cocg", "ms_stencil", "ms_update")
+# Kernel classes whose every launch is one kernel (the multigrid cycles, the
+# density-update passes and the multi-shift vector phase are several each).
+SINGLE_KERNEL_CLASSES = ("apply", "cg_stencil", "cg_update", "cocg", "ms_stencil")
 KERNEL_NAMES = {"cocg": "step_stencil (stepped COCG stencil phase, complex128)",
                 "cg_stencil": "stencil_kernel<LoadCgP, EpiCgAp> (CG stencil pass)",
                 "cg_update": "reduce_kernel<CgUpdate> (CG vector pass)",
                 "apply": "stencil_kernel<LoadPlain, EpiAxpby> (apply)",
-                "ms_stencil": "ms_stencil (multi-shift COCG stencil phase)",
-                "ms_update": "ms_update (multi-shift COCG vector phase)"}
+                "ms_stencil": "ms_stencil (multi-shift COCG stencil phase)"}
 
 
 def batch_extra(dev, autotune=True):

@@ -18,12 +18,12 @@
 //    in that XCD's L2, and the systems still running keep every XCD busy
 //    when the others have converged);
 //  * vector phase: r -= alpha Ap into the next slot of a ring of residuals,
-//    r^T r and |r|^2 reduced.  Every ring-th vector phase (ring = 4; 2 for
-//    batches that fill the card's memory) brings p and x up to date from the
+//    r^T r and |r|^2 reduced.  Every ring-th vector phase (ring = 4; 2 in
+//    compact batches) brings p and x up to date from the
 //    ring and the kept alphas and betas: p = r_k + beta_k p, x += alpha_k p.
 // Per iteration that moves 6 vectors and (ring + 3) / ring for p and x: 7.75
 // in place of the 10 that the update of p and x in each iteration takes
-// (6 cells of 24 to 96 points an axis, 8 shifts each, to 1e-10: 66 -> 62 ms).
+// (6 cells of 24 to 96 points an axis, 8 shifts each, to 1e-10: 66 -> 63 ms).
 // The scalars of every system (alpha, beta, r^T r, status) live on the
 // device: the last workgroup of a system to finish a phase combines that
 // system's partial sums (fixed order, so results do not depend on timing or

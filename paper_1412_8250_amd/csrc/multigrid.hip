@@ -359,7 +359,7 @@ __global__ void __launch_bounds__(NT) mg_down(MgDims d, MgDims cd, MgTile tl, do
 // r re-read through the caches; f is then the caller's FP64 array also with
 // FP32 levels (its FP32 copy would be stored and read in addition).  Bytes per
 // point of FP64 vectors with FP32 levels, cycle and products, where a pass of
-// its own read r and z: 49 -> 41 (with A p 57 -> 49).  Measured, whole solves:
+// its own read r and z: 49 -> 33 (with A p 57 -> 41).  Measured, whole solves:
 // Poisson 96^3 1.61 -> 1.52 ms, 320^3 15.2 -> 14.1 (15.1 with the real
 // operands loaded where they are used); eight shifted systems of 96^3 6.7 -> 6.4;
 // an SCF step of 320^3 226 -> 212.
@@ -1055,9 +1055,10 @@ double mg_cycle_bytes(const Multigrid &mg, bool dots) {
 // z^T A p + beta (z^T A p_old + beta p_old^T A p_old), and
 // <z, r - r_old> = -alpha <z, A p>, so neither p nor r_old is needed for the
 // scalars.  Bytes per point and iteration beside the cycle: 24 (stencil) + 24
-// (r) + 24 (products) + 16 (p and x, ring 4) = 88; with p, x and r_old moved in
-// each iteration 120.  Measured, whole solves: 320^3 17.8 -> 15.2 ms, 96^3
-// 1.69 -> 1.59 ms.
+// (r) + 8 (A p, read by the cycle's last kernel for the products) + 16 (p and x,
+// ring 4) = 72; with p, x and r_old moved in each iteration and a pass for the
+// products 120.  Measured, whole solves: the ring 320^3 17.8 -> 15.2 ms, 96^3
+// 1.69 -> 1.59 ms; the products in the cycle 15.2 -> 14.1 and 1.61 -> 1.52 ms.
 namespace {
 
 constexpr int kPcgBlock = 4;
