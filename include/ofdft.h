@@ -228,7 +228,7 @@ int ofdft_poisson_set_refinement(ofdft_poisson *s, double inner_min, double inne
  *   schedule (group 0 at solve time, else the solve returns INVALID_ARG);
  *   every axis of every grid must halve evenly down to at most 16 points.
  *   Allocates one complex128 vector per system and multigrid level arrays
- *   per system (about 1.3 fine-grid vectors); consecutive systems on one
+ *   per system (about 0.7 fine-grid vectors, 1.4 in FP64); consecutive systems on one
  *   grid (up to 64) form a group whose cycles run as one launch per kernel.
  *   A batch becomes compact where they would not fit otherwise.
  *   INVALID_ARG (nothing changed) or NO_MEMORY.

@@ -904,7 +904,7 @@ int density_update_dev(ofdft_scf *s, const double *v, double *u, int &iters, dou
     prof_add(K_U_VECTOR, nd * (32.0 * Uh->n_kb + 32.0 * ndots + 24.0 * Uh->n_eval + 24.0 * Uh->n_step),
              eager ? 0 : nvec);
     if (P.pre)
-        prof_add(K_MULTIGRID, (mg_cycle_bytes(*s->umg, fused) + (fused ? 16.0 * nd : 0.0)) * Uh->n_dots,
+        prof_add(K_MULTIGRID, (mg_cycle_bytes(*s->umg) + (fused ? 16.0 * nd : 0.0)) * Uh->n_dots,
                  eager ? 0 : Uh->n_dots);
     s->s_prev = Uh->s_prev;
     iters = Uh->q;

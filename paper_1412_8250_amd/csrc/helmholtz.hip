@@ -1018,7 +1018,7 @@ static int batch_solve(ofdft_batch *b, const double *kappa, const void *const *r
                     // after the init phase and after each iteration but the last
                     const int cycles = it_pass[j];
                     if (!mg_forms_dots(*b->mg_of[j])) bu += n * e * 2.0 * cycles;
-                    prof_add(K_MULTIGRID_C, mg_cycle_bytes(*b->mg_of[j], true) * cycles, 0);
+                    prof_add(K_MULTIGRID_C, mg_cycle_bytes(*b->mg_of[j]) * cycles, 0);
                 }
             }
             prof_add(K_COCG, bs, 0);

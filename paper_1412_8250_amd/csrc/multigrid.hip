@@ -220,12 +220,11 @@ struct PcgRho {          // {<z, Ap>, <r, z>}: beta and the next rho
 // u = 0 (with the Jacobi factor s = omega / (diag + kappa), u1 = s f and
 // u2 = u1 + s (f - A u1) = s (2 f - s A f)), the residual r = f - A u2 and its
 // full weighting fc[I] = sum over the 27 fine points around 2I of
-// (1/8) w(dx) w(dy) w(dz) r, w(0) = 1, w(+-1) = 1/2 (= P^T / 8).  Stores u2,
-// fc and, when fl is given, f in S (the upward half then reads the narrower
-// copy); r is never stored.
+// (1/8) w(dx) w(dy) w(dz) r, w(0) = 1, w(+-1) = 1/2 (= P^T / 8).  Stores u2 and
+// fc; r is never stored.
 //
-// Bound by HBM: 16.5 B/point for FP64 f and FP32 levels (read f; write u, its
-// FP32 copy and 1/8 fc) where three separate passes moved 32.5.  The tile is
+// Bound by HBM: 12.5 B/point for FP64 f and FP32 levels (read f; write u and 1/8
+// fc) where three separate passes moved 32.5.  The tile is
 // marched along z with one plane of f, u and r each in LDS (double-buffered:
 // every step writes one buffer and reads the one the step before wrote, so
 // one barrier per plane serves all three stages, each one plane behind the
@@ -236,7 +235,7 @@ struct PcgRho {          // {<z, Ap>, <r, z>}: beta and the next rho
 // 393 us, 160^3 169 -> 102 us, 96^3 109 -> 58 us; complex 160^3 260 -> 157 us.
 template <typename TF, typename S, int NT, int SL>
 __global__ void __launch_bounds__(NT) mg_down(MgDims d, MgDims cd, MgTile tl, double w, MgArr<const TF> fa,
-                                              MgArr<S> ua, MgArr<S> fla, MgArr<S> cfa, MgShift sh) {
+                                              MgArr<S> ua, MgArr<S> cfa, MgShift sh) {
     using V = VT<S>;
     using R = typename MgT<S>::R;
     using C = typename MgT<S>::C;
@@ -246,8 +245,7 @@ __global__ void __launch_bounds__(NT) mg_down(MgDims d, MgDims cd, MgTile tl, do
     // global-space views: a pointer from a table is generic to the compiler,
     // and flat loads would share the LDS wait counter
     const GPtr<TF> f(fa.at(m.q));
-    const GPtr<S> u(ua.at(m.q)), fl(fla.at(m.q)), fc(cfa.at(m.q));
-    const bool keep = fla.base != nullptr;
+    const GPtr<S> u(ua.at(m.q)), fc(cfa.at(m.q));
     const int RW = tl.W + 5, RH = tl.H + 5;
     MgCols<SL> co;
     mg_cols<NT, SL>(d, tl, m.x0, m.y0, 3, RW, RH, co);
@@ -294,7 +292,6 @@ __global__ void __launch_bounds__(NT) mg_down(MgDims d, MgDims cd, MgTile tl, do
             for (int i = 0; i < SL; ++i) {
                 const int c = tid + i * NT;
                 fb[B][c] = f2[i];
-                if (keep && co.own[i] && t >= 3 && t <= m.zl + 2) fl.st(p * nxy + co.off[i], f2[i]);
                 un[i] = V::zero();
                 if (t >= 2 && co.depth[i] >= 1) {
                     const S af = mg_op<S>(d, kap, f1[i], fb[Q][c + 1], fb[Q][c - 1], fb[Q][c + RW], fb[Q][c - RW],
@@ -347,8 +344,8 @@ __global__ void __launch_bounds__(NT) mg_down(MgDims d, MgDims cd, MgTile tl, do
 // odd), then the two post-smoothing sweeps t = v + s (f - A v) and
 // z = t + s (f - A t); v and t are never stored.
 //
-// Bound by HBM: 16.5 B/point for FP32 levels and FP64 z (read f, u, 1/8 uc;
-// write z) where two passes moved 28.5.  The march of mg_down with halo 2 and
+// Bound by HBM: 20.5 B/point for FP32 levels and FP64 f and z (read f, u, 1/8 uc;
+// write z) where two passes moved 28.5 (with f in FP32).  The march of mg_down with halo 2 and
 // four warm-up planes per z chunk: v[p], t[p-1] and z[p-2] are formed in the
 // step of plane p.  A column keeps the (x, y)-interpolated coarse value of the
 // two coarse planes around it; the next one's corners are fetched a step
@@ -356,9 +353,9 @@ __global__ void __launch_bounds__(NT) mg_down(MgDims d, MgDims cd, MgTile tl, do
 //
 // With a Dot (level 0 inside a Krylov loop) the products of z with r = f (and
 // with A p) that the loop takes next are reduced here, from the z at hand and
-// r re-read through the caches; f is then the caller's FP64 array also with
-// FP32 levels (its FP32 copy would be stored and read in addition).  Bytes per
-// point of FP64 vectors with FP32 levels, cycle and products, where a pass of
+// r re-read through the caches.  f is the caller's FP64 array also with FP32
+// levels: a copy in FP32 would save here what the downward half would write.
+// Bytes per point of FP64 vectors with FP32 levels, cycle and products, where a pass of
 // its own read r and z: 49 -> 33 (with A p 57 -> 41).  Measured, whole solves:
 // Poisson 96^3 1.61 -> 1.52 ms, 320^3 15.2 -> 14.1 (15.1 with the real
 // operands loaded where they are used); eight shifted systems of 96^3 6.7 -> 6.4;
@@ -717,7 +714,7 @@ MgPick mg_pick_up(const MgLevel &L, int count, size_t elem) { return mg_pick_til
 
 template <typename TF, typename S>
 int launch_down(const MgLevel &L, const MgLevel &C, int count, double2 kappa, double omega, MgArr<const TF> f,
-                MgArr<S> u, MgArr<S> fl, MgArr<S> cf, MgShift sh, hipStream_t s) {
+                MgArr<S> u, MgArr<S> cf, MgShift sh, hipStream_t s) {
     const MgPick pick = L.down[0].count == count   ? L.down[0]
                         : L.down[1].count == count ? L.down[1]
                                                    : mg_pick_down(L, count, sizeof(S));
@@ -725,12 +722,12 @@ int launch_down(const MgLevel &L, const MgLevel &C, int count, double2 kappa, do
     const MgDims d = dims_of(L, kappa), cd = dims_of(C, kappa);
     const dim3 grid(t.blocks() * count);
     switch (pick.cap) {
-        case 256: hipLaunchKernelGGL((mg_down<TF, S, 256, 1>), grid, dim3(256), 0, s, d, cd, t, omega, f, u, fl, cf, sh); break;
-        case 512: hipLaunchKernelGGL((mg_down<TF, S, 256, 2>), grid, dim3(256), 0, s, d, cd, t, omega, f, u, fl, cf, sh); break;
-        case 1024: hipLaunchKernelGGL((mg_down<TF, S, 512, 2>), grid, dim3(512), 0, s, d, cd, t, omega, f, u, fl, cf, sh); break;
+        case 256: hipLaunchKernelGGL((mg_down<TF, S, 256, 1>), grid, dim3(256), 0, s, d, cd, t, omega, f, u, cf, sh); break;
+        case 512: hipLaunchKernelGGL((mg_down<TF, S, 256, 2>), grid, dim3(256), 0, s, d, cd, t, omega, f, u, cf, sh); break;
+        case 1024: hipLaunchKernelGGL((mg_down<TF, S, 512, 2>), grid, dim3(512), 0, s, d, cd, t, omega, f, u, cf, sh); break;
         default:
             if constexpr (sizeof(S) <= 8)
-                hipLaunchKernelGGL((mg_down<TF, S, 512, 4>), grid, dim3(512), 0, s, d, cd, t, omega, f, u, fl, cf, sh);
+                hipLaunchKernelGGL((mg_down<TF, S, 512, 4>), grid, dim3(512), 0, s, d, cd, t, omega, f, u, cf, sh);
     }
     OFDFT_CHECK_HIP(hipGetLastError());
     return OFDFT_OK;
@@ -774,8 +771,7 @@ int vcycle_coarse(Multigrid &mg, int l, int q0, int count, double2 kappa, MgShif
         return OFDFT_OK;
     }
     MgLevel &C = mg.lv[l + 1];
-    const MgArr<S> none{nullptr, 0, nullptr};
-    OFDFT_TRY((launch_down<S, S>(L, C, count, kappa, mg.omega, f, u, none, lvl<S>(C.f, C, q0), sh, s)));
+    OFDFT_TRY((launch_down<S, S>(L, C, count, kappa, mg.omega, f, u, lvl<S>(C.f, C, q0), sh, s)));
     OFDFT_TRY(vcycle_coarse<S>(mg, l + 1, q0, count, kappa, sh, s));
     const MgArr<const S> ct{(const S *)C.t + (int64_t)q0 * C.n, C.n, nullptr};
     return launch_up<MgNoDot, S, S, S>(L, C, count, kappa, mg.omega, f, uc, ct, t, sh, {}, s);
@@ -783,10 +779,7 @@ int vcycle_coarse(Multigrid &mg, int l, int q0, int count, double2 kappa, MgShif
 
 // The whole cycle z = M f for `count` systems from q0 of the hierarchy: level
 // 0 reads f and writes z in FP64 (TIO), its work arrays are S.  V(2,2), two
-// kernels per level.  With S narrower than TIO the downward half also stores
-// f in S (level 0's f array), which the upward half reads instead of the FP64
-// input, unless that half forms products (see mg_up; a one-level cycle forms
-// none).  f, z, sh and dot address system q0 first.
+// kernels per level.  f, z, sh and dot address system q0 first.
 template <typename TIO, typename S, class Dot = MgNoDot>
 int vcycle(Multigrid &mg, int q0, int count, MgArr<const TIO> f, MgArr<TIO> z, double2 kappa, MgShift sh,
            hipStream_t s, Dot prod = {}) {
@@ -802,20 +795,11 @@ int vcycle(Multigrid &mg, int q0, int count, MgArr<const TIO> f, MgArr<TIO> z, d
     MgLevel &C = mg.lv[1];
     const MgArr<S> cf = lvl<S>(C.f, C, q0);
     const MgArr<const S> ct{(const S *)C.t + (int64_t)q0 * C.n, C.n, nullptr};
-    if constexpr (sizeof(S) < sizeof(TIO) && Dot::kSums == 0) {
-        const MgArr<S> fl = lvl<S>(L.f, L, q0);
-        const MgArr<const S> flc{fl.base, fl.stride, nullptr};
-        OFDFT_TRY((launch_down<TIO, S>(L, C, count, kappa, mg.omega, f, u, fl, cf, sh, s)));
-        OFDFT_TRY(vcycle_coarse<S>(mg, 1, q0, count, kappa, sh, s));
-        return launch_up<MgNoDot, S, S, TIO>(L, C, count, kappa, mg.omega, flc, uc, ct, z, sh, {}, s);
-    } else {
-        const MgArr<S> none{nullptr, 0, nullptr};
-        OFDFT_TRY((launch_down<TIO, S>(L, C, count, kappa, mg.omega, f, u, none, cf, sh, s)));
-        OFDFT_TRY(vcycle_coarse<S>(mg, 1, q0, count, kappa, sh, s));
-        const MgDot<Dot> dot{prod, mg.dpart + (int64_t)q0 * Multigrid::kDotSums * mg.dot_cap, mg.dctr + (int64_t)q0 * kArriveWords,
-                             mg.dot_cap};
-        return launch_up<Dot, TIO, S, TIO>(L, C, count, kappa, mg.omega, f, uc, ct, z, sh, dot, s);
-    }
+    OFDFT_TRY((launch_down<TIO, S>(L, C, count, kappa, mg.omega, f, u, cf, sh, s)));
+    OFDFT_TRY(vcycle_coarse<S>(mg, 1, q0, count, kappa, sh, s));
+    const MgDot<Dot> dot{prod, mg.dpart + (int64_t)q0 * Multigrid::kDotSums * mg.dot_cap, mg.dctr + (int64_t)q0 * kArriveWords,
+                         mg.dot_cap};
+    return launch_up<Dot, TIO, S, TIO>(L, C, count, kappa, mg.omega, f, uc, ct, z, sh, dot, s);
 }
 
 }  // namespace
@@ -866,15 +850,16 @@ int mg_create(Multigrid &mg, const ofdft_grid &g, int elem_bytes, bool fp32, int
     for (int l = 0; l < nlev; ++l) {
         MgLevel &M = mg.lv[l];
         const size_t b = es * (size_t)M.n * (size_t)groups;
-        // u: every level with a coarser one; f: levels below the first, and an
-        // FP32 copy of the caller's f on the first when the levels are FP32;
-        // t: the level's solution, below the first (the caller's z there).  A
+        // u: every level with a coarser one; f and t, the level's right-hand side
+        // and solution: below the first (the caller's f and z there).  A
         // one-level hierarchy needs nothing.
         void **own[3];
         int count = 0;
         if (l + 1 < nlev) own[count++] = &M.u;
-        if (nlev > 1 && (l > 0 || fp32)) own[count++] = &M.f;
-        if (l > 0) own[count++] = &M.t;
+        if (l > 0) {
+            own[count++] = &M.f;
+            own[count++] = &M.t;
+        }
         for (int k = 0; k < count; ++k) {
             void *p = nullptr;
             if (hipMalloc(&p, b) != hipSuccess) {
@@ -1021,20 +1006,17 @@ int mg_apply_shifted_group(Multigrid &mg, int count, const double2 *const *r, do
                    : vcycle<double2, double2>(mg, 0, count, f, o, k, sh, s, rho);
 }
 
-// Algorithmic bytes of one cycle.  Fine level, FP64 levels: the downward half
-// reads f and writes u and an eighth of an element (the restricted residual),
-// the upward half reads f, u and an eighth (the coarse correction) and writes
-// z: 5.25 elements per point.  FP32 levels: f (FP64) is read once and stored
-// as FP32, which the upward half reads, unless that half forms products: it
-// then reads f.  Each coarser level moves 5.25
-// elements per point, and they hold 1/7 of the fine points in all.
-double mg_cycle_bytes(const Multigrid &mg, bool dots) {
+// Algorithmic bytes of one cycle.  Fine level: the downward half reads f and
+// writes u and an eighth of an element (the restricted residual), the upward
+// half reads f, u and an eighth (the coarse correction) and writes z.  Each
+// coarser level moves 5.25 elements per point, and they hold 1/7 of the fine
+// points in all.
+double mg_cycle_bytes(const Multigrid &mg) {
     if (mg.lv.empty()) return 0.0;
     const double E = (double)mg.elem, e = mg.fp32 ? E / 2 : E;
     const double n = (double)mg.lv[0].n;
     if (mg.lv.size() == 1) return 2.0 * n * E;
-    const double fine = mg.fp32 && !dots ? 2.0 * E + 4.25 * e : 3.0 * E + 2.25 * e;
-    return n * fine + n / 7.0 * 5.25 * e;
+    return n * (3.0 * E + 2.25 * e) + n / 7.0 * 5.25 * e;
 }
 
 // CG on the projected Poisson system preconditioned by the V-cycle (flexible
@@ -1323,7 +1305,7 @@ int poisson_solve_mg(ofdft_poisson *s, double *x, double rel_tol, int max_iter, 
     prof_add(K_CG_UPDATE, nd * 8.0 * (3.0 * Dh->n_step + (mg_forms_dots(*s->mg) ? 0.0 : 3.0) * Dh->n_dots + (flushes ? (ring + 4.0) * flushes - 1.0 : 0.0)),
              eager ? 0 : Dh->n_step + (mg_forms_dots(*s->mg) ? 0 : Dh->n_dots));
     const double extra = mg_forms_dots(*s->mg) ? 8.0 * nd : 0.0;
-    prof_add(K_MULTIGRID, (mg_cycle_bytes(*s->mg, true) + extra) * Dh->n_dots, eager ? 0 : Dh->n_dots);
+    prof_add(K_MULTIGRID, (mg_cycle_bytes(*s->mg) + extra) * Dh->n_dots, eager ? 0 : Dh->n_dots);
     stats.iters = Dh->iters;
     switch (Dh->done) {
         case P_OK: return OFDFT_OK;

@@ -133,7 +133,7 @@ inline bool mg_forms_dots(const Multigrid &mg) { return mg.lv.size() > 1; }
 // null); rho as above, of system 0.  Not accounted in the profile.
 int mg_apply_shifted_group(Multigrid &mg, int count, const double2 *const *r, double2 *const *z, const StepRho &rho,
                            const double *kappa, int kstride, const int *run, int rstride, hipStream_t s);
-// Algorithmic HBM bytes of one cycle (dots: one that forms products of r and z).
-double mg_cycle_bytes(const Multigrid &mg, bool dots = false);
+// Algorithmic HBM bytes of one cycle (products of r and z come with it).
+double mg_cycle_bytes(const Multigrid &mg);
 
 }  // namespace ofdft

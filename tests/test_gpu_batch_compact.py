@@ -98,7 +98,7 @@ def test_two_slots_where_four_do_not_fit():
 
 def test_preconditioner_takes_the_room_of_two_slots():
     """The batch holds 6 vectors with four slots and 4 with two, z and the levels
-    (complex64: 16 B per point and 24 on an eighth of it, and so on) 2.2 more:
+    (complex64: 8 B per point and 24 on an eighth of it, and so on) 1.7 more:
     with 7.2 free the preconditioner fits only beside two slots."""
     torch = torch_cuda()
     shape, vec = (512, 512, 512), 16 * 512 ** 3

@@ -1,5 +1,6 @@
 """A multigrid cycle's launches cost the host no more on a large grid than on a
-small one: what a launch needs of the grid alone is found at creation."""
+small one (what a launch needs of the grid alone is found at creation), and its
+hierarchy holds no array that no kernel uses."""
 import time
 
 import pytest
@@ -34,3 +35,21 @@ def test_large_grids_take_no_more_host_time():
     small, large = _enqueue_time(64), _enqueue_time(512)
     announce("cycle host time", small, large)
     assert large <= 2.4 * small
+
+
+@pytest.mark.parametrize("kind,elem", [(ofd.PRECOND_MULTIGRID, 8), (ofd.PRECOND_MULTIGRID_F64, 16)])
+def test_hierarchy_holds_what_it_uses(kind, elem):
+    """z; u on the finest level; u, f and t on the levels below (256^3 has 4 of
+    them: 1/8 + 1/64 + 1/512 + 1/4096 of the points)."""
+    torch = torch_cuda()
+    n = 256
+    announce("hierarchy memory", kind)
+    b = ofd.HelmholtzBatch([(n,) * 3], [(0.4,) * 3])
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    b.set_preconditioner(kind)
+    used = before - torch.cuda.mem_get_info()[0]
+    b.close()
+    coarse = 1 / 8 + 1 / 64 + 1 / 512 + 1 / 4096
+    # each allocation is a whole number of 2 MiB pages; streams and events besides
+    assert used <= n ** 3 * (16 + elem * (1 + 3 * coarse)) + (64 << 20)

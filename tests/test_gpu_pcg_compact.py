@@ -51,8 +51,8 @@ def test_other_solvers_have_no_compact_form():
 
 
 def test_two_slots_where_four_do_not_fit():
-    """Six vectors and the levels' (FP32: 8 B per point and 12 on an eighth of
-    it, and so on: 1.2 vectors) with two slots, two more with four; 8.2 are
+    """Six vectors and the levels' (FP32: 4 B per point and 12 on an eighth of
+    it, and so on: 0.7 vectors) with two slots, two more with four; 8.2 are
     free."""
     torch = torch_cuda()
     shape, h = (512, 512, 512), 0.4
