@@ -45,7 +45,7 @@ __device__ inline double tiny_sum(double x, double *scratch) {
     return s;
 }
 
-template <typename T, int KZ>
+template <typename T, int KZ, bool Resume>
 __global__ void __launch_bounds__(kTinyThreads)
 cg_tiny_kernel(int nx, int ny, int nz, Coef<typename VT<T>::S> w, T *__restrict__ x, T *__restrict__ r,
                T *__restrict__ pkeep, CgState *st) {
@@ -78,11 +78,13 @@ cg_tiny_kernel(int nx, int ny, int nz, Coef<typename VT<T>::S> w, T *__restrict_
         const int64_t i = (int64_t)(z0 + k) * nxy + col;
         xv[k] = own ? x[i] : T(0);
         rv[k] = own ? r[i] : T(0);
-        pv[k] = own && !s.first ? pkeep[i] : T(0);
+        pv[k] = Resume && own ? pkeep[i] : T(0);
         av[k] = T(0);
     }
-    S beta = (S)s.beta;
-    for (int left = kTinyIters; s.done == CG_RUNNING && left > 0; --left) {
+    S beta = Resume ? (S)s.beta : S(0);
+    const int maxit = s.maxit, cap = min(maxit, s.iter + kTinyIters);
+    s.maxit = cap;                                       // one test serves the launch's cap and the solve's
+    while (s.done == CG_RUNNING) {
         // p = r + beta p_old (first iteration: p = r)
 #pragma unroll
         for (int k = 0; k < KZ; ++k)
@@ -156,19 +158,22 @@ cg_tiny_kernel(int nx, int ny, int nz, Coef<typename VT<T>::S> w, T *__restrict_
             const int64_t i = (int64_t)(z0 + k) * nxy + col;
             x[i] = xv[k];
             r[i] = rv[k];
-            pkeep[i] = pv[k];
         }
+    if (s.done == CG_MAXIT && cap < maxit) {             // p for the next launch
+        s.done = CG_RUNNING;
+        for (int k = 0; k < planes && k < KZ; ++k) pkeep[(int64_t)(z0 + k) * nxy + col] = p[(z0 + k) * SL + row];
+    }
+    s.maxit = maxit;
     if (threadIdx.x == 0) *st = s;
 }
 
 template <typename T>
 inline int launch_cg_tiny(const ofdft_grid &g, int kz, const Coef<typename VT<T>::S> &c, T *x, T *r, T *p,
-                          CgState *st, hipStream_t s) {
+                          CgState *st, bool resume, hipStream_t s) {
     const size_t lds = (size_t)(g.nx + 2 * kMaxRadius) * g.ny * g.nz * sizeof(T);
-    if (kz == 4)
-        hipLaunchKernelGGL((cg_tiny_kernel<T, 4>), dim3(1), dim3(kTinyThreads), lds, s, g.nx, g.ny, g.nz, c, x, r, p, st);
-    else
-        hipLaunchKernelGGL((cg_tiny_kernel<T, 8>), dim3(1), dim3(kTinyThreads), lds, s, g.nx, g.ny, g.nz, c, x, r, p, st);
+    auto kern = kz == 4 ? (resume ? cg_tiny_kernel<T, 4, true> : cg_tiny_kernel<T, 4, false>)
+                        : (resume ? cg_tiny_kernel<T, 8, true> : cg_tiny_kernel<T, 8, false>);
+    hipLaunchKernelGGL(kern, dim3(1), dim3(kTinyThreads), lds, s, g.nx, g.ny, g.nz, c, x, r, p, st);
     OFDFT_CHECK_HIP(hipGetLastError());
     return OFDFT_OK;
 }

@@ -493,11 +493,9 @@ void batch_compact(ofdft_batch *b) {
         (void)hipGraphExecDestroy(b->step_graph);
         b->step_graph = nullptr;
     }
-    for (int k = 2; k < kRingMax; ++k) {
-        for (void *p : b->slot[k])
-            if (p) (void)hipFree(p);
-        b->slot[k].clear();
-    }
+    for (void *p : b->slot[2])                   // a system's further slots are one allocation
+        if (p) (void)hipFree(p);
+    for (int k = 2; k < kRingMax; ++k) b->slot[k].clear();
     b->ring = 2;
 }
 
@@ -512,16 +510,17 @@ int upload_ztab(ofdft_batch *b) {
 // From two ring slots to four; NO_MEMORY (nothing changed) if they do not fit.
 int batch_extend(ofdft_batch *b) {
     const size_t e = b->dtype == OFDFT_C64 ? sizeof(float2) : sizeof(double2);
-    for (int k = 2; k < kRingMax; ++k) {
-        b->slot[k].assign(b->nsys, nullptr);
-        for (int j = 0; j < b->nsys; ++j)
-            if (hipMalloc(&b->slot[k][j], (size_t)npoints(b->grids[j]) * e) != hipSuccess) {
-                (void)hipGetLastError();
-                b->slot[k][j] = nullptr;
-                batch_compact(b);
-                set_error("ofdft_batch: out of device memory");
-                return OFDFT_NO_MEMORY;
-            }
+    for (int k = 2; k < kRingMax; ++k) b->slot[k].assign(b->nsys, nullptr);
+    for (int j = 0; j < b->nsys; ++j) {
+        const size_t bytes = (size_t)npoints(b->grids[j]) * e;
+        void *p = nullptr;
+        if (hipMalloc(&p, (kRingMax - 2) * bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            batch_compact(b);
+            set_error("ofdft_batch: out of device memory");
+            return OFDFT_NO_MEMORY;
+        }
+        for (int k = 2; k < kRingMax; ++k) b->slot[k][j] = (char *)p + (k - 2) * bytes;
     }
     if (b->step_graph) {
         (void)hipGraphExecDestroy(b->step_graph);

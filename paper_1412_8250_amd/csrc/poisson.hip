@@ -211,13 +211,15 @@ int cg_iterate(const ofdft_grid &g, const Coef<typename VT<T>::S> &c, T *x, T *r
                int &done, CgGraph *graph) {
     // a grid of one workgroup: many iterations in one launch
     if (const int kz = tiny_planes(g, sizeof(T))) {
+        bool resume = false;
         do {
             {
                 ProfScope ps(K_CG_STENCIL, 0.0, s);
-                OFDFT_TRY(launch_cg_tiny<T>(g, kz, c, x, r, pA, st, s));
+                OFDFT_TRY(launch_cg_tiny<T>(g, kz, c, x, r, pA, st, resume, s));
             }
             OFDFT_CHECK_HIP(hipMemcpyAsync(st_host, st, sizeof(CgState), hipMemcpyDeviceToHost, s));
             OFDFT_CHECK_HIP(hipStreamSynchronize(s));
+            resume = true;
         } while (st_host->done == CG_RUNNING);
         iters = st_host->iter;
         done = st_host->done;
