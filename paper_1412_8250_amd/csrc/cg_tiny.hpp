@@ -23,11 +23,18 @@ constexpr int kTinyMinAxis = 6;          // one periodic wrap per offset
 constexpr size_t kTinyLds = 140 * 1024;
 constexpr int kTinyIters = 512;          // per launch: 3 ms at 16^3, 5 ms at most
 
-// Planes per thread (4 or 8) if the grid fits one workgroup, else 0.
+// Planes per thread (4 or 8) if the grid fits one workgroup, else 0.  1024
+// threads leave 128 registers: of a kernel of 4 planes 50 spill, of 8 180.  Per
+// iteration to 1e-10, so and with two launches on bricks: FP64 4096 points 7.9 /
+// 17.0 us, 4608 14.2 / 14.5, 5120 14.1 / 14.4, 6144 14.8 / 14.0, 8192 15.3 / 14.6; FP32
+// 5120 11.5 / 17.1, 8192 12.5 / 16.4.  So FP64 grids of over 6000 points run two
+// launches where their axes admit bricks (8 x 32 x 32, which does not: 15.2 / 23.0).
 inline int tiny_planes(const ofdft_grid &g, size_t elem) {
     if (g.nx < kTinyMinAxis || g.ny < kTinyMinAxis || g.nz < kTinyMinAxis) return 0;
     if ((int64_t)g.nx * g.ny * g.nz > 8 * kTinyThreads) return 0;
     if ((size_t)(g.nx + 2 * kMaxRadius) * g.ny * g.nz * elem > kTinyLds) return 0;
+    const bool bricks = g.nx >= kBrickMinAxis && g.ny >= kBrickMinAxis && g.nz >= kBrickMinAxis;
+    if (elem == 8 && bricks && (int64_t)g.nx * g.ny * g.nz > 6000) return 0;
     for (int kz : {4, 8})
         if (g.nx * g.ny * ((g.nz + kz - 1) / kz) <= kTinyThreads) return kz;
     return 0;

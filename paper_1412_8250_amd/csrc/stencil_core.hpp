@@ -354,12 +354,17 @@ stencil_kernel(TileGeom g, Coef<typename VT<T>::S> w, Load ld, Epi ep) {
 // Every load is issued up front -- each thread its column's KZ + 12 z values,
 // and the planes' star halos (12 (W + H) cells each, no corners) shared out
 // among the threads -- then the KZ planes stand in LDS and are computed after
-// one barrier.  Bound by latency and then by L1 (about 12 / KZ + 1 + 12 (W +
-// H) / (W H) loads per point); it has no prologue of 15 planes before the first
-// output, which is most of the march's time on a small grid, and its bricks
-// spread over the chip where the march has few tiles.  Same operations in
-// the same order per point as the march.  Needs every axis to reach
-// kBrickMinAxis points (one periodic wrap per z offset).
+// one barrier.  12 / KZ + 1 + 12 (W + H) / (W H) loads per point; it has no
+// prologue of 15 planes before the first output, which is most of the march's
+// time on a small grid, and its bricks spread over the chip where the march has
+// few tiles.  Bound by waiting: counters of the complex128 apply at 110 x 75 x 91
+// (759 bricks, three a CU, 11 us) show the address units busy for 59% of the
+// time, L1 held up by pending L2 reads (390 cycles each) for 50%, its accesses
+// at a third of its rate, and LDS bank conflicts for 19%; of the shifted systems'
+// stencil phase on eight grids of 96^3 53%, 56% (540 cycles), 22% and 18%, with
+// 1.28 times the bytes it cannot do without.  Same operations in the same
+// order per point as the march.  Needs every axis to reach kBrickMinAxis
+// points (one periodic wrap per z offset).
 constexpr int kBrickThreads = 256;
 constexpr int kBrickMinAxis = 10;
 constexpr int kBrickRing = 4;           // halo cells per thread and plane at most

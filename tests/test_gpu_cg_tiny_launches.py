@@ -1,6 +1,6 @@
 """Poisson CG of grids that fit one workgroup, over more iterations than one
 launch runs: the iteration goes on where it stopped (a new start from the
-iterate would take 8% and 45% more steps here), and a solve whose tolerance cannot be
+iterate would take 8% and 57% more steps here), and a solve whose tolerance cannot be
 met is made of bounded launches."""
 import numpy as np
 import pytest
@@ -28,7 +28,7 @@ def _solve(shape, h, g, tol, maxit, noalloc=False):
 
 @pytest.mark.parametrize("noalloc", [False, True])
 # four planes a thread and eight
-@pytest.mark.parametrize("shape,h", [((16, 16, 16), (1.5, 0.7, 0.02)), ((32, 16, 16), (0.05, 0.4, 2.0))])
+@pytest.mark.parametrize("shape,h", [((16, 16, 16), (1.5, 0.7, 0.02)), ((32, 8, 32), (0.05, 0.4, 2.0))])
 def test_goes_on_in_the_next_launch(shape, h, noalloc):
     torch_cuda()
     announce("tiny cg launches", shape, noalloc)
@@ -53,3 +53,16 @@ def test_cap_around_launches(steps):
     x, st, launches = _solve(shape, h, g - g.mean(), 1e-300, steps)
     assert st["iters"] == steps and st["status"] == ofd.NOT_CONVERGED and np.isfinite(x).all()
     assert launches == -(-steps // PER_LAUNCH)
+
+
+@pytest.mark.parametrize("shape,one", [((14, 20, 20), True), ((8, 32, 32), True), ((24, 16, 16), False)])
+def test_which_grids_take_one_launch(shape, one):
+    """Over 6000 points FP64 iterations run two launches each where every axis
+    admits bricks (at least ten points)."""
+    torch_cuda()
+    announce("tiny cg rule", shape)
+    g = np.random.default_rng(6).normal(size=shape)
+    h = (0.4, 0.45, 0.5)
+    x, st, launches = _solve(shape, h, g, 1e-10, 1000)
+    assert st["status"] == ofd.OK and poisson.residual(x, g - g.mean(), h) <= 1e-10
+    assert (launches == 1) == one
