@@ -559,7 +559,7 @@ int ofdft_density_update(ofdft_scf *s, const double *v, double *u, int *iters,
  *   minimising the energy-norm error): precondition 0 (default) = plain FP64
  *   CG to the tolerance; 1 = flexible CG preconditioned by the network,
  *   falling back to plain CG from the best iterate when it stalls (less than
- *   10x residual reduction in the first 20 iterations, or than 2x in 500 later
+ *   10x residual reduction in the first 20 iterations, or than 2x in 200 later
  *   ones) or breaks down.  OFDFT_LEARNED
  *   only (OFDFT_LEARNED_REFINED always continues with the refined form).
  * ------------------------------------------------------------------------ */

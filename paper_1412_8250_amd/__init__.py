@@ -275,13 +275,14 @@ SHAPE_NAMES = ("64x16/256", "64x8/256", "32x16/256", "64x16/512", "64x8/512", "6
 def tune_stencil(shape_zyx, h_xyz, dtype: int = F64, family: int = TUNE_APPLY, reps: int = 5,
                  radius: int = 6, stream=None) -> dict:
     """Time every legal launch shape / z chunk of one kernel family on the grid
-    and record the fastest (see ofdft_tune_stencil); shape_name says what runs."""
+    and record the fastest (see ofdft_tune_stencil); shape_name says what runs
+    (the tile and threads of a march, or bricks/planes)."""
     g = grid_of(shape_zyx, h_xyz)
     r = TuneResult()
     _check(lib().ofdft_tune_stencil(ctypes.byref(g), int(radius), int(dtype), int(family), int(reps),
                                     ctypes.byref(r), _stream(stream)))
     out = r.as_dict()
-    out["shape_name"] = f"bricks of {r.group} planes" if r.group else SHAPE_NAMES[r.shape]
+    out["shape_name"] = f"bricks/{r.group}" if r.group else SHAPE_NAMES[r.shape]
     return out
 
 

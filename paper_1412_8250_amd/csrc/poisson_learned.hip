@@ -11,8 +11,8 @@
 //     z_new = M(r_new);  beta = <z_new, r_new - r> / <z, r>;  p = z_new + beta p
 // All vectors FP64.  Plain FP64 CG from the best iterate takes over if the
 // residual has not dropped 10x after 20 iterations, on NaN/Inf, and from a run
-// that stalls later: less than 2x in 500 iterations, which is a pace of over
-// 10,000 to a reduction of 1e-6 (plain CG takes 1100 for 1e-8 at 320^3).
+// that stalls later: less than 2x in 200 iterations, which is a pace of over
+// 4000 to a reduction of 1e-6 (plain CG takes 1100 for 1e-8 at 320^3).
 #include <algorithm>
 #include <cmath>
 
@@ -117,7 +117,7 @@ int poisson_solve_learned(ofdft_poisson *s, double *x, double rel_tol, int max_i
                 OFDFT_TRY((launch_reduce<1>(n, CopyOp2{xb, x}, NoFin{}, s->rb, st)));
             }
             if (r2 <= tol2) break;
-            if (iters % 500 == 20) {    // residual norm against the last look's: 10x at the first, 2x later
+            if (iters % 200 == 20) {    // residual norm against the last look's: 10x at the first, 2x later
                 if (best > (iters == 20 ? 0.01 : 0.25) * r2_mark) {
                     fall_back = true;
                     break;

@@ -1,6 +1,6 @@
 """When the network-preconditioned flexible CG gives way to plain CG after its
 first look (10x in 20 iterations): not while it converges, however unevenly, and
-once it stalls (less than 2x in 500 iterations).  The networks are set by hand:
+once it stalls (less than 2x in 200 iterations).  The networks are set by hand:
 their outputs are known functions of the residual."""
 import numpy as np
 import pytest
@@ -66,4 +66,4 @@ def test_stalled_run_is_given_up():
     g = (xp - xp.mean()) + 0.01 * (yz - yz.mean())[:, :, None]
     st = _solve(_network({CENTRE: (2.0 + 1e-5, -2.0), XM: (-1.0, 1.0), XP: (-1.0, 1.0)}), g, 1e-8)
     # one application for the start, one for z_0 and one per iteration to the look that ends it
-    assert st["fell_back"] == 1 and st["nn_applies"] in (521, 1021)
+    assert st["fell_back"] == 1 and st["nn_applies"] in (221, 421)

@@ -46,7 +46,7 @@ def test_bricks_stay(family, hand, tmp_path):
         if not hand:
             ofd.set_stencil_config(SHAPE, 8, -1)
         r = ofd.tune_stencil(SHAPE, H, ofd.F64, family, reps=20)
-        assert r["group"] == 1 and r["shape_name"] == "bricks of 1 planes"
+        assert r["group"] == 1 and r["shape_name"] == "bricks/1"
         assert 0 <= r["shape"] < 6 and r["best_ms"] == r["default_ms"]
         assert _table(tmp_path) == ({1 - family: HAND} if hand else {})
         runs_bricks = family == ofd.TUNE_PASS or not hand
